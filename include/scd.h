@@ -42,9 +42,8 @@
  *   - "Allowed ids" A = [v_lo, v_hi), n = |A|.  Tokens in x / y / the state are
  *     OFFSETS into A (0..n-1); emitted tokens (out) are real ids v_lo + offset.
  *     Processed logits z hold only the n allowed columns.
- *   - Rows of up to 65536 allowed ids run through one fused kernel per row (plus the LM
- *     head).  Longer rows are supported with top-k and the maximal coupling only (one kernel
- *     per stage: select, MRS, commit); Gumbel sharing, sjd_mix > 0, top_p and diagnostics on
+ *   - Rows of up to 65536 allowed ids support every option.  Longer rows are supported with
+ *     top-k and the maximal coupling only; Gumbel sharing, sjd_mix > 0, top_p and diagnostics on
  *     such rows are refused by scd_create with SCD_EUNSUPPORTED.
  *   - Window order: row s of a [B, L, ...] array belongs to position pos0[b]+s.
  *     Lw_b = min(L, N - pos0[b]) rows are live; the rest are ignored on input
@@ -218,7 +217,8 @@ int scd_couple_draft(scd_ctx* ctx, const float* d_z_cur, const float* d_z_prev,
  * does not touch the context's workspace.  Returns SCD_ESCRATCH when the configuration needs
  * more: 24 bytes per window row (B * L rows, each of the six arrays rounded up to 256 bytes),
  * plus 51200 bytes per window row when top-k filters rows of 16385..65536 ids with
- * top_k <= 3072 (the slice kernel's candidate lists), i.e. up to 163 such rows.
+ * top_k <= 3072 (the slice kernel's candidate lists), i.e. up to 163 such rows.  (Longer rows take
+ * the lists while they fit and do without them beyond.)
  * All calls on one GPU share that array and it keeps the last call's contents (nothing in it has
  * to start at zero): calls that overlap in time on one GPU -- different streams or contexts --
  * race.  The array's address is looked up once per GPU, in scd_create when a GPU is present,

@@ -1,14 +1,11 @@
-// First rejection, emission and window slide (appendix "Algorithms",
-// Alg. SCD(pi_MC): "find first rejection index", i <- Accept + 1), plus the
-// state initialisation ("p <- Random(), X ~ p": uniform initial drafts) and the
+// First rejection and emission on their own (appendix "Algorithms", Alg. SCD(pi_MC):
+// "find first rejection index"; inside an iteration the row kernel does both and slides
+// the window), plus the state initialisation ("p <- Random(), X ~ p": uniform initial drafts) and the
 // copy of caller-supplied logits into the ring.
 //
 // Window of exactly L positions [i, i+L) clipped to N (Lw live rows).  With the
 // first rejection at window offset r the step emits a = min(r+1, Lw) tokens
-// (a = Lw when nothing was rejected).  Rows a..Lw-1 keep their MRS output as
-// the next draft (coupled redraft) and age by one; rows 0..a-1 retire, and
-// their ring slots receive the entering positions i+L .. i+L+a-1 (below N)
-// with a uniform initial draft and age 0.
+// (a = Lw when nothing was rejected).
 #include "scd_device.h"
 #include "scd_kernels.h"
 
@@ -35,25 +32,7 @@ __global__ void commit_kernel(const CommitArgs a) {
   __syncthreads();
   const int acc = min(s_first + 1, live);
   if (s < acc) a.out[static_cast<size_t>(b) * a.N + i + s] = a.v_lo + y;
-  if (a.slide && s < live) {
-    const size_t sidx = static_cast<size_t>(b) * a.L + (i + s) % a.L;
-    if (s >= acc) {
-      a.X[sidx] = y;
-      a.age[sidx] += 1;
-    } else {
-      const int np = i + a.L + s;      // position entering this slot
-      a.X[sidx] = np < a.N ? init_token(a.seed, b, np, a.n) : -1;
-      a.age[sidx] = 0;
-    }
-  }
-  if (s == 0) {
-    a.accept_len[b] = acc;
-    if (a.slide) {
-      a.pos[b] = i + acc;
-      a.iter[b] += 1;
-      a.verified[b] += live;
-    }
-  }
+  if (s == 0) a.accept_len[b] = acc;
 }
 
 __global__ void reset_kernel(const ResetArgs a) {

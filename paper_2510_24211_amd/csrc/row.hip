@@ -30,6 +30,10 @@
 // layouts) or top-k is off, the row kernel falls back to a complete in-place
 // path: one coalesced read of the row, 16-bit key prefixes parked in LDS,
 // histogram select, candidate list or in-place scans.
+// Rows of more than 65536 logits (the LONG instance; top-k and the maximal coupling only) take the
+// slice kernel and the candidate path like the others.  32 rows of 131072 ids under top-k 2000: 16 us +
+// 18 us, where one kernel per stage (radix select over the row, MRS, commit) took 124 + 64 + 5 us.
+// Their complete path (long_path) makes whole passes over the row in memory.
 // The K-th largest key is always found by integer counting (LDS histograms
 // whose bins adapt to the key range, so lanes rarely collide); all
 // floating-point sums use a fixed assignment of ids to threads and a fixed
@@ -520,15 +524,14 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
     }
     return;
   }
-  const bool vec_ok = (n & 3) == 0;
   float zv[PS];
   int vid[PS];
   bool ok[PS];
 #pragma unroll
   for (int u = 0; u < PS / 4; ++u) {
     const int v0 = lo_id + ((tid + u * ST) << 2);
-    if (vec_ok && v0 + 3 < hi_id) {
-      const float4 t = *reinterpret_cast<const float4*>(R.zc + v0);
+    if (v0 + 3 < hi_id) {
+      const float4 t = load4(R.zc + v0);
       zv[u * 4 + 0] = t.x; zv[u * 4 + 1] = t.y; zv[u * 4 + 2] = t.z; zv[u * 4 + 3] = t.w;
     } else {
 #pragma unroll
@@ -1243,6 +1246,220 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   }
 }
 
+// Rows of more than kRowKernelMaxN ids whose candidates were not certified, or that have none
+// (no top-k, or one too large for the lists): whole passes over the row in memory -- the key prefixes
+// of full_path would not fit LDS.  Bound by what one CU can load (about 10 us per pass over 131072
+// ids, 2 to 4 passes); in the decode it serves the rare row only.
+__device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, unsigned char* smem, float zcx,
+                                          float zpx, Small& sm, RowOut& out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = a.n;
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(smem);
+  uint32_t* const kid = hist + NBINS;                       // kept ids (or members of a bin) ...
+  float* const kz = reinterpret_cast<float*>(kid + kKeptCap);   // ... and their logits
+  const int ngroups = n >> 2;                                // whole groups of four ids
+  constexpr int UNR = 4;
+  // f(v0, z) for every group of four ids v0 .. v0 + 3, z[e] = pad where there is no such id; the same
+  // groups in the same order in every pass of a thread
+  auto groups = [&](float pad, auto&& f) {
+    for (int g0 = tid; g0 < ngroups; g0 += THREADS * UNR) {
+      float4 t[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const int g = g0 + u * THREADS;
+        t[u] = load4(R.zc + (g < ngroups ? g << 2 : 0));
+      }
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const float z[4] = {t[u].x, t[u].y, t[u].z, t[u].w};
+        if (g0 + u * THREADS < ngroups) f((g0 + u * THREADS) << 2, z);
+      }
+    }
+    if ((n & 3) != 0 && tid == 0) {                          // the last ids of a ragged row
+      float z[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = (ngroups << 2) + e < n ? R.zc[(ngroups << 2) + e] : pad;
+      f(ngroups << 2, z);
+    }
+  };
+  // f(v, z) for every id
+  auto each = [&](auto&& f) {
+    groups(0.f, [&](int v0, const float (&z)[4]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (v0 + e < n) f(v0 + e, z[e]);
+    });
+  };
+  uint32_t kmax = 0, kmin = 0xFFFFFFFFu;
+  {
+    float hi = -INFINITY, lo = INFINITY, nan = 0.f;
+    groups(-INFINITY, [&](int, const float (&z)[4]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hi = fmaxf(hi, z[e]);
+        lo = z[e] > kRangeFloor ? fminf(lo, z[e]) : lo;
+        nan = z[e] != z[e] ? z[e] : nan;                     // NaN of either sign
+      }
+    });
+    kmax = zkey(hi);
+    kmin = zkey(lo);
+    if (nan != 0.f) {
+      kmax = 0xFFFFFFFFu;                                    // sorts above every logit: the normaliser shows it too
+      if (a.flags) atomicOr(a.flags, 1);
+    }
+  }
+  __syncthreads();                                           // earlier users of LDS are done
+  zero_hist(hist);
+  if (tid == 0) sm.cursor = 0u;
+  block_minmax(kmin, kmax, sm);                              // its barriers publish the zeroed bins
+  const float m = key_to_float(kmax);
+  const bool filter = a.top_k > 0 && a.top_k < n;
+  float thr = -INFINITY;
+  if (filter) {
+    // first level linear in the logit (see select_regs), then radix levels over the key bits of the
+    // selected bin's members, which are kept in LDS when they fit
+    const float zlo = key_to_float(kmin);
+    const float scale = (m > zlo) ? __fdiv_rn(static_cast<float>(NBINS - 1), m - zlo) : 0.f;
+    auto lin_bin = [&](float z) {
+      const float t = z > kRangeFloor ? (z - zlo) * scale : 0.f;
+      return t >= 0.f ? (t >= static_cast<float>(NBINS - 1) ? NBINS - 1 : static_cast<int>(t)) : 0;
+    };
+    each([&](int, float z) { atomicAdd(&hist[lin_bin(z)], 1u); });
+    __syncthreads();
+    uint32_t need = static_cast<uint32_t>(a.top_k);
+    const int b1 = static_cast<int>(find_bin(hist, need, sm));
+    const uint32_t members = hist[b1];
+    const bool parked = members <= static_cast<uint32_t>(kKeptCap);
+    if (parked)                                              // in any order: they are only counted
+      each([&](int, float z) {
+        if (lin_bin(z) == b1) kid[atomicAdd(&sm.cursor, 1u)] = zkey(z);
+      });
+    uint32_t lo = 0;
+    for (int width = 32; width > 0;) {
+      const int s2 = width > 12 ? width - 12 : 0;
+      __syncthreads();
+      zero_hist(hist);
+      __syncthreads();
+      auto count = [&](uint32_t key) {
+        if (key >= lo && (width == 32 || (key - lo) >> width == 0u)) atomicAdd(&hist[(key - lo) >> s2], 1u);
+      };
+      if (parked) {
+        for (uint32_t i = tid; i < members; i += THREADS) count(kid[i]);
+      } else {
+        each([&](int, float z) {
+          if (lin_bin(z) == b1) count(zkey(z));
+        });
+      }
+      __syncthreads();
+      lo += find_bin(hist, need, sm) << s2;
+      width = s2;
+    }
+    thr = key_to_float(lo);
+    if (tid == 0) sm.cursor = 0u;
+    __syncthreads();
+  }
+  // sum in a fixed order; with a filter the kept ids are parked for the race (in any order: the
+  // race's winner does not depend on it)
+  float sum = 0.f;
+  int cnt = 0;
+  each([&](int v, float z) {
+    if (z >= thr) {
+      sum += expf(z - m);
+      ++cnt;
+      if (filter) {                       // a few thousand appends
+        const uint32_t slot = atomicAdd(&sm.cursor, 1u);
+        if (slot < static_cast<uint32_t>(kKeptCap)) {
+          kid[slot] = static_cast<uint32_t>(v);
+          kz[slot] = z;
+        }
+      }
+    }
+  });
+  sum = wave_sum(sum);
+  cnt = wave_sum_i32(cnt);
+  if (lane == 0) {
+    sm.fred[wave] = sum;
+    sm.ired[wave] = cnt;
+  }
+  __syncthreads();
+  float S = 0.f;
+  int Cn = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    S += sm.fred[w];
+    Cn += sm.ired[w];
+  }
+  const float lse_c = m + logf(S);
+  if (tid == 0) {
+    a.thr[R.oidx] = thr;
+    a.lse[R.oidx] = lse_c;
+    a.nkept[R.oidx] = Cn;
+    if (a.flags && !(lse_c == lse_c && fabsf(lse_c) < INFINITY)) atomicOr(a.flags, 1);
+  }
+  if (a.mode == kRowSelectOnly) return;
+  const int j = R.p0 + R.s;
+  const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
+  const uint2 key = seed_key(a.seed);
+  const uint32_t w3 = static_cast<uint32_t>(R.b) << 8;
+  const bool x_ok = R.x >= 0 && R.x < n;
+  out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
+  out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
+  const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(j), static_cast<uint32_t>(R.it),
+                                            w3 | kStreamAccept), key);
+  out.accept = __fmul_rn(u01(ra.x), out.qx) <= out.px;
+  out.best = INFINITY;
+  out.best_id = 0x7FFFFFFF;
+  if (out.accept) return;
+  auto enter = [&](uint32_t bits, int v, float rv) {          // exponential-race entry of id v
+    const float sc = __fdiv_rn(-logf(u01(bits)), rv);
+    if (sc < out.best || (sc == out.best && v < out.best_id)) {
+      out.best = sc;
+      out.best_id = v;
+    }
+  };
+  auto noise = [&](int v) {                                   // random bits of ids v & ~3 .. v | 3
+    return philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
+                                    static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
+  };
+  if (filter && Cn <= kKeptCap) {
+    for (int i = tid; i < Cn; i += THREADS) {
+      const int v = static_cast<int>(kid[i]);
+      const float rv = __fsub_rn(expf(kz[i] - lse_c), R.fresh ? q_uniform : prob(R.zp[v], R.thr_p, R.lse_p));
+      if (!(rv > 0.f)) continue;
+      const uint4 rr = noise(v);
+      const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
+      enter(lanes[v & 3], v, rv);
+    }
+    return;
+  }
+  groups(-INFINITY, [&](int v0, const float (&z)[4]) {
+    float q[4] = {0.f, 0.f, 0.f, 0.f};
+    if (!R.fresh) {
+      if (v0 + 3 < n) {
+        const float4 t = load4(R.zp + v0);
+        q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[e] = v0 + e < n ? R.zp[v0 + e] : 0.f;
+      }
+    }
+    float rv[4];
+    bool any = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float pv = v0 + e < n ? prob(z[e], thr, lse_c) : 0.f;
+      rv[e] = __fsub_rn(pv, R.fresh ? q_uniform : prob(q[e], R.thr_p, R.lse_p));
+      any |= pv > 0.f && rv[e] > 0.f;
+    }
+    if (!any) return;
+    const uint4 rr = noise(v0);
+    const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (rv[e] > 0.f) enter(lanes[e], v0 + e, rv[e]);
+  });
+}
+
 // The whole row in registers, PER logits per thread (n <= PER * THREADS).
 template <int PER, bool GS, bool EXTRA>
 __device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, unsigned char* smem,
@@ -1284,8 +1501,9 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, u
 
 // GS: the row also makes a Gumbel-max draw from p; EXTRA: the optional parts are compiled in
 // (nucleus filter, per-position statistics; kept out of the other instances: their live ranges
-// cost the hot kernels registers)
-template <bool GS, bool EXTRA>
+// cost the hot kernels registers); LONG: rows of more than kRowKernelMaxN ids, for which only the
+// candidate path and long_path exist
+template <bool GS, bool EXTRA, bool LONG = false>
 __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
                                                       const int mode_, const int L_, const int N_,
                                                       const int P, const int capE, const RowArgs a) {
@@ -1320,14 +1538,16 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
   RowOut out{};
   out.accept = true;
   bool done = false;
-  if (n <= kDirectMaxN) {
+  if (!LONG && n <= kDirectMaxN) {
     // ---- the whole row in registers ------------------------------------------------
     if (n <= kDirectMaxN / 2) direct_path<PER_DIRECT / 2, GS, EXTRA>(a, R, smem, filter, zcx, zpx, sm, out);
     else direct_path<PER_DIRECT, GS, EXTRA>(a, R, smem, filter, zcx, zpx, sm, out);
     done = true;
   } else if (filter && a.cand && P > 0) {
     // ---- candidates emitted by the slice kernel ----------------------------------
-    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + static_cast<size_t>((n + 7) & ~7) * 2);
+    // LDS: the compaction arrays, then the histogram (behind the space of full_path's key prefixes)
+    const size_t arrays = LONG ? static_cast<size_t>(kKeptCap) * 12 : static_cast<size_t>((n + 7) & ~7) * 2;
+    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + arrays);
     // The P counts and cuts of the row's lists (P slices of the slice kernel, or P column tiles
     // of the LM head's epilogue; thread t holds those of list t), the count that governs each
     // of this thread's candidate slots, and the slots themselves are fetched in ONE round trip:
@@ -1386,13 +1606,17 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
       float zq[PER_LIST];                      // unused: finish_regs gathers what it needs
 #pragma unroll
       for (int e = 0; e < PER_LIST; ++e) zq[e] = 0.f;
-      const int ccap = min(kKeptCap, static_cast<int>(static_cast<size_t>((n + 7) & ~7) * 2 / 12));
+      const int ccap = min(kKeptCap, static_cast<int>(arrays / 12));
       done = finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zq, ok, true, cut_max, zcx, zpx, hist,
                                    reinterpret_cast<uint32_t*>(smem), reinterpret_cast<float*>(smem) + ccap,
                                    reinterpret_cast<float*>(smem) + 2 * ccap, ccap, sm, out);
     }
   }
-  if (!done) full_path<GS, EXTRA>(a, R, smem, zcx, zpx, sm, out);
+  if constexpr (LONG) {
+    if (!done) long_path(a, R, smem, zcx, zpx, sm, out);
+  } else {
+    if (!done) full_path<GS, EXTRA>(a, R, smem, zcx, zpx, sm, out);
+  }
   if (a.mode == kRowSelectOnly) return;
 
   // ---- winner of the race (lexicographic (score, id) minimum) -------------------
@@ -1542,7 +1766,7 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
 }
 
 size_t lds_bytes_for(int n) {
-  if (n <= kDirectMaxN) return NBINS * sizeof(uint32_t) + kKeptCap * 12;
+  if (n <= kDirectMaxN || n > kRowKernelMaxN) return NBINS * sizeof(uint32_t) + kKeptCap * 12;
   return static_cast<size_t>((n + 7) & ~7) * 2 + NBINS * sizeof(uint32_t) + kListCap * sizeof(uint16_t);
 }
 
@@ -1568,7 +1792,9 @@ void row_candidate_layout(void* base_, int rows, uint2** cand, uint32_t** cnt, u
 
 bool row_uses_candidates(int n, int top_k) {
   const bool filter = top_k > 0 && top_k < n;
-  return n > kDirectMaxN && n <= kRowKernelMaxN && filter && top_k <= kListCap / 2;
+  // one list per slice, at most kRowMaxTiles lists per row (longer rows are read whole).  top-k: a slice
+  // emits about twice its share of the row's top_k logits, which has to fit its part of the lists.
+  return n > kDirectMaxN && n <= kRowMaxTiles * kSliceMax && filter && top_k <= kListCap / 2;
 }
 
 #endif  // !SCD_ROW_BATCHED
@@ -1593,7 +1819,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       P = a.tiles;
       capE = kListCap / P;
     } else {
-      P = (a.n + kSliceMax - 1) / kSliceMax;                     // <= 8 for n <= 65536
+      P = (a.n + kSliceMax - 1) / kSliceMax;                     // 3 .. kRowMaxTiles
       capE = kListCap / P;
       int rank = (2 * a.top_k + P - 1) / P;
       rank = rank < 64 ? 64 : rank;
@@ -1615,7 +1841,11 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   size_t& configured = lds_configured ? *lds_configured : none;
   if (configured == 0) {
     const size_t most = lds_bytes_for(kRowKernelMaxN);
-    for (const void* f : {reinterpret_cast<const void*>(row_kernel<false, false>),
+    for (const void* f : {
+#ifndef SCD_ROW_BATCHED
+                          reinterpret_cast<const void*>(row_kernel<false, false, true>),
+#endif
+                          reinterpret_cast<const void*>(row_kernel<false, false>),
                           reinterpret_cast<const void*>(row_kernel<true, false>),
                           reinterpret_cast<const void*>(row_kernel<false, true>),
                           reinterpret_cast<const void*>(row_kernel<true, true>)}) {
@@ -1627,8 +1857,14 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   }
   const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
   const bool topp = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
-  auto* const kernel = gs ? (topp ? row_kernel<true, true> : row_kernel<true, false>)
+  auto* kernel = gs ? (topp ? row_kernel<true, true> : row_kernel<true, false>)
                           : (topp ? row_kernel<false, true> : row_kernel<false, false>);
+#ifndef SCD_ROW_BATCHED
+  if (a.n > kRowKernelMaxN) {
+    if (gs || topp) return hipErrorInvalidValue;            // refused when the context is created
+    kernel = row_kernel<false, false, true>;
+  }
+#endif
   a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;
   hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(THREADS), lds, s, a.pos, a.iter, a.mode, a.L, a.N, P, capE, a);
   return hipGetLastError();

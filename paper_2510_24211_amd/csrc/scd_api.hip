@@ -148,94 +148,47 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 int run_tail(scd_ctx* c, void* st, int tiles = 0) {
   // z of this iteration is in place in the ring.
   const size_t half = static_cast<size_t>(c->cfg.B) * c->cfg.L * c->n;
-  if (c->n <= scd::kRowKernelMaxN) {
-    // one fused launch: select + softmax + MRS per row, commit by each sequence's last row
-    scd::RowArgs ra{};
-    ra.alpha = 1.0f;
-    ra.mode = scd::kRowRing;
-    ra.z_cur = field<float>(c, st, SCD_F_Z);
-    ra.parity_stride = half;
-    ra.thr = field<float>(c, st, SCD_F_THR);
-    ra.lse = field<float>(c, st, SCD_F_LSE);
-    ra.nkept = field<int32_t>(c, st, SCD_F_NKEPT);
-    ra.x = field<int32_t>(c, st, SCD_F_X);
-    ra.age = field<int32_t>(c, st, SCD_F_AGE);
-    ra.pos = field<int32_t>(c, st, SCD_F_POS);
-    ra.iter = field<int32_t>(c, st, SCD_F_ITER);
-    ra.y = field<int32_t>(c, st, SCD_F_Y);
-    ra.k = field<uint8_t>(c, st, SCD_F_K);
-    ra.px = field<float>(c, st, SCD_F_PX);
-    ra.qx = field<float>(c, st, SCD_F_QX);
-    ra.flags = field<int32_t>(c, st, SCD_F_FLAGS);
-    ra.ticket = field<int32_t>(c, st, SCD_F_TICKET);
-    ra.X = field<int32_t>(c, st, SCD_F_X);
-    ra.age_w = field<int32_t>(c, st, SCD_F_AGE);
-    ra.verified = field<int32_t>(c, st, SCD_F_VERIFIED);
-    ra.accept_len = field<int32_t>(c, st, SCD_F_ACCEPT);
-    ra.out = field<int32_t>(c, st, SCD_F_OUT);
-    ra.rows = c->cfg.B * c->cfg.L;
-    ra.B = c->cfg.B; ra.L = c->cfg.L; ra.N = c->cfg.N; ra.n = c->n; ra.top_k = c->cfg.top_k;
-    ra.top_p24 = top_p24_of(c->cfg);
-    ra.v_lo = c->cfg.v_lo; ra.seed = c->cfg.seed;
-    ra.cand_base = static_cast<char*>(c->ws) + small_need(c->cfg);
-    ra.tiles = tiles;            // > 0: the LM head has already written the candidate lists
-    ra.gumbel = c->cfg.coupling == SCD_COUPLING_GS;
-    ra.alpha = 1.0f - c->cfg.sjd_mix;
-    ra.g = field<int32_t>(c, st, SCD_F_G);
-    if (c->cfg.diagnostics) {
-      ra.diag = field<float>(c, st, SCD_F_DIAG);
-      ra.s2 = field<float>(c, st, SCD_F_S2);
-      ra.hamm = field<int32_t>(c, st, SCD_F_HAMM);
-      ra.xhist = field<int32_t>(c, st, SCD_F_XHIST);
-      ra.phist = field<int32_t>(c, st, SCD_F_PHIST);
-    }
-    return hip_rc(scd::launch_row(ra, c->stream, c->row_lds));
+  // one fused launch: select + softmax + MRS per row, commit by each sequence's last row
+  scd::RowArgs ra{};
+  ra.alpha = 1.0f;
+  ra.mode = scd::kRowRing;
+  ra.z_cur = field<float>(c, st, SCD_F_Z);
+  ra.parity_stride = half;
+  ra.thr = field<float>(c, st, SCD_F_THR);
+  ra.lse = field<float>(c, st, SCD_F_LSE);
+  ra.nkept = field<int32_t>(c, st, SCD_F_NKEPT);
+  ra.x = field<int32_t>(c, st, SCD_F_X);
+  ra.age = field<int32_t>(c, st, SCD_F_AGE);
+  ra.pos = field<int32_t>(c, st, SCD_F_POS);
+  ra.iter = field<int32_t>(c, st, SCD_F_ITER);
+  ra.y = field<int32_t>(c, st, SCD_F_Y);
+  ra.k = field<uint8_t>(c, st, SCD_F_K);
+  ra.px = field<float>(c, st, SCD_F_PX);
+  ra.qx = field<float>(c, st, SCD_F_QX);
+  ra.flags = field<int32_t>(c, st, SCD_F_FLAGS);
+  ra.ticket = field<int32_t>(c, st, SCD_F_TICKET);
+  ra.X = field<int32_t>(c, st, SCD_F_X);
+  ra.age_w = field<int32_t>(c, st, SCD_F_AGE);
+  ra.verified = field<int32_t>(c, st, SCD_F_VERIFIED);
+  ra.accept_len = field<int32_t>(c, st, SCD_F_ACCEPT);
+  ra.out = field<int32_t>(c, st, SCD_F_OUT);
+  ra.rows = c->cfg.B * c->cfg.L;
+  ra.B = c->cfg.B; ra.L = c->cfg.L; ra.N = c->cfg.N; ra.n = c->n; ra.top_k = c->cfg.top_k;
+  ra.top_p24 = top_p24_of(c->cfg);
+  ra.v_lo = c->cfg.v_lo; ra.seed = c->cfg.seed;
+  ra.cand_base = static_cast<char*>(c->ws) + small_need(c->cfg);
+  ra.tiles = tiles;            // > 0: the LM head has already written the candidate lists
+  ra.gumbel = c->cfg.coupling == SCD_COUPLING_GS;
+  ra.alpha = 1.0f - c->cfg.sjd_mix;
+  ra.g = field<int32_t>(c, st, SCD_F_G);
+  if (c->cfg.diagnostics) {
+    ra.diag = field<float>(c, st, SCD_F_DIAG);
+    ra.s2 = field<float>(c, st, SCD_F_S2);
+    ra.hamm = field<int32_t>(c, st, SCD_F_HAMM);
+    ra.xhist = field<int32_t>(c, st, SCD_F_XHIST);
+    ra.phist = field<int32_t>(c, st, SCD_F_PHIST);
   }
-  // rows too long for the LDS-resident kernel: select -> MRS -> commit
-  scd::SelectArgs sa{};
-  sa.z = field<float>(c, st, SCD_F_Z);
-  sa.parity_stride = half;
-  sa.pos = field<int32_t>(c, st, SCD_F_POS);
-  sa.iter = field<int32_t>(c, st, SCD_F_ITER);
-  sa.thr = field<float>(c, st, SCD_F_THR);
-  sa.lse = field<float>(c, st, SCD_F_LSE);
-  sa.nkept = field<int32_t>(c, st, SCD_F_NKEPT);
-  sa.flags = field<int32_t>(c, st, SCD_F_FLAGS);
-  sa.rows = c->cfg.B * c->cfg.L;
-  sa.B = c->cfg.B; sa.L = c->cfg.L; sa.N = c->cfg.N; sa.n = c->n; sa.top_k = c->cfg.top_k;
-  if (hipError_t e = scd::launch_select(sa, c->stream); e != hipSuccess) return SCD_EHIP;
-
-  scd::MrsArgs ma{};
-  ma.z_cur = field<float>(c, st, SCD_F_Z);
-  ma.parity_stride = half;
-  ma.thr_cur = field<float>(c, st, SCD_F_THR);
-  ma.lse_cur = field<float>(c, st, SCD_F_LSE);
-  ma.x = field<int32_t>(c, st, SCD_F_X);
-  ma.age = field<int32_t>(c, st, SCD_F_AGE);
-  ma.pos = field<int32_t>(c, st, SCD_F_POS);
-  ma.iter = field<int32_t>(c, st, SCD_F_ITER);
-  ma.ring = 1;
-  ma.y = field<int32_t>(c, st, SCD_F_Y);
-  ma.k = field<uint8_t>(c, st, SCD_F_K);
-  ma.px = field<float>(c, st, SCD_F_PX);
-  ma.qx = field<float>(c, st, SCD_F_QX);
-  ma.B = c->cfg.B; ma.L = c->cfg.L; ma.N = c->cfg.N; ma.n = c->n; ma.seed = c->cfg.seed;
-  if (hipError_t e = scd::launch_mrs(ma, c->stream); e != hipSuccess) return SCD_EHIP;
-
-  scd::CommitArgs ca{};
-  ca.k = field<uint8_t>(c, st, SCD_F_K);
-  ca.y = field<int32_t>(c, st, SCD_F_Y);
-  ca.pos = field<int32_t>(c, st, SCD_F_POS);
-  ca.iter = field<int32_t>(c, st, SCD_F_ITER);
-  ca.X = field<int32_t>(c, st, SCD_F_X);
-  ca.age = field<int32_t>(c, st, SCD_F_AGE);
-  ca.verified = field<int32_t>(c, st, SCD_F_VERIFIED);
-  ca.accept_len = field<int32_t>(c, st, SCD_F_ACCEPT);
-  ca.out = field<int32_t>(c, st, SCD_F_OUT);
-  ca.slide = 1;
-  ca.B = c->cfg.B; ca.L = c->cfg.L; ca.N = c->cfg.N; ca.n = c->n; ca.v_lo = c->cfg.v_lo;
-  ca.seed = c->cfg.seed;
-  return hip_rc(scd::launch_commit(ca, c->stream));
+  return hip_rc(scd::launch_row(ra, c->stream, c->row_lds));
 }
 
 }  // namespace
@@ -254,7 +207,7 @@ int scd_create(scd_ctx** out, const scd_config* cfg, void* d_workspace, size_t w
                void* hip_stream) {
   if (!out || !valid_config(cfg)) return SCD_EINVAL;
   if (cfg->coupling != SCD_COUPLING_MC && cfg->coupling != SCD_COUPLING_GS) return SCD_EUNSUPPORTED;
-  // the Gumbel draw lives in the fused row kernel only
+  // the row kernel's instance for longer rows holds top-k and the maximal coupling only
   if (top_p24_of(*cfg) != 0u && cfg->v_hi - cfg->v_lo > scd::kRowKernelMaxN) return SCD_EUNSUPPORTED;
   if (cfg->diagnostics && cfg->v_hi - cfg->v_lo > scd::kRowKernelMaxN) return SCD_EUNSUPPORTED;
   if ((cfg->coupling == SCD_COUPLING_GS || cfg->sjd_mix > 0.f) &&
@@ -334,29 +287,22 @@ int scd_lm_head(scd_ctx* c, const uint16_t* d_h, const uint16_t* d_W, float* d_z
 namespace {
 
 // scd_select with the candidate scratch at `ws` (layout of the workspace: small_need bytes of
-// per-row scalars, then the candidate lists)
-int select_impl(scd_ctx* c, char* ws, const float* d_z, int32_t rows, float* d_thr, float* d_lse,
+// per-row scalars, then, if `cands`, the candidate lists)
+int select_impl(scd_ctx* c, char* ws, bool cands, const float* d_z, int32_t rows, float* d_thr, float* d_lse,
                 int32_t* d_nkept) {
   if (!c || !d_z || rows < 0 || !d_thr || !d_lse || !d_nkept) return SCD_EINVAL;
-  if (c->n <= scd::kRowKernelMaxN) {
-    scd::RowArgs ra{};
-    ra.alpha = 1.0f;
-    ra.mode = scd::kRowSelectOnly;
-    ra.z_cur = d_z; ra.thr = d_thr; ra.lse = d_lse; ra.nkept = d_nkept;
-    ra.rows = rows;
-    ra.B = c->cfg.B; ra.L = c->cfg.L; ra.N = c->cfg.N; ra.n = c->n; ra.top_k = c->cfg.top_k;
-    ra.top_p24 = top_p24_of(c->cfg);
-    if (rows <= c->cfg.B * c->cfg.L) ra.cand_base = ws + small_need(c->cfg);
-    return hip_rc(scd::launch_row(ra, c->stream, c->row_lds));
-  }
-  scd::SelectArgs a{};
-  a.z = d_z; a.thr = d_thr; a.lse = d_lse; a.nkept = d_nkept;
-  a.rows = rows;
-  a.B = c->cfg.B; a.L = c->cfg.L; a.N = c->cfg.N; a.n = c->n; a.top_k = c->cfg.top_k;
-  return hip_rc(scd::launch_select(a, c->stream));
+  scd::RowArgs ra{};
+  ra.alpha = 1.0f;
+  ra.mode = scd::kRowSelectOnly;
+  ra.z_cur = d_z; ra.thr = d_thr; ra.lse = d_lse; ra.nkept = d_nkept;
+  ra.rows = rows;
+  ra.B = c->cfg.B; ra.L = c->cfg.L; ra.N = c->cfg.N; ra.n = c->n; ra.top_k = c->cfg.top_k;
+  ra.top_p24 = top_p24_of(c->cfg);
+  if (cands && rows <= c->cfg.B * c->cfg.L) ra.cand_base = ws + small_need(c->cfg);
+  return hip_rc(scd::launch_row(ra, c->stream, c->row_lds));
 }
 
-int couple_draft_impl(scd_ctx* c, char* w, const float* d_z_cur, const float* d_z_prev,
+int couple_draft_impl(scd_ctx* c, char* w, bool cands, const float* d_z_cur, const float* d_z_prev,
                       const int32_t* d_x, const uint8_t* d_fresh, const int32_t* d_pos0, int32_t iter,
                       int32_t* d_y, uint8_t* d_k) {
   if (!c || !d_z_cur || !d_z_prev || !d_x || !d_pos0 || !d_y || !d_k || iter < 0)
@@ -369,33 +315,22 @@ int couple_draft_impl(scd_ctx* c, char* w, const float* d_z_cur, const float* d_
   float* thr_p = reinterpret_cast<float*>(w + 3 * seg);
   float* lse_p = reinterpret_cast<float*>(w + 4 * seg);
   int32_t* nk_p = reinterpret_cast<int32_t*>(w + 5 * seg);
-  if (int rc = select_impl(c, w, d_z_prev, rows, thr_p, lse_p, nk_p); rc != SCD_OK) return rc;
-  if (c->n <= scd::kRowKernelMaxN) {
-    scd::RowArgs ra{};
-    ra.alpha = 1.0f;
-    ra.mode = scd::kRowPlain;
-    ra.z_cur = d_z_cur; ra.z_prev = d_z_prev;
-    ra.thr = thr_c; ra.lse = lse_c; ra.nkept = nk_c;
-    ra.thr_prev = thr_p; ra.lse_prev = lse_p;
-    ra.x = d_x; ra.fresh = d_fresh; ra.pos = const_cast<int32_t*>(d_pos0);
-    ra.iter_scalar = iter;
-    ra.y = d_y; ra.k = d_k;
-    ra.rows = rows;
-    ra.B = c->cfg.B; ra.L = c->cfg.L; ra.N = c->cfg.N; ra.n = c->n; ra.top_k = c->cfg.top_k;
-    ra.top_p24 = top_p24_of(c->cfg);
-    ra.v_lo = c->cfg.v_lo; ra.seed = c->cfg.seed;
-    ra.cand_base = w + small_need(c->cfg);
-    return hip_rc(scd::launch_row(ra, c->stream, c->row_lds));
-  }
-  if (int rc = select_impl(c, w, d_z_cur, rows, thr_c, lse_c, nk_c); rc != SCD_OK) return rc;
-  scd::MrsArgs a{};
-  a.z_cur = d_z_cur; a.z_prev = d_z_prev;
-  a.thr_cur = thr_c; a.lse_cur = lse_c; a.thr_prev = thr_p; a.lse_prev = lse_p;
-  a.x = d_x; a.fresh = d_fresh; a.pos = d_pos0;
-  a.iter_scalar = iter; a.ring = 0;
-  a.y = d_y; a.k = d_k;
-  a.B = c->cfg.B; a.L = c->cfg.L; a.N = c->cfg.N; a.n = c->n; a.seed = c->cfg.seed;
-  return hip_rc(scd::launch_mrs(a, c->stream));
+  if (int rc = select_impl(c, w, cands, d_z_prev, rows, thr_p, lse_p, nk_p); rc != SCD_OK) return rc;
+  scd::RowArgs ra{};
+  ra.alpha = 1.0f;
+  ra.mode = scd::kRowPlain;
+  ra.z_cur = d_z_cur; ra.z_prev = d_z_prev;
+  ra.thr = thr_c; ra.lse = lse_c; ra.nkept = nk_c;
+  ra.thr_prev = thr_p; ra.lse_prev = lse_p;
+  ra.x = d_x; ra.fresh = d_fresh; ra.pos = const_cast<int32_t*>(d_pos0);
+  ra.iter_scalar = iter;
+  ra.y = d_y; ra.k = d_k;
+  ra.rows = rows;
+  ra.B = c->cfg.B; ra.L = c->cfg.L; ra.N = c->cfg.N; ra.n = c->n; ra.top_k = c->cfg.top_k;
+  ra.top_p24 = top_p24_of(c->cfg);
+  ra.v_lo = c->cfg.v_lo; ra.seed = c->cfg.seed;
+  if (cands) ra.cand_base = w + small_need(c->cfg);
+  return hip_rc(scd::launch_row(ra, c->stream, c->row_lds));
 }
 
 }  // namespace
@@ -405,14 +340,14 @@ extern "C" {
 int scd_select(scd_ctx* c, const float* d_z, int32_t rows, float* d_thr, float* d_lse,
                int32_t* d_nkept) {
   if (!c) return SCD_EINVAL;
-  return select_impl(c, static_cast<char*>(c->ws), d_z, rows, d_thr, d_lse, d_nkept);
+  return select_impl(c, static_cast<char*>(c->ws), true, d_z, rows, d_thr, d_lse, d_nkept);
 }
 
 int scd_couple_draft(scd_ctx* c, const float* d_z_cur, const float* d_z_prev, const int32_t* d_x,
                      const uint8_t* d_fresh, const int32_t* d_pos0, int32_t iter, int32_t* d_y,
                      uint8_t* d_k) {
   if (!c) return SCD_EINVAL;
-  return couple_draft_impl(c, static_cast<char*>(c->ws), d_z_cur, d_z_prev, d_x, d_fresh, d_pos0, iter,
+  return couple_draft_impl(c, static_cast<char*>(c->ws), true, d_z_cur, d_z_prev, d_x, d_fresh, d_pos0, iter,
                            d_y, d_k);
 }
 
@@ -422,14 +357,18 @@ int scd_couple_draft_static(scd_ctx* c, const float* d_z_cur, const float* d_z_p
   if (!c) return SCD_EINVAL;
   // what this configuration really uses of the workspace layout: the per-row scalars, and the
   // candidate lists only when its rows go through the slice kernel
-  const bool cands = scd::row_uses_candidates(c->n, c->cfg.top_k);
-  const size_t need = small_need(c->cfg) + (cands ? align_up(scd::row_candidate_bytes(c->cfg.B * c->cfg.L)) : 0);
-  if (need > static_cast<size_t>(SCD_STATIC_SCRATCH_BYTES)) return SCD_ESCRATCH;
+  bool cands = scd::row_uses_candidates(c->n, c->cfg.top_k);
+  const size_t lists = align_up(scd::row_candidate_bytes(c->cfg.B * c->cfg.L));
+  // rows of more than 65536 ids also run without the lists: more of them than the array can hold
+  // lists for are read whole
+  if (c->n > scd::kRowKernelMaxN && small_need(c->cfg) + lists > static_cast<size_t>(SCD_STATIC_SCRATCH_BYTES))
+    cands = false;
+  if (small_need(c->cfg) + (cands ? lists : 0) > static_cast<size_t>(SCD_STATIC_SCRATCH_BYTES)) return SCD_ESCRATCH;
   void* base = nullptr;
   if (int rc = static_scratch(&base); rc != SCD_OK) return rc;
   // nothing in the scratch has to start at zero: the per-row scalars and, for every live row,
   // all slice counts / cuts the row kernel reads are written by the launches of this call first
-  return couple_draft_impl(c, static_cast<char*>(base), d_z_cur, d_z_prev, d_x, d_fresh, d_pos0, iter,
+  return couple_draft_impl(c, static_cast<char*>(base), cands, d_z_cur, d_z_prev, d_x, d_fresh, d_pos0, iter,
                            d_y, d_k);
 }
 
@@ -437,11 +376,9 @@ int scd_verify(scd_ctx* c, const uint8_t* d_k, const int32_t* d_y, const int32_t
                int32_t* d_accept_len, int32_t* d_out) {
   if (!c || !d_k || !d_y || !d_pos0 || !d_accept_len || !d_out) return SCD_EINVAL;
   scd::CommitArgs a{};
-  a.k = d_k; a.y = d_y; a.pos = const_cast<int32_t*>(d_pos0);
+  a.k = d_k; a.y = d_y; a.pos = d_pos0;
   a.accept_len = d_accept_len; a.out = d_out;
-  a.slide = 0;
-  a.B = c->cfg.B; a.L = c->cfg.L; a.N = c->cfg.N; a.n = c->n; a.v_lo = c->cfg.v_lo;
-  a.seed = c->cfg.seed;
+  a.B = c->cfg.B; a.L = c->cfg.L; a.N = c->cfg.N; a.v_lo = c->cfg.v_lo;
   return hip_rc(scd::launch_commit(a, c->stream));
 }
 

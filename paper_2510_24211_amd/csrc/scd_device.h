@@ -58,6 +58,14 @@ __device__ __forceinline__ float key_to_float(uint32_t k) {
 // key with -0 folded onto +0, so that key order == float order for non-NaNs
 __device__ __forceinline__ uint32_t zkey(float f) { return float_to_key(f == 0.f ? 0.f : f); }
 
+// Four neighbouring floats in one 16-byte load from any 4-byte-aligned address (rows of odd length
+// start at such addresses): global memory needs dword alignment only.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4(const float* p) {
+  const f32x4_u v = *reinterpret_cast<const f32x4_u*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // ---- wavefront collectives ---------------------------------------------------------
 // Lane exchanges through the vector ALU's data-parallel primitives (DPP) and v_readlane:
 // no round trip through the LDS crossbar, which a shuffle costs.  All of them must be

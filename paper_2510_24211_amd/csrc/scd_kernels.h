@@ -38,49 +38,11 @@ int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap);
 // emit per-tile candidates, else 0 (only B, C, L, d, n are read).
 int lm_head_tiles(const LmHeadArgs& a);
 
-// ---- top-k threshold + softmax normaliser -------------------------------
-struct SelectArgs {
-  const float* z;       // rows of n floats
-  size_t parity_stride; // floats between the two halves (ring mode)
-  const int32_t* pos;   // ring mode: [B]; null => plain mode, row r at z + r*n
-  const int32_t* iter;  // ring mode: [B]
-  float* thr;           // plain: [rows]; ring: [2, B, L]
-  float* lse;
-  int32_t* nkept;
-  int32_t* flags;       // numeric-fault bits (may be null)
-  int rows;             // plain mode: number of rows; ring mode: B*L
-  int B, L, N, n, top_k;
-};
-hipError_t launch_select(const SelectArgs& a, hipStream_t s);
-
-// ---- vectorised Modified Rejection Sampling ------------------------------
-struct MrsArgs {
-  const float* z_cur;   // plain: [B, L, n]; ring: base of [2, B, L, n]
-  const float* z_prev;  // plain: [B, L, n]; ring: unused
-  size_t parity_stride; // ring: floats between the halves of z
-  const float* thr_cur; // plain: [B*L];   ring: base of [2, B, L]
-  const float* lse_cur;
-  const float* thr_prev;
-  const float* lse_prev;
-  const int32_t* x;     // plain: [B, L] window order; ring: [B, L] by slot
-  const uint8_t* fresh; // plain: [B, L] or null
-  const int32_t* age;   // ring: [B, L] by slot (fresh <=> age == 0)
-  const int32_t* pos;   // [B]
-  const int32_t* iter;  // ring: [B]; plain: null (iter_scalar is used)
-  int iter_scalar;
-  int ring;
-  int32_t* y;           // [B, L] window order
-  uint8_t* k;           // [B, L] window order
-  float* px;            // [B, L] or null
-  float* qx;            // [B, L] or null
-  int B, L, N, n;
-  uint64_t seed;
-};
-hipError_t launch_mrs(const MrsArgs& a, hipStream_t s);
-
 // ---- fused row kernel: select + softmax + MRS (+ commit by the last arriver) --
 enum { kRowSelectOnly = 0, kRowPlain = 1, kRowRing = 2 };
-constexpr int kRowKernelMaxN = 65536;   // the LDS copy of the key prefixes must fit
+// longest row whose key prefixes fit LDS; longer ones run the LONG instance (top-k and the maximal
+// coupling only)
+constexpr int kRowKernelMaxN = 65536;
 struct RowArgs {
   int mode;
   const float* z_cur;    // select-only: [rows, n]; plain: [B, L, n]; ring: base of [2, B, L, n]
@@ -127,7 +89,7 @@ struct RowArgs {
   int32_t* xhist;        // [3, B, L] drafts at the start of the last three iterations, by ring slot
   int32_t* phist;        // [3, B]    window start of those iterations (far negative: none)
   uint64_t seed;
-  // scratch for the slice kernel (rows longer than 8192 ids): row_candidate_bytes(rows)
+  // scratch for the slice kernel (rows longer than 16384 ids): row_candidate_bytes(rows)
   // bytes of device memory, 256-byte aligned, or null (then rows are processed whole)
   void* cand_base;
   // tiles > 0: the LM head's epilogue has already filled the candidate scratch with `tiles`
@@ -155,20 +117,14 @@ hipError_t launch_row(const RowArgs& a, hipStream_t s, size_t* lds_configured);
 constexpr int kRowBatchedMaxN = 8192;
 hipError_t launch_row_batched(const RowArgs& a, hipStream_t s, size_t* lds_configured);
 
-// ---- first rejection, emit, slide -----------------------------------------
+// ---- first rejection and emission on their own (scd_verify) -----------------
 struct CommitArgs {
   const uint8_t* k;     // [B, L]
   const int32_t* y;     // [B, L]
-  int32_t* pos;         // [B]  (read; advanced only when slide != 0)
-  int32_t* iter;        // [B]  (slide only)
-  int32_t* X;           // [B, L] ring (slide only)
-  int32_t* age;         // [B, L] ring (slide only)
-  int32_t* verified;    // [B] (slide only)
+  const int32_t* pos;   // [B]
   int32_t* accept_len;  // [B]
   int32_t* out;         // [B, N]
-  int slide;
-  int B, L, N, n, v_lo;
-  uint64_t seed;
+  int B, L, N, v_lo;
 };
 hipError_t launch_commit(const CommitArgs& a, hipStream_t s);
 
