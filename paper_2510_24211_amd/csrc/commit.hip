@@ -1,7 +1,6 @@
 // First rejection and emission on their own (appendix "Algorithms", Alg. SCD(pi_MC):
 // "find first rejection index"; inside an iteration the row kernel does both and slides
-// the window), plus the state initialisation ("p <- Random(), X ~ p": uniform initial drafts) and the
-// copy of caller-supplied logits into the ring.
+// the window), plus the state initialisation ("p <- Random(), X ~ p": uniform initial drafts).
 //
 // Window of exactly L positions [i, i+L) clipped to N (Lw live rows).  With the
 // first rejection at window offset r the step emits a = min(r+1, Lw) tokens
@@ -55,17 +54,6 @@ __global__ void reset_kernel(const ResetArgs a) {
   if (gid < 4) a.flags[gid] = 0;
 }
 
-__global__ void copy_in_kernel(const CopyInArgs a) {
-  const int r = blockIdx.x;
-  const int b = r / a.L, s = r % a.L;
-  const int p0 = a.pos[b];
-  if (s >= min(a.L, a.N - p0)) return;
-  const float* src = a.src + static_cast<size_t>(r) * a.n;
-  float* dst = a.z + static_cast<size_t>(a.iter[b] & 1) * a.parity_stride +
-               (static_cast<size_t>(b) * a.L + (p0 + s) % a.L) * a.n;
-  for (int v = threadIdx.x; v < a.n; v += blockDim.x) dst[v] = src[v];
-}
-
 }  // namespace
 
 hipError_t launch_commit(const CommitArgs& a, hipStream_t s) {
@@ -76,11 +64,6 @@ hipError_t launch_commit(const CommitArgs& a, hipStream_t s) {
 
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(reset_kernel, dim3(256), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_copy_in(const CopyInArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(copy_in_kernel, dim3(a.B * a.L), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

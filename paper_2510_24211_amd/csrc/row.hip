@@ -34,6 +34,9 @@
 // slice kernel and the candidate path like the others.  32 rows of 131072 ids under top-k 2000: 16 us +
 // 18 us, where one kernel per stage (radix select over the row, MRS, commit) took 124 + 64 + 5 us.
 // Their complete path (long_path) makes whole passes over the row in memory.
+// Logits supplied by the caller (a.src) are copied into the ring by whichever kernel reads them first; a
+// copy kernel of its own took 66 us for 32 rows of 65536 ids (32 workgroups, 4-byte accesses), more than
+// twice the rest of the iteration (9 + 19 us), and one of two launches of 6.8 us each for short rows.
 // The K-th largest key is always found by integer counting (LDS histograms
 // whose bins adapt to the key range, so lanes rarely collide); all
 // floating-point sums use a fixed assignment of ids to threads and a fixed
@@ -432,6 +435,7 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
 struct RowRef {
   const float* zc;
   const float* zp;
+  float* zw;      // supplied logits: the ring row that takes a copy of zc, else null
   float thr_p, lse_p;
   bool fresh, active;
   int x, b, s, p0, live, it;
@@ -473,7 +477,9 @@ __device__ __forceinline__ RowRef locate_row(const RowArgs& a, int r, const int3
     R.pidx = (par ^ 1) * half + sidx;
     R.x = a.x[sidx];
     R.fresh = a.age[sidx] == 0;
-    R.zc = a.z_cur + static_cast<size_t>(par) * a.parity_stride + sidx * n;
+    float* const ring = const_cast<float*>(a.z_cur) + static_cast<size_t>(par) * a.parity_stride + sidx * n;
+    R.zc = a.src ? a.src + R.widx * n : ring;
+    R.zw = a.src ? ring : nullptr;
     R.zp = a.z_cur + static_cast<size_t>(par ^ 1) * a.parity_stride + sidx * n;
     if (!R.fresh) {
       R.thr_p = a.thr[(par ^ 1) * half + sidx];
@@ -541,6 +547,15 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
     for (int e = 0; e < 4; ++e) {
       vid[u * 4 + e] = v0 + e;
       ok[u * 4 + e] = v0 + e < hi_id;
+    }
+    if (R.zw) {
+      if (v0 + 3 < hi_id) {
+        store4(R.zw + v0, zv[u * 4], zv[u * 4 + 1], zv[u * 4 + 2], zv[u * 4 + 3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v0 + e < hi_id) R.zw[v0 + e] = zv[u * 4 + e];
+      }
     }
   }
   uint32_t kv[PS], kmax = 0, kmin = 0xFFFFFFFFu;
@@ -899,6 +914,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + static_cast<size_t>(n8) * 2 + NBINS * 4);
   const float* zc = R.zc;
   const float* zp = R.zp;
+  float* const zw = a.cand ? nullptr : R.zw;     // the slice kernel has made the copy already
 
   // pass 1: batches of 8 independent 16-byte loads per thread
   const bool vec_ok = (n & 3) == 0;
@@ -938,6 +954,15 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
           }
         }
         *reinterpret_cast<uint2*>(&k16[v0]) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+        if (zw) {
+          if (v0 + 3 < n) {
+            store4(zw + v0, f[u][0], f[u][1], f[u][2], f[u][3]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (v0 + e < n) zw[v0 + e] = f[u][e];
+          }
+        }
       }
     }
   }
@@ -1248,8 +1273,10 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
 
 // Rows of more than kRowKernelMaxN ids whose candidates were not certified, or that have none
 // (no top-k, or one too large for the lists): whole passes over the row in memory -- the key prefixes
-// of full_path would not fit LDS.  Bound by what one CU can load (about 10 us per pass over 131072
-// ids, 2 to 4 passes); in the decode it serves the rare row only.
+// of full_path would not fit LDS.  Bound by the vector instructions of one CU, 30 to 40 us per pass
+// over 131072 ids: three passes without a filter (111 us; 137 us as three kernels of one stage each),
+// four with a top-k of 5000 (148 us; 200 us).  Odd rows are read with 16-byte loads too (100003 ids
+// without a filter: 87 us against 121 us with 4-byte loads).
 __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, unsigned char* smem, float zcx,
                                           float zpx, Small& sm, RowOut& out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1293,7 +1320,17 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   uint32_t kmax = 0, kmin = 0xFFFFFFFFu;
   {
     float hi = -INFINITY, lo = INFINITY, nan = 0.f;
-    groups(-INFINITY, [&](int, const float (&z)[4]) {
+    float* const zw = a.cand ? nullptr : R.zw;               // the slice kernel has made the copy already
+    groups(-INFINITY, [&](int v0, const float (&z)[4]) {
+      if (zw) {
+        if (v0 + 3 < n) {
+          store4(zw + v0, z[0], z[1], z[2], z[3]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (v0 + e < n) zw[v0 + e] = z[e];
+        }
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         hi = fmaxf(hi, z[e]);
@@ -1491,6 +1528,19 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, u
     for (int e = 0; e < 4; ++e) {
       vid[u * 4 + e] = v0 + e;
       ok[u * 4 + e] = v0 + e < n;
+    }
+  }
+  if (R.zw) {                                  // supplied logits: keep them for the next iteration
+#pragma unroll
+    for (int u = 0; u < PER / 4; ++u) {
+      const int v0 = (tid + u * THREADS) << 2;
+      if (v0 + 3 < n) {
+        store4(R.zw + v0, zv[u * 4], zv[u * 4 + 1], zv[u * 4 + 2], zv[u * 4 + 3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v0 + e < n) R.zw[v0 + e] = zv[u * 4 + e];
+      }
     }
   }
   uint32_t* cid = hist + NBINS;

@@ -145,14 +145,16 @@ inline T* field(const scd_ctx* c, void* st, int f) {
 inline int hip_rc(hipError_t e) { return e == hipSuccess ? SCD_OK : SCD_EHIP; }
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-int run_tail(scd_ctx* c, void* st, int tiles = 0) {
-  // z of this iteration is in place in the ring.
+// Everything after the LM head.  tiles > 0: it has left its candidate lists; z of this iteration is in
+// place in the ring, or at `src` in window order.
+int run_tail(scd_ctx* c, void* st, int tiles, const float* src) {
   const size_t half = static_cast<size_t>(c->cfg.B) * c->cfg.L * c->n;
   // one fused launch: select + softmax + MRS per row, commit by each sequence's last row
   scd::RowArgs ra{};
   ra.alpha = 1.0f;
   ra.mode = scd::kRowRing;
   ra.z_cur = field<float>(c, st, SCD_F_Z);
+  ra.src = src;
   ra.parity_stride = half;
   ra.thr = field<float>(c, st, SCD_F_THR);
   ra.lse = field<float>(c, st, SCD_F_LSE);
@@ -415,7 +417,7 @@ int scd_step(scd_ctx* c, const uint16_t* d_h, const uint16_t* d_W, void* st) {
   if (hipError_t e = scd::launch_lm_head(a, c->stream, timed ? c->ev_start : nullptr, timed ? c->ev_stop : nullptr);
       e != hipSuccess)
     return SCD_EHIP;
-  return run_tail(c, st, tiles);
+  return run_tail(c, st, tiles, nullptr);
 }
 
 int scd_set_lm_head_events(scd_ctx* c, void* ev_start, void* ev_stop) {
@@ -435,15 +437,7 @@ int scd_lm_head_kernel_name(scd_ctx* c, char* host_buf, size_t cap) {
 
 int scd_step_logits(scd_ctx* c, const float* d_z, void* st) {
   if (!c || !d_z || !st || !aligned(st, kAlign)) return SCD_EINVAL;
-  scd::CopyInArgs a{};
-  a.src = d_z;
-  a.z = field<float>(c, st, SCD_F_Z);
-  a.parity_stride = static_cast<size_t>(c->cfg.B) * c->cfg.L * c->n;
-  a.pos = field<int32_t>(c, st, SCD_F_POS);
-  a.iter = field<int32_t>(c, st, SCD_F_ITER);
-  a.B = c->cfg.B; a.L = c->cfg.L; a.N = c->cfg.N; a.n = c->n;
-  if (hipError_t e = scd::launch_copy_in(a, c->stream); e != hipSuccess) return SCD_EHIP;
-  return run_tail(c, st);
+  return run_tail(c, st, 0, d_z);
 }
 
 int scd_status(scd_ctx* c, void* st, int32_t host_flags[4]) {

@@ -65,6 +65,9 @@ __device__ __forceinline__ float4 load4(const float* p) {
   const f32x4_u v = *reinterpret_cast<const f32x4_u*>(p);
   return make_float4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ void store4(float* p, float a, float b, float c, float d) {
+  *reinterpret_cast<f32x4_u*>(p) = f32x4_u{a, b, c, d};
+}
 
 // ---- wavefront collectives ---------------------------------------------------------
 // Lane exchanges through the vector ALU's data-parallel primitives (DPP) and v_readlane:

@@ -47,6 +47,10 @@ struct RowArgs {
   int mode;
   const float* z_cur;    // select-only: [rows, n]; plain: [B, L, n]; ring: base of [2, B, L, n]
   const float* z_prev;   // plain: [B, L, n]
+  // ring mode with logits supplied by the caller: [B, L, n] in window order, read instead of the ring
+  // and copied into it on the way (by the slice kernel where it runs, else by the row kernel);
+  // null: this iteration's logits are in the ring
+  const float* src;
   size_t parity_stride;  // ring: floats between the halves of z
   float* thr;            // select-only / plain: [rows]; ring: [2, B, L] (both parities)
   float* lse;
@@ -128,7 +132,7 @@ struct CommitArgs {
 };
 hipError_t launch_commit(const CommitArgs& a, hipStream_t s);
 
-// ---- state initialisation / logits copy-in --------------------------------
+// ---- state initialisation ---------------------------------------------------
 struct ResetArgs {
   int32_t* pos; int32_t* iter; int32_t* X; int32_t* age; int32_t* out; int32_t* accept_len;
   int32_t* verified; int32_t* flags; int32_t* ticket;
@@ -137,14 +141,5 @@ struct ResetArgs {
   uint64_t seed;
 };
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s);
-
-struct CopyInArgs {
-  const float* src;     // [B, L, n] window order
-  float* z;             // [2, B, L, n]
-  size_t parity_stride;
-  const int32_t* pos; const int32_t* iter;
-  int B, L, N, n;
-};
-hipError_t launch_copy_in(const CopyInArgs& a, hipStream_t s);
 
 }  // namespace scd
