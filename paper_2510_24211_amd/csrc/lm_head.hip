@@ -6,36 +6,30 @@
 // Only the allowed vocabulary rows of W are streamed (the mask to -inf of the
 // other ids is realised by never forming their columns).
 //
-// gfx950 mapping.  The contraction is skinny: M = B*C*L rows (32..1024) against
-// n = |allowed| columns (8k..64k) over d = 1k..4k, i.e. a stream over W that
-// must keep many bytes in flight per CU and must not stall on barriers.
-//   * A wavefront owns 32 vocabulary rows of W.  It fetches its own slab with
-//     coalesced 16-byte loads (8 lanes cover one 128-byte row segment), D k-tiles
-//     ahead in registers, parks a tile in a wavefront-PRIVATE LDS region (pitch
-//     144 bytes against bank conflicts) and reads it back in the operand layout
-//     of v_mfma_f32_32x32x16_bf16 (lane l: row l%32, k-group l/32, 8 consecutive
-//     k).  Private staging needs no workgroup barrier, so the wavefronts of a
-//     workgroup drift apart and the W stream never drains.
-//   * The NW wavefronts of a workgroup take NW x 32 neighbouring columns and
-//     SHARE the h tile through LDS (double buffered, loaded two tiles ahead, one
-//     barrier per h tile): h comes out of L2 once per workgroup, not per wavefront.
-//   * The accumulators of a wavefront are RBW "row blocks" x C tiles: a row block
-//     is 32 window positions of one sequence, its cond and uncond tiles live in
-//     the SAME lanes, so the guidance mix needs no data movement.
-//   * Every workgroup walks k cyclically from its own starting tile: rows of W
-//     are d*2 bytes apart, and without the rotation all wavefronts of the chip
-//     ask for the same address bits at the same time and camp on a few channels.
-//   * Narrow vocabularies give too few 128-column tiles to fill 256 CUs.  They use
-//     lm_head_splitk_kernel: a workgroup owns 32 columns, its KS wavefronts take a
-//     1/KS part of k each, stage their own h tiles privately as well (no barrier in
-//     the loop), and their partial sums are added in wavefront order through LDS at
-//     the end (a fixed order: deterministic).
+// gfx950 mapping.  The contraction is skinny: M = B*C*L rows (1..1024) against n = |allowed| columns
+// (1k..128k) over d = 1k..4k: a stream over W for few rows, a GEMM for many.  choose() picks among
+//   * lm_head_tile_kernel: LDS-staged tiles fed by LDS-direct loads (see there); most shapes.
+//   * lm_head_splitk_kernel (few rows, few columns): a workgroup owns only 32 columns, so that enough of
+//     them exist; its KS wavefronts take a 1/KS part of k each and stage their own W and h tiles
+//     PRIVATELY: coalesced 16-byte loads (8 lanes cover one 128-byte row segment), D k-tiles ahead in
+//     registers, parked in LDS (pitch 144 bytes against bank conflicts) and read back in the operand layout
+//     of v_mfma_f32_32x32x16_bf16 (lane l: row l%32, k-group l/32, 8 consecutive k); no barrier in the loop.
+//     The partial sums are added in wavefront order through LDS at the end (a fixed order: deterministic).
+//   * lm_head_kernel (32 rows without guidance on long streams; tiny d): NW wavefronts take 32 neighbouring
+//     columns each with private W staging as above and SHARE the h tile through LDS (double buffered, one
+//     barrier per h tile).
+// Common to all: window rows are packed into blocks of 32 (p = b * L + s), a block's cond and uncond tiles
+// live in the same lanes, so the guidance mix needs no data movement; every workgroup walks k cyclically
+// from its own starting tile: rows of W are d*2 bytes apart, and without the rotation all of the chip asks for
+// the same address bits at the same time and camps on a few channels.
 #include "scd_device.h"
 #include "scd_kernels.h"
 
 #include <hip/hip_ext.h>
 
 #include <stdio.h>
+
+#include <utility>
 
 namespace scd {
 namespace {
@@ -111,33 +105,42 @@ struct Cfg {
   static constexpr int LDS_BYTES = (W_LDS + H_LDS) * 2;
 };
 
-// Where the 32 window positions of row block rb (sequence b, positions sbase..sbase+31 of
-// its window) are stored: ring slot (pos[b] + s) % L of half iter[b] & 1 when the decode
-// state is given, row s otherwise.
-struct RowBlockDst {
-  float* zb;
-  int b, sbase, p0, live;
-  int lmask;    // L - 1 if L is a power of two (ring slot by masking), else -1 (by division)
+// Window rows are packed: row p = b * L + s of the B * L rows, blocks of 32 whatever the window length.
+// row_dest: where window row p is stored, as a row of z [2, B, L] (ring slot (pos[b] + s) % L of half
+// iter[b] & 1 when the decode state is given, else row p), or -1 if it is not live.  The kernels leave it
+// in a table in LDS.  The two words of the state are fetched ahead of everything else and without a branch
+// (from h where there is no state), so that nothing waits for them before they are used.
+struct RowState {
+  int p, b, p0, it;
 };
-__device__ __forceinline__ RowBlockDst row_block_dst(const LmHeadArgs& a, int rb, int nLb) {
-  RowBlockDst r;
-  r.b = rb / nLb;
-  r.sbase = (rb % nLb) * 32;
-  r.p0 = 0;
-  r.live = a.L;
-  r.zb = a.z;
-  if (a.pos) {
-    r.p0 = a.pos[r.b];
-    r.live = min(a.L, a.N - r.p0);
-  }
-  if (a.iter) r.zb += static_cast<size_t>(a.iter[r.b] & 1) * a.parity_stride;
-  r.lmask = (a.L & (a.L - 1)) == 0 ? a.L - 1 : -1;
+__device__ __forceinline__ RowState row_state(const LmHeadArgs& a, int p) {
+  const int q = min(p, a.B * a.L - 1);
+  RowState r{p, q / a.L, 0, 0};
+  const int32_t* const any = reinterpret_cast<const int32_t*>(a.h);
+  r.p0 = (a.pos ? a.pos : any)[a.pos ? r.b : 0];
+  r.it = (a.iter ? a.iter : any)[a.iter ? r.b : 0];
   return r;
 }
-// Ring slot of window position s (an integer division per logit otherwise: 16 of them per lane)
-__device__ __forceinline__ int ring_slot(const LmHeadArgs& a, const RowBlockDst& r, int s) {
-  if (!a.pos) return s;
-  return r.lmask >= 0 ? ((r.p0 + s) & r.lmask) : (r.p0 + s) % a.L;
+__device__ __forceinline__ int row_dest(const LmHeadArgs& a, const RowState& r) {
+  if (r.p >= a.B * a.L) return -1;
+  if (!a.pos) return r.p;
+  const int s = r.p - r.b * a.L, par = a.iter ? (r.it & 1) : 0;
+  return s < a.N - r.p0 ? (par * a.B + r.b) * a.L + (r.p0 + s) % a.L : -1;
+}
+// h row (of [B, C, L]) of row r < 32 of the block that starts at window row p0 (uniform; the last row where
+// there is none: its results are not stored).  Windows of 32 or more positions end at most once in a block.
+__device__ __forceinline__ int h_row(int p0, int r, int c, int C, int L, int rows) {
+  int b = p0 / L, s = p0 - b * L + min(r, rows - 1 - p0);
+  if (L >= 32) {
+    const bool next = s >= L;
+    b += next ? 1 : 0;
+    s -= next ? L : 0;
+  } else {
+    const int w = s / L;
+    b += w;
+    s -= w * L;
+  }
+  return (b * C + c) * L + s;
 }
 
 // Guidance mix and temperature of one logit (cond sum c, uncond sum u): three fp32 roundings
@@ -148,175 +151,151 @@ __device__ __forceinline__ float processed_logit(const LmHeadArgs& a, float c, f
   if (C == 2) z = __fsub_rn(__fmul_rn(a.one_plus_lam, c), __fmul_rn(a.lam, u));
   return a.tau == 1.0f ? z : __fdiv_rn(z, a.tau);
 }
-// Stores processed logit z of window position s and allowed id v.
-__device__ __forceinline__ void store_z(const LmHeadArgs& a, const RowBlockDst& r, int s, int v, float z) {
-  if (s >= r.live) return;
-  // the sequence's part of the address is uniform (scalar unit); slot * n + v fits 32 bits
-  // (L * n < 2^31 is checked when the context is created)
-  float* const zseq = r.zb + static_cast<size_t>(r.b) * a.L * a.n;
-  zseq[static_cast<uint32_t>(ring_slot(a, r, s)) * static_cast<uint32_t>(a.n) + static_cast<uint32_t>(v)] = z;
-}
-template <int C>
-__device__ __forceinline__ void store_logit(const LmHeadArgs& a, const RowBlockDst& r, int s, int v,
-                                            float c, float u) {
-  store_z(a, r, s, v, processed_logit<C>(a, c, u));
-}
-
 // Epilogue of a wavefront that holds whole sums.  Element j of lane (ln, lg) is row
 // (j/4)*8 + lg*4 + j%4, column ln of the 32x32 tile.  zout takes the processed logits.
-// rbd[rbw]: where row block rb0 + rbw goes (fetched at kernel start: window start and iteration
-// parity come from memory, and the epilogue should not begin with that round trip).
+// table: row_dest of the workgroup's RBW * 32 window rows.
 template <int RBW, int C>
-__device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc)[RBW * C], int nRB, int rb0,
-                                         const RowBlockDst (&rbd)[RBW], int v, int lg, float (&zout)[RBW][16]) {
-#pragma unroll
-  for (int rbw = 0; rbw < RBW; ++rbw)
-#pragma unroll
-    for (int j = 0; j < 16; ++j) zout[rbw][j] = processed_logit<C>(a, acc[rbw * C][j], acc[rbw * C + C - 1][j]);
-  if (v >= a.n) return;
+__device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc)[RBW * C], const int* table, int v,
+                                         int lg, float (&zout)[RBW][16]) {
 #pragma unroll
   for (int rbw = 0; rbw < RBW; ++rbw) {
-    if (rb0 + rbw >= nRB) break;
-    const RowBlockDst& r = rbd[rbw];
+    int4 to[4];
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
-      store_z(a, r, r.sbase + (j >> 2) * 8 + lg * 4 + (j & 3), v, zout[rbw][j]);
+    for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[rbw * 32 + g * 8 + lg * 4]);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int4 t = to[j >> 2];
+      const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
+      zout[rbw][j] = processed_logit<C>(a, acc[rbw * C][j], acc[rbw * C + C - 1][j]);
+      if (row >= 0 && v < a.n) a.z[static_cast<int64_t>(row) * a.n + v] = zout[rbw][j];
+    }
   }
 }
 
 // ---- per-tile top-k candidates (first half of the top-k selection, fused into the epilogue) ----
-// A workgroup that owns 256 neighbouring columns parks its processed logits in LDS as a tile
-// zt[row][kTilePitch] and every wavefront then reduces some rows of it: of the row's 256
-// logits it emits the `cap` largest as (id, logit) pairs in a FIXED order (lane, then column),
-// their number, and the cut = the smallest emitted logit (as a key): every logit of the tile row
-// that was not emitted lies strictly below it.  The row kernel selects the K-th largest among the
-// emitted logits of all tiles and accepts it only if it is not below any tile's cut (then no
+// A workgroup that owns COLS = 256 or 128 neighbouring columns parks its processed logits in LDS as a tile
+// zt[row][COLS + 8] and every wavefront then reduces some rows of it: of the row's COLS
+// logits it emits the `cap` largest or a few less as (id, logit) pairs in a FIXED order (column within
+// the lane, then lane), their number, and the cut = the smallest emitted logit (as a key): every logit of
+// the tile row that was not emitted lies strictly below it.  The row kernel selects the K-th largest
+// among the emitted logits of all tiles and accepts it only if it is not below any tile's cut (then no
 // logit that was not emitted can reach it): exact, and certified per row.
-//   The emitted set is found by bisection, not on the logits themselves but on a monotone
-// 12-bit fixed-point image of them, q = trunc(1 + (z - min) * 4095 / (max - min)) (equal q:
-// both emitted or neither).  Then the halving runs on the scalar unit (integer bounds in
-// SGPRs); the vector unit only compares, one instruction per logit and halving, and wave
-// ballots + population counts do the counting.  13 steps end exactly at the smallest q whose
-// upper set holds at most `cap` logits.  If more than `cap` logits share the top q (massive
-// ties, or a non-finite logit, which collapses the image) the tile reports an overflowing count
-// and the row kernel reads the row whole.
-constexpr int kTileCols = 256;
-constexpr int kTilePitch = kTileCols + 8;   // floats; rows 4 apart fall into disjoint banks
-constexpr int kTileQBits = 12;
+//   The emitted set is found on a monotone 8-bit image of the logits, linear between the row's smallest
+// and largest (equal images: both emitted or neither), by counting it: one LDS histogram of 256 bins per
+// row, four per lane, a prefix sum over the lanes, and the lowest bin whose upper set holds at most
+// `cap` logits (a bin near the cut holds about one logit, so 23 to 24 of 24 slots are used).  If more than
+// `cap` logits share the top image (massive ties, or a non-finite logit, which collapses the image) the
+// tile reports an overflowing count and the row kernel reads the row whole.
+//   Bound by the vector and LDS instructions of a CU (about 100 per row).  A bisection on a 12-bit image
+// with wave ballots, 13 steps of about ten scalar operations per row, waited for the one scalar unit of
+// the CU: two sequences x 64 positions x 64000 ids, 16 rows per wavefront, 26 us against 18 us now; one
+// sequence x 32 x 65536, 4 rows per wavefront, 7 us against 3 us.
+constexpr int kTilePad = 8;                 // floats: rows 4 apart fall into disjoint banks
+constexpr int kTileBins = 256;
+constexpr int kTileRows = 2;                // rows that a wavefront reduces side by side
+constexpr int kTileHist = kTileRows * kTileBins * 4;   // LDS bytes per wavefront
 
-// Rows q0 .. q0 + 3 of the tile; wrow[i] = window row index (b * L + s) of tile row q0 + i, or -1
+// Rows q0, q0 + 1 of the tile; wrow[i] = window row index (b * L + s) of tile row q0 + i, or -1
 // if it is not a live window row; v0 = id of the tile's first column; tile / T = its index and the
-// number of tiles per row.  Uniform over the wavefront.
-__device__ __forceinline__ void tile_candidates4(const LmHeadArgs& a, const float* zt, int lane, int q0,
-                                                 const int (&wrow)[4], int v0, int tile, int T) {
+// number of tiles per row.  Uniform over the wavefront.  hist: kTileHist bytes of this wavefront's own.
+template <int COLS>
+__device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, const float* zt, uint32_t* hist, int lane,
+                                                int q0, const int (&wrow)[kTileRows], int v0, int tile, int T) {
   const int cap = a.cand_cap;
-  const int nvalid = min(kTileCols, a.n - v0);           // columns of this tile that exist
-  constexpr uint32_t QMAX = (1u << kTileQBits) - 1u;
-  const bool ragged = nvalid < kTileCols;                // only the last tile of a row
-  bool ok[4];
+  constexpr int E = COLS / 64;                           // logits per lane
+  const int nvalid = min(COLS, a.n - v0);                // columns of this tile that exist
+  const bool ragged = nvalid < COLS;                     // only the last tile of a row
+  bool ok[E];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) ok[e] = 4 * lane + e < nvalid;
-  float v[4][4];
-  uint32_t q[4][4];                                      // 0 .. QMAX + 2; 0 also for a column that does not exist
+  for (int e = 0; e < E; ++e) ok[e] = E * lane + e < nvalid;
+  float v[kTileRows][E];
+  int q[kTileRows][E];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float4 t = *reinterpret_cast<const float4*>(&zt[(q0 + i) * kTilePitch + 4 * lane]);
-    v[i][0] = t.x; v[i][1] = t.y; v[i][2] = t.z; v[i][3] = t.w;
+  for (int i = 0; i < kTileRows; ++i) {
+    const float* const src = &zt[(q0 + i) * (COLS + kTilePad) + E * lane];
+    if constexpr (E == 4) {
+      const float4 t = *reinterpret_cast<const float4*>(src);
+      v[i][0] = t.x; v[i][1] = t.y; v[i][2] = t.z; v[i][3] = t.w;
+    } else {
+      const float2 t = *reinterpret_cast<const float2*>(src);
+      v[i][0] = t.x; v[i][1] = t.y;
+    }
+    *reinterpret_cast<uint4*>(&hist[i * kTileBins + 4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float mx, mn;
-    if (!ragged) {
-      mx = fmaxf(fmaxf(v[i][0], v[i][1]), fmaxf(v[i][2], v[i][3]));
-      mn = fminf(fminf(v[i][0], v[i][1]), fminf(v[i][2], v[i][3]));
-    } else {
-      mx = -INFINITY;
-      mn = INFINITY;
+  for (int i = 0; i < kTileRows; ++i) {
+    float mx = -INFINITY, mn = INFINITY, sum = 0.f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[i][e] = ok[e] ? v[i][e] : 0.f;
-        mx = ok[e] ? fmaxf(mx, v[i][e]) : mx;
-        mn = ok[e] ? fminf(mn, v[i][e]) : mn;
-      }
+    for (int e = 0; e < E; ++e) {
+      if (ragged) v[i][e] = ok[e] ? v[i][e] : 0.f;
+      mx = !ragged || ok[e] ? fmaxf(mx, v[i][e]) : mx;
+      mn = !ragged || ok[e] ? fminf(mn, v[i][e]) : mn;
+      sum += v[i][e];
     }
-    // a NaN (or +inf next to -inf) among the four poisons their sum
-    const float sum4 = (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
-    if (sum4 != sum4 && a.flags && wrow[i] >= 0) atomicOr(a.flags, 1);
+    // a NaN (or +inf next to -inf) among the lane's logits poisons their sum
+    if (sum != sum && a.flags && wrow[i] >= 0) atomicOr(a.flags, 1);
     const float hi = wave_max_f32(mx), lo = wave_min_f32(mn);
-    // q = trunc(1 + (z - lo) * scale), one fused multiply-add per logit: monotone in z.  For
-    // non-finite logits scale / shift degenerate, every q collapses and the tile row reports an
-    // overflow below.
-    const float scale = hi > lo ? __fdiv_rn(static_cast<float>(QMAX), hi - lo) : 0.f;
-    const float shift = 1.0f - lo * scale;
+    // one fused multiply-add per logit: monotone in z.  For non-finite logits scale / shift degenerate,
+    // every image collapses to 0 and the tile row reports an overflow below.
+    const float scale = hi > lo ? __fdiv_rn(static_cast<float>(kTileBins - 1), hi - lo) : 0.f;
+    const float shift = -(lo * scale);
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      q[i][e] = static_cast<int>(fminf(fmaxf(__fmaf_rn(v[i][e], scale, shift), 0.f), static_cast<float>(kTileBins - 1)));
+  }
+  // LDS operations of a wavefront are performed in order: the zeroing above, the counting, the reading
+  compiler_fence();
+#pragma unroll
+  for (int i = 0; i < kTileRows; ++i)
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (!ragged || ok[e]) atomicAdd(&hist[i * kTileBins + q[i][e]], 1u);
+  compiler_fence();
+#pragma unroll
+  for (int i = 0; i < kTileRows; ++i) {
+    const uint4 c4 = *reinterpret_cast<const uint4*>(&hist[i * kTileBins + 4 * lane]);
+    const int c[4] = {static_cast<int>(c4.x), static_cast<int>(c4.y), static_cast<int>(c4.z), static_cast<int>(c4.w)};
+    const int mine = (c[0] + c[1]) + (c[2] + c[3]);
+    int above = nvalid - wave_inclusive_sum_i32(mine, lane) + mine;      // logits in bins >= 4 * lane
+    int cutq = 0;                                        // bins whose upper set holds more than cap logits
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      q[i][e] = static_cast<uint32_t>(fmaxf(__fmaf_rn(v[i][e], scale, shift), 0.f));
-      if (ragged) q[i][e] = ok[e] ? q[i][e] : 0u;
+      cutq += __builtin_popcountll(__builtin_amdgcn_ballot_w64(above > cap));
+      above -= c[e];
     }
-  }
-  // The largest c with #(q >= c) > cap, built bit by bit from the top (q < 2^(kTileQBits + 1)); the
-  // cut is c + 1.  One scalar unit serves the whole compute unit, so the loop is kept to ten scalar
-  // operations per row and step.  #(q >= 0) is the whole tile row: above cap unless the row has at
-  // most cap columns, which is handled apart.
-  uint32_t cq[4] = {0u, 0u, 0u, 0u};
-#pragma unroll 1
-  for (uint32_t bit = 1u << kTileQBits; bit != 0u; bit >>= 1) {
-    // the four rows side by side: all compares first, so that the scalar unit's population
-    // counts do not each wait for a compare of their own
-    unsigned long long m[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m[i][e] = __builtin_amdgcn_ballot_w64(q[i][e] >= cq[i] + bit);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int n = __builtin_popcountll(m[i][0]) + __builtin_popcountll(m[i][1]) +
-                    __builtin_popcountll(m[i][2]) + __builtin_popcountll(m[i][3]);
-      cq[i] = n > cap ? cq[i] + bit : cq[i];
-    }
-  }
-  const unsigned long long below = (1ull << lane) - 1ull;        // lanes before this one
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
     if (wrow[i] < 0) continue;                           // uniform
-    const bool all = nvalid <= cap;                      // the whole tile row is emitted: cut 0
-    const uint32_t cutq = all ? 0u : cq[i] + 1u;
     // emitted logits in the fixed order (column within the lane, then lane)
-    bool take[4];
-    unsigned long long tm[4];
+    bool take[E];
+    int at[E], total = 0;
     float vmin = INFINITY;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < E; ++e) {
       take[e] = q[i][e] >= cutq && (!ragged || ok[e]);
-      tm[e] = __builtin_amdgcn_ballot_w64(take[e]);
+      const unsigned long long m = __builtin_amdgcn_ballot_w64(take[e]);
+      at[e] = total + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+      total += __builtin_popcountll(m);
       vmin = take[e] ? fminf(vmin, v[i][e]) : vmin;
     }
-    const int c0 = __builtin_popcountll(tm[0]), c1 = __builtin_popcountll(tm[1]),
-              c2 = __builtin_popcountll(tm[2]), c3 = __builtin_popcountll(tm[3]);
-    const int total = c0 + c1 + c2 + c3;
-    const int base[4] = {0, c0, c0 + c1, c0 + c1 + c2};
     vmin = wave_min_f32(vmin);                           // smallest emitted logit (NaNs are never smallest)
     const size_t slot = static_cast<size_t>(wrow[i]) * T + tile;
     const bool fits = total > 0 && total <= cap;         // nothing emitted: more than cap tie at the top
     if (fits) {
       uint2* dst = a.cand + (static_cast<size_t>(wrow[i]) * kRowListCap + static_cast<size_t>(tile) * cap);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (take[e])
-          dst[base[e] + __builtin_popcountll(tm[e] & below)] =
-              make_uint2(static_cast<uint32_t>(v0 + 4 * lane + e), __float_as_uint(v[i][e]));
+      for (int e = 0; e < E; ++e)
+        if (take[e]) dst[at[e]] = make_uint2(static_cast<uint32_t>(v0 + E * lane + e), __float_as_uint(v[i][e]));
     }
     if (lane == 0) {
       a.cand_cnt[slot] = fits ? static_cast<uint32_t>(total) : static_cast<uint32_t>(cap) + 1u;   // > cap: overflow
-      a.cand_cut[slot] = all ? 0u : zkey(vmin);
+      a.cand_cut[slot] = cutq == 0 ? 0u : zkey(vmin);    // 0: the whole tile row is emitted
     }
   }
 }
 
 template <int RBW, int C, int NWV, bool NT>
 __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
-    const LmHeadArgs a, const int nLb, const int nRB, const int VT, const int MT, const RowMap rm) {
+    const LmHeadArgs a, const int VT, const int MT, const RowMap rm) {
   using K = Cfg<RBW, C, NWV>;
   constexpr int NBLK = K::NBLK, HROWS = K::HROWS, D = K::D, DH = K::DH, HT = K::HT;
   constexpr int THREADS = K::THREADS;
@@ -332,10 +311,8 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   const int vt = jt * 8 + xcd;
   const int mt = (id / 8) % MT;
   if (mapped_row(rm, xcd, jt, Cfg<RBW, C, NWV>::BN, 0) >= a.n) return;   // no row left for this tile
-  const int rb0 = mt * RBW;
-  RowBlockDst rbd[RBW];
-#pragma unroll
-  for (int rbw = 0; rbw < RBW; ++rbw) rbd[rbw] = row_block_dst(a, min(rb0 + rbw, nRB - 1), nLb);
+  const int p_base = mt * RBW * 32, rows = a.B * a.L;     // first window row; all of them
+  __shared__ __attribute__((aligned(16))) int table[RBW * 32];
 
   const int tid = threadIdx.x;
   const int wave = tid >> 6;
@@ -400,21 +377,17 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   const int hchunk = tid % CH, hr0 = tid / CH;
   const char* const Hb = reinterpret_cast<const char*>(a.h);
   uint32_t hoff[HL];
-  bool hok[HL];
 #pragma unroll
   for (int i = 0; i < HL; ++i) {
-    const int rr = hr0 + RPP * i;                // tile row 0..HROWS-1
-    const int blk = rr >> 5, r = rr & 31;
-    const int rb = rb0 + blk / C, c = blk % C;
-    const int b = rb / nLb, s = (rb % nLb) * 32 + r;
-    hok[i] = rb < nRB && s < a.L;
-    hoff[i] = hok[i] ? static_cast<uint32_t>((b * C + c) * a.L + s) * static_cast<uint32_t>(d) * 2u : 0u;
+    const int rr = hr0 + RPP * i, blk = rr >> 5;  // tile row 0..HROWS-1
+    hoff[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), rr & 31, blk % C, C, a.L, rows)) *
+              static_cast<uint32_t>(d) * 2u;
   }
   u32x4 hreg[DH][HL];
   bool hkok[DH];
   // logical h tile st = logical W tiles st*HT .. st*HT+HT-1; after the rotation these
   // need not be neighbours in k (wrap-around), so every 64-wide part is placed on its own.
-  // Loaded unconditionally from a clamped address, then zeroed where the row or k is not real.
+  // Loaded unconditionally from a clamped address, then zeroed where k is not real.
   auto hload = [&](int slot, int st) {
     bool valid;
     const int kt = ktile(st * HT + hchunk / CHW, valid);
@@ -431,9 +404,8 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
 #pragma unroll
     for (int i = 0; i < HL; ++i) {
       const u32x4 t4 = hreg[slot][i];
-      const bool keep = hok[i] && hkok[slot];
       *reinterpret_cast<u32x4*>(&dst[(hr0 + RPP * i) * K::PITCH_H + hchunk * 8]) =
-          (keep ? t4 : u32x4{0u, 0u, 0u, 0u});
+          (hkok[slot] ? t4 : u32x4{0u, 0u, 0u, 0u});
     }
   };
 
@@ -483,6 +455,7 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   hstore(0, 0);
   hload(1, 1);
   hload(0, 2);
+  const RowState mine = row_state(a, p_base + tid);
   __syncthreads();
   // One pass over D tiles.  The last pass (PF false) issues no load that would fall past
   // the end: such a load would fetch real bytes a second time.
@@ -507,235 +480,404 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
     }
   };
   for (int t0 = 0; t0 < ntiles_pad - D; t0 += D) body(t0, TrueT{});
+  if (tid < RBW * 32) table[tid] = row_dest(a, mine);     // published by the last pass's barriers
   body(ntiles_pad - D, FalseT{});
 
   float zv[RBW][16];
-  epilogue<RBW, C>(a, acc, nRB, rb0, rbd, mapped_row(rm, xcd, jt, K::BN, wave * 32 + ln), lg, zv);
+  epilogue<RBW, C>(a, acc, table, mapped_row(rm, xcd, jt, K::BN, wave * 32 + ln), lg, zv);
 
   if constexpr (RBW == 1 && NWV == 8) {
     // ---- per-tile candidates for the row kernel (a.cand is uniform) --------------------------
-    static_assert(K::BN == kTileCols && K::LDS_BYTES >= 32 * kTilePitch * 4, "logit tile must fit");
+    constexpr int PITCH_Z = K::BN + kTilePad, ZT = 32 * PITCH_Z;   // floats of the logit tile; the histograms follow
+    static_assert(K::BN == 256 && K::LDS_BYTES >= ZT * 4 + NWV * kTileHist, "logit tile must fit");
     if (a.cand == nullptr) return;
     __syncthreads();                       // every wavefront is done with the staging buffers
     float* const zt = reinterpret_cast<float*>(lds_raw);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) zt[((j >> 2) * 8 + lg * 4 + (j & 3)) * kTilePitch + wave * 32 + ln] = zv[0][j];
+    for (int j = 0; j < 16; ++j) zt[((j >> 2) * 8 + lg * 4 + (j & 3)) * PITCH_Z + wave * 32 + ln] = zv[0][j];
     __syncthreads();
-    const RowBlockDst& r = rbd[0];
-    int wrow[4];
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(zt + ZT) + wave * (kTileHist / 4);
+#pragma unroll 1
+    for (int g = 0; g < 4; g += kTileRows) {
+      int wrow[kTileRows];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int s = r.sbase + wave * 4 + i;
-      wrow[i] = (rb0 < nRB && s < r.live) ? r.b * a.L + s : -1;
+      for (int i = 0; i < kTileRows; ++i) {
+        const int row = wave * 4 + g + i;
+        wrow[i] = __builtin_amdgcn_readfirstlane(table[row]) >= 0 ? p_base + row : -1;
+      }
+      tile_candidates<K::BN>(a, zt, hist, lane, wave * 4 + g, wrow, vt * K::BN, vt, VT);
     }
-    tile_candidates4(a, zt, lane, wave * 4, wrow, vt * K::BN, vt, VT);
   }
 }
 
-// Scheduling pattern "one MFMA, then its share of OPS memory-side operations (LDS reads, LDS
-// writes, global loads)", NM times: the counts must be compile-time constants.
-template <int M, int NM, int OPS>
-struct Interleave {
-  static __device__ __forceinline__ void run() {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x320, (OPS * (M + 1)) / NM - (OPS * M) / NM, 0);
-    Interleave<M + 1, NM, OPS>::run();
-  }
-};
-template <int NM, int OPS>
-struct Interleave<NM, NM, OPS> {
-  static __device__ __forceinline__ void run() {}
+// ---- many rows: LDS-staged tiles of HR h rows x BN columns, fed by LDS-direct loads -------------------
+// With more than about 64 h rows per byte of W the matrix pipe carries real load and the work is a GEMM.
+// A workgroup of 8 wavefronts owns HR h rows (HR / C window rows, cond and uncond) x BN columns and walks
+// k in tiles of 64.  What is done against each of the limits that were met:
+//   * Rows are packed: h rows of a tile are HR / C consecutive window rows p = b * L + s whatever the
+//     window length (blocks of 32 per sequence would multiply 37 % padding at L = 20, 75 % at L = 8).
+//   * W and h tiles go from memory straight into LDS (global_load_lds, 16 bytes per lane), SW / SH stages
+//     deep, one to two tiles ahead, so no registers are spent on loads in flight.  A load instruction moves
+//     8 rows of 128 bytes; lane l writes slot l % 8 of row l / 8 (the hardware's fixed layout) and
+//     therefore READS chunk (l % 8) ^ ((row >> 1) & 7): operand reads are then free of bank conflicts
+//     without padding.
+//   * The loads are inline assembly that names no output register: the compiler, which cannot see which
+//     LDS bytes such a load fills, otherwise waits for ALL loads in flight before the next LDS read.  The
+//     waits are written out: s_waitcnt vmcnt counts a wavefront's own loads, the barrier that follows
+//     publishes them to the others.
+//   * One barrier per k-tile, in the middle of the last k-step: when it is passed the next tile is in
+//     LDS, its first operands are read under the last MFMAs of this tile, and the stage just read is free.
+//   * The loads of a tile are issued one by one between MFMAs: eight wavefronts issuing all of theirs after
+//     the barrier queue at the CU's one address unit (16 clocks per instruction) with their MFMAs behind them
+//     (256 x 128 tiles, 64 workgroups: 52 -> 43 us).
+//   * A wavefront multiplies 64 x 128 or 64 x 64 (NC x NB accumulator tiles of 32 x 32): the LDS reads of a
+//     k-tile take less than its MFMAs.
+// What is left is power: with real operands all 256 CUs sustain about 1.45 PFLOP/s (MFMAs alone, operands
+// fixed in registers; 1.9 on zeros), and loads on top share that budget.  Against register-staged kernels:
+// 1024 h rows x 8192 ids over 4096 84 -> 62 us (1.10 PFLOP/s; the vendor GEMM 66), 256 x 64000 148 -> 124
+// without candidates (4.2 TB/s and 1.08 PFLOP/s at once), 128 x 65536 107 -> 88, 64 x 30000 71 -> 44,
+// 120 packed rows x 51285 over 2048 63 -> 42.
+template <int C_, int HR_, int BN_, int S_>
+struct TileCfg {
+  static constexpr int C = C_, HR = HR_, BN = BN_;
+  static constexpr int NW = HR == 64 && BN == 128 ? 4 : 8;                  // wavefronts
+  static constexpr int THREADS = NW * 64;
+  static constexpr int CW = HR * BN <= 128 * 128 ? 32 : 64;                 // columns per wavefront
+  static constexpr int NC = CW / 32;
+  static constexpr int WCOL = BN / CW, WROW = NW / WCOL;
+  static constexpr int RW = HR / WROW;               // h rows per wavefront
+  static constexpr int NB = RW / 32;
+  static constexpr int RB = NB / C;                  // blocks of 32 window rows per wavefront
+  static constexpr int WR = HR / C;                  // window rows per workgroup
+  static constexpr int WL = BN / 8 / NW, HL = HR / 8 / NW;   // loads per wavefront and k-tile
+  static constexpr int WB = BN * 128, HB = HR * 128; // bytes per stage
+  static constexpr int SW = S_, SH = HR == 256 && BN == 256 ? S_ - 1 : S_;   // stages
+  static_assert(SW >= 3 && SH >= 2, "stages");
+  static constexpr int STAGES = SW * WB + SH * HB;
+  // epilogue: row table, then the logit tile of up to 128 window rows and the histograms
+  static constexpr int ZROWS = WR < 128 ? WR : 128;
+  static constexpr int TABLE = 1024;
+  static constexpr int PITCH_Z = BN + kTilePad;
+  static constexpr int EPI = TABLE + ZROWS * PITCH_Z * 4 + NW * kTileHist;
+  static constexpr int LDS_BYTES = STAGES > EPI ? STAGES : EPI;
+  static_assert(WCOL * WROW == NW && NB % C == 0 && WR * 4 <= TABLE && LDS_BYTES <= 160 * 1024, "tile shape");
 };
 
-// ---- exactly 4 row blocks (B * ceil(L / 32) = 4, e.g. 2 sequences x 64 positions or one window
-// of 128): one workgroup holds ALL rows, so W is read exactly once and nothing depends on L2 --------
-// With 128-256 h rows per byte of W the matrix pipe and the LDS carry real load; the kernels above
-// re-stage the whole h tile for every 128 columns.  Here a workgroup of 8 wavefronts owns 256
-// columns x all 4 row blocks (half the LDS writes of h per column), tiled 4 x 2: wavefront (wc, wr)
-// multiplies 64 columns by 2 row blocks (6 operand reads per 8 MFMAs).  W and h tiles are shared,
-// double buffered in LDS, fetched ahead into registers by all 512 threads, one barrier per k-tile;
-// inside a wavefront the operand reads of k-step kk + 1, the LDS writes of the next tile and the
-// global loads of the tile after it are issued one by one between the MFMAs of k-step kk.
-template <int C>
-struct Gemm8Cfg {
-  static constexpr int THREADS = 512;
-  static constexpr int RBW = 4;
-  static constexpr int BN = 256;
-  static constexpr int HROWS = RBW * C * 32;
-  static constexpr int NB = 2 * C;                 // h-row tiles per wavefront (2 row blocks)
-  static constexpr int WL = BN * 8 / THREADS;      // 4
-  static constexpr int HL = HROWS * 8 / THREADS;   // 4 (C = 2) or 2
-  static constexpr int W_LDS = BN * PITCH;
-  static constexpr int H_LDS = HROWS * PITCH;
-  static constexpr int LDS_BYTES = 2 * (W_LDS + H_LDS) * 2;
-};
+// 16 bytes per lane from base + off (per lane) to LDS byte address lds + ADD + 16 * lane (lds uniform).  The
+// LDS address travels in m0, which the compiler sets right before the few instructions that need it and
+// keeps nothing in.
+template <bool NT, int ADD>
+__device__ __forceinline__ void load_lds16(uint64_t base, uint32_t off, uint32_t lds) {
+  if constexpr (NT)
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 ::"s"(lds), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+  else
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 ::"s"(lds), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {       // until at most N of this wavefront's loads are in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(IntT<I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
-template <int C, bool NT>
-__global__ __launch_bounds__(512) void lm_head_gemm8_kernel(const LmHeadArgs a, const int nLb,
-                                                            const int nRB, const int VT) {
-  using K = Gemm8Cfg<C>;
-  constexpr int NB = K::NB, WL = K::WL, HL = K::HL, KK = BK / 16;
-  __shared__ __attribute__((aligned(16))) unsigned char lds_raw[K::LDS_BYTES];
-  uint16_t* const Ws_all = reinterpret_cast<uint16_t*>(lds_raw);
-  uint16_t* const Hs_all = Ws_all + 2 * K::W_LDS;
-
-  const int vt = blockIdx.x;
+template <int C, int HR, int BN, int S, bool NT>
+__global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile_kernel(const LmHeadArgs a, const int VT, const int MT) {
+  using K = TileCfg<C, HR, BN, S>;
+  constexpr int NC = K::NC, NB = K::NB, WL = K::WL, HL = K::HL, SW = K::SW, SH = K::SH;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[K::LDS_BYTES];
+  // Workgroups with consecutive ids land on different XCDs; the MT row tiles that share a slab of W get
+  // ids 8 apart: the same XCD, the same L2.
+  const int id = blockIdx.x, xcd = id % 8;
+  const int vt = (id / (8 * MT)) * 8 + xcd, mt = (id / 8) % MT;
   if (vt >= VT) return;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wc = wave & 3, wr = wave >> 2;
-  // where this wavefront's two row blocks go, and the row block whose candidates it selects:
-  // fetched now, so that the epilogue does not begin with a round trip for the window starts
-  RowBlockDst rbd[2];
-#pragma unroll
-  for (int r2 = 0; r2 < 2; ++r2) rbd[r2] = row_block_dst(a, min(wr * 2 + r2, nRB - 1), nLb);
-  const RowBlockDst rbd_sel = row_block_dst(a, min(wave >> 1, nRB - 1), nLb);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wave % K::WCOL, wr = wave / K::WCOL;
   const int ln = lane & 31, lg = lane >> 5;
-  const int chunk = tid & 7, trow = tid >> 3;          // row 0..63 of a 64-row pass
-  const int d = a.d;
-  const int KT = (d + BK - 1) / BK;
-  const int rot = (vt * 5) % KT;
-  const uint32_t kclamp = static_cast<uint32_t>(d - 8) * 2u;
+  const int d = a.d, rows = a.B * a.L, p_base = mt * K::WR;
+  const int KT = d / 64, dtail = d % 64;             // whole k-tiles; elements of the ragged one
+  const int rot = (MT > 1 ? xcd * 5 : vt * 5) % KT;  // where this workgroup's cyclic walk over k starts
 
-  const char* const Wb = reinterpret_cast<const char*>(a.W);
-  const char* const Hb = reinterpret_cast<const char*>(a.h);
-  uint32_t woff[WL], hoff[HL];
-  bool hok[HL];
+  const RowState mine = row_state(a, p_base + tid);  // for the epilogue's row table
+
+  // byte offsets of this lane's pieces; rows past the end read the last one (their results are not stored)
+  auto piece_row = [&](int per_wave, int i) { return (wave * per_wave + i) * 8 + (lane >> 3); };
+  auto piece_chunk = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };
+  uint32_t wo[WL], ho[HL];
 #pragma unroll
-  for (int i = 0; i < WL; ++i)
-    woff[i] = static_cast<uint32_t>(min(vt * K::BN + trow + 64 * i, a.n - 1)) * static_cast<uint32_t>(d) * 2u;
-#pragma unroll
-  for (int i = 0; i < HL; ++i) {                       // tile row = 64 * i + trow
-    const int blk = 2 * i + (trow >> 5);
-    const int rb = blk / C, c = blk % C;
-    const int b = rb / nLb, s = (rb % nLb) * 32 + (trow & 31);
-    hok[i] = rb < nRB && s < a.L;
-    hoff[i] = hok[i] ? static_cast<uint32_t>((b * C + c) * a.L + s) * static_cast<uint32_t>(d) * 2u : 0u;
+  for (int i = 0; i < WL; ++i) {
+    const int r = piece_row(WL, i);
+    wo[i] = static_cast<uint32_t>(min(r, a.n - 1 - vt * BN)) * static_cast<uint32_t>(d) * 2u + piece_chunk(r) * 16;
   }
-  u32x4 wreg[1][WL], hreg[1][HL];   // one stage: a second one would not fit 256 registers
-  bool kok[1];
-  auto gload = [&](int stage, int t) {
-    int kt = min(t, KT - 1) + rot;
-    if (kt >= KT) kt -= KT;
-    const int k = kt * BK + chunk * 8;
-    kok[stage] = t < KT && k < d;                      // a tile past the end counts as zeros
-    const uint32_t kb = min(static_cast<uint32_t>(k) * 2u, kclamp);
 #pragma unroll
-    for (int i = 0; i < WL; ++i) wreg[stage][i] = load_w<NT>(reinterpret_cast<const u32x4*>(Wb + (woff[i] + kb)));
-#pragma unroll
-    for (int i = 0; i < HL; ++i) hreg[stage][i] = *reinterpret_cast<const u32x4*>(Hb + (hoff[i] + kb));
+  for (int i = 0; i < HL; ++i) {
+    // tile row r: block r / 32 holds the (cond, uncond) pair in turn, row r % 32 of its 32 window rows
+    const int r = piece_row(HL, i), blk = r >> 5;
+    ho[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), r & 31, blk % C, C, a.L, rows)) *
+                static_cast<uint32_t>(d) * 2u + piece_chunk(r) * 16;
+  }
+  const uint64_t wbase = reinterpret_cast<uint64_t>(a.W) + static_cast<uint64_t>(vt) * BN * d * 2;
+  const uint64_t hbase = reinterpret_cast<uint64_t>(a.h);
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)lds));
+  const uint32_t ldsW = lds0 + wave * WL * 1024, ldsH = lds0 + SW * K::WB + wave * HL * 1024;
+
+  // Loads of the next k-tile of h and of W, one piece at a time (h first).  With one wavefront per SIMD a
+  // k-tile of the small tiles is bound by instruction issue, so a piece is three instructions; COND: not
+  // past the end of the walk.
+  struct Walk {
+    uint64_t at;          // the k-tile's column of the operand
+    uint32_t lds;         // the stage it goes to
+    int k, n;             // its index; tiles issued before it
   };
-  auto lstore = [&](int stage, int buf) {
-    uint16_t* const Wd = Ws_all + buf * K::W_LDS;
-    uint16_t* const Hd = Hs_all + buf * K::H_LDS;
-#pragma unroll
-    for (int i = 0; i < WL; ++i)
-      *reinterpret_cast<u32x4*>(&Wd[(trow + 64 * i) * PITCH + chunk * 8]) = wreg[stage][i];
-#pragma unroll
-    for (int i = 0; i < HL; ++i) {
-      const bool keep = hok[i] && kok[stage];
-      *reinterpret_cast<u32x4*>(&Hd[(trow + 64 * i) * PITCH + chunk * 8]) =
-          keep ? hreg[stage][i] : u32x4{0u, 0u, 0u, 0u};
+  Walk hw{hbase + static_cast<uint32_t>(rot) * 128u, ldsH, rot, 0}, ww{wbase + static_cast<uint32_t>(rot) * 128u, ldsW, rot, 0};
+  auto advance = [&](Walk& w, uint64_t base, uint32_t first, uint32_t bytes, int stages) {
+    w.k = w.k + 1 == KT ? 0 : w.k + 1;
+    w.at = base + static_cast<uint32_t>(w.k) * 128u;
+    w.lds = w.lds + bytes == first + bytes * stages ? first : w.lds + bytes;
+    ++w.n;
+  };
+  auto piece = [&](auto qq, auto cond) {
+    constexpr int q = decltype(qq)::value;
+    constexpr bool COND = decltype(cond)::value;
+    if constexpr (q < HL) {
+      if (!COND || hw.n < KT) load_lds16<false, q * 1024>(hw.at, ho[q], hw.lds);
+      if constexpr (q == HL - 1) advance(hw, hbase, ldsH, K::HB, SH);
+    } else {
+      if (!COND || ww.n < KT) load_lds16<NT, (q - HL) * 1024>(ww.at, wo[q - HL], ww.lds);
+      if constexpr (q == HL + WL - 1) advance(ww, wbase, ldsW, K::WB, SW);
     }
   };
-  f32x16 acc[2][NB];
+  auto load_h = [&]() { static_for<HL>([&](auto i) { piece(i, TrueT{}); }); };
+  auto load_w = [&]() { static_for<WL>([&](auto i) { piece(IntT<HL + decltype(i)::value>{}, TrueT{}); }); };
+
+  f32x16 acc[NC][NB];
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
       for (int j = 0; j < 16; ++j) acc[c][i][j] = 0.f;
-
-  // tile t: registers <- memory during tile t - 2; LDS buffer t % 2 <- registers during tile
-  // t - 1; MFMAs during tile t.  The barrier that ends tile t - 1 publishes it.
-  gload(0, 0);
-  lstore(0, 0);
-  gload(0, 1);
-  __syncthreads();
-  for (int t = 0; t < KT; t += 2) {            // an odd KT is padded by one all-zero tile
+  // Operand sets in registers.  FLAT: one per k-step of a tile, each refilled from the next tile right after
+  // its MFMAs, so that the LDS round trip is covered by three k-steps (two MFMAs each in these small tiles);
+  // it takes a stage more.  Otherwise (tiles that fill LDS with three stages) two sets, one k-step ahead.
+  constexpr bool FLAT = S >= 4;
+  u32x4 bq[FLAT ? 4 : 2][NC], aq[FLAT ? 4 : 2][NB];
+  auto fetch = [&](int q, uint32_t sw, uint32_t sh, int kk) {
+    const uint32_t slot = ((kk * 2 + lg) ^ ((ln >> 1) & 7)) * 16;
+    const unsigned char* const Wt = lds + sw + (wc * K::CW + ln) * 128 + slot;
+    const unsigned char* const Ht = lds + SW * K::WB + sh + (wr * K::RW + ln) * 128 + slot;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {              // tile t + u sits in buffer u
-      hard_fence();
-      const uint16_t* const Wt = Ws_all + u * K::W_LDS + (wc * 64 + ln) * PITCH + lg * 8;
-      const uint16_t* const Ht = Hs_all + u * K::H_LDS + (wr * NB * 32 + ln) * PITCH + lg * 8;
-      u32x4 bq[2][2], aq[2][NB];
-      auto fetch = [&](int q, int kk) {
+    for (int c = 0; c < NC; ++c) bq[q][c] = *reinterpret_cast<const u32x4*>(Wt + c * 4096);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) bq[q][c] = *reinterpret_cast<const u32x4*>(&Wt[c * 32 * PITCH + kk * 16]);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) aq[q][i] = *reinterpret_cast<const u32x4*>(&Ht[i * 32 * PITCH + kk * 16]);
-      };
-      fetch(0, 0);
-      lstore(0, u ^ 1);                        // tile t + u + 1 -> the other buffer
-      gload(0, t + u + 2);
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        if (kk + 1 < KK) fetch((kk + 1) & 1, kk + 1);
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int i = 0; i < NB; ++i)
-            acc[c][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, aq[kk & 1][i]),
-                                                                __builtin_bit_cast(bf16x8, bq[kk & 1][c]),
-                                                                acc[c][i], 0, 0, 0);
+    for (int i = 0; i < NB; ++i) aq[q][i] = *reinterpret_cast<const u32x4*>(Ht + i * 4096);
+  };
+  // the MFMAs of one k-step on operand set q, with quarter Q of a k-tile's loads between them (Q = 4: none)
+  constexpr int NM = NC * NB, NP = HL + WL;
+  auto mma = [&](int q, auto quarter, auto cond) {
+    constexpr int Q = decltype(quarter)::value;
+    constexpr int P0 = Q < 4 ? NP * Q / 4 : 0, P1 = Q < 4 ? NP * (Q + 1) / 4 : 0;
+    static_for<NM>([&](auto ii) {
+      constexpr int I = decltype(ii)::value, c = I / NB, i = I % NB;
+      acc[c][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, aq[q][i]),
+                                                          __builtin_bit_cast(bf16x8, bq[q][c]), acc[c][i], 0, 0, 0);
+      constexpr int A = P0 + (P1 - P0) * I / NM, E = P0 + (P1 - P0) * (I + 1) / NM;
+      if constexpr (E > A) {
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<E - A>([&](auto k) { piece(IntT<A + decltype(k)::value>{}, cond); });
+        __builtin_amdgcn_sched_barrier(0);
       }
-      // first the operands of k-step 0, then one memory-side operation between two MFMAs
-      constexpr int OPS = 2 * (WL + HL) + (KK - 1) * (NB + 2), NM = KK * 2 * NB;
-      __builtin_amdgcn_sched_group_barrier(0x100, NB + 2, 0);
-      Interleave<0, NM, OPS>::run();
-      hard_fence();
-      __syncthreads();
-    }
-  }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
-  float zv[2][2][16];                       // processed logits [column half][row block][element]
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) zv[c][r2][j] = processed_logit<C>(a, acc[c][r2 * C][j], acc[c][r2 * C + C - 1][j]);
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int v = vt * K::BN + wc * 64 + c * 32 + ln;
-    if (v >= a.n) continue;
-#pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2) {
-      const int rb = wr * 2 + r2;
-      if (rb >= nRB) break;
-      const RowBlockDst& r = rbd[r2];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) store_z(a, r, r.sbase + (j >> 2) * 8 + lg * 4 + (j & 3), v, zv[c][r2][j]);
-    }
-  }
-
-  if constexpr (K::LDS_BYTES >= 128 * kTilePitch * 4) {
-    // ---- per-tile candidates for the row kernel (a.cand is uniform) --------------------------
-    static_assert(K::BN == kTileCols, "logit tile width");
-    if (a.cand == nullptr) return;
-    __syncthreads();                       // (also the loop's last barrier) staging buffers are free
-    float* const zt = reinterpret_cast<float*>(lds_raw);
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int r2 = 0; r2 < 2; ++r2)
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-          zt[((wr * 2 + r2) * 32 + (j >> 2) * 8 + lg * 4 + (j & 3)) * kTilePitch + wc * 64 + c * 32 + ln] = zv[c][r2][j];
-    __syncthreads();
-#pragma unroll 1
-    for (int g = 0; g < 4; ++g) {          // 16 tile rows per wavefront, four at a time
-      const int q0 = wave * 16 + g * 4;
-      const int rb = q0 >> 5;                // == wave >> 1
-      int wrow[4] = {-1, -1, -1, -1};
-      if (rb < nRB) {
-        const RowBlockDst& r = rbd_sel;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int s = r.sbase + (q0 & 31) + i;
-          wrow[i] = s < r.live ? r.b * a.L + s : -1;
+  uint32_t sw = 0, sh = 0;                           // stages of the tile whose operands are read next
+  auto next_stage = [&]() {
+    sw = sw + K::WB == SW * K::WB ? 0 : sw + K::WB;
+    sh = sh + K::HB == SH * K::HB ? 0 : sh + K::HB;
+  };
+  if constexpr (FLAT) {
+    // Tile t: the barrier at its top says that tile t + 1 is in LDS and that every wavefront holds tile t's
+    // operands, hence is done with the stage of tile t - 1, which takes the loads of tile t + S - 1.
+    // wait_tile(left): until the tile that `left` tiles follow is there; of those S - 3 have been issued.
+    auto wait_tile = [&](int left) {
+      bool done = false;
+      static_for<S - 2>([&](auto k) {
+        constexpr int N = S - 3 - decltype(k)::value;
+        if (!done && left >= N) {
+          wait_loads<N * NP>();
+          done = true;
         }
+      });
+    };
+    static_for<S - 2>([&](auto) {
+      load_h();
+      load_w();
+    });
+    wait_tile(KT - 1);
+    load_h();
+    load_w();
+    __builtin_amdgcn_s_barrier();
+    hard_fence();
+    static_for<4>([&](auto kk) { fetch(decltype(kk)::value, 0, 0, decltype(kk)::value); });
+    hard_fence();
+    auto tile = [&](auto quarter_of) {
+      __builtin_amdgcn_s_barrier();
+      hard_fence();
+      next_stage();
+      static_for<4>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        mma(k, IntT<decltype(quarter_of)::value ? k : 4>{}, FalseT{});
+        fetch(k, sw, sh, k);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    int t = 0;
+#pragma unroll 1
+    for (; t + S - 1 < KT; ++t) {
+      wait_loads<(S - 3) * NP>();
+      tile(TrueT{});
+    }
+#pragma unroll 1
+    for (; t + 1 < KT; ++t) {                        // everything is on its way
+      wait_tile(KT - 2 - t);
+      tile(FalseT{});
+    }
+    static_for<4>([&](auto kk) { mma(decltype(kk)::value, IntT<4>{}, FalseT{}); });
+  } else {
+    // Window t of the loads ends at the barrier of tile t; it brings W of tile t + 2 and h of tile
+    // t + SH - 1, h first (a stage is free once the barrier of the tile that it held is passed).  At the
+    // barrier of tile t both parts of tile t + 1 have to be in LDS; what was issued after them may be in flight.
+    constexpr int AHEAD = WL + (SH == 3 ? HL : 0);
+    load_h();
+    load_w();
+    if constexpr (SH == 3) load_h();
+    load_w();
+    if (KT > 1) wait_loads<AHEAD>();
+    else wait_loads<0>();
+    __builtin_amdgcn_s_barrier();
+    hard_fence();
+    static_for<NP / 4>([&](auto i) { piece(i, TrueT{}); });
+    fetch(0, 0, 0, 0);
+    hard_fence();
+    auto tile = [&](auto cond, bool more, bool next) {   // loads go on past this tile's barrier; a tile follows
+      fetch(1, sw, sh, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(0, IntT<1>{}, cond);
+      fetch(0, sw, sh, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(1, IntT<2>{}, cond);
+      fetch(1, sw, sh, 3);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(0, IntT<3>{}, cond);
+      hard_fence();
+      if (more) wait_loads<AHEAD>();
+      else wait_loads<0>();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this tile's operands are in registers
+      __builtin_amdgcn_s_barrier();
+      hard_fence();
+      next_stage();
+      if (next) fetch(0, sw, sh, 0);
+      hard_fence();
+      mma(1, IntT<0>{}, cond);
+      hard_fence();
+    };
+    int t = 0;
+#pragma unroll 1
+    for (; t + 3 < KT; ++t) tile(FalseT{}, true, true);
+#pragma unroll 1
+    for (; t < KT; ++t) tile(TrueT{}, t + 2 < KT, t + 1 < KT);
+  }
+  if (dtail != 0) {
+    // the ragged k-tile on its own: chunks past the end read the last one of the row and are zeroed in h
+    // (finite weights) by the wavefront that loaded them
+    const int nch = dtail / 8;
+    __syncthreads();                                 // every wavefront has its operands: the stages are free
+#pragma unroll
+    for (int i = 0; i < HL; ++i) {
+      const int ch = piece_chunk(piece_row(HL, i));
+      load_lds16<false, 0>(hbase + static_cast<uint32_t>(KT) * 128u, ho[i] - max(ch - (nch - 1), 0) * 16, ldsH + i * 1024);
+    }
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int ch = piece_chunk(piece_row(WL, i));
+      load_lds16<NT, 0>(wbase + static_cast<uint32_t>(KT) * 128u, wo[i] - max(ch - (nch - 1), 0) * 16, ldsW + i * 1024);
+    }
+    wait_loads<0>();
+#pragma unroll
+    for (int i = 0; i < HL; ++i)
+      if (piece_chunk(piece_row(HL, i)) >= nch)
+        *reinterpret_cast<u32x4*>(lds + SW * K::WB + (wave * HL + i) * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    for (int kk = 0; kk * 2 < nch; ++kk) {
+      fetch(0, 0, 0, kk);
+      mma(0, IntT<4>{}, FalseT{});
+    }
+  }
+
+  // ---- epilogue: guidance mix, temperature, z; then the per-tile candidates ---------------------------
+  __syncthreads();                                   // every wavefront is done with the stages
+  int* const table = reinterpret_cast<int*>(lds);    // (the stages take all of LDS: no table before)
+  if (tid < K::WR) table[tid] = row_dest(a, mine);
+  __syncthreads();
+  // element j of a block: window row 8 * (j / 4) + 4 * lg + j % 4 of its 32, column ln; the processed logits
+  // replace the cond sums
+#pragma unroll
+  for (int r = 0; r < K::RB; ++r) {
+    int4 to[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[(wr * K::RB + r) * 32 + g * 8 + lg * 4]);
+    const int v = vt * BN + wc * K::CW + ln;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int4 t = to[j >> 2];
+      const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
+      float* const zr = a.z + (static_cast<int64_t>(row) * a.n + v);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const float z = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
+        acc[c][r * C][j] = z;
+        if (row >= 0 && v + c * 32 < a.n) zr[c * 32] = z;
       }
-      tile_candidates4(a, zt, lane, q0, wrow, vt * K::BN, vt, VT);
+    }
+  }
+  if (a.cand == nullptr) return;                     // uniform
+  float* const zt = reinterpret_cast<float*>(lds + K::TABLE);
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(zt + K::ZROWS * K::PITCH_Z) + wave * (kTileHist / 4);
+  constexpr int PASSES = K::WR / K::ZROWS;           // 128 window rows at a time
+  constexpr int WROW_PASS = K::WROW / PASSES;        // wavefront rows that hold them
+#pragma unroll
+  for (int pass = 0; pass < PASSES; ++pass) {
+    if (pass > 0) __syncthreads();
+    if (wr / WROW_PASS == pass) {
+#pragma unroll
+      for (int r = 0; r < K::RB; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int j = 0; j < 16; ++j)
+            zt[(((wr % WROW_PASS) * K::RB + r) * 32 + (j >> 2) * 8 + lg * 4 + (j & 3)) * K::PITCH_Z + wc * K::CW + c * 32 + ln] =
+                acc[c][r * C][j];
+    }
+    __syncthreads();
+    constexpr int PER_WAVE = K::ZROWS / K::NW;
+#pragma unroll 1
+    for (int g = 0; g < PER_WAVE; g += kTileRows) {
+      const int q0 = wave * PER_WAVE + g;
+      int wrow[kTileRows];
+#pragma unroll
+      for (int i = 0; i < kTileRows; ++i) {
+        const int row = pass * K::ZROWS + q0 + i;
+        wrow[i] = __builtin_amdgcn_readfirstlane(table[row]) >= 0 ? p_base + row : -1;
+      }
+      tile_candidates<BN>(a, zt, hist, lane, q0, wrow, vt * BN, vt, VT);
     }
   }
 }
@@ -759,8 +901,7 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
     // plain leading arguments: the hardware preloads them into SGPRs at wavefront launch, so the
     // first loads do not wait for a fetch of the kernel-argument segment
     const uint16_t* const W_, const uint16_t* const h_, const int d_, const int n_, const int L_,
-    const int nLb, const int nRB, const int MT, const int rm_gshift, const int rm_rot,
-    const LmHeadArgs a) {
+    const int rows, const int MT, const int rm_gshift, const int rm_rot, const LmHeadArgs a) {
   const RowMap rm{rm_gshift, rm_rot};
   using K = SplitCfg<RBW, C, KS>;
   constexpr int NBLK = K::NBLK, HROWS = K::HROWS, D = K::D, DH = K::DH, NWAVE = K::NW;
@@ -770,10 +911,8 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
   const int vt = jt * 8 + xcd;
   const int mt = (id / 8) % MT;
   if (mapped_row(rm, xcd, jt, 32, 0) >= n_) return;   // no row left for this tile
-  const int rb0 = mt * RBW;
-  RowBlockDst rbd[RBW];                               // fetched now: not a round trip in the epilogue
-#pragma unroll
-  for (int rbw = 0; rbw < RBW; ++rbw) rbd[rbw] = row_block_dst(a, min(rb0 + rbw, nRB - 1), nLb);
+  const int p_base = mt * RBW * 32;                   // first window row
+  __shared__ __attribute__((aligned(16))) int table[RBW * 32];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int ln = lane & 31, lg = lane >> 5, chunk = lane & 7, lrow = lane >> 3;
   const int d = d_;
@@ -802,20 +941,7 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
     const int v = mapped_row(rm, xcd, jt, 32, lrow + 8 * i);
     woff[i] = static_cast<uint32_t>(min(v, n_ - 1)) * static_cast<uint32_t>(d) * 2u;
   }
-  constexpr int HL = HROWS / 8;                  // loads per lane per h tile
-  uint32_t hoff[HL];
-  bool hok[HL];
-#pragma unroll
-  for (int i = 0; i < HL; ++i) {
-    const int rr = lrow + 8 * i;
-    const int blk = rr >> 5, r = rr & 31;
-    const int rb = rb0 + blk / C, c = blk % C;
-    const int b = rb / nLb, s = (rb % nLb) * 32 + r;
-    hok[i] = rb < nRB && s < L_;
-    hoff[i] = hok[i] ? static_cast<uint32_t>((b * C + c) * L_ + s) * static_cast<uint32_t>(d) * 2u : 0u;
-  }
-  u32x4 wreg[D][4], hreg[DH][HL];
-  bool hkok[DH];
+  u32x4 wreg[D][4];
   auto wload = [&](int slot, int t) {
     bool valid;
     const int kt = ktile(t, valid);
@@ -823,6 +949,19 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
 #pragma unroll
     for (int i = 0; i < 4; ++i) wreg[slot][i] = load_w<false>(reinterpret_cast<const u32x4*>(Wb + (woff[i] + kb)));
   };
+  static_assert(D % DH == 0, "register stages of h must be static in the unrolled body");
+#pragma unroll
+  for (int j = 0; j < D; ++j) wload(j, j);      // on their way while the addresses of h are worked out
+  constexpr int HL = HROWS / 8;                  // loads per lane per h tile
+  uint32_t hoff[HL];
+#pragma unroll
+  for (int i = 0; i < HL; ++i) {
+    const int rr = lrow + 8 * i, blk = rr >> 5;
+    hoff[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), rr & 31, blk % C, C, L_, rows)) *
+              static_cast<uint32_t>(d) * 2u;
+  }
+  u32x4 hreg[DH][HL];
+  bool hkok[DH];
   auto hload = [&](int slot, int t) {
     bool valid;
     const int kt = ktile(t, valid);
@@ -839,11 +978,9 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
 
-  static_assert(D % DH == 0, "register stages of h must be static in the unrolled body");
-#pragma unroll
-  for (int j = 0; j < D; ++j) wload(j, j);
 #pragma unroll
   for (int j = 0; j < DH; ++j) hload(j, j);
+  const RowState mine = row_state(a, p_base + tid);
   // one pass over CNT <= D tiles; PF false: the last pass, no loads past the end
   auto body = [&](int t0, auto pf, auto cnt) {
     constexpr bool PF = decltype(pf)::value;
@@ -857,9 +994,8 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
 #pragma unroll
       for (int i = 0; i < HL; ++i) {          // zeroing here: at the load it would wait for it
         const u32x4 t4 = hreg[j % DH][i];
-        const bool keep = hok[i] && hkok[j % DH];
         *reinterpret_cast<u32x4*>(&Hs[(lrow + 8 * i) * PITCH + chunk * 8]) =
-            (keep ? t4 : u32x4{0u, 0u, 0u, 0u});
+            (hkok[j % DH] ? t4 : u32x4{0u, 0u, 0u, 0u});
       }
       if (PF) wload(j, t0 + j + D);
       if (PF || j + DH < CNT) hload(j % DH, t0 + j + DH);
@@ -892,6 +1028,7 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
     }
   }
   // the partial accumulators meet in LDS
+  if (tid < RBW * 32) table[tid] = row_dest(a, mine);
   __syncthreads();
   float* red = reinterpret_cast<float*>(lds_raw);
 #pragma unroll
@@ -905,12 +1042,10 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
   if (v >= a.n) return;
 #pragma unroll
   for (int rbw = 0; rbw < RBW; ++rbw) {
-    const int rb = rb0 + rbw;
-    if (rb >= nRB) break;
-    const RowBlockDst& r = rbd[rbw];
 #pragma unroll
     for (int jj = 0; jj < 16 / NWAVE; ++jj) {
       const int j = wave + jj * NWAVE;
+      const int row = table[rbw * 32 + (j >> 2) * 8 + lg * 4 + (j & 3)];
       float c = red[((0 * NBLK + rbw * C) * 16 + j) * 64 + lane];
       float u = red[((0 * NBLK + rbw * C + C - 1) * 16 + j) * 64 + lane];
 #pragma unroll
@@ -918,7 +1053,7 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
         c += red[((w * NBLK + rbw * C) * 16 + j) * 64 + lane];
         u += red[((w * NBLK + rbw * C + C - 1) * 16 + j) * 64 + lane];
       }
-      store_logit<C>(a, r, r.sbase + (j >> 2) * 8 + lg * 4 + (j & 3), v, c, u);
+      if (row >= 0) a.z[static_cast<int64_t>(row) * a.n + v] = processed_logit<C>(a, c, u);
     }
   }
 }
@@ -961,47 +1096,41 @@ bool stream_w(const LmHeadArgs& a) { return 2.0 * a.d * a.n > 192.0 * 1024 * 102
 template <int RBW, int C, int NWV>
 hipError_t launch_wide(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   using K = Cfg<RBW, C, NWV>;
-  const int nLb = (a.L + 31) / 32;
-  const int nRB = a.B * nLb;
   const int VT = (a.n + K::BN - 1) / K::BN;
-  const int MT = (nRB + RBW - 1) / RBW;
+  const int MT = (a.B * a.L + 32 * RBW - 1) / (32 * RBW);
   int JT;
   // The wavefronts of this kernel walk k in step (shared h tile): with all rows of a workgroup
   // in one residue class its requests would pile onto one channel at a time (measured: 124 us
   // against 94 us for the full vocabulary), so rows stay consecutive here.
   const RowMap rm = make_row_map(a, K::BN, VT, false, &JT);
   if (stream_w(a))
-    launch_kernel(lm_head_kernel<RBW, C, NWV, true>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a, nLb, nRB, VT,
-                  MT, rm);
+    launch_kernel(lm_head_kernel<RBW, C, NWV, true>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a, VT, MT,
+                  rm);
   else
-    launch_kernel(lm_head_kernel<RBW, C, NWV, false>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a, nLb, nRB, VT,
-                  MT, rm);
+    launch_kernel(lm_head_kernel<RBW, C, NWV, false>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a, VT, MT,
+                  rm);
   return hipGetLastError();
 }
 
 template <int RBW, int C, int KS>
 hipError_t launch_split(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   using K = SplitCfg<RBW, C, KS>;
-  const int nLb = (a.L + 31) / 32;
-  const int nRB = a.B * nLb;
   const int VT = (a.n + 31) / 32;
-  const int MT = (nRB + RBW - 1) / RBW;
+  const int MT = (a.B * a.L + 32 * RBW - 1) / (32 * RBW);
   int JT;
   const RowMap rm = make_row_map(a, 32, VT, true, &JT);
   launch_kernel(lm_head_splitk_kernel<RBW, C, KS>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a.W, a.h, a.d, a.n,
-                a.L, nLb, nRB, MT, rm.gshift, rm.rot, a);
+                a.L, a.B * a.L, MT, rm.gshift, rm.rot, a);
   return hipGetLastError();
 }
 
-template <int C>
-hipError_t launch_gemm8(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
-  using K = Gemm8Cfg<C>;
-  const int nLb = (a.L + 31) / 32;
-  const int VT = (a.n + K::BN - 1) / K::BN;
-  if (stream_w(a))
-    launch_kernel(lm_head_gemm8_kernel<C, true>, dim3(VT), dim3(K::THREADS), s, ev, a, nLb, a.B * nLb, VT);
-  else
-    launch_kernel(lm_head_gemm8_kernel<C, false>, dim3(VT), dim3(K::THREADS), s, ev, a, nLb, a.B * nLb, VT);
+template <int C, int HR, int BN, int S>
+hipError_t launch_tile(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
+  using K = TileCfg<C, HR, BN, S>;
+  const int VT = (a.n + BN - 1) / BN, MT = (a.B * a.L + K::WR - 1) / K::WR;
+  const dim3 grid((VT + 7) / 8 * 8 * MT);
+  if (stream_w(a)) launch_kernel(lm_head_tile_kernel<C, HR, BN, S, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
+  else launch_kernel(lm_head_tile_kernel<C, HR, BN, S, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
   return hipGetLastError();
 }
 
@@ -1009,37 +1138,58 @@ hipError_t launch_gemm8(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& 
 struct Variant {
   bool split;   // lm_head_splitk_kernel (else lm_head_kernel)
   int rbw, nw;  // row blocks per workgroup; wavefronts (= k parts for the split kernel)
-  bool gemm8;   // lm_head_gemm8_kernel
+  int hr, bn;   // hr > 0: lm_head_tile_kernel with tiles of hr h rows x bn columns ...
+  int stages;   // ... and as many stages of W
 };
+// The lines were drawn by timing every kernel on 32 to 512 window rows x 1000 to 65536 ids over d = 64 to
+// 4096 (us; the rows' W not in a cache).
 Variant choose(const LmHeadArgs& a) {
-  const int nRB = a.B * ((a.L + 31) / 32);
+  const int nRB = (a.B * a.L + 31) / 32;
   const int KT = (a.d + BK - 1) / BK;
-  // Narrow vocabularies: with 128-column workgroups fewer than ~1.5 per CU would exist;
-  // split k inside the workgroup instead and give every workgroup 32 columns.
-  const bool narrow = (a.n + 127) / 128 < 384 && KT >= 16;
-  // many row blocks: 2 per workgroup.  4 per workgroup would read W from L2 half as often, but
-  // its 91 KB of LDS and ~390 registers allow one workgroup per CU, and with one wavefront per
-  // SIMD the load / LDS / MFMA phases of a tile run back to back (C3: 98 us against 85 us).
-  // all rows in one workgroup when there are 3 or 4 row blocks and enough 256-column tiles to
-  // fill the chip
-  if ((nRB == 4 || nRB == 3) && (a.n + 255) / 256 >= 200) return {false, 4, 8, true};
-  if (nRB >= 4) return {false, 2, 4, false};
-  if (nRB >= 2) return {narrow, 2, 4, false};
-  if (narrow) return {true, 1, KT >= 48 ? 8 : 4, false};
-  // wide vocabulary: 8 wavefronts share each h tile (halves the h traffic out of L2)
-  return {false, 1, (a.n + 255) / 256 >= 200 ? 8 : 4, false};
+  const long m = static_cast<long>(a.B) * a.L * a.C;
+  if (a.d < 64) return {false, 1, 4, 0, 0, 0};           // no whole k-tile
+  // Few rows and columns: 32-column workgroups with k split, as long as all of them run at once (LDS: one
+  // per CU with guidance, two without).  32 rows x 8192 ids over 4096: 16 : 20 of the best tile; x 11000,
+  // two rounds, 29 : 30; without guidance x 16384 28 : 33, x 22000 39 : 36; over d = 320 the two are even.
+  if (KT >= 8 && nRB == 1 && (a.n + 31) / 32 <= (a.C == 2 ? 256 : 512)) return {true, 1, 8, 0, 0, 0};
+  // 33 to 128 rows without guidance: 64 x 8192 over 4096 17.5 : 21, x 11000 31 : 32; 128 x 2048 15 : 20,
+  // x 6000 (two rounds) 23 : 21
+  if (KT >= 8 && a.C == 1 && nRB > 1 && nRB <= 4 && (nRB + 1) / 2 * ((a.n + 31) / 32) <= 256)
+    return {true, 2, 4, 0, 0, 0};
+  // 32 rows without guidance: half of a tile's MFMAs would be wasted on the longest streams, 84 : 85 at 65536
+  // ids, even at 45000 (44 : 44 at 32768, where 128-column tiles still run at once)
+  if (a.C == 1 && nRB == 1 && a.n > 32768) return {false, 1, 8, 0, 0, 0};
+  // otherwise tiles: rounds of one workgroup per CU, times what a round takes (us over d = 4096 with 64
+  // or fewer workgroups, when neither memory nor power is short)
+  struct Shape { int hr, bn, stages, cost; };
+  constexpr Shape shapes[] = {{64, 128, 6, 20}, {64, 256, 4, 28}, {128, 128, 5, 27}, {128, 256, 3, 41},
+                              {256, 128, 3, 40}, {256, 256, 3, 73}};
+  const Shape* best = nullptr;
+  long least = 0;
+  for (const Shape& t : shapes) {
+    const long g = (m + t.hr - 1) / t.hr * ((a.n + t.bn - 1) / t.bn);
+    const long cost = (g + 255) / 256 * t.cost;
+    if (!best || cost < least) {
+      best = &t;
+      least = cost;
+    }
+  }
+  return {false, 0, 0, best->hr, best->bn, best->stages};
 }
 
 template <int C>
 hipError_t launch_c(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   const Variant v = choose(a);
-  if (v.gemm8) return launch_gemm8<C>(a, s, ev);
-  if (v.split) {
-    if (v.rbw == 2) return launch_split<2, C, 4>(a, s, ev);
-    return v.nw == 8 ? launch_split<1, C, 8>(a, s, ev) : launch_split<1, C, 4>(a, s, ev);
+  if (v.hr == 256) return v.bn == 256 ? launch_tile<C, 256, 256, 3>(a, s, ev) : launch_tile<C, 256, 128, 3>(a, s, ev);
+  if (v.hr == 128) return v.bn == 256 ? launch_tile<C, 128, 256, 3>(a, s, ev) : launch_tile<C, 128, 128, 5>(a, s, ev);
+  if (v.hr == 64) return v.bn == 256 ? launch_tile<C, 64, 256, 4>(a, s, ev) : launch_tile<C, 64, 128, 6>(a, s, ev);
+  if constexpr (C == 1) {
+    if (v.split) return v.rbw == 2 ? launch_split<2, 1, 4>(a, s, ev) : launch_split<1, 1, 8>(a, s, ev);
+    if (v.nw == 8) return launch_wide<1, 1, 8>(a, s, ev);
+  } else {
+    if (v.split) return launch_split<1, 2, 8>(a, s, ev);
   }
-  if (v.rbw == 2) return launch_wide<2, C, 4>(a, s, ev);
-  return v.nw == 8 ? launch_wide<1, C, 8>(a, s, ev) : launch_wide<1, C, 4>(a, s, ev);
+  return launch_wide<1, C, 4>(a, s, ev);
 }
 
 }  // namespace
@@ -1051,17 +1201,16 @@ hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_star
 
 int lm_head_tiles(const LmHeadArgs& a) {
   const Variant v = choose(a);
-  const int tiles = (a.n + kTileCols - 1) / kTileCols;
-  if (tiles > kRowMaxTiles) return 0;
-  if (v.gemm8) return Gemm8Cfg<2>::LDS_BYTES >= 128 * kTilePitch * 4 && a.C == 2 ? tiles : 0;
-  if (!v.split && v.rbw == 1 && v.nw == 8) return tiles;
-  return 0;
+  const int bn = v.hr > 0 ? v.bn : (!v.split && v.nw == 8) ? 256 : 0;
+  if (bn == 0) return 0;
+  const int tiles = (a.n + bn - 1) / bn;
+  return tiles <= kRowMaxTiles ? tiles : 0;
 }
 
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap) {
   const Variant v = choose(a);
   const char* nt = stream_w(a) ? "true" : "false";
-  if (v.gemm8) return snprintf(buf, cap, "lm_head_gemm8_kernel<%d, %s>", a.C, nt);
+  if (v.hr > 0) return snprintf(buf, cap, "lm_head_tile_kernel<%d, %d, %d, %d, %s>", a.C, v.hr, v.bn, v.stages, nt);
   if (v.split) return snprintf(buf, cap, "lm_head_splitk_kernel<%d, %d, %d>", v.rbw, a.C, v.nw);
   return snprintf(buf, cap, "lm_head_kernel<%d, %d, %d, %s>", v.rbw, a.C, v.nw, nt);
 }

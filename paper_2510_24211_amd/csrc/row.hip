@@ -26,7 +26,7 @@
 //                 commit follow from the same registers.
 // Rows of <= 16384 logits need no candidates (the whole row fits the row
 // kernel's registers); on longer ones the lists come from the LM head's
-// epilogue, one per 256-column tile, when that kernel emits them.  If the verification fails (massive ties, adversarial
+// epilogue, one per column tile, when that kernel emits them.  If the verification fails (massive ties, adversarial
 // layouts) or top-k is off, the row kernel falls back to a complete in-place
 // path: one coalesced read of the row, 16-bit key prefixes parked in LDS,
 // histogram select, candidate list or in-place scans.
@@ -1865,7 +1865,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   if (a.cand_base && row_uses_candidates(a.n, a.top_k)) {
     row_candidate_layout(a.cand_base, a.rows, &a.cand, &a.cand_cnt, &a.cand_cut);
     if (a.tiles > 0) {
-      // the LM head's epilogue has filled the lists: one per 256-column tile
+      // the LM head's epilogue has filled the lists: one per column tile
       P = a.tiles;
       capE = kListCap / P;
     } else {

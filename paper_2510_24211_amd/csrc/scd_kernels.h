@@ -18,7 +18,7 @@ struct LmHeadArgs {
   int B, C, L, N, d, n;
   float lam, one_plus_lam, tau;
   // Optional (scd_step only, and only when lm_head_tiles() says the chosen kernel can): the
-  // epilogue also emits, per window row and per 256-column tile, the tile's cand_cap largest
+  // epilogue also emits, per window row and per tile of 256 or 128 columns, the tile's cand_cap largest
   // logits as (id, logit) pairs, their number and the cut below which nothing was emitted --
   // the input of the row kernel's candidate path, which then needs no slice kernel.  Layout as
   // row_candidate_layout() gives it; window row index = b * L + s.  All null / 0 => off.
@@ -34,7 +34,7 @@ hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_star
 // Name (as a profiler prints it, without namespaces and arguments) of the kernel that
 // launch_lm_head picks for these sizes (only B, C, L, d, n are read); snprintf semantics.
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap);
-// Number of 256-column tiles per row if the kernel that launch_lm_head picks for these sizes can
+// Number of column tiles per row (256 or 128 columns each) if the kernel that launch_lm_head picks for these sizes can
 // emit per-tile candidates, else 0 (only B, C, L, d, n are read).
 int lm_head_tiles(const LmHeadArgs& a);
 

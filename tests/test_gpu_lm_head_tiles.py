@@ -1,0 +1,100 @@
+"""LM-head kernels over the shapes where their choice, their tiles or their tails change: logits against
+64 bits, and the candidate lists of the epilogue against a selection over the stored logits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_24211_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(Bn, C, L, n, d, v_lo, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    W = (0.05 * torch.randn(v_lo + n + 3, d, device=DEV, generator=g)).to(torch.bfloat16)
+    h = torch.randn(Bn, C, L, d, device=DEV, generator=g).to(torch.bfloat16)
+    return W, h
+
+
+def _want(W, h, n, v_lo, lam, tau):
+    w = W[v_lo:v_lo + n].double()
+    a = torch.stack([h[:, c].double().reshape(-1, h.shape[3]) @ w.t() for c in range(h.shape[1])])
+    z = a[0] if len(a) == 1 else (1 + lam) * a[0] - lam * a[1]
+    # every raw logit is a sum of d products: the worst order of 32-bit additions errs by less than
+    # d * 2^-24 * sum |h w|, a realistic one by sqrt(d) of that; sum |h w| <= |h| |w|
+    size = torch.stack([h[:, c].double().norm(dim=2).reshape(-1) for c in range(h.shape[1])]).max(0).values
+    bound = 4 * np.sqrt(h.shape[3]) * 2.0 ** -24 * size[:, None] * w.norm(dim=1)[None] * (1 + 2 * lam) / tau
+    return (z / tau).reshape(h.shape[0], h.shape[2], n), bound.reshape(h.shape[0], h.shape[2], n)
+
+
+SHAPES = [
+    # Bn, L, n, d, lam     the kernel that serves it
+    (1, 1, 1, 64, 0.0),            # one row, one id, one k-tile
+    (1, 5, 70, 8, 3.0),            # no whole k-tile
+    (3, 7, 129, 72, 3.0),          # 64 x 128 tiles, a ragged k-tile of one chunk, rows of three sequences packed
+    (2, 16, 1000, 120, 0.0),       # two rows past a block, 15 chunks
+    (2, 17, 8300, 200, 3.0),       # 34 rows: two blocks, three whole k-tiles
+    (1, 32, 8193, 512, 3.0),       # one workgroup more than the split kernel takes
+    (5, 6, 16384, 520, 0.0),       # split kernel, packed rows
+    (1, 33, 8192, 576, 0.0),       # split kernel with two row blocks
+    (1, 20, 32769, 328, 3.0),      # 64 x 256 tiles, last one a single column
+    (1, 31, 33000, 256, 0.0),      # shared h tile, 8 wavefronts
+    (2, 33, 20000, 392, 3.0),      # 128 x 128
+    (1, 100, 44000, 264, 0.0),     # 128 x 256
+    (7, 21, 20001, 328, 3.0),      # 256 x 128, rows ragged in blocks and tiles, odd ids
+    (4, 40, 60001, 136, 3.0),      # 256 x 256, five rows blocks of ten
+    (9, 29, 65535, 64, 0.0),       # 256 x 256 without guidance: two passes of the epilogue, one k-tile
+    (300, 1, 3000, 640, 0.0),      # many sequences of one position
+]
+
+
+@pytest.mark.parametrize("Bn,L,n,d,lam", SHAPES)
+def test_logits_against_64_bits(Bn, L, n, d, lam):
+    C, v_lo, tau = (2 if lam else 1), 5, 0.8
+    W, h = _inputs(Bn, C, L, n, d, v_lo, Bn * n + d)
+    sc = B.Scd(B.make_config(B=Bn, L=L, N=300, V=W.shape[0], d=d, v_lo=v_lo, v_hi=v_lo + n, temperature=tau,
+                             cfg_lambda=lam), DEV)
+    buf = torch.full((Bn * L * n + 64,), float("nan"), device=DEV)
+    sc.lm_head(h, W, buf[:Bn * L * n])
+    z = buf[:Bn * L * n].view(Bn, L, n)
+    want, bound = _want(W, h, n, v_lo, lam, tau)
+    assert bool(((z.double() - want).abs() <= bound).all()), float(((z.double() - want).abs() / bound).max())
+    assert bool(buf[Bn * L * n:].isnan().all())                        # nothing past the last row
+
+
+@pytest.mark.parametrize("Bn,L,n,d,lam,top_k", [
+    (1, 32, 17000, 256, 3.0, 500),      # 64 x 128 tiles: lists of 128 columns
+    (2, 17, 32768, 128, 3.0, 2000),     # 128 x 128: 256 lists of 128 columns
+    (3, 40, 20003, 192, 3.0, 1500),     # 256 x 128, rows packed over sequences, ragged columns
+    (1, 32, 65536, 128, 3.0, 2000),     # 64 x 256
+    (1, 20, 50001, 200, 0.0, 900),      # shared h tile
+    (1, 64, 65500, 128, 3.0, 2000),     # 128 x 256
+    (4, 33, 64000, 136, 3.0, 1000),     # 256 x 256, a second row tile with 8 of 128 rows
+    (5, 50, 65536, 64, 0.0, 2000),      # 256 x 256 without guidance: 250 rows in two passes
+    (1, 8, 40000, 64, 3.0, 2900),       # lists nearly too short for this top-k
+])
+def test_step_selects_what_a_selection_over_its_logits_does(Bn, L, n, d, lam, top_k):
+    C = 2 if lam else 1
+    W, h = _inputs(Bn, C, L, n, d, 0, n + top_k)
+    rows = Bn * L
+    W[:40] = W[0].clone()                      # ids that tie in every row
+    cfg = dict(B=Bn, L=L, N=L + 20, V=W.shape[0], d=d, v_lo=0, v_hi=n, top_k=top_k, cfg_lambda=lam, seed=9)
+    sc = B.Scd(B.make_config(**cfg), DEV)
+    st = sc.alloc_state()
+    sc.reset(st)
+    f = lambda field, *shape: sc.state_field(st, field).view(*shape)  # noqa: E731
+    pos = torch.zeros(Bn, dtype=torch.int64)
+    for it in range(3):                        # the windows of later iterations wrap around the ring and end
+        live = [[b, (int(pos[b]) + s) % L] for b in range(Bn) for s in range(min(L, L + 20 - int(pos[b])))]
+        sc.step(h, W, st)
+        sel = torch.tensor(live, device=DEV)
+        z = f(B.F_Z, 2, Bn, L, n)[it & 1, sel[:, 0], sel[:, 1]].contiguous()
+        thr, lse = torch.empty(rows, device=DEV), torch.empty(rows, device=DEV)
+        nk = torch.empty(rows, dtype=torch.int32, device=DEV)
+        sc.select(z, len(live), thr, lse, nk)
+        got = [f(field, 2, Bn, L)[it & 1, sel[:, 0], sel[:, 1]] for field in (B.F_THR, B.F_LSE, B.F_NKEPT)]
+        assert torch.equal(got[0], thr[:len(live)]) and torch.equal(got[2], nk[:len(live)])
+        assert bool(((got[1] - lse[:len(live)]).abs() <= 1e-6 * lse[:len(live)].abs().clamp(min=1.0)).all())
+        pos = f(B.F_POS, Bn).cpu().long()
+    assert bool((pos > 0).all())
