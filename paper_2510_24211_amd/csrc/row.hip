@@ -144,8 +144,10 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t* hist, uint32_t& nee
   uint32_t incl = static_cast<uint32_t>(wave_inclusive_sum_i32(static_cast<int>(local), lane));
   if (lane == 63) sm.wtot[wave] = incl;
   __syncthreads();
+  // all totals read at once: a loop up to this wavefront waits for one LDS round trip per entry
   uint32_t base = 0;
-  for (int w = 0; w < wave; ++w) base += sm.wtot[w];
+#pragma unroll
+  for (int w = 0; w < T / kWave; ++w) base += w < wave ? sm.wtot[w] : 0u;
   incl += base;
   const uint32_t excl = incl - local;
   if (excl < need && need <= incl) {     // exactly one thread
@@ -219,9 +221,66 @@ __device__ __forceinline__ void block_minmax(uint32_t& kmin, uint32_t& kmax, Sma
   if (trailing) __syncthreads();
 }
 
-// `need`-th largest key among the register-resident logits zv[e] (keys kv[e], valid
-// where ok[e]).  kmin_in is the smallest key among the valid logits above -1e30,
-// kmax the largest key (both from block_minmax).
+constexpr float kRangeFloor = -1.0e30f;
+// Three-way maximum / minimum of floats; a NaN operand is ignored.  As builtins they would come with a
+// quieting instruction per operand.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// This thread's share of the row's range: keys of its largest logit (all ones if one is NaN) and of the
+// smallest above kRangeFloor, of PER logits valid where ok[e].  One instruction per logit where all of the
+// wavefront's are valid and above the floor; the rest (ragged rows, masked ids, NaN) is looked at one by one.
+template <int PER>
+__device__ __forceinline__ void thread_range(const float (&zv)[PER], const bool (&ok)[PER], uint32_t& kmin,
+                                             uint32_t& kmax, bool& nan) {
+  float hi = zv[0], lo = zv[0], sum = 0.f;
+  bool plain = true, some = false;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) some |= ok[e];
+  kmax = 0u;
+  kmin = 0xFFFFFFFFu;
+  nan = false;
+  if (__ballot(some) == 0ull) return;      // a wavefront past the end of a short row
+#pragma unroll
+  for (int e = 0; e + 1 < PER; e += 2) {
+    hi = max3(hi, zv[e], zv[e + 1]);
+    lo = min3(lo, zv[e], zv[e + 1]);
+  }
+  if (PER & 1) {
+    hi = max3(hi, zv[PER - 1], zv[PER - 1]);
+    lo = min3(lo, zv[PER - 1], zv[PER - 1]);
+  }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    sum += zv[e];
+    plain &= ok[e];
+  }
+  if (__ballot(!(plain && lo > kRangeFloor && sum == sum)) != 0ull) {
+    hi = -INFINITY;
+    lo = INFINITY;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      hi = ok[e] ? fmaxf(hi, zv[e]) : hi;
+      lo = ok[e] && zv[e] > kRangeFloor ? fminf(lo, zv[e]) : lo;
+      nan |= ok[e] && zv[e] != zv[e];
+    }
+    kmax = nan ? 0xFFFFFFFFu : zkey(hi);
+    kmin = lo < INFINITY ? zkey(lo) : 0xFFFFFFFFu;
+  } else {
+    kmax = zkey(hi);
+    kmin = zkey(lo);
+  }
+}
+
+// `need`-th largest key among the register-resident logits zv[e] (valid where ok[e]).  zlo is the
+// smallest of the valid logits above -1e30, zhi the largest.
 //   Level 1 bins the logits LINEARLY in value between those two (any monotone map
 //   of the value preserves the order statistic; a linear one spreads a bell-shaped
 //   row over all bins, where the float bit pattern would pile it into a few
@@ -229,25 +288,18 @@ __device__ __forceinline__ void block_minmax(uint32_t& kmin, uint32_t& kmax, Sma
 //   Level 2 ranks the handful of members of the selected bin against each other.
 //   Should that bin hold more than NBINS members (massive ties), radix levels over
 //   the key bits finish the job.
-constexpr float kRangeFloor = -1.0e30f;
 template <int PER, int T = THREADS>
-__device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const uint32_t (&kv)[PER],
-                                                const bool (&ok)[PER], uint32_t kmin_in,
-                                                uint32_t kmax, uint32_t need, uint32_t* hist,
+__device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bool (&ok)[PER], float zlo,
+                                                float zhi, uint32_t need, uint32_t* hist,
                                                 uint32_t* arr, Small& sm) {
   // hist was zeroed by the caller before the barrier of block_minmax; arr (NBINS entries,
   // disjoint from hist) takes the members of the selected bin.
-  const float zlo = key_to_float(kmin_in), zhi = key_to_float(kmax);
   const float scale = (zhi > zlo) ? __fdiv_rn(static_cast<float>(NBINS - 1), zhi - zlo) : 0.f;
   int bin[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    int bb = 0;
-    if (ok[e] && zv[e] > kRangeFloor) {
-      const float t = (zv[e] - zlo) * scale;
-      bb = t >= 0.f ? (t >= static_cast<float>(NBINS - 1) ? NBINS - 1 : static_cast<int>(t)) : 0;
-    }
-    bin[e] = bb;
+    // below the floor, or where the range is empty or infinite (NaN): bin 0
+    bin[e] = static_cast<int>(fminf(fmaxf((zv[e] - zlo) * scale, 0.f), static_cast<float>(NBINS - 1)));
   }
   if (threadIdx.x == 0) sm.cursor = 0u;          // append cursor, published by the next barrier
 #pragma unroll
@@ -260,18 +312,19 @@ __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const ui
   if (members <= static_cast<uint32_t>(NBINS)) {
 #pragma unroll
     for (int e = 0; e < PER; ++e)
-      if (ok[e] && bin[e] == b1) arr[atomicAdd(&sm.cursor, 1u)] = kv[e];
+      if (ok[e] && bin[e] == b1) arr[atomicAdd(&sm.cursor, 1u)] = zkey(zv[e]);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       if (ok[e] && bin[e] == b1) {
+        const uint32_t mine = zkey(zv[e]);
         uint32_t gt = 0, ge = 0;
         for (uint32_t i = 0; i < members; ++i) {
           const uint32_t k = arr[i];
-          gt += k > kv[e] ? 1u : 0u;
-          ge += k >= kv[e] ? 1u : 0u;
+          gt += k > mine ? 1u : 0u;
+          ge += k >= mine ? 1u : 0u;
         }
-        if (gt < need && need <= ge) sm.sel_bin = kv[e];   // equal keys write the same value
+        if (gt < need && need <= ge) sm.sel_bin = mine;    // equal keys write the same value
       }
     }
     __syncthreads();
@@ -288,8 +341,9 @@ __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const ui
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      if (ok[e] && bin[e] == b1 && kv[e] >= lo && static_cast<uint64_t>(kv[e] - lo) < width)
-        atomicAdd(&hist[(kv[e] - lo) >> s2], 1u);
+      const uint32_t k = zkey(zv[e]);
+      if (ok[e] && bin[e] == b1 && k >= lo && static_cast<uint64_t>(k - lo) < width)
+        atomicAdd(&hist[(k - lo) >> s2], 1u);
     }
     __syncthreads();
     const uint32_t dgt = find_bin<T>(hist, need, sm);
@@ -558,31 +612,29 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
       }
     }
   }
-  uint32_t kv[PS], kmax = 0, kmin = 0xFFFFFFFFu;
-#pragma unroll
-  for (int e = 0; e < PS; ++e) {
-    kv[e] = zkey(zv[e]);
-    if (ok[e]) {
-      kmax = kv[e] > kmax ? kv[e] : kmax;
-      if (zv[e] > kRangeFloor) kmin = kv[e] < kmin ? kv[e] : kmin;
-      if (zv[e] != zv[e] && a.flags) atomicOr(a.flags, 1);     // NaN of either sign
-    }
-  }
+  uint32_t kmax, kmin;
+  bool nan;
+  thread_range<PS>(zv, ok, kmin, kmax, nan);
+  if (nan && a.flags) atomicOr(a.flags, 1);                    // NaN of either sign
   zero_hist<ST>(hist);                        // published by the barrier inside block_minmax
   block_minmax<ST>(kmin, kmax, sm, false);
   const int nvalid = hi_id - lo_id;
   uint32_t cut = 0;                       // 0: the whole slice is emitted
   if (nvalid > rank)
-    cut = select_regs<PS, ST>(zv, kv, ok, kmin, kmax, static_cast<uint32_t>(rank), hist, arr, sm);
+    cut = select_regs<PS, ST>(zv, ok, key_to_float(kmin), key_to_float(kmax), static_cast<uint32_t>(rank), hist, arr, sm);
+  bool take[PS];
   int mine = 0;
 #pragma unroll
-  for (int e = 0; e < PS; ++e) mine += (ok[e] && kv[e] >= cut) ? 1 : 0;
+  for (int e = 0; e < PS; ++e) {
+    take[e] = ok[e] && zkey(zv[e]) >= cut;
+    mine += take[e] ? 1 : 0;
+  }
   int total;
   int off = block_offsets<ST>(mine, total, sm, 0, false);
   uint2* const dst = a.cand + (static_cast<size_t>(r) * kListCap + static_cast<size_t>(p) * capE);
 #pragma unroll
   for (int e = 0; e < PS; ++e) {
-    if (ok[e] && kv[e] >= cut) {
+    if (take[e]) {
       if (off < capE) dst[off] = make_uint2(static_cast<uint32_t>(vid[e]), __float_as_uint(zv[e]));
       ++off;
     }
@@ -691,24 +743,17 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
                                             bool have_thr = false, float thr_given = 0.f) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = a.n;
-  uint32_t kv[PER], kmax = 0, kmin = 0xFFFFFFFFu;
-#pragma unroll
-  for (int e = 0; e < PER; ++e) {
-    kv[e] = zkey(zv[e]);
-    if (ok[e]) {
-      kmax = kv[e] > kmax ? kv[e] : kmax;
-      if (zv[e] > kRangeFloor) kmin = kv[e] < kmin ? kv[e] : kmin;
-      if (zv[e] != zv[e] && a.flags) atomicOr(a.flags, 1);     // NaN of either sign
-    }
-  }
+  uint32_t kmin, kmax;
+  bool nan;
+  thread_range<PER>(zv, ok, kmin, kmax, nan);
+  if (nan && a.flags) atomicOr(a.flags, 1);                    // NaN of either sign
   if (filter) zero_hist(hist);            // published by the barrier inside block_minmax
   block_minmax(kmin, kmax, sm, false);
   const float m = key_to_float(kmax);
   float thr = have_thr ? thr_given : -INFINITY;   // given: the caller has applied the filters
   if (filter) {
     // cid (ccap entries, all of them free until the compaction) takes the selected bin's members
-    const uint32_t tkey = select_regs<PER>(zv, kv, ok, kmin, kmax, static_cast<uint32_t>(a.top_k), hist,
-                                           cid, sm);
+    const uint32_t tkey = select_regs<PER>(zv, ok, key_to_float(kmin), m, static_cast<uint32_t>(a.top_k), hist, cid, sm);
     if (tkey < cut_max) return false;     // an unseen logit could be >= the K-th candidate
     thr = key_to_float(tkey);
   }
@@ -718,7 +763,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
     auto each = [&](auto&& f) {
 #pragma unroll
       for (int e = 0; e < PER; ++e)
-        if (ok[e] && zv[e] >= thr_k) f(kv[e], zv[e]);
+        if (ok[e] && zv[e] >= thr_k) f(zkey(zv[e]), zv[e]);
     };
     const uint32_t pkey = nucleus_key(each, [](uint32_t, uint32_t) {}, each, m, zmin, a.top_p24,
                                       reinterpret_cast<unsigned long long*>(hist), sm);
