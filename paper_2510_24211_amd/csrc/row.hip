@@ -1596,9 +1596,12 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, u
 
 // GS: the row also makes a Gumbel-max draw from p; EXTRA: the optional parts are compiled in
 // (nucleus filter, per-position statistics; kept out of the other instances: their live ranges
-// cost the hot kernels registers); LONG: rows of more than kRowKernelMaxN ids, for which only the
-// candidate path and long_path exist
-template <bool GS, bool EXTRA, bool LONG = false>
+// cost the hot kernels registers).  PATH: which way rows of this length go.  One instance per way, because
+// with all of them in one kernel the compiler keeps every way's arguments in scalar registers and spills them
+// (184 spills; 46 vector registers spilled in the optional instances).  Four-step decodes over 8192 ids: 132 ->
+// 129 us, with every option 206 -> 193 us.
+enum Path { kDirectHalf, kDirectWhole, kLists, kLong };
+template <bool GS, bool EXTRA, int PATH>
 __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
                                                       const int mode_, const int L_, const int N_,
                                                       const int P, const int capE, const RowArgs a) {
@@ -1633,15 +1636,14 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
   RowOut out{};
   out.accept = true;
   bool done = false;
-  if (!LONG && n <= kDirectMaxN) {
+  if constexpr (PATH == kDirectHalf || PATH == kDirectWhole) {
     // ---- the whole row in registers ------------------------------------------------
-    if (n <= kDirectMaxN / 2) direct_path<PER_DIRECT / 2, GS, EXTRA>(a, R, smem, filter, zcx, zpx, sm, out);
-    else direct_path<PER_DIRECT, GS, EXTRA>(a, R, smem, filter, zcx, zpx, sm, out);
+    direct_path<PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, zcx, zpx, sm, out);
     done = true;
   } else if (filter && a.cand && P > 0) {
     // ---- candidates emitted by the slice kernel ----------------------------------
     // LDS: the compaction arrays, then the histogram (behind the space of full_path's key prefixes)
-    const size_t arrays = LONG ? static_cast<size_t>(kKeptCap) * 12 : static_cast<size_t>((n + 7) & ~7) * 2;
+    const size_t arrays = PATH == kLong ? static_cast<size_t>(kKeptCap) * 12 : static_cast<size_t>((n + 7) & ~7) * 2;
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + arrays);
     // The P counts and cuts of the row's lists (P slices of the slice kernel, or P column tiles
     // of the LM head's epilogue; thread t holds those of list t), the count that governs each
@@ -1707,9 +1709,9 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
                                    reinterpret_cast<float*>(smem) + 2 * ccap, ccap, sm, out);
     }
   }
-  if constexpr (LONG) {
+  if constexpr (PATH == kLong) {
     if (!done) long_path(a, R, smem, zcx, zpx, sm, out);
-  } else {
+  } else if constexpr (PATH == kLists) {
     if (!done) full_path<GS, EXTRA>(a, R, smem, zcx, zpx, sm, out);
   }
   if (a.mode == kRowSelectOnly) return;
@@ -1929,6 +1931,17 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
     }
   }
   const size_t lds = lds_bytes_for(a.n);
+  const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
+  const bool extra = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
+  using Kernel = void (*)(const int32_t*, const int32_t*, int, int, int, int, int, RowArgs);
+#define SCD_ROW_INSTANCES(PATH) \
+  {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
+  static const Kernel kernels[][4] = {SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
+#ifndef SCD_ROW_BATCHED
+                                      SCD_ROW_INSTANCES(kLists), {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr}
+#endif
+  };
+#undef SCD_ROW_INSTANCES
   // The dynamic-LDS limit is an attribute of the function on a device.  Every context asks
   // for the same value, the largest any row needs, once (a context has one stream, hence one
   // device), so contexts of different row lengths cannot lower each other's limit.
@@ -1936,30 +1949,19 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   size_t& configured = lds_configured ? *lds_configured : none;
   if (configured == 0) {
     const size_t most = lds_bytes_for(kRowKernelMaxN);
-    for (const void* f : {
-#ifndef SCD_ROW_BATCHED
-                          reinterpret_cast<const void*>(row_kernel<false, false, true>),
-#endif
-                          reinterpret_cast<const void*>(row_kernel<false, false>),
-                          reinterpret_cast<const void*>(row_kernel<true, false>),
-                          reinterpret_cast<const void*>(row_kernel<false, true>),
-                          reinterpret_cast<const void*>(row_kernel<true, true>)}) {
-      hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(most));
-      if (e != hipSuccess) return e;
-    }
+    for (const auto& row : kernels)
+      for (Kernel f : row)
+        if (f)
+          if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 static_cast<int>(most));
+              e != hipSuccess)
+            return e;
     configured = most;
   }
-  const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
-  const bool topp = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
-  auto* kernel = gs ? (topp ? row_kernel<true, true> : row_kernel<true, false>)
-                          : (topp ? row_kernel<false, true> : row_kernel<false, false>);
-#ifndef SCD_ROW_BATCHED
-  if (a.n > kRowKernelMaxN) {
-    if (gs || topp) return hipErrorInvalidValue;            // refused when the context is created
-    kernel = row_kernel<false, false, true>;
-  }
-#endif
+  const int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
+                   : a.n <= kRowKernelMaxN ? kLists : kLong;
+  const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
+  if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
   a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;
   hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(THREADS), lds, s, a.pos, a.iter, a.mode, a.L, a.N, P, capE, a);
   return hipGetLastError();
