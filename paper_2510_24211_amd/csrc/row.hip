@@ -370,6 +370,7 @@ __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bo
 // mh: NBINS_P 64-bit bins (the space of the count histogram).  Uniform over the workgroup.
 constexpr int NBINS_P = NBINS / 2;
 static_assert(NBINS_P % THREADS == 0 || THREADS % NBINS_P == 0, "nucleus: bins per thread");
+static_assert(THREADS >= 512, "nucleus: a member per thread");
 
 __device__ __forceinline__ unsigned long long mass_of(float z, float m) {
   return static_cast<unsigned long long>(expf(z - m) * 1099511627776.0f);   // <= 2^40
@@ -444,8 +445,7 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
   const float zlo = fmaxf(zmin, m - 110.f);
   const float scale = (m > zlo) ? __fdiv_rn(static_cast<float>(NBINS_P - 1), m - zlo) : 0.f;
   auto lin_bin = [&](float z) {
-    const float t = (z - zlo) * scale;
-    return t >= 0.f ? (t >= static_cast<float>(NBINS_P - 1) ? NBINS_P - 1 : static_cast<int>(t)) : 0;
+    return static_cast<int>(fminf(fmaxf((z - zlo) * scale, 0.f), static_cast<float>(NBINS_P - 1)));
   };
   auto zero = [&]() {
     for (int i = tid; i < NBINS_P; i += THREADS) mh[i] = 0ull;
@@ -466,7 +466,43 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
     if (b1 < NBINS_P - 2) near_hi = zkey(zlo + static_cast<float>(b1 + 2) * inv);
   }
   prepare(near_lo, near_hi);
-  // radix levels over the key bits of the members of bin b1
+  // A bin near the boundary holds a few dozen ids: they are parked in LDS, and each adds up the masses of
+  // those above it; the smallest key whose sum stays below the target is the threshold.
+  constexpr uint32_t kFew = 512;
+  unsigned long long* const mm = mh;
+  uint32_t* const mk = reinterpret_cast<uint32_t*>(mh + kFew);
+  static_assert(NBINS_P * 8 >= kFew * 12, "members' masses and keys in the histogram's space");
+  __syncthreads();                                  // the cursor may still be read by prepare()'s users
+  if (tid == 0) {
+    sm.cursor = 0u;
+    sm.sel_bin = 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  near([&](uint32_t key, float z) {
+    if (lin_bin(z) == b1) {
+      const uint32_t slot = atomicAdd(&sm.cursor, 1u);
+      if (slot < kFew) {
+        mk[slot] = key;
+        mm[slot] = mass_of(z, m);
+      }
+    }
+  });
+  __syncthreads();
+  const uint32_t members = sm.cursor;
+  if (members <= kFew) {
+    if (static_cast<uint32_t>(tid) < members) {
+      const uint32_t key = mk[tid];
+      unsigned long long sum = above;
+      for (uint32_t i = 0; i < members; ++i) sum += mk[i] > key ? mm[i] : 0ull;
+      if (sum < target) atomicMin(&sm.sel_bin, key);
+    }
+    __syncthreads();
+    const uint32_t key = sm.sel_bin;
+    __syncthreads();                                // the next user of the space or of sel_bin
+    return key;
+  }
+  __syncthreads();                                  // everybody has read the cursor
+  // many (ties): radix levels over the key bits of the members of bin b1
   uint32_t lo = 0;
   int s2 = 32;
   while (s2 > 0) {
