@@ -127,6 +127,9 @@ __device__ __forceinline__ int row_dest(const LmHeadArgs& a, const RowState& r) 
   const int s = r.p - r.b * a.L, par = a.iter ? (r.it & 1) : 0;
   return s < a.N - r.p0 ? (par * a.B + r.b) * a.L + (r.p0 + s) % a.L : -1;
 }
+// First h row (of [B, C, L]) of the sequence that holds window row p.  A workgroup addresses its h rows from
+// there: the whole of h may exceed the 4 GiB that a 32-bit offset reaches.
+__device__ __forceinline__ int first_h_row(int p, int C, int L) { return p / L * C * L; }
 // h row (of [B, C, L]) of row r < 32 of the block that starts at window row p0 (uniform; the last row where
 // there is none: its results are not stored).  Windows of 32 or more positions end at most once in a block.
 __device__ __forceinline__ int h_row(int p0, int r, int c, int C, int L, int rows) {
@@ -153,10 +156,10 @@ __device__ __forceinline__ float processed_logit(const LmHeadArgs& a, float c, f
 }
 // Epilogue of a wavefront that holds whole sums.  Element j of lane (ln, lg) is row
 // (j/4)*8 + lg*4 + j%4, column ln of the 32x32 tile.  zout takes the processed logits.
-// table: row_dest of the workgroup's RBW * 32 window rows.
+// table: row_dest of the workgroup's RBW * 32 window rows.  v: this lane's column, `there` if it exists.
 template <int RBW, int C>
-__device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc)[RBW * C], const int* table, int v,
-                                         int lg, float (&zout)[RBW][16]) {
+__device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc)[RBW * C], const int* table, int64_t v,
+                                         bool there, int lg, float (&zout)[RBW][16]) {
 #pragma unroll
   for (int rbw = 0; rbw < RBW; ++rbw) {
     int4 to[4];
@@ -167,7 +170,7 @@ __device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc
       const int4 t = to[j >> 2];
       const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
       zout[rbw][j] = processed_logit<C>(a, acc[rbw * C][j], acc[rbw * C + C - 1][j]);
-      if (row >= 0 && v < a.n) a.z[static_cast<int64_t>(row) * a.n + v] = zout[rbw][j];
+      if (row >= 0 && there) a.z[static_cast<int64_t>(row) * a.n + v] = zout[rbw][j];
     }
   }
 }
@@ -295,7 +298,7 @@ __device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, const float
 
 template <int RBW, int C, int NWV, bool NT>
 __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
-    const LmHeadArgs a, const int VT, const int MT, const RowMap rm) {
+    const LmHeadArgs a, const int VT, const int MT) {
   using K = Cfg<RBW, C, NWV>;
   constexpr int NBLK = K::NBLK, HROWS = K::HROWS, D = K::D, DH = K::DH, HT = K::HT;
   constexpr int THREADS = K::THREADS;
@@ -310,7 +313,8 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   const int xcd = id % 8, jt = id / (8 * MT);
   const int vt = jt * 8 + xcd;
   const int mt = (id / 8) % MT;
-  if (mapped_row(rm, xcd, jt, Cfg<RBW, C, NWV>::BN, 0) >= a.n) return;   // no row left for this tile
+  if (vt >= VT) return;
+  const int v_base = vt * K::BN, v_left = a.n - v_base;   // first column; columns that exist from there
   const int p_base = mt * RBW * 32, rows = a.B * a.L;     // first window row; all of them
   __shared__ __attribute__((aligned(16))) int table[RBW * 32];
 
@@ -344,15 +348,13 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   uint16_t* const Ws = Ws_all + wave * 32 * PITCH;          // private W staging
 
   // ---- W: coalesced private loads, D tiles ahead -----------------------------------
-  // 32-bit byte offsets from the (uniform) base; rows past the end are clamped to the last
+  // 32-bit byte offsets from the workgroup's first row; rows past the end are clamped to the last
   // row (their columns are never stored), k past the end to the last 16-byte chunk.
-  const char* const Wb = reinterpret_cast<const char*>(a.W);
+  const char* const Wb = reinterpret_cast<const char*>(a.W) + static_cast<size_t>(v_base) * d * 2;
   uint32_t woff[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int v = mapped_row(rm, xcd, jt, K::BN, wave * 32 + lrow + 8 * i);
-    woff[i] = static_cast<uint32_t>(min(v, a.n - 1)) * static_cast<uint32_t>(d) * 2u;
-  }
+  for (int i = 0; i < 4; ++i)
+    woff[i] = static_cast<uint32_t>(min(wave * 32 + lrow + 8 * i, v_left - 1)) * static_cast<uint32_t>(d) * 2u;
   const uint32_t kclamp = static_cast<uint32_t>(d - 8) * 2u;
   u32x4 wreg[D][4];
   auto wload = [&](int slot, int t) {       // logical tile index t
@@ -375,12 +377,13 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   constexpr int HL = HROWS / RPP;                // loads per thread per h tile
   static_assert(HROWS % RPP == 0, "h tile must divide over the workgroup");
   const int hchunk = tid % CH, hr0 = tid / CH;
-  const char* const Hb = reinterpret_cast<const char*>(a.h);
+  const int h0 = first_h_row(p_base, C, a.L);
+  const char* const Hb = reinterpret_cast<const char*>(a.h) + static_cast<size_t>(h0) * d * 2;
   uint32_t hoff[HL];
 #pragma unroll
   for (int i = 0; i < HL; ++i) {
     const int rr = hr0 + RPP * i, blk = rr >> 5;  // tile row 0..HROWS-1
-    hoff[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), rr & 31, blk % C, C, a.L, rows)) *
+    hoff[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), rr & 31, blk % C, C, a.L, rows) - h0) *
               static_cast<uint32_t>(d) * 2u;
   }
   u32x4 hreg[DH][HL];
@@ -484,7 +487,7 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
   body(ntiles_pad - D, FalseT{});
 
   float zv[RBW][16];
-  epilogue<RBW, C>(a, acc, table, mapped_row(rm, xcd, jt, K::BN, wave * 32 + ln), lg, zv);
+  epilogue<RBW, C>(a, acc, table, static_cast<int64_t>(v_base) + wave * 32 + ln, wave * 32 + ln < v_left, lg, zv);
 
   if constexpr (RBW == 1 && NWV == 8) {
     // ---- per-tile candidates for the row kernel (a.cand is uniform) --------------------------
@@ -505,7 +508,7 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
         const int row = wave * 4 + g + i;
         wrow[i] = __builtin_amdgcn_readfirstlane(table[row]) >= 0 ? p_base + row : -1;
       }
-      tile_candidates<K::BN>(a, zt, hist, lane, wave * 4 + g, wrow, vt * K::BN, vt, VT);
+      tile_candidates<K::BN>(a, zt, hist, lane, wave * 4 + g, wrow, v_base, vt, VT);
     }
   }
 }
@@ -603,6 +606,7 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
   const int wc = wave % K::WCOL, wr = wave / K::WCOL;
   const int ln = lane & 31, lg = lane >> 5;
   const int d = a.d, rows = a.B * a.L, p_base = mt * K::WR;
+  const int v_left = a.n - vt * BN;                  // columns that exist from this tile's first
   const int KT = d / 64, dtail = d % 64;             // whole k-tiles; elements of the ragged one
   const int rot = (MT > 1 ? xcd * 5 : vt * 5) % KT;  // where this workgroup's cyclic walk over k starts
 
@@ -611,21 +615,22 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
   // byte offsets of this lane's pieces; rows past the end read the last one (their results are not stored)
   auto piece_row = [&](int per_wave, int i) { return (wave * per_wave + i) * 8 + (lane >> 3); };
   auto piece_chunk = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };
+  const int h0 = first_h_row(p_base, C, a.L);
   uint32_t wo[WL], ho[HL];
 #pragma unroll
   for (int i = 0; i < WL; ++i) {
     const int r = piece_row(WL, i);
-    wo[i] = static_cast<uint32_t>(min(r, a.n - 1 - vt * BN)) * static_cast<uint32_t>(d) * 2u + piece_chunk(r) * 16;
+    wo[i] = static_cast<uint32_t>(min(r, v_left - 1)) * static_cast<uint32_t>(d) * 2u + piece_chunk(r) * 16;
   }
 #pragma unroll
   for (int i = 0; i < HL; ++i) {
     // tile row r: block r / 32 holds the (cond, uncond) pair in turn, row r % 32 of its 32 window rows
     const int r = piece_row(HL, i), blk = r >> 5;
-    ho[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), r & 31, blk % C, C, a.L, rows)) *
+    ho[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), r & 31, blk % C, C, a.L, rows) - h0) *
                 static_cast<uint32_t>(d) * 2u + piece_chunk(r) * 16;
   }
   const uint64_t wbase = reinterpret_cast<uint64_t>(a.W) + static_cast<uint64_t>(vt) * BN * d * 2;
-  const uint64_t hbase = reinterpret_cast<uint64_t>(a.h);
+  const uint64_t hbase = reinterpret_cast<uint64_t>(a.h) + static_cast<uint64_t>(h0) * d * 2;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)lds));
   const uint32_t ldsW = lds0 + wave * WL * 1024, ldsH = lds0 + SW * K::WB + wave * HL * 1024;
 
@@ -834,17 +839,17 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
     int4 to[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[(wr * K::RB + r) * 32 + g * 8 + lg * 4]);
-    const int v = vt * BN + wc * K::CW + ln;
+    const int v = wc * K::CW + ln;                    // column of the tile
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int4 t = to[j >> 2];
       const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
-      float* const zr = a.z + (static_cast<int64_t>(row) * a.n + v);
+      float* const zr = a.z + (static_cast<int64_t>(row) * a.n + vt * BN + v);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const float z = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
         acc[c][r * C][j] = z;
-        if (row >= 0 && v + c * 32 < a.n) zr[c * 32] = z;
+        if (row >= 0 && v + c * 32 < v_left) zr[c * 32] = z;
       }
     }
   }
@@ -1059,10 +1064,9 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
 }
 
 // Row map for these operands and the number of workgroup tiles per XCD it needs.
-RowMap make_row_map(const LmHeadArgs& a, int BN, int VT, bool affine, int* tiles_per_xcd) {
+RowMap make_row_map(const LmHeadArgs& a, int BN, int VT, int* tiles_per_xcd) {
   RowMap m{-1, 0};
   *tiles_per_xcd = (VT + 7) / 8;
-  if (!affine) return m;
   const size_t row_bytes = static_cast<size_t>(a.d) * 2;
   constexpr size_t kBlock = 128 * 1024;
   if (kBlock % row_bytes != 0) return m;
@@ -1096,19 +1100,14 @@ bool stream_w(const LmHeadArgs& a) { return 2.0 * a.d * a.n > 192.0 * 1024 * 102
 template <int RBW, int C, int NWV>
 hipError_t launch_wide(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   using K = Cfg<RBW, C, NWV>;
-  const int VT = (a.n + K::BN - 1) / K::BN;
+  const int VT = (a.n - 1) / K::BN + 1;
   const int MT = (a.B * a.L + 32 * RBW - 1) / (32 * RBW);
-  int JT;
   // The wavefronts of this kernel walk k in step (shared h tile): with all rows of a workgroup
-  // in one residue class its requests would pile onto one channel at a time (measured: 124 us
+  // in one residue class (RowMap) its requests would pile onto one channel at a time (measured: 124 us
   // against 94 us for the full vocabulary), so rows stay consecutive here.
-  const RowMap rm = make_row_map(a, K::BN, VT, false, &JT);
-  if (stream_w(a))
-    launch_kernel(lm_head_kernel<RBW, C, NWV, true>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a, VT, MT,
-                  rm);
-  else
-    launch_kernel(lm_head_kernel<RBW, C, NWV, false>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a, VT, MT,
-                  rm);
+  const dim3 grid((VT + 7) / 8 * 8 * MT);
+  if (stream_w(a)) launch_kernel(lm_head_kernel<RBW, C, NWV, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
+  else launch_kernel(lm_head_kernel<RBW, C, NWV, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
   return hipGetLastError();
 }
 
@@ -1118,7 +1117,7 @@ hipError_t launch_split(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& 
   const int VT = (a.n + 31) / 32;
   const int MT = (a.B * a.L + 32 * RBW - 1) / (32 * RBW);
   int JT;
-  const RowMap rm = make_row_map(a, 32, VT, true, &JT);
+  const RowMap rm = make_row_map(a, 32, VT, &JT);
   launch_kernel(lm_head_splitk_kernel<RBW, C, KS>, dim3(JT * 8 * MT), dim3(K::THREADS), s, ev, a.W, a.h, a.d, a.n,
                 a.L, a.B * a.L, MT, rm.gshift, rm.rot, a);
   return hipGetLastError();
@@ -1127,7 +1126,7 @@ hipError_t launch_split(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& 
 template <int C, int HR, int BN, int S>
 hipError_t launch_tile(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   using K = TileCfg<C, HR, BN, S>;
-  const int VT = (a.n + BN - 1) / BN, MT = (a.B * a.L + K::WR - 1) / K::WR;
+  const int VT = (a.n - 1) / BN + 1, MT = (a.B * a.L + K::WR - 1) / K::WR;
   const dim3 grid((VT + 7) / 8 * 8 * MT);
   if (stream_w(a)) launch_kernel(lm_head_tile_kernel<C, HR, BN, S, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
   else launch_kernel(lm_head_tile_kernel<C, HR, BN, S, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
@@ -1148,13 +1147,15 @@ Variant choose(const LmHeadArgs& a) {
   const int KT = (a.d + BK - 1) / BK;
   const long m = static_cast<long>(a.B) * a.L * a.C;
   if (a.d < 64) return {false, 1, 4, 0, 0, 0};           // no whole k-tile
+  const int columns32 = (a.n - 1) / 32 + 1;
+  const bool reach = 2L * a.d * a.n < 1L << 32;          // the split kernel's offsets into W have 32 bits
   // Few rows and columns: 32-column workgroups with k split, as long as all of them run at once (LDS: one
   // per CU with guidance, two without).  32 rows x 8192 ids over 4096: 16 : 20 of the best tile; x 11000,
   // two rounds, 29 : 30; without guidance x 16384 28 : 33, x 22000 39 : 36; over d = 320 the two are even.
-  if (KT >= 8 && nRB == 1 && (a.n + 31) / 32 <= (a.C == 2 ? 256 : 512)) return {true, 1, 8, 0, 0, 0};
+  if (reach && KT >= 8 && nRB == 1 && columns32 <= (a.C == 2 ? 256 : 512)) return {true, 1, 8, 0, 0, 0};
   // 33 to 128 rows without guidance: 64 x 8192 over 4096 17.5 : 21, x 11000 31 : 32; 128 x 2048 15 : 20,
   // x 6000 (two rounds) 23 : 21
-  if (KT >= 8 && a.C == 1 && nRB > 1 && nRB <= 4 && (nRB + 1) / 2 * ((a.n + 31) / 32) <= 256)
+  if (reach && KT >= 8 && a.C == 1 && nRB > 1 && nRB <= 4 && (nRB + 1) / 2 * columns32 <= 256)
     return {true, 2, 4, 0, 0, 0};
   // 32 rows without guidance: half of a tile's MFMAs would be wasted on the longest streams, 84 : 85 at 65536
   // ids, even at 45000 (44 : 44 at 32768, where 128-column tiles still run at once)
@@ -1167,7 +1168,7 @@ Variant choose(const LmHeadArgs& a) {
   const Shape* best = nullptr;
   long least = 0;
   for (const Shape& t : shapes) {
-    const long g = (m + t.hr - 1) / t.hr * ((a.n + t.bn - 1) / t.bn);
+    const long g = (m + t.hr - 1) / t.hr * ((a.n - 1) / t.bn + 1);
     const long cost = (g + 255) / 256 * t.cost;
     if (!best || cost < least) {
       best = &t;
@@ -1203,7 +1204,7 @@ int lm_head_tiles(const LmHeadArgs& a) {
   const Variant v = choose(a);
   const int bn = v.hr > 0 ? v.bn : (!v.split && v.nw == 8) ? 256 : 0;
   if (bn == 0) return 0;
-  const int tiles = (a.n + bn - 1) / bn;
+  const int tiles = (a.n - 1) / bn + 1;
   return tiles <= kRowMaxTiles ? tiles : 0;
 }
 
