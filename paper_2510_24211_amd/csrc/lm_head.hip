@@ -535,6 +535,10 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
 //     (256 x 128 tiles, 64 workgroups: 52 -> 43 us).
 //   * A wavefront multiplies 64 x 128 or 64 x 64 (NC x NB accumulator tiles of 32 x 32): the LDS reads of a
 //     k-tile take less than its MFMAs.
+//   * Small calls add k up in 4 or 8 partial sums (k_parts): every `per` k-tiles the accumulators are added to
+//     whole sums and start again from zero.  In the register form of the MFMAs (launch bounds of 512: with one
+//     wavefront per SIMD the compiler takes accumulation registers, and each fold copies them out and back)
+//     this takes 0 to 6 % (64 rows with guidance x 2000 ids over 4096: 17.7 -> 18.8 us).
 // What is left is power: with real operands all 256 CUs sustain about 1.45 PFLOP/s (MFMAs alone, operands
 // fixed in registers; 1.9 on zeros), and loads on top share that budget.  Against register-staged kernels:
 // 1024 h rows x 8192 ids over 4096 84 -> 62 us (1.10 PFLOP/s; the vendor GEMM 66), 256 x 64000 148 -> 124
@@ -556,6 +560,7 @@ struct TileCfg {
   static constexpr int WB = BN * 128, HB = HR * 128; // bytes per stage
   static constexpr int SW = S_, SH = HR == 256 && BN == 256 ? S_ - 1 : S_;   // stages
   static_assert(SW >= 3 && SH >= 2, "stages");
+  static constexpr bool PARTS = HR * BN < 256 * 256; // registers left for whole sums beside the partial ones
   static constexpr int STAGES = SW * WB + SH * HB;
   // epilogue: row table, then the logit tile of up to 128 window rows and the histograms
   static constexpr int ZROWS = WR < 128 ? WR : 128;
@@ -592,7 +597,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 template <int C, int HR, int BN, int S, bool NT>
-__global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile_kernel(const LmHeadArgs a, const int VT, const int MT) {
+__global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, const int VT, const int MT, const int per) {
   using K = TileCfg<C, HR, BN, S>;
   constexpr int NC = K::NC, NB = K::NB, WL = K::WL, HL = K::HL, SW = K::SW, SH = K::SH;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[K::LDS_BYTES];
@@ -663,13 +668,34 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
   auto load_h = [&]() { static_for<HL>([&](auto i) { piece(i, TrueT{}); }); };
   auto load_w = [&]() { static_for<WL>([&](auto i) { piece(IntT<HL + decltype(i)::value>{}, TrueT{}); }); };
 
-  f32x16 acc[NC][NB];
+  f32x16 acc[NC][NB], whole[NC][NB];                 // partial sums, and the sum of the finished ones
 #pragma unroll
   for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int i = 0; i < NB; ++i)
+    for (int i = 0; i < NB; ++i) {
+      acc[c][i] = f32x16{};
+      if constexpr (K::PARTS) whole[c][i] = f32x16{};
+    }
+  // step(t) for the k-tiles from t up to `last`, one partial sum after the other
+  int t = 0, complete = per;                         // the partial sums are complete before this k-tile
+  auto walk = [&](int last, auto&& step) {
+    while (t < last) {
+      const int stop = K::PARTS ? min(last, complete) : last;
+#pragma unroll 1
+      for (; t < stop; ++t) step(t);
+      if constexpr (K::PARTS) {
+        if (t < complete) return;
+        complete += per;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc[c][i][j] = 0.f;
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            whole[c][i] += acc[c][i];
+            acc[c][i] = f32x16{};
+          }
+      }
+    }
+  };
   // Operand sets in registers.  FLAT: one per k-step of a tile, each refilled from the next tile right after
   // its MFMAs, so that the LDS round trip is covered by three k-steps (two MFMAs each in these small tiles);
   // it takes a stage more.  Otherwise (tiles that fill LDS with three stages) two sets, one k-step ahead.
@@ -744,17 +770,14 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
         __builtin_amdgcn_sched_barrier(0);
       });
     };
-    int t = 0;
-#pragma unroll 1
-    for (; t + S - 1 < KT; ++t) {
+    walk(KT - S + 1, [&](int) {
       wait_loads<(S - 3) * NP>();
       tile(TrueT{});
-    }
-#pragma unroll 1
-    for (; t + 1 < KT; ++t) {                        // everything is on its way
+    });
+    walk(KT - 1, [&](int t) {                        // everything is on its way
       wait_tile(KT - 2 - t);
       tile(FalseT{});
-    }
+    });
     static_for<4>([&](auto kk) { mma(decltype(kk)::value, IntT<4>{}, FalseT{}); });
   } else {
     // Window t of the loads ends at the barrier of tile t; it brings W of tile t + 2 and h of tile
@@ -794,11 +817,8 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
       mma(1, IntT<0>{}, cond);
       hard_fence();
     };
-    int t = 0;
-#pragma unroll 1
-    for (; t + 3 < KT; ++t) tile(FalseT{}, true, true);
-#pragma unroll 1
-    for (; t < KT; ++t) tile(TrueT{}, t + 2 < KT, t + 1 < KT);
+    walk(KT - 3, [&](int) { tile(FalseT{}, true, true); });
+    walk(KT, [&](int t) { tile(TrueT{}, t + 2 < KT, t + 1 < KT); });
   }
   if (dtail != 0) {
     // the ragged k-tile on its own: chunks past the end read the last one of the row and are zeroed in h
@@ -824,6 +844,15 @@ __global__ __launch_bounds__((TileCfg<C, HR, BN, S>::THREADS)) void lm_head_tile
     for (int kk = 0; kk * 2 < nch; ++kk) {
       fetch(0, 0, 0, kk);
       mma(0, IntT<4>{}, FalseT{});
+    }
+  }
+
+  if constexpr (K::PARTS) {
+    if (per <= KT) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < NB; ++i) acc[c][i] += whole[c][i];
     }
   }
 
@@ -1123,13 +1152,25 @@ hipError_t launch_split(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& 
   return hipGetLastError();
 }
 
+// In how many partial sums the k of a logit is added up outside the split kernel.  The rounding error of one
+// chain of 32-bit additions grows with its length: against 64 bits, over d = 4096 4.0e-7 of the logits' size in one
+// chain, 1.9e-7 in 4 parts, 1.4e-7 in 8.  Calls of up to 96 rows and 49024 ids have it at the lower levels (the
+// lines of the split kernel, which served them all at first); larger ones are bound by the matrix pipe and the
+// power it draws, and take one chain in every kernel.
+int k_parts(const LmHeadArgs& a) {
+  const int rows = a.B * a.L, KT = (a.d + BK - 1) / BK;
+  if (rows > 96 || a.n > 49024 || KT < 16) return 1;
+  return rows <= 32 && KT >= 48 ? 8 : 4;
+}
+
 template <int C, int HR, int BN, int S>
 hipError_t launch_tile(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   using K = TileCfg<C, HR, BN, S>;
   const int VT = (a.n - 1) / BN + 1, MT = (a.B * a.L + K::WR - 1) / K::WR;
   const dim3 grid((VT + 7) / 8 * 8 * MT);
-  if (stream_w(a)) launch_kernel(lm_head_tile_kernel<C, HR, BN, S, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
-  else launch_kernel(lm_head_tile_kernel<C, HR, BN, S, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT);
+  const int KT = a.d / 64, parts = k_parts(a), per = parts > 1 ? (KT + parts - 1) / parts : KT + 1;
+  if (stream_w(a)) launch_kernel(lm_head_tile_kernel<C, HR, BN, S, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT, per);
+  else launch_kernel(lm_head_tile_kernel<C, HR, BN, S, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT, per);
   return hipGetLastError();
 }
 
@@ -1159,7 +1200,8 @@ Variant choose(const LmHeadArgs& a) {
     return {true, 2, 4, 0, 0, 0};
   // 32 rows without guidance: half of a tile's MFMAs would be wasted on the longest streams, 84 : 85 at 65536
   // ids, even at 45000 (44 : 44 at 32768, where 128-column tiles still run at once)
-  if (a.C == 1 && nRB == 1 && a.n > 32768) return {false, 1, 8, 0, 0, 0};
+  const bool chain = k_parts(a) == 1;
+  if (a.C == 1 && nRB == 1 && a.n > 32768 && chain) return {false, 1, 8, 0, 0, 0};
   // otherwise tiles: rounds of one workgroup per CU, times what a round takes (us over d = 4096 with 64
   // or fewer workgroups, when neither memory nor power is short)
   struct Shape { int hr, bn, stages, cost; };
@@ -1168,6 +1210,9 @@ Variant choose(const LmHeadArgs& a) {
   const Shape* best = nullptr;
   long least = 0;
   for (const Shape& t : shapes) {
+    // no registers for partial sums: 96 rows with guidance x 49024 ids over 1280 take two rounds of 256 x 128,
+    // 41 us for 35
+    if (t.hr * t.bn == 256 * 256 && !chain) continue;
     const long g = (m + t.hr - 1) / t.hr * ((a.n - 1) / t.bn + 1);
     const long cost = (g + 255) / 256 * t.cost;
     if (!best || cost < least) {

@@ -98,3 +98,28 @@ def test_step_selects_what_a_selection_over_its_logits_does(Bn, L, n, d, lam, to
         assert bool(((got[1] - lse[:len(live)]).abs() <= 1e-6 * lse[:len(live)].abs().clamp(min=1.0)).all())
         pos = f(B.F_POS, Bn).cpu().long()
     assert bool((pos > 0).all())
+
+
+@pytest.mark.parametrize("Bn,L,n,d,lam,parts,kernel", [
+    (1, 8, 32768, 4096, 0.0, 8, "tile_kernel<1, 64, 128, 6, true>"),
+    (1, 32, 8193, 3072, 3.0, 8, "tile_kernel<2, 64, 128, 6, false>"),     # 48 k-tiles, the fewest for 8 parts
+    (1, 32, 49024, 4096, 0.0, 8, "tile_kernel<1, 64, 256, 4, true>"),     # the longest rows that are split
+    (3, 20, 2000, 1032, 3.0, 4, "tile_kernel<2, 64, 128, 6, false>"),     # 16 k-tiles and a ragged one
+    (1, 64, 40000, 1280, 0.0, 4, "tile_kernel<1, 64, 256, 4, false>"),
+    (2, 32, 30001, 2048, 3.0, 4, "tile_kernel<2, 128, 128, 5, false>"),
+    (3, 32, 45000, 1280, 0.0, 4, "tile_kernel<1, 128, 256, 3, false>"),
+    (3, 32, 49024, 2048, 3.0, 4, "tile_kernel<2, 256, 128, 3, false>"),
+])
+def test_small_calls_add_up_in_parts(Bn, L, n, d, lam, parts, kernel):
+    W, h = _inputs(Bn, 2 if lam else 1, L, n, d, 0, n + d)
+    sc = B.Scd(B.make_config(B=Bn, L=L, N=300, V=W.shape[0], d=d, v_hi=n, cfg_lambda=lam), DEV)
+    assert sc.lm_head_kernel_name() == "lm_head_" + kernel
+    z = torch.empty(Bn, L, n, device=DEV)
+    sc.lm_head(h, W, z)
+    want, _ = _want(W, h, n, 0, lam, 1.0)
+    err = float((z.double() - want).norm() / want.norm())
+    # T = d / 16 accumulations per logit, each rounding a sum that has grown like a random walk: over `parts`
+    # chains of T / parts and the chain that adds them up the error is u sqrt(T / (2 parts) + (parts + 1) / 2) of
+    # the result, u the rms of a rounding error in units of the value, at most 2^-24 / sqrt(3) * 1.2 (one chain
+    # would be u sqrt(T / 2), 1.4 times this bound and more)
+    assert err <= 0.7 * 2.0 ** -24 * np.sqrt(d / 32 / parts + (parts + 1) / 2), err
