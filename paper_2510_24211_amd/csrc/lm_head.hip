@@ -186,9 +186,12 @@ __device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc
 //   The emitted set is found on a monotone 8-bit image of the logits, linear between the row's smallest
 // and largest (equal images: both emitted or neither), by counting it: one LDS histogram of 256 bins per
 // row, four per lane, a prefix sum over the lanes, and the lowest bin whose upper set holds at most
-// `cap` logits (a bin near the cut holds about one logit, so 23 to 24 of 24 slots are used).  If more than
-// `cap` logits share the top image (massive ties, or a non-finite logit, which collapses the image) the
-// tile reports an overflowing count and the row kernel reads the row whole.
+// `cap` logits (a bin near the cut holds about one logit, so 23 to 24 of 24 slots are used).  Where the row's
+// range is wide against its spread (one far logit is enough) a bin holds tens of logits and the list would come
+// out short or empty: if more than kTileSlack slots stay free, the bin below the cut is counted again on an image
+// of its own range (refine_cut).  A step of one sequence x 32 x 65536 with one logit per tile 100 times the
+// others' size: 255 us with rows read whole, 146 with full lists, 110 without such logits.  If more than `cap` logits tie at the top (or a logit is not finite, which
+// collapses the image) the tile reports an overflowing count and the row kernel reads the row whole.
 //   Bound by the vector and LDS instructions of a CU (about 100 per row).  A bisection on a 12-bit image
 // with wave ballots, 13 steps of about ten scalar operations per row, waited for the one scalar unit of
 // the CU: two sequences x 64 positions x 64000 ids, 16 rows per wavefront, 26 us against 18 us now; one
@@ -197,6 +200,70 @@ constexpr int kTilePad = 8;                 // floats: rows 4 apart fall into di
 constexpr int kTileBins = 256;
 constexpr int kTileRows = 2;                // rows that a wavefront reduces side by side
 constexpr int kTileHist = kTileRows * kTileBins * 4;   // LDS bytes per wavefront
+
+// Monotone image of a logit, linear over [lo, hi]: one fused multiply-add.  For non-finite logits scale / shift
+// degenerate and every image collapses to 0.
+struct TileImage {
+  float scale, shift;
+};
+__device__ __forceinline__ TileImage tile_image(float lo, float hi) {
+  const float scale = hi > lo ? __fdiv_rn(static_cast<float>(kTileBins - 1), hi - lo) : 0.f;
+  return {scale, -(lo * scale)};
+}
+__device__ __forceinline__ int image_of(const TileImage& t, float v) {
+  return static_cast<int>(fminf(fmaxf(__fmaf_rn(v, t.scale, t.shift), 0.f), static_cast<float>(kTileBins - 1)));
+}
+// How many bins' upper sets hold more than `room` of the `all` logits counted in a row's histogram: the lowest bin
+// that can be emitted.
+__device__ __forceinline__ int find_cut(const uint32_t* hist, int lane, int all, int room) {
+  const uint4 c4 = *reinterpret_cast<const uint4*>(&hist[4 * lane]);
+  const int c[4] = {static_cast<int>(c4.x), static_cast<int>(c4.y), static_cast<int>(c4.z), static_cast<int>(c4.w)};
+  const int mine = (c[0] + c[1]) + (c[2] + c[3]);
+  int above = all - wave_inclusive_sum_i32(mine, lane) + mine;           // logits in bins >= 4 * lane
+  int cut = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    cut += __builtin_popcountll(__builtin_amdgcn_ballot_w64(above > room));
+    above -= c[e];
+  }
+  return cut;
+}
+// The logits `in` (those of the bin below the cut, more than there are free slots) are counted on an image of
+// their own range, and those of its upper bins join `take`, `total` of them in all; again on the next bin while
+// more than kTileSlack slots are free and the members differ (each round resolves the range 255 times finer).
+template <int E>
+__device__ __forceinline__ void refine_cut(const float (&v)[E], bool (&in)[E], bool (&take)[E], int& total, int cap,
+                                           uint32_t* hist, int lane) {
+#pragma unroll 1
+  for (int round = 0; round < 4 && total < cap - kTileSlack; ++round) {
+    float mx = -INFINITY, mn = INFINITY;
+    int all = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      mx = in[e] ? fmaxf(mx, v[e]) : mx;
+      mn = in[e] ? fminf(mn, v[e]) : mn;
+      all += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in[e]));
+    }
+    const float hi = wave_max_f32(mx), lo = wave_min_f32(mn);
+    if (!(hi > lo)) return;                              // uniform: they tie
+    const TileImage image = tile_image(lo, hi);
+    *reinterpret_cast<uint4*>(&hist[4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+    compiler_fence();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (in[e]) atomicAdd(&hist[image_of(image, v[e])], 1u);
+    compiler_fence();
+    const int cut = find_cut(hist, lane, all, cap - total);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int q = image_of(image, v[e]);
+      const bool up = in[e] && q >= cut;
+      take[e] |= up;
+      total += __builtin_popcountll(__builtin_amdgcn_ballot_w64(up));
+      in[e] = in[e] && q == cut - 1;
+    }
+  }
+}
 
 // Rows q0, q0 + 1 of the tile; wrow[i] = window row index (b * L + s) of tile row q0 + i, or -1
 // if it is not a live window row; v0 = id of the tile's first column; tile / T = its index and the
@@ -238,13 +305,9 @@ __device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, const float
     // a NaN (or +inf next to -inf) among the lane's logits poisons their sum
     if (sum != sum && a.flags && wrow[i] >= 0) atomicOr(a.flags, 1);
     const float hi = wave_max_f32(mx), lo = wave_min_f32(mn);
-    // one fused multiply-add per logit: monotone in z.  For non-finite logits scale / shift degenerate,
-    // every image collapses to 0 and the tile row reports an overflow below.
-    const float scale = hi > lo ? __fdiv_rn(static_cast<float>(kTileBins - 1), hi - lo) : 0.f;
-    const float shift = -(lo * scale);
+    const TileImage image = tile_image(lo, hi);
 #pragma unroll
-    for (int e = 0; e < E; ++e)
-      q[i][e] = static_cast<int>(fminf(fmaxf(__fmaf_rn(v[i][e], scale, shift), 0.f), static_cast<float>(kTileBins - 1)));
+    for (int e = 0; e < E; ++e) q[i][e] = image_of(image, v[i][e]);
   }
   // LDS operations of a wavefront are performed in order: the zeroing above, the counting, the reading
   compiler_fence();
@@ -256,29 +319,32 @@ __device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, const float
   compiler_fence();
 #pragma unroll
   for (int i = 0; i < kTileRows; ++i) {
-    const uint4 c4 = *reinterpret_cast<const uint4*>(&hist[i * kTileBins + 4 * lane]);
-    const int c[4] = {static_cast<int>(c4.x), static_cast<int>(c4.y), static_cast<int>(c4.z), static_cast<int>(c4.w)};
-    const int mine = (c[0] + c[1]) + (c[2] + c[3]);
-    int above = nvalid - wave_inclusive_sum_i32(mine, lane) + mine;      // logits in bins >= 4 * lane
-    int cutq = 0;                                        // bins whose upper set holds more than cap logits
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      cutq += __builtin_popcountll(__builtin_amdgcn_ballot_w64(above > cap));
-      above -= c[e];
-    }
+    const int cutq = find_cut(&hist[i * kTileBins], lane, nvalid, cap);
     if (wrow[i] < 0) continue;                           // uniform
     // emitted logits in the fixed order (column within the lane, then lane)
     bool take[E];
     int at[E], total = 0;
     float vmin = INFINITY;
+    auto place = [&]() {
+      total = 0;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      take[e] = q[i][e] >= cutq && (!ragged || ok[e]);
-      const unsigned long long m = __builtin_amdgcn_ballot_w64(take[e]);
-      at[e] = total + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                       __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
-      total += __builtin_popcountll(m);
-      vmin = take[e] ? fminf(vmin, v[i][e]) : vmin;
+      for (int e = 0; e < E; ++e) {
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(take[e]);
+        at[e] = total + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+        total += __builtin_popcountll(m);
+        vmin = take[e] ? fminf(vmin, v[i][e]) : vmin;
+      }
+    };
+#pragma unroll
+    for (int e = 0; e < E; ++e) take[e] = q[i][e] >= cutq && (!ragged || ok[e]);
+    place();
+    if (cutq > 0 && total < cap - kTileSlack) {          // uniform
+      bool in[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) in[e] = q[i][e] == cutq - 1 && (!ragged || ok[e]);
+      refine_cut<E>(v[i], in, take, total, cap, &hist[i * kTileBins], lane);
+      place();
     }
     vmin = wave_min_f32(vmin);                           // smallest emitted logit (NaNs are never smallest)
     const size_t slot = static_cast<size_t>(wrow[i]) * T + tile;

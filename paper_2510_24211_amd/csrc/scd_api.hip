@@ -401,11 +401,11 @@ int scd_step(scd_ctx* c, const uint16_t* d_h, const uint16_t* d_W, void* st) {
   a.tau = c->cfg.temperature;
   // First half of the top-k selection inside the LM head's epilogue (per-tile candidate lists in
   // the workspace) when the kernel for this shape can do it and the lists are long enough: on
-  // average a tile holds top_k / tiles of the row's top_k logits; demand twice that plus 8.
+  // average a tile holds top_k / tiles of the row's top_k logits; demand twice that plus the slack.
   int tiles = 0;
   if (scd::row_uses_candidates(c->n, c->cfg.top_k)) {
     const int t = scd::lm_head_tiles(a);
-    if (t > 0 && 2L * c->cfg.top_k <= static_cast<long>(t) * (scd::kRowListCap / t - 8)) tiles = t;
+    if (t > 0 && 2L * c->cfg.top_k <= static_cast<long>(t) * (scd::kRowListCap / t - scd::kTileSlack)) tiles = t;
   }
   if (tiles > 0) {
     scd::row_candidate_layout(static_cast<char*>(c->ws) + small_need(c->cfg), c->cfg.B * c->cfg.L, &a.cand,

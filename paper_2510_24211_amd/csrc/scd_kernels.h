@@ -34,6 +34,8 @@ hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_star
 // Name (as a profiler prints it, without namespaces and arguments) of the kernel that
 // launch_lm_head picks for these sizes (only B, C, L, d, n are read); snprintf semantics.
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap);
+// Slots that the epilogue may leave free in a tile's list of cand_cap (unless logits tie or are not finite).
+constexpr int kTileSlack = 8;
 // Number of column tiles per row (256 or 128 columns each) if the kernel that launch_lm_head picks for these sizes can
 // emit per-tile candidates, else 0 (only B, C, L, d, n are read).
 int lm_head_tiles(const LmHeadArgs& a);
