@@ -638,17 +638,20 @@ struct TileCfg {
 };
 
 // 16 bytes per lane from base + off (per lane) to LDS byte address lds + ADD + 16 * lane (lds uniform).  The
-// LDS address travels in m0, which the compiler sets right before the few instructions that need it and
-// keeps nothing in.
+// LDS address travels in m0, a reserved register: the compiler warns that it does not save what a statement
+// clobbers there.  It has nothing to save, but has to see that whatever it sets m0 for itself is set again behind.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool NT, int ADD>
 __device__ __forceinline__ void load_lds16(uint64_t base, uint32_t off, uint32_t lds) {
   if constexpr (NT)
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
-                 ::"s"(lds), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+                 ::"s"(lds), "v"(off), "s"(base), "n"(ADD) : "memory", "m0", "scc");
   else
     asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 ::"s"(lds), "v"(off), "s"(base), "n"(ADD) : "memory", "scc");
+                 ::"s"(lds), "v"(off), "s"(base), "n"(ADD) : "memory", "m0", "scc");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_loads() {       // until at most N of this wavefront's loads are in flight
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
