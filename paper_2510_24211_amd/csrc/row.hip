@@ -1371,7 +1371,8 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
 // (no top-k, or one too large for the lists): whole passes over the row in memory -- the key prefixes
 // of full_path would not fit LDS.  Bound by the vector instructions of one CU, 30 to 40 us per pass
 // over 131072 ids: three passes without a filter (111 us; 137 us as three kernels of one stage each),
-// four with a top-k of 5000 (148 us; 200 us).  Odd rows are read with 16-byte loads too (100003 ids
+// four with a top-k of 5000 or more (an iteration on supplied logits 32 x 131072 ids: 144 us; 154 us with every
+// kept id appended to a full list, 338 us as one kernel per stage).  Odd rows are read with 16-byte loads too (100003 ids
 // without a filter: 87 us against 121 us with 4-byte loads).
 __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, unsigned char* smem, float zcx,
                                           float zpx, Small& sm, RowOut& out) {
@@ -1491,15 +1492,16 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
     if (tid == 0) sm.cursor = 0u;
     __syncthreads();
   }
-  // sum in a fixed order; with a filter the kept ids are parked for the race (in any order: the
-  // race's winner does not depend on it)
+  // sum in a fixed order; the kept ids are parked for the race where a top-k says that they are few (in any
+  // order: the race's winner does not depend on it)
+  const bool park = filter && a.top_k <= kKeptCap;
   float sum = 0.f;
   int cnt = 0;
   each([&](int v, float z) {
     if (z >= thr) {
       sum += expf(z - m);
       ++cnt;
-      if (filter) {                       // a few thousand appends
+      if (park) {                         // ties at the threshold may be more than fit
         const uint32_t slot = atomicAdd(&sm.cursor, 1u);
         if (slot < static_cast<uint32_t>(kKeptCap)) {
           kid[slot] = static_cast<uint32_t>(v);
@@ -1554,7 +1556,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
     return philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
                                     static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
   };
-  if (filter && Cn <= kKeptCap) {
+  if (park && Cn <= kKeptCap) {
     for (int i = tid; i < Cn; i += THREADS) {
       const int v = static_cast<int>(kid[i]);
       const float rv = __fsub_rn(expf(kz[i] - lse_c), R.fresh ? q_uniform : prob(R.zp[v], R.thr_p, R.lse_p));
