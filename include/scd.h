@@ -217,8 +217,9 @@ int scd_couple_draft(scd_ctx* ctx, const float* d_z_cur, const float* d_z_prev,
  * does not touch the context's workspace.  Returns SCD_ESCRATCH when the configuration needs
  * more: 24 bytes per window row (B * L rows, each of the six arrays rounded up to 256 bytes),
  * plus 51200 bytes per window row when top-k filters rows of 16385..65536 ids with
- * top_k <= 3072 (the slice kernel's candidate lists), i.e. up to 163 such rows.  (Longer rows take
- * the lists while they fit and do without them beyond.)
+ * top_k <= 3072 (the slice kernel's candidate lists), i.e. up to 163 such rows.  Longer rows take
+ * the lists while they fit; beyond that they are read whole, and their normalisers, summed in
+ * another order, may differ from scd_couple_draft's in the last bits.
  * All calls on one GPU share that array and it keeps the last call's contents (nothing in it has
  * to start at zero): calls that overlap in time on one GPU -- different streams or contexts --
  * race.  The array's address is looked up once per GPU, in scd_create when a GPU is present,
@@ -251,8 +252,10 @@ int scd_step(scd_ctx* ctx, const uint16_t* d_h, const uint16_t* d_W, void* d_sta
 int scd_set_lm_head_events(scd_ctx* ctx, void* ev_start, void* ev_stop);
 
 /* For reports: writes the name of the LM-head kernel that scd_step / scd_lm_head launch
- * for this context's sizes, e.g. "lm_head_splitk_kernel<1, 2, 8>" (template arguments:
- * row blocks per workgroup, 1 + CFG, wavefronts), NUL-terminated, into host_buf[0..cap).
+ * for this context's sizes, NUL-terminated, into host_buf[0..cap).  Template arguments:
+ * lm_head_tile_kernel<1 + CFG, h rows, columns, stages, W past the caches>,
+ * lm_head_splitk_kernel<row blocks, 1 + CFG, wavefronts>,
+ * lm_head_kernel<row blocks, 1 + CFG, wavefronts, W past the caches>.
  * Returns SCD_OK, or SCD_EINVAL (NULL argument, cfg.d == 0, or cap too small).
  * Host-only call. */
 int scd_lm_head_kernel_name(scd_ctx* ctx, char* host_buf, size_t cap);

@@ -28,33 +28,48 @@ def _want(W, h, n, v_lo, lam, tau):
     return (z / tau).reshape(h.shape[0], h.shape[2], n), bound.reshape(h.shape[0], h.shape[2], n)
 
 
+# every kernel and tile, at its edges in rows, ids and k
 SHAPES = [
-    # Bn, L, n, d, lam     the kernel that serves it
-    (1, 1, 1, 64, 0.0),            # one row, one id, one k-tile
-    (1, 5, 70, 8, 3.0),            # no whole k-tile
-    (3, 7, 129, 72, 3.0),          # 64 x 128 tiles, a ragged k-tile of one chunk, rows of three sequences packed
-    (2, 16, 1000, 120, 0.0),       # two rows past a block, 15 chunks
-    (2, 17, 8300, 200, 3.0),       # 34 rows: two blocks, three whole k-tiles
-    (1, 32, 8193, 512, 3.0),       # one workgroup more than the split kernel takes
-    (5, 6, 16384, 520, 0.0),       # split kernel, packed rows
-    (1, 33, 8192, 576, 0.0),       # split kernel with two row blocks
-    (1, 20, 32769, 328, 3.0),      # 64 x 256 tiles, last one a single column
-    (1, 31, 33000, 256, 0.0),      # shared h tile, 8 wavefronts
-    (2, 33, 20000, 392, 3.0),      # 128 x 128
-    (1, 100, 44000, 264, 0.0),     # 128 x 256
-    (7, 21, 20001, 328, 3.0),      # 256 x 128, rows ragged in blocks and tiles, odd ids
-    (4, 40, 60001, 136, 3.0),      # 256 x 256, five rows blocks of ten
-    (9, 29, 65535, 64, 0.0),       # 256 x 256 without guidance: two passes of the epilogue, one k-tile
-    (300, 1, 3000, 640, 0.0),      # many sequences of one position
+    # Bn, L, n, d, lam, kernel
+    (1, 1, 1, 64, 0.0, "tile_kernel<1, 64, 128, 6, false>"),          # one row, one id, one k-tile
+    (2, 40, 300, 56, 0.0, "kernel<1, 1, 4, false>"),                  # no whole k-tile
+    (1, 5, 70, 8, 3.0, "kernel<1, 2, 4, false>"),
+    (3, 7, 129, 72, 3.0, "tile_kernel<2, 64, 128, 6, false>"),        # a ragged k-tile of one chunk, rows of three sequences packed
+    (2, 16, 1000, 120, 0.0, "tile_kernel<1, 64, 128, 6, false>"),     # one whole k-tile and 7 chunks
+    (2, 17, 8300, 200, 3.0, "tile_kernel<2, 64, 128, 6, false>"),     # 34 rows: two blocks, three whole k-tiles
+    (1, 32, 8193, 512, 3.0, "tile_kernel<2, 64, 128, 6, false>"),     # one workgroup more than the split kernel takes
+    (300, 1, 3000, 640, 0.0, "tile_kernel<1, 64, 128, 6, false>"),    # many sequences of one position
+    (5, 6, 16384, 520, 0.0, "splitk_kernel<1, 1, 8>"),                # packed rows
+    (1, 33, 8192, 576, 0.0, "splitk_kernel<2, 1, 4>"),
+    (1, 20, 32769, 328, 3.0, "tile_kernel<2, 64, 256, 4, false>"),    # last tile a single column
+    (3, 20, 51210, 136, 0.0, "tile_kernel<1, 64, 256, 4, false>"),
+    (2, 33, 33000, 4104, 3.0, "tile_kernel<2, 64, 256, 4, true>"),    # W past the caches, rows over two sequences
+    (1, 31, 33000, 256, 0.0, "kernel<1, 1, 8, false>"),
+    (1, 20, 65000, 1608, 0.0, "kernel<1, 1, 8, true>"),
+    (2, 17, 32700, 392, 3.0, "tile_kernel<2, 128, 128, 5, false>"),   # six whole k-tiles and one chunk
+    (1, 100, 24000, 392, 0.0, "tile_kernel<1, 128, 128, 5, false>"),
+    (1, 128, 25001, 4168, 0.0, "tile_kernel<1, 128, 128, 5, true>"),
+    (7, 21, 20001, 328, 3.0, "tile_kernel<2, 128, 256, 3, false>"),   # rows ragged in blocks and tiles, odd ids
+    (1, 100, 44000, 264, 0.0, "tile_kernel<1, 128, 256, 3, false>"),
+    (9, 29, 65535, 64, 0.0, "tile_kernel<1, 128, 256, 3, false>"),    # one k-tile
+    (1, 64, 50001, 2200, 3.0, "tile_kernel<2, 128, 256, 3, true>"),
+    (3, 40, 20003, 200, 3.0, "tile_kernel<2, 256, 128, 3, false>"),
+    (2, 100, 20001, 328, 0.0, "tile_kernel<1, 256, 128, 3, false>"),
+    (2, 128, 25000, 4160, 0.0, "tile_kernel<1, 256, 128, 3, true>"),
+    (2, 33, 44000, 264, 3.0, "tile_kernel<2, 256, 256, 3, false>"),
+    (3, 40, 60001, 136, 3.0, "tile_kernel<2, 256, 256, 3, false>"),   # two whole k-tiles and one chunk
+    (5, 50, 65535, 72, 0.0, "tile_kernel<1, 256, 256, 3, false>"),    # one whole k-tile and one chunk
+    (2, 64, 56000, 1800, 3.0, "tile_kernel<2, 256, 256, 3, true>"),
 ]
 
 
-@pytest.mark.parametrize("Bn,L,n,d,lam", SHAPES)
-def test_logits_against_64_bits(Bn, L, n, d, lam):
+@pytest.mark.parametrize("Bn,L,n,d,lam,kernel", SHAPES)
+def test_logits_against_64_bits(Bn, L, n, d, lam, kernel):
     C, v_lo, tau = (2 if lam else 1), 5, 0.8
     W, h = _inputs(Bn, C, L, n, d, v_lo, Bn * n + d)
     sc = B.Scd(B.make_config(B=Bn, L=L, N=300, V=W.shape[0], d=d, v_lo=v_lo, v_hi=v_lo + n, temperature=tau,
                              cfg_lambda=lam), DEV)
+    assert sc.lm_head_kernel_name() == "lm_head_" + kernel
     buf = torch.full((Bn * L * n + 64,), float("nan"), device=DEV)
     sc.lm_head(h, W, buf[:Bn * L * n])
     z = buf[:Bn * L * n].view(Bn, L, n)
@@ -63,31 +78,37 @@ def test_logits_against_64_bits(Bn, L, n, d, lam):
     assert bool(buf[Bn * L * n:].isnan().all())                        # nothing past the last row
 
 
-@pytest.mark.parametrize("Bn,L,n,d,lam,top_k", [
-    (1, 32, 17000, 256, 3.0, 500),      # 64 x 128 tiles: lists of 128 columns
-    (2, 17, 32768, 128, 3.0, 2000),     # 128 x 128: 256 lists of 128 columns
-    (3, 40, 20003, 192, 3.0, 1500),     # 256 x 128, rows packed over sequences, ragged columns
-    (1, 32, 65536, 128, 3.0, 2000),     # 64 x 256
-    (1, 20, 50001, 200, 0.0, 900),      # shared h tile
-    (1, 64, 65500, 128, 3.0, 2000),     # 128 x 256
-    (4, 33, 64000, 136, 3.0, 1000),     # 256 x 256, a second row tile with 8 of 128 rows
-    (5, 50, 65536, 64, 0.0, 2000),      # 256 x 256 without guidance: 250 rows in two passes
-    (1, 8, 40000, 64, 3.0, 2900),       # lists nearly too short for this top-k
+@pytest.mark.parametrize("Bn,L,n,d,lam,top_k,kernel,lists", [
+    (1, 32, 17000, 256, 3.0, 500, "tile_kernel<2, 64, 128, 6, false>", 133),
+    (2, 17, 32768, 128, 3.0, 2000, "tile_kernel<2, 128, 128, 5, false>", 256),    # as many lists as a row has room for
+    (3, 40, 20003, 192, 3.0, 1500, "tile_kernel<2, 256, 128, 3, false>", 157),    # rows packed over sequences, ragged ids
+    (1, 32, 65536, 128, 3.0, 2000, "tile_kernel<2, 64, 256, 4, false>", 256),
+    (1, 20, 50001, 200, 0.0, 900, "kernel<1, 1, 8, false>", 196),
+    (1, 64, 65500, 128, 3.0, 2000, "tile_kernel<2, 128, 256, 3, false>", 256),
+    (4, 33, 32768, 136, 3.0, 1000, "tile_kernel<2, 256, 256, 3, false>", 128),    # a second row tile with 4 of 128 rows
+    (5, 50, 65536, 64, 0.0, 2000, "tile_kernel<1, 256, 256, 3, false>", 256),     # 250 rows in two passes
+    (1, 8, 40000, 64, 3.0, 2433, "tile_kernel<2, 64, 256, 4, false>", 157),       # the largest top-k for these lists
+    (1, 8, 40000, 64, 3.0, 2434, "tile_kernel<2, 64, 256, 4, false>", 5),         # one more: slices
 ])
-def test_step_selects_what_a_selection_over_its_logits_does(Bn, L, n, d, lam, top_k):
+def test_step_selects_what_a_selection_over_its_logits_does(Bn, L, n, d, lam, top_k, kernel, lists):
     C = 2 if lam else 1
     W, h = _inputs(Bn, C, L, n, d, 0, n + top_k)
     rows = Bn * L
     W[:40] = W[0].clone()                      # ids that tie in every row
     cfg = dict(B=Bn, L=L, N=L + 20, V=W.shape[0], d=d, v_lo=0, v_hi=n, top_k=top_k, cfg_lambda=lam, seed=9)
     sc = B.Scd(B.make_config(**cfg), DEV)
+    assert sc.lm_head_kernel_name() == "lm_head_" + kernel
     st = sc.alloc_state()
     sc.reset(st)
     f = lambda field, *shape: sc.state_field(st, field).view(*shape)  # noqa: E731
+    # the lists' lengths, behind six per-row arrays and 6144 pairs per row
+    lengths = sc.workspace[6 * ((4 * rows + 255) // 256 * 256) + rows * 6144 * 8:][:4 * 256 * rows].view(torch.int32)
+    lengths.fill_(-1)
     pos = torch.zeros(Bn, dtype=torch.int64)
     for it in range(3):                        # the windows of later iterations wrap around the ring and end
         live = [[b, (int(pos[b]) + s) % L] for b in range(Bn) for s in range(min(L, L + 20 - int(pos[b])))]
         sc.step(h, W, st)
+        assert it > 0 or int((lengths >= 0).sum()) == rows * lists
         sel = torch.tensor(live, device=DEV)
         z = f(B.F_Z, 2, Bn, L, n)[it & 1, sel[:, 0], sel[:, 1]].contiguous()
         thr, lse = torch.empty(rows, device=DEV), torch.empty(rows, device=DEV)

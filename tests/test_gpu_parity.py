@@ -33,22 +33,22 @@ def _require_gpu_and_library():
     (1, 32, 1280, 2000, 0, 2000, 0.0, 1.0),     # ragged vocabulary tail (2000 = 15*128 + 80)
     (1, 32, 512, 4096, 4, 1300, 3.0, 1.0),      # CFG + unaligned id range
     (2, 64, 520, 777, 0, 777, 3.0, 0.7),        # d not a multiple of the k tile, tau != 1
-    (3, 8, 64, 300, 10, 290, 3.0, 1.0),         # window shorter than a row block
+    (3, 8, 64, 300, 10, 290, 3.0, 1.0),         # windows shorter than a row block: packed
     (5, 40, 128, 640, 0, 640, 1.5, 1.0),        # L not a multiple of 32, odd B
     (1, 1, 64, 256, 0, 256, 0.0, 1.0),          # L = 1
     (16, 32, 256, 512, 0, 512, 3.0, 1.0),       # several row-block tiles share a W slab
-    # split-k kernel with XCD-affine row groups of G = 128 KB / row bytes rows, ragged against 8 G,
-    # first allowed row not on a block boundary:
-    (1, 32, 2048, 4096, 3, 4000, 3.0, 1.0),     # G = 32, 4 k parts
+    # split-k kernel (8 k parts) with XCD-affine row groups of G = 128 KB / row bytes rows, ragged against
+    # 8 G, first allowed row not on a block boundary:
+    (1, 32, 2048, 4096, 3, 4000, 3.0, 1.0),     # G = 32
     (1, 32, 1024, 3000, 0, 3000, 0.0, 1.0),     # G = 64
-    (1, 32, 8192, 1500, 5, 1400, 3.0, 1.0),     # G = 8, 8 k parts
-    (2, 32, 4096, 2500, 7, 2407, 3.0, 1.0),     # G = 16, two row blocks per workgroup
-    (4, 32, 4096, 1000, 0, 1000, 3.0, 1.0),     # G = 16 available but many row blocks: wide kernel
-    # exactly 4 (or 3) row blocks and a wide vocabulary: the all-rows-in-one-workgroup kernel
+    (1, 32, 8192, 1500, 5, 1400, 3.0, 1.0),     # G = 8
+    (2, 32, 4096, 2500, 7, 2407, 3.0, 1.0),     # more rows: 64 x 128 tiles, k in 4 parts
+    (4, 32, 4096, 1000, 0, 1000, 3.0, 1.0),     # 64 x 128 tiles, k in one
+    # a wide vocabulary: 256 x 256 tiles
     (2, 64, 256, 52000, 0, 52000, 3.0, 1.0),
     (1, 100, 192, 51300, 5, 51290, 3.0, 1.0),   # ragged n, ragged L, odd number of k tiles
-    (3, 20, 136, 51210, 0, 51210, 0.0, 0.9),    # 3 row blocks, no CFG, d not a multiple of the k tile
-    (2, 64, 128, 51200, 0, 51200, 3.0, 1.0),    # its shortest k loop: 2 tiles
+    (3, 20, 136, 51210, 0, 51210, 0.0, 0.9),    # 64 x 256 tiles, no CFG, d not a multiple of the k tile
+    (2, 64, 128, 51200, 0, 51200, 3.0, 1.0),    # 2 k tiles
 ])
 def test_lm_head_against_oracle(Bn, L, d, V, v_lo, v_hi, lam, tau):
     g = np.random.default_rng(hash((Bn, L, d, V)) % 2 ** 32)
@@ -172,7 +172,7 @@ def test_select_nucleus_against_oracle(n, top_k, top_p):
 # ------------------------------------------------------------- MRS stage
 @pytest.mark.parametrize("Bn,L,n,top_k,N,pos0,top_p", [
     (1, 8, 1024, 0, 64, [0], 0.0),
-    (2, 16, 1000, 100, 40, [3, 30], 0.0),      # ragged n (scalar loads), second window clipped to 10 rows
+    (2, 16, 1000, 100, 40, [3, 30], 0.0),      # ragged n, second window clipped to 10 rows
     (1, 32, 8192, 2000, 2304, [100], 0.0),
     (3, 5, 37, 7, 50, [0, 45, 49], 0.0),       # tiny vocabulary, windows of 5 / 5 / 1 rows
     (2, 16, 4096, 500, 100, [0, 90], 0.7),     # nucleus filter after top-k
