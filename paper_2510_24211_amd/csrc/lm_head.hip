@@ -339,7 +339,7 @@ __device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, const float
 #pragma unroll
     for (int e = 0; e < E; ++e) take[e] = q[i][e] >= cutq && (!ragged || ok[e]);
     place();
-    if (cutq > 0 && total < cap - kTileSlack) {          // uniform
+    if (__builtin_expect(cutq > 0 && total < cap - kTileSlack, 0)) {   // uniform
       bool in[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) in[e] = q[i][e] == cutq - 1 && (!ragged || ok[e]);
