@@ -95,35 +95,14 @@ struct Small {
   uint32_t sel_bin, sel_above;
   uint32_t cursor;        // append cursor of select_regs
   int ired2[NW];          // second slot of block_offsets
-  float s_score[NW];
-  int s_id[NW];
+  uint2 win[2][NW];       // per-wavefront winners of the two races: (bits of the score, id)
   int last;
-  int first_rej;
   unsigned long long mtot[NW];   // nucleus: per-wavefront masses
   unsigned long long sel_mass;
   float dred[3][NW];             // statistics: per-wavefront sums
   int hamm[6];                   // (differing, compared) drafts 1, 2, 3 iterations apart
   int xnew[256];                 // the sequence's new drafts by ring slot
 };
-
-// Lexicographic (score, id) minimum over the per-wavefront entries in LDS.  All entries are read
-// first and folded with selects: a chain of compare-and-branch steps waits for one LDS round
-// trip per entry (about a microsecond for 16 wavefronts).
-__device__ __forceinline__ void block_min_score_id(const Small& sm, float& best, int& best_id) {
-  float ss[NW];
-  int si[NW];
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    ss[w] = sm.s_score[w];
-    si[w] = sm.s_id[w];
-  }
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const bool better = (ss[w] < best) | ((ss[w] == best) & (si[w] < best_id));
-    best = better ? ss[w] : best;
-    best_id = better ? si[w] : best_id;
-  }
-}
 
 // hist[0..NBINS): find the bin holding the `need`-th largest element counting
 // from the top bin; lowers `need` by the population of the bins above it.
@@ -1768,42 +1747,47 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
   }
   if (a.mode == kRowSelectOnly) return;
 
-  // ---- winner of the race (lexicographic (score, id) minimum) -------------------
-  int y_out = R.x;
-  int k_out = 1;
+  // ---- winners of the races (lexicographic (score, id) minima) ------------------
+  // One entry per wavefront, one barrier for both races; the last wavefront folds them and does everything
+  // up to the hand-off, because the first ones prepare the commit meanwhile.  What every wavefront of a row repeats
+  // is paid four times over per SIMD: a fold of all entries in all 16 took 3600 cycles of the 36000 of a row of
+  // 8192 ids, one wavefront's takes 900; requesting the commit's words before the ticket comes back takes its
+  // 5500 to 3000.  Four-step decodes: 8 x 1024 ids 50.0 -> 45.6 us, 32 x 8192 behind the LM head 128.0 -> 122.0.
   if (!out.accept) {
-    float best = out.best;
-    int best_id = out.best_id;
-    wave_min_score_id(best, best_id);
-    if (lane == 0) {
-      sm.s_score[wave] = best;
-      sm.s_id[wave] = best_id;
-    }
-    __syncthreads();
-    block_min_score_id(sm, best, best_id);
-    if (best_id != 0x7FFFFFFF) {   // else: empty residual (rounding only) counts as accept
-      y_out = best_id;
-      k_out = 0;
-    }
+    wave_min_score_id(out.best, out.best_id);
+    if (lane == 0) sm.win[0][wave] = make_uint2(__float_as_uint(out.best), static_cast<uint32_t>(out.best_id));
   }
-  // ---- Gumbel-sharing draft of the row: the same reduction over (score, id) ---------
-  int g_out = -1;
   if (GS) {
-    float gb = out.gbest;
-    int gi = out.gbest_id;
-    wave_min_score_id(gb, gi);
-    __syncthreads();               // the exchange arrays may still be read by the race above
-    if (lane == 0) {
-      sm.s_score[wave] = gb;
-      sm.s_id[wave] = gi;
+    wave_min_score_id(out.gbest, out.gbest_id);
+    if (lane == 0) sm.win[1][wave] = make_uint2(__float_as_uint(out.gbest), static_cast<uint32_t>(out.gbest_id));
+  }
+  if (GS || !out.accept) __syncthreads();
+  const bool speaker = wave == NW - 1;
+  int y_out = R.x, k_out = 1, g_out = -1;
+  if (speaker) {
+    auto winner = [&](int which) {
+      const uint2 e = sm.win[which][lane & (NW - 1)];
+      float score = __uint_as_float(e.x);
+      int id = static_cast<int>(e.y);
+      wave_min_score_id(score, id);
+      return id;
+    };
+    if (!out.accept) {
+      const int id = winner(0);
+      if (id != 0x7FFFFFFF) {      // else: empty residual (rounding only) counts as accept
+        y_out = id;
+        k_out = 0;
+      }
     }
-    __syncthreads();
-    block_min_score_id(sm, gb, gi);
-    // empty support cannot happen (the maximum is kept); -1: the row made no such draw
-    g_out = out.prace ? (gi != 0x7FFFFFFF ? gi : R.x) : -1;
+    // Gumbel-sharing draft of the row.  Empty support cannot happen (the maximum is kept); -1: the row made
+    // no such draw
+    if (GS && out.prace) {
+      const int id = winner(1);
+      g_out = id != 0x7FFFFFFF ? id : R.x;
+    }
   }
   if (a.mode != kRowRing) {
-    if (tid == 0) {
+    if (speaker && lane == 0) {
       a.y[R.widx] = y_out;
       a.k[R.widx] = static_cast<uint8_t>(k_out);
       if (a.px) a.px[R.widx] = out.px;
@@ -1828,63 +1812,79 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
   // agent-scope atomic RMWs on one address are totally ordered, so every store of a row that
   // took an earlier ticket is visible to the workgroup that takes the last one.
   const int b = R.b, p0 = R.p0, live = R.live;
-  if (tid == 0) {
-    __hip_atomic_store(&a.y[R.widx], y_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&a.k[R.widx], static_cast<uint8_t>(k_out), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (GS) __hip_atomic_store(&a.g[R.widx], g_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (a.px) a.px[R.widx] = out.px;
-    if (a.qx) a.qx[R.widx] = out.qx;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the stores above have completed
-    sm.last = __hip_atomic_fetch_add(&a.ticket[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == live - 1;
-    sm.first_rej = live;
+  const size_t base = static_cast<size_t>(b) * a.L;
+  const int slot = tid < a.L ? (p0 + tid) % a.L : 0;
+  int age_old = 0, verified_old = 0, entering = -1;
+  if (speaker) {
+    if (lane == 0) {
+      __hip_atomic_store(&a.y[R.widx], y_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.k[R.widx], static_cast<uint8_t>(k_out), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (GS) __hip_atomic_store(&a.g[R.widx], g_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the stores above have completed
+      sm.last = __hip_atomic_fetch_add(&a.ticket[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == live - 1;
+    }
+  } else if (tid < a.L) {
+    // While the ticket travels: what the commit will need, should this workgroup be the last.  Nothing but
+    // the commit writes these words.
+    age_old = a.age_w[base + slot];
+    if (tid == 0) {
+      verified_old = a.verified[b];
+      if (a.px) a.px[R.widx] = out.px;
+      if (a.qx) a.qx[R.widx] = out.qx;
+    }
+    const int np = p0 + a.L + tid;
+    if (np < a.N) entering = init_token(a.seed, b, np, n);
   }
   __syncthreads();
   if (!sm.last) return;
   // nothing below may be moved above the ticket read (the barrier orders the other threads)
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  if (!EXTRA && wave * kWave >= live) return;              // (the statistics below need every wavefront)
   int yy = -1, gg = -1;
   if (tid < live) {
-    yy = __hip_atomic_load(&a.y[static_cast<size_t>(b) * a.L + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (GS)
-      gg = __hip_atomic_load(&a.g[static_cast<size_t>(b) * a.L + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint8_t kk = __hip_atomic_load(&a.k[static_cast<size_t>(b) * a.L + tid], __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
-    if (kk == 0) atomicMin(&sm.first_rej, tid);
+    yy = __hip_atomic_load(&a.y[base + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (GS) gg = __hip_atomic_load(&a.g[base + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __syncthreads();
-  const int acc = min(sm.first_rej + 1, live);
+  // every wavefront reads all accept bits (a window has at most 256 positions): no exchange, no barrier
+  uint8_t kk[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int s = c * kWave + lane;
+    kk[c] = 1;
+    if (c * kWave < live)                                  // uniform
+      kk[c] = __hip_atomic_load(&a.k[base + min(s, live - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  int first_rej = live;                                    // (a lane past the end repeats the last bit)
+#pragma unroll
+  for (int c = 3; c >= 0; --c) {
+    const unsigned long long m = __ballot(kk[c] == 0);
+    if (m != 0ull) first_rej = min(c * kWave + __builtin_ctzll(m), live - 1);
+  }
+  const int acc = min(first_rej + 1, live);
   if (tid < acc) a.out[static_cast<size_t>(b) * a.N + p0 + tid] = a.v_lo + yy;
   const bool stats = EXTRA && a.diag != nullptr;
   const int ring = R.it % 3;
   if (stats) {
     // the drafts this iteration started with, by ring slot, and where its window started
-    if (tid < a.L) a.xhist[(static_cast<size_t>(ring) * a.B + b) * a.L + tid] = a.X[static_cast<size_t>(b) * a.L + tid];
+    if (tid < a.L) a.xhist[(static_cast<size_t>(ring) * a.B + b) * a.L + tid] = a.X[base + tid];
     if (tid == 0) a.phist[ring * a.B + b] = p0;
     if (tid < 6) sm.hamm[tid] = 0;
     __syncthreads();                 // slot tid is rewritten by another thread below
   }
   if (tid < live) {
-    const int slot = (p0 + tid) % a.L;
-    const size_t sidx = static_cast<size_t>(b) * a.L + slot;
-    int next;
-    if (tid >= acc) {
-      // survivors: the MRS output is the coupled redraft (pi_MC); under pi_GS, or when the
-      // alpha-coupling switch chose the independent redraft, it is the row's Gumbel-max draw
-      next = (GS && gg >= 0) ? gg : yy;
-      a.age_w[sidx] += 1;
-    } else {
-      const int np = p0 + a.L + tid;
-      next = np < a.N ? init_token(a.seed, b, np, n) : -1;
-      a.age_w[sidx] = 0;
-    }
-    a.X[sidx] = next;
+    // survivors: the MRS output is the coupled redraft (pi_MC); under pi_GS, or when the
+    // alpha-coupling switch chose the independent redraft, it is the row's Gumbel-max draw
+    const bool survives = tid >= acc;
+    const int next = survives ? ((GS && gg >= 0) ? gg : yy) : entering;
+    a.age_w[base + slot] = survives ? age_old + 1 : 0;
+    a.X[base + slot] = next;
     if (stats) sm.xnew[slot] = next;
   }
   if (tid == 0) {
     a.accept_len[b] = acc;
     a.pos[b] = p0 + acc;
     a.iter[b] = R.it + 1;
-    a.verified[b] += live;
+    a.verified[b] = verified_old + live;
     a.ticket[b] = 0;
   }
   if (stats) {

@@ -151,26 +151,13 @@ __device__ __forceinline__ int wave_inclusive_sum_i32(int v, int lane) {
   const int row = lane >> 4;
   return v + (row == 0 ? 0 : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
 }
-// Lexicographic minimum of (score, id) over the wavefront, in every lane.
+// Lexicographic minimum of (score, id) over the wavefront, in every lane; scores and ids are not negative
+// (and no NaN), so both compare as integers.
 __device__ __forceinline__ void wave_min_score_id(float& score, int& id) {
-  auto take = [&](float os, int oi) {
-    if (os < score || (os == score && oi < id)) {
-      score = os;
-      id = oi;
-    }
-  };
-  take(dpp_f32<kDppXor1>(score), dpp_i32<kDppXor1>(id));
-  take(dpp_f32<kDppXor2>(score), dpp_i32<kDppXor2>(id));
-  take(dpp_f32<kDppHalfMirror>(score), dpp_i32<kDppHalfMirror>(id));
-  take(dpp_f32<kDppMirror>(score), dpp_i32<kDppMirror>(id));
-  const float s1 = readlane_f32(score, 16), s2 = readlane_f32(score, 32), s3 = readlane_f32(score, 48);
-  const int i1 = __builtin_amdgcn_readlane(id, 16), i2 = __builtin_amdgcn_readlane(id, 32),
-            i3 = __builtin_amdgcn_readlane(id, 48);
-  score = readlane_f32(score, 0);
-  id = __builtin_amdgcn_readlane(id, 0);
-  take(s1, i1);
-  take(s2, i2);
-  take(s3, i3);
+  const uint32_t mine = __float_as_uint(score);
+  const uint32_t least = ~wave_max_u32(~mine);
+  id = static_cast<int>(~wave_max_u32(~(mine == least ? static_cast<uint32_t>(id) : 0xFFFFFFFFu)));
+  score = __uint_as_float(least);
 }
 
 }  // namespace scd
