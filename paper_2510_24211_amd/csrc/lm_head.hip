@@ -219,7 +219,7 @@ __device__ __forceinline__ int find_cut(const uint32_t* hist, int lane, int all,
   const uint4 c4 = *reinterpret_cast<const uint4*>(&hist[4 * lane]);
   const int c[4] = {static_cast<int>(c4.x), static_cast<int>(c4.y), static_cast<int>(c4.z), static_cast<int>(c4.w)};
   const int mine = (c[0] + c[1]) + (c[2] + c[3]);
-  int above = all - wave_inclusive_sum_i32(mine, lane) + mine;           // logits in bins >= 4 * lane
+  int above = all - wave_inclusive_sum_i32(mine) + mine;           // logits in bins >= 4 * lane
   int cut = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {

@@ -88,11 +88,12 @@ constexpr int kKeptCap = 4096;               // kept ids compacted in LDS
 struct Small {
   float fred[NW];
   uint32_t ured[NW];
-  uint32_t umin[NW];
+  uint32_t umin[NW];      // complements
   uint32_t umax[NW];
   int ired[NW];
-  uint32_t wtot[NW];
-  uint32_t sel_bin, sel_above;
+  int wtot[NW];
+  uint4 sel;              // find_bin's bin, the population above it and its own
+  uint32_t sel_bin;
   uint32_t cursor;        // append cursor of select_regs
   int ired2[NW];          // second slot of block_offsets
   uint2 win[2][NW];       // per-wavefront winners of the two races: (bits of the score, id)
@@ -105,53 +106,59 @@ struct Small {
 };
 
 // hist[0..NBINS): find the bin holding the `need`-th largest element counting
-// from the top bin; lowers `need` by the population of the bins above it.
-// The trailing barrier keeps a later writer of sel_bin / sel_above / wtot away from slow
+// from the top bin; lowers `need` by the population of the bins above it.  members: its population.
+// The trailing barrier keeps a later writer of sel / wtot away from slow
 // readers; a caller whose next such write comes after another barrier anyway may drop it.
 // T: threads of the workgroup (the row kernel's, or the slice kernel's smaller one).
 template <int T = THREADS>
-__device__ __forceinline__ uint32_t find_bin(const uint32_t* hist, uint32_t& need, Small& sm,
+__device__ __forceinline__ uint32_t find_bin(const uint32_t* hist, uint32_t& need, uint32_t& members, Small& sm,
                                              bool trailing = true) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   constexpr int PER = NBINS / T;         // consecutive bins per thread, top bins in thread 0
+  static_assert(PER % 4 == 0, "find_bin: 16-byte reads");
   uint32_t c[PER], local = 0;
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    c[j] = hist[NBINS - 1 - (tid * PER + j)];
-    local += c[j];
+  for (int j = 0; j < PER; j += 4) {
+    const uint4 t = *reinterpret_cast<const uint4*>(&hist[NBINS - 4 - (tid * PER + j)]);
+    c[j] = t.w; c[j + 1] = t.z; c[j + 2] = t.y; c[j + 3] = t.x;
+    local += (t.w + t.z) + (t.y + t.x);
   }
-  uint32_t incl = static_cast<uint32_t>(wave_inclusive_sum_i32(static_cast<int>(local), lane));
-  if (lane == 63) sm.wtot[wave] = incl;
+  const uint32_t incl_wave = static_cast<uint32_t>(wave_inclusive_sum_i32(static_cast<int>(local)));
+  if (lane == 63) sm.wtot[wave] = static_cast<int>(incl_wave);
   __syncthreads();
-  // all totals read at once: a loop up to this wavefront waits for one LDS round trip per entry
-  uint32_t base = 0;
-#pragma unroll
-  for (int w = 0; w < T / kWave; ++w) base += w < wave ? sm.wtot[w] : 0u;
-  incl += base;
+  int total;
+  const uint32_t incl = incl_wave + static_cast<uint32_t>(fold_before<T / kWave>(sm.wtot, wave, total));
   const uint32_t excl = incl - local;
   if (excl < need && need <= incl) {     // exactly one thread
     uint32_t above = excl;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
       if (above + c[j] >= need) {
-        sm.sel_bin = static_cast<uint32_t>(NBINS - 1 - (tid * PER + j));
-        sm.sel_above = above;
+        sm.sel = make_uint4(static_cast<uint32_t>(NBINS - 1 - (tid * PER + j)), above, c[j], 0u);
         break;
       }
       above += c[j];
     }
   }
   __syncthreads();
-  const uint32_t bin = sm.sel_bin;
-  need -= sm.sel_above;
+  const uint4 sel = sm.sel;
+  need -= sel.y;
+  members = sel.z;
   if (trailing) __syncthreads();
-  return bin;
+  return sel.x;
+}
+template <int T = THREADS>
+__device__ __forceinline__ uint32_t find_bin(const uint32_t* hist, uint32_t& need, Small& sm,
+                                             bool trailing = true) {
+  uint32_t members;
+  return find_bin<T>(hist, need, members, sm, trailing);
 }
 
 template <int T = THREADS>
 __device__ __forceinline__ void zero_hist(uint32_t* hist) {
 #pragma unroll
-  for (int j = 0; j < NBINS / T; ++j) hist[threadIdx.x + j * T] = 0u;
+  for (int j = 0; j < NBINS / T; j += 4)
+    *reinterpret_cast<uint4*>(&hist[threadIdx.x * 4 + j * T]) = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __device__ __forceinline__ float prob(float z, float thr, float lse) {
@@ -164,18 +171,12 @@ __device__ __forceinline__ float prob(float z, float thr, float lse) {
 template <int T = THREADS>
 __device__ __forceinline__ int block_offsets(int cnt, int& total, Small& sm, int slot = 0,
                                              bool trailing = true) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int incl = wave_inclusive_sum_i32(cnt, lane);
+  const int lane = threadIdx.x & 63, wave = wave_index();
+  const int incl = wave_inclusive_sum_i32(cnt);
   int* const ex = slot ? sm.ired2 : sm.ired;
   if (lane == 63) ex[wave] = incl;
   __syncthreads();
-  int base = 0;
-  total = 0;
-#pragma unroll
-  for (int w = 0; w < T / kWave; ++w) {
-    base += w < wave ? ex[w] : 0;
-    total += ex[w];
-  }
+  const int base = fold_before<T / kWave>(ex, wave, total);
   if (trailing) __syncthreads();
   return base + incl - cnt;
 }
@@ -184,19 +185,16 @@ __device__ __forceinline__ int block_offsets(int cnt, int& total, Small& sm, int
 template <int T = THREADS>
 __device__ __forceinline__ void block_minmax(uint32_t& kmin, uint32_t& kmax, Small& sm,
                                              bool trailing = true) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = wave_index();
   kmax = wave_max_u32(kmax);
   kmin = ~wave_max_u32(~kmin);
   if (lane == 0) {
     sm.umax[wave] = kmax;
-    sm.umin[wave] = kmin;
+    sm.umin[wave] = ~kmin;
   }
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < T / kWave; ++w) {
-    kmax = sm.umax[w] > kmax ? sm.umax[w] : kmax;
-    kmin = sm.umin[w] < kmin ? sm.umin[w] : kmin;
-  }
+  kmax = fold_max<T / kWave>(sm.umax);
+  kmin = ~fold_max<T / kWave>(sm.umin);
   if (trailing) __syncthreads();
 }
 
@@ -258,61 +256,63 @@ __device__ __forceinline__ void thread_range(const float (&zv)[PER], const bool 
   }
 }
 
+// To an unsigned integer: what is negative or NaN becomes 0, what is too large the largest.
+__device__ __forceinline__ uint32_t saturating_u32(float f) {
+  uint32_t r;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(f));
+  return r;
+}
+
 // `need`-th largest key among the register-resident logits zv[e] (valid where ok[e]).  zlo is the
 // smallest of the valid logits above -1e30, zhi the largest.
 //   Level 1 bins the logits LINEARLY in value between those two (any monotone map
 //   of the value preserves the order statistic; a linear one spreads a bell-shaped
 //   row over all bins, where the float bit pattern would pile it into a few
 //   exponent bins and serialise the LDS atomics).
-//   Level 2 ranks the handful of members of the selected bin against each other.
+//   Level 2 ranks the handful of members of the selected bin against each other, in every wavefront for
+//   itself (lane to lane: an exchange through LDS costs a barrier and a round trip per member).
 //   Should that bin hold more than kRankMax members (massive ties, or a few far logits that widen the
 //   range and with it every bin), radix levels over the key bits finish the job: three histograms, 4 us
-//   whatever their number, where comparing each with all others takes 0.16 us per member (scd_select on 32 rows
-//   of 8192 ids with two logits 1000 away: 220 -> 13 us, 100 away 25 -> 12 us; about 25 members are even).
-constexpr uint32_t kRankMax = 32;
+//   whatever their number.
+constexpr uint32_t kRankMax = 64;            // one per lane
 template <int PER, int T = THREADS>
 __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bool (&ok)[PER], float zlo,
                                                 float zhi, uint32_t need, uint32_t* hist,
                                                 uint32_t* arr, Small& sm) {
   // hist was zeroed by the caller before the barrier of block_minmax; arr (NBINS entries,
   // disjoint from hist) takes the members of the selected bin.
-  const float scale = (zhi > zlo) ? __fdiv_rn(static_cast<float>(NBINS - 1), zhi - zlo) : 0.f;
-  int bin[PER];
+  const float scale = (zhi > zlo) ? fminf(__fdiv_rn(static_cast<float>(NBINS - 1), zhi - zlo), 3.0e38f) : 0.f;
+  uint32_t bin[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    // below the floor, or where the range is empty or infinite (NaN): bin 0
-    bin[e] = static_cast<int>(fminf(fmaxf((zv[e] - zlo) * scale, 0.f), static_cast<float>(NBINS - 1)));
+    // Below the floor, or where the range is empty or infinite (NaN): bin 0, which the conversion gives for
+    // what is negative or no number.  At most (zhi - zlo) * scale < NBINS (the scale is kept finite for ranges
+    // of a few denormal numbers).
+    bin[e] = saturating_u32((zv[e] - zlo) * scale);
   }
   if (threadIdx.x == 0) sm.cursor = 0u;          // append cursor, published by the next barrier
 #pragma unroll
   for (int e = 0; e < PER; ++e)
     if (ok[e]) atomicAdd(&hist[bin[e]], 1u);
   __syncthreads();
-  // no trailing barrier: sel_bin is next written after the barrier that follows the append
-  const int b1 = static_cast<int>(find_bin<T>(hist, need, sm, false));
-  const uint32_t members = hist[b1];
+  // no trailing barrier: sm.sel is next written after the barrier that follows the append
+  uint32_t members;
+  const uint32_t b1 = find_bin<T>(hist, need, members, sm, false);
   if (members <= kRankMax) {
 #pragma unroll
     for (int e = 0; e < PER; ++e)
       if (ok[e] && bin[e] == b1) arr[atomicAdd(&sm.cursor, 1u)] = zkey(zv[e]);
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      if (ok[e] && bin[e] == b1) {
-        const uint32_t mine = zkey(zv[e]);
-        uint32_t gt = 0, ge = 0;
-        for (uint32_t i = 0; i < members; ++i) {
-          const uint32_t k = arr[i];
-          gt += k > mine ? 1u : 0u;
-          ge += k >= mine ? 1u : 0u;
-        }
-        if (gt < need && need <= ge) sm.sel_bin = mine;    // equal keys write the same value
-      }
-    }
-    __syncthreads();
-    return sm.sel_bin;      // its next writer sits behind the barriers of the caller's next step
+    // Every wavefront holds one member per lane and ranks them against each other: the smallest that has fewer
+    // than `need` above it is the one.
+    const int lane = threadIdx.x & 63, m = __builtin_amdgcn_readfirstlane(static_cast<int>(members));
+    const uint32_t mine = lane < m ? arr[lane] : 0u;
+    uint32_t above = 0;
+    for (int i = 0; i < m; ++i)
+      above += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mine), i)) > mine ? 1u : 0u;
+    return ~wave_max_u32(lane < m && above < need ? ~mine : 0u);
   }
-  __syncthreads();          // every thread has read hist[b1] before the histogram is reused
+  __syncthreads();          // every thread has read its bins before the histogram is reused
   // radix levels over the key bits of the members, range [lo, lo + width)
   uint32_t lo = 0;
   uint64_t width = 1ull << 32;
@@ -358,11 +358,11 @@ __device__ __forceinline__ unsigned long long mass_of(float z, float m) {
   return static_cast<unsigned long long>(expf(z - m) * 1099511627776.0f);   // <= 2^40
 }
 
-__device__ __forceinline__ unsigned long long wave_inclusive_sum_u64(unsigned long long v, int lane) {
+__device__ __forceinline__ unsigned long long wave_inclusive_sum_u64(unsigned long long v) {
   // three 24-bit limbs: 64 lanes x 2^24 stays inside an int
-  const int l0 = wave_inclusive_sum_i32(static_cast<int>(v & 0xFFFFFFull), lane);
-  const int l1 = wave_inclusive_sum_i32(static_cast<int>((v >> 24) & 0xFFFFFFull), lane);
-  const int l2 = wave_inclusive_sum_i32(static_cast<int>(v >> 48), lane);
+  const int l0 = wave_inclusive_sum_i32(static_cast<int>(v & 0xFFFFFFull));
+  const int l1 = wave_inclusive_sum_i32(static_cast<int>((v >> 24) & 0xFFFFFFull));
+  const int l2 = wave_inclusive_sum_i32(static_cast<int>(v >> 48));
   return static_cast<unsigned long long>(static_cast<uint32_t>(l0)) +
          (static_cast<unsigned long long>(static_cast<uint32_t>(l1)) << 24) +
          (static_cast<unsigned long long>(static_cast<uint32_t>(l2)) << 48);
@@ -388,7 +388,7 @@ __device__ __forceinline__ uint32_t find_bin_mass(const unsigned long long* mh, 
     c[j] = idx < NBINS_P ? mh[NBINS_P - 1 - idx] : 0ull;
     local += c[j];
   }
-  unsigned long long incl = wave_inclusive_sum_u64(local, lane);
+  unsigned long long incl = wave_inclusive_sum_u64(local);
   if (lane == 63) sm.mtot[wave] = incl;
   __syncthreads();
   unsigned long long base = above, total = 0;
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
                                                         const int mode_, const int L_, const int N_,
                                                         const int P, const int capE, const int rank,
                                                         const RowArgs a) {
-  __shared__ uint32_t hist[NBINS];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[NBINS];
   __shared__ uint32_t arr[NBINS];
   __shared__ Small sm;
   constexpr int PS = kSliceMax / ST;   // logits per thread
@@ -840,9 +840,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   sum = wave_sum(sum);
   if (lane == 0) sm.fred[wave] = sum;
   __syncthreads();
-  float S = 0.f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) S += sm.fred[w];
+  const float S = fold_sum<NW>(sm.fred);
   const float lse_c = m + logf(S);
   if (tid == 0) {
     a.thr[R.oidx] = thr;
@@ -1044,8 +1042,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   kmax = wave_max_u32(kmax);
   if (lane == 0) sm.ured[wave] = kmax;
   block_minmax(p16min, p16max, sm);      // its barriers also publish ured and the LDS prefixes
-#pragma unroll
-  for (int w = 0; w < NW; ++w) kmax = sm.ured[w] > kmax ? sm.ured[w] : kmax;
+  kmax = fold_max<NW>(sm.ured);
   const float m = key_to_float(kmax);
 
   const int nchunks = n8 >> 3;           // thread owns the 8-id chunks tid, tid + THREADS, ...
@@ -1273,13 +1270,9 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
     sm.ired[wave] = cnt;
   }
   __syncthreads();
-  float S = 0.f;
-  int Cn = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    S += sm.fred[w];
-    Cn += sm.ired[w];
-  }
+  const float S = fold_sum<NW>(sm.fred);
+  int Cn;
+  fold_before<NW>(sm.ired, 0, Cn);
   const float lse_c = m + logf(S);
   if (tid == 0) {
     a.thr[R.oidx] = thr;
@@ -1440,8 +1433,8 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
     each([&](int, float z) { atomicAdd(&hist[lin_bin(z)], 1u); });
     __syncthreads();
     uint32_t need = static_cast<uint32_t>(a.top_k);
-    const int b1 = static_cast<int>(find_bin(hist, need, sm));
-    const uint32_t members = hist[b1];
+    uint32_t members;
+    const int b1 = static_cast<int>(find_bin(hist, need, members, sm));
     const bool parked = members <= static_cast<uint32_t>(kKeptCap);
     if (parked)                                              // in any order: they are only counted
       each([&](int, float z) {
@@ -1496,13 +1489,9 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
     sm.ired[wave] = cnt;
   }
   __syncthreads();
-  float S = 0.f;
-  int Cn = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    S += sm.fred[w];
-    Cn += sm.ired[w];
-  }
+  const float S = fold_sum<NW>(sm.fred);
+  int Cn;
+  fold_before<NW>(sm.ired, 0, Cn);
   const float lse_c = m + logf(S);
   if (tid == 0) {
     a.thr[R.oidx] = thr;
@@ -1708,20 +1697,16 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
       const bool anybad = __ballot(tc > static_cast<uint32_t>(capE)) != 0ull;
       if (lane == 0) {
         sm.ired2[wave] = tot;
-        sm.wtot[wave] = cm;
+        sm.ured[wave] = cm;
         sm.ired[wave] = anybad ? 1 : 0;
       }
     }
     __syncthreads();                // their next writers sit behind the barrier of block_minmax
-    bool fits = true;
-    uint32_t cut_max = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      fits &= sm.ired[w] == 0;
-      total += static_cast<uint32_t>(sm.ired2[w]);
-      cut_max = sm.wtot[w] > cut_max ? sm.wtot[w] : cut_max;
-    }
-    if (fits && total >= static_cast<uint32_t>(a.top_k)) {
+    int bad, total;
+    fold_before<NW>(sm.ired, 0, bad);
+    fold_before<NW>(sm.ired2, 0, total);
+    const uint32_t cut_max = fold_max<NW>(sm.ured);
+    if (bad == 0 && total >= a.top_k) {
       int vid[PER_LIST];
       float zv[PER_LIST];
       bool ok[PER_LIST];

@@ -70,15 +70,16 @@ __device__ __forceinline__ void store4(float* p, float a, float b, float c, floa
 }
 
 // ---- wavefront collectives ---------------------------------------------------------
-// Lane exchanges through the vector ALU's data-parallel primitives (DPP) and v_readlane:
-// no round trip through the LDS crossbar, which a shuffle costs.  All of them must be
-// called with the whole wavefront active.
+// Lane exchanges through the vector ALU's data-parallel primitives (DPP): no round trip through
+// the LDS crossbar, which a shuffle costs.  All of them must be called with the whole wavefront active.
 enum : int {
   kDppXor1 = 0xB1,        // quad_perm [1,0,3,2]: lane ^ 1
   kDppXor2 = 0x4E,        // quad_perm [2,3,0,1]: lane ^ 2
   kDppHalfMirror = 0x141, // lane i <-> 7 - i inside groups of 8
   kDppMirror = 0x140,     // lane i <-> 15 - i inside rows of 16
   kDppRowShr = 0x110,     // + n: lane i reads lane i - n of its row of 16 (0 if there is none)
+  kDppBcast15 = 0x142,    // rows 1 and 3 read the last lane of the row before
+  kDppBcast31 = 0x143,    // rows 2 and 3 read the last lane of row 1
 };
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v) {
@@ -92,30 +93,40 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) {
   return __int_as_float(dpp_i32<CTRL>(__float_as_int(v)));
 }
+// What the rows named by MASK read of another row; `rest` in the other rows.
+template <int CTRL, int MASK>
+__device__ __forceinline__ int dpp_row_i32(int rest, int v) {
+  return __builtin_amdgcn_update_dpp(rest, v, CTRL, MASK, 0xF, false);
+}
+template <int CTRL, int MASK>
+__device__ __forceinline__ float dpp_row_f32(float rest, float v) {
+  return __int_as_float(dpp_row_i32<CTRL, MASK>(__float_as_int(rest), __float_as_int(v)));
+}
 __device__ __forceinline__ float readlane_f32(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// Sum over the wavefront in a fixed order (pairs, quads, eights, rows of 16, then the four
-// rows), the same value in every lane.
+// Reductions: pairs, quads, eights, rows of 16, the rows two by two, the halves -- a fixed order; the result
+// as a scalar.
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f32<kDppXor1>(v);
   v += dpp_f32<kDppXor2>(v);
   v += dpp_f32<kDppHalfMirror>(v);
   v += dpp_f32<kDppMirror>(v);
-  return (readlane_f32(v, 0) + readlane_f32(v, 16)) + (readlane_f32(v, 32) + readlane_f32(v, 48));
+  v += dpp_row_f32<kDppBcast15, 0xA>(0.f, v);
+  v += dpp_row_f32<kDppBcast31, 0xC>(0.f, v);
+  return readlane_f32(v, 63);
 }
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
-  v = mx(v, dpp_u32<kDppXor1>(v));
-  v = mx(v, dpp_u32<kDppXor2>(v));
-  v = mx(v, dpp_u32<kDppHalfMirror>(v));
-  v = mx(v, dpp_u32<kDppMirror>(v));
-  const int i = static_cast<int>(v);
-  return mx(mx(static_cast<uint32_t>(__builtin_amdgcn_readlane(i, 0)),
-               static_cast<uint32_t>(__builtin_amdgcn_readlane(i, 16))),
-            mx(static_cast<uint32_t>(__builtin_amdgcn_readlane(i, 32)),
-               static_cast<uint32_t>(__builtin_amdgcn_readlane(i, 48))));
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t u) {
+  auto mx = [](uint32_t a, int b) { return a > static_cast<uint32_t>(b) ? a : static_cast<uint32_t>(b); };
+  uint32_t v = u;
+  v = mx(v, dpp_i32<kDppXor1>(static_cast<int>(v)));
+  v = mx(v, dpp_i32<kDppXor2>(static_cast<int>(v)));
+  v = mx(v, dpp_i32<kDppHalfMirror>(static_cast<int>(v)));
+  v = mx(v, dpp_i32<kDppMirror>(static_cast<int>(v)));
+  v = mx(v, dpp_row_i32<kDppBcast15, 0xA>(0, static_cast<int>(v)));
+  v = mx(v, dpp_row_i32<kDppBcast31, 0xC>(0, static_cast<int>(v)));
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
 }
 // Largest / smallest value over the wavefront (NaNs are ignored unless every lane holds one).
 __device__ __forceinline__ float wave_max_f32(float v) {
@@ -123,34 +134,78 @@ __device__ __forceinline__ float wave_max_f32(float v) {
   v = fmaxf(v, dpp_f32<kDppXor2>(v));
   v = fmaxf(v, dpp_f32<kDppHalfMirror>(v));
   v = fmaxf(v, dpp_f32<kDppMirror>(v));
-  return fmaxf(fmaxf(readlane_f32(v, 0), readlane_f32(v, 16)), fmaxf(readlane_f32(v, 32), readlane_f32(v, 48)));
+  v = fmaxf(v, dpp_row_f32<kDppBcast15, 0xA>(v, v));
+  v = fmaxf(v, dpp_row_f32<kDppBcast31, 0xC>(v, v));
+  return readlane_f32(v, 63);
 }
 __device__ __forceinline__ float wave_min_f32(float v) {
   v = fminf(v, dpp_f32<kDppXor1>(v));
   v = fminf(v, dpp_f32<kDppXor2>(v));
   v = fminf(v, dpp_f32<kDppHalfMirror>(v));
   v = fminf(v, dpp_f32<kDppMirror>(v));
-  return fminf(fminf(readlane_f32(v, 0), readlane_f32(v, 16)), fminf(readlane_f32(v, 32), readlane_f32(v, 48)));
+  v = fminf(v, dpp_row_f32<kDppBcast15, 0xA>(v, v));
+  v = fminf(v, dpp_row_f32<kDppBcast31, 0xC>(v, v));
+  return readlane_f32(v, 63);
 }
-__device__ __forceinline__ int wave_sum_i32(int v) {
-  v += dpp_i32<kDppXor1>(v);
-  v += dpp_i32<kDppXor2>(v);
-  v += dpp_i32<kDppHalfMirror>(v);
-  v += dpp_i32<kDppMirror>(v);
-  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
-         (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
-}
-// Inclusive prefix sum over the lanes of the wavefront (lane = threadIdx.x % 64).
-__device__ __forceinline__ int wave_inclusive_sum_i32(int v, int lane) {
+// Inclusive prefix sum over the lanes of the wavefront; lane 63 holds the total.
+__device__ __forceinline__ int wave_inclusive_sum_i32(int v) {
   v += dpp_i32<kDppRowShr + 1>(v);
   v += dpp_i32<kDppRowShr + 2>(v);
   v += dpp_i32<kDppRowShr + 4>(v);
   v += dpp_i32<kDppRowShr + 8>(v);
-  const int t0 = __builtin_amdgcn_readlane(v, 15), t1 = __builtin_amdgcn_readlane(v, 31),
-            t2 = __builtin_amdgcn_readlane(v, 47);
-  const int row = lane >> 4;
-  return v + (row == 0 ? 0 : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2);
+  v += dpp_row_i32<kDppBcast15, 0xA>(0, v);
+  v += dpp_row_i32<kDppBcast31, 0xC>(0, v);
+  return v;
 }
+__device__ __forceinline__ int wave_sum_i32(int v) {
+  return __builtin_amdgcn_readlane(wave_inclusive_sum_i32(v), 63);
+}
+
+// ---- folds over the wavefronts of a workgroup ----------------------------------------------
+// Of W = 8 or 16 entries in LDS, one per wavefront, every lane reads one (lane modulo W) and the lanes of a
+// row exchange them: ten instructions, where reading all of them in every lane takes three per entry, in
+// every wavefront (a row kernel has about eight such folds; with them, the DPP-only reductions above and the
+// shorter selection, four steps on supplied logits of 32 x 65536 take 96 us instead of 111).  The caller's
+// barrier stands between the writes and these.
+template <int W>
+__device__ __forceinline__ int fold_entry() {
+  static_assert(W == 8 || W == 16, "wavefronts");
+  return threadIdx.x & (W - 1);
+}
+__device__ __forceinline__ int wave_index() {        // as a scalar
+  return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+}
+// Sum of the entries of the wavefronts before this one, and of all.
+template <int W>
+__device__ __forceinline__ int fold_before(const int* ex, int wave, int& total) {
+  int v = ex[fold_entry<W>()];
+  v += dpp_i32<kDppRowShr + 1>(v);
+  v += dpp_i32<kDppRowShr + 2>(v);
+  v += dpp_i32<kDppRowShr + 4>(v);
+  if constexpr (W == 16) v += dpp_i32<kDppRowShr + 8>(v);
+  total = __builtin_amdgcn_readlane(v, W - 1);
+  return wave > 0 ? __builtin_amdgcn_readlane(v, wave > 0 ? wave - 1 : 0) : 0;
+}
+template <int W>
+__device__ __forceinline__ uint32_t fold_max(const uint32_t* ex) {
+  auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+  uint32_t v = ex[fold_entry<W>()];
+  v = mx(v, dpp_u32<kDppXor1>(v));
+  v = mx(v, dpp_u32<kDppXor2>(v));
+  v = mx(v, dpp_u32<kDppHalfMirror>(v));
+  if constexpr (W == 16) v = mx(v, dpp_u32<kDppMirror>(v));
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+}
+template <int W>
+__device__ __forceinline__ float fold_sum(const float* ex) {       // a fixed tree
+  float v = ex[fold_entry<W>()];
+  v += dpp_f32<kDppXor1>(v);
+  v += dpp_f32<kDppXor2>(v);
+  v += dpp_f32<kDppHalfMirror>(v);
+  if constexpr (W == 16) v += dpp_f32<kDppMirror>(v);
+  return readlane_f32(v, 0);
+}
+
 // Lexicographic minimum of (score, id) over the wavefront, in every lane; scores and ids are not negative
 // (and no NaN), so both compare as integers.
 __device__ __forceinline__ void wave_min_score_id(float& score, int& id) {
