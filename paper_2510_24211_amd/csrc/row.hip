@@ -51,14 +51,18 @@
 #include "scd_device.h"
 #include "scd_kernels.h"
 
+#include <algorithm>
+
 #ifdef SCD_ROW_BATCHED
 #define SCD_ROW_THREADS 512
 #define SCD_ROW_DIRECT_MAX 8192
 #define row_kernel row_kernel_batched        // distinct names in traces
 #define slice_kernel slice_kernel_batched
 #define LAUNCH_ROW launch_row_batched
+#define SCD_ROW_WAVES(EXTRA) ((EXTRA) ? 2 : 4)   // wavefronts per SIMD: two workgroups per CU
 #else
 #define LAUNCH_ROW launch_row
+#define SCD_ROW_WAVES(EXTRA) 4
 #endif
 
 namespace scd {
@@ -83,7 +87,7 @@ constexpr int kSliceMax = 8192;              // logits per slice workgroup
 constexpr int PER_SLICE = kSliceMax / THREADS;
 static_assert(THREADS >= 256 && kListCap % THREADS == 0 && PER_DIRECT % 8 == 0 && PER_SLICE % 4 == 0,
               "row kernels: unsupported workgroup size");
-constexpr int kKeptCap = 4096;               // kept ids compacted in LDS
+constexpr int kKeptCap = 4096;               // kept ids that long_path parks in LDS
 
 struct Small {
   float fred[NW];
@@ -94,7 +98,9 @@ struct Small {
   int wtot[NW];
   uint4 sel;              // find_bin's bin, the population above it and its own
   uint32_t sel_bin;
-  uint32_t cursor;        // append cursor of select_regs
+  uint32_t cursor;        // append cursor of select_regs ...
+  uint32_t members[64];   // ... and what it appends
+  float u_accept;         // the accept test's uniform
   int ired2[NW];          // second slot of block_offsets
   uint2 win[2][NW];       // per-wavefront winners of the two races: (bits of the score, id)
   int last;
@@ -130,15 +136,15 @@ __device__ __forceinline__ uint32_t find_bin(const uint32_t* hist, uint32_t& nee
   const uint32_t incl = incl_wave + static_cast<uint32_t>(fold_before<T / kWave>(sm.wtot, wave, total));
   const uint32_t excl = incl - local;
   if (excl < need && need <= incl) {     // exactly one thread
-    uint32_t above = excl;
+    uint32_t above = excl, skipped = 0, mine = c[0];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      if (above + c[j] >= need) {
-        sm.sel = make_uint4(static_cast<uint32_t>(NBINS - 1 - (tid * PER + j)), above, c[j], 0u);
-        break;
-      }
-      above += c[j];
+    for (int j = 0; j + 1 < PER; ++j) {
+      const bool further = skipped == static_cast<uint32_t>(j) && above + c[j] < need;
+      above += further ? c[j] : 0u;
+      mine = further ? c[j + 1] : mine;
+      skipped += further ? 1u : 0u;
     }
+    sm.sel = make_uint4(static_cast<uint32_t>(NBINS - 1 - tid * PER) - skipped, above, mine, 0u);
   }
   __syncthreads();
   const uint4 sel = sm.sel;
@@ -274,13 +280,13 @@ __device__ __forceinline__ uint32_t saturating_u32(float f) {
 //   Should that bin hold more than kRankMax members (massive ties, or a few far logits that widen the
 //   range and with it every bin), radix levels over the key bits finish the job: three histograms, 4 us
 //   whatever their number.
-constexpr uint32_t kRankMax = 64;            // one per lane
+constexpr uint32_t kRankMax = kWave;         // one per lane
+static_assert(sizeof(Small::members) == kRankMax * 4, "a member per lane");
 template <int PER, int T = THREADS>
 __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bool (&ok)[PER], float zlo,
-                                                float zhi, uint32_t need, uint32_t* hist,
-                                                uint32_t* arr, Small& sm) {
-  // hist was zeroed by the caller before the barrier of block_minmax; arr (NBINS entries,
-  // disjoint from hist) takes the members of the selected bin.
+                                                float zhi, uint32_t need, uint32_t* hist, Small& sm) {
+  // hist was zeroed by the caller before the barrier of block_minmax.  When a wavefront returns, no other
+  // reads hist any more.
   const float scale = (zhi > zlo) ? fminf(__fdiv_rn(static_cast<float>(NBINS - 1), zhi - zlo), 3.0e38f) : 0.f;
   uint32_t bin[PER];
 #pragma unroll
@@ -301,12 +307,12 @@ __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bo
   if (members <= kRankMax) {
 #pragma unroll
     for (int e = 0; e < PER; ++e)
-      if (ok[e] && bin[e] == b1) arr[atomicAdd(&sm.cursor, 1u)] = zkey(zv[e]);
+      if (ok[e] && bin[e] == b1) sm.members[atomicAdd(&sm.cursor, 1u)] = zkey(zv[e]);
     __syncthreads();
     // Every wavefront holds one member per lane and ranks them against each other: the smallest that has fewer
     // than `need` above it is the one.
     const int lane = threadIdx.x & 63, m = __builtin_amdgcn_readfirstlane(static_cast<int>(members));
-    const uint32_t mine = lane < m ? arr[lane] : 0u;
+    const uint32_t mine = lane < m ? sm.members[lane] : 0u;
     uint32_t above = 0;
     for (int i = 0; i < m; ++i)
       above += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(mine), i)) > mine ? 1u : 0u;
@@ -511,7 +517,7 @@ struct RowRef {
   float thr_p, lse_p;
   bool fresh, active;
   int x, b, s, p0, live, it;
-  size_t widx, oidx;
+  size_t widx, oidx, sidx;
   size_t pidx;    // where the previous evaluation of the slot left its per-slot results (ring mode)
 };
 
@@ -547,28 +553,34 @@ __device__ __forceinline__ RowRef locate_row(const RowArgs& a, int r, const int3
     const size_t half = static_cast<size_t>(a.B) * L;
     R.oidx = par * half + sidx;
     R.pidx = (par ^ 1) * half + sidx;
-    R.x = a.x[sidx];
-    R.fresh = a.age[sidx] == 0;
     float* const ring = const_cast<float*>(a.z_cur) + static_cast<size_t>(par) * a.parity_stride + sidx * n;
     R.zc = a.src ? a.src + R.widx * n : ring;
     R.zw = a.src ? ring : nullptr;
     R.zp = a.z_cur + static_cast<size_t>(par ^ 1) * a.parity_stride + sidx * n;
-    if (!R.fresh) {
-      R.thr_p = a.thr[(par ^ 1) * half + sidx];
-      R.lse_p = a.lse[(par ^ 1) * half + sidx];
-    }
+    R.sidx = sidx;
   } else {
     R.oidx = R.widx;
-    R.x = a.x[R.widx];
-    R.fresh = a.fresh ? a.fresh[R.widx] != 0 : false;
     R.zc = a.z_cur + R.widx * n;
     R.zp = a.z_prev + R.widx * n;
-    if (!R.fresh) {
-      R.thr_p = a.thr_prev[R.widx];
-      R.lse_p = a.lse_prev[R.widx];
-    }
   }
   return R;
+}
+// The rest, for the caller to read once the row's logits are on their way: draft, whether its position is new,
+// what the slot's previous evaluation left (memory that exists and holds nothing useful for a new one; read
+// without waiting for the answer).  Before the loads of the logits this is a round trip of its own.
+__device__ __forceinline__ void read_row_scalars(const RowArgs& a, RowRef& R) {
+  if (a.mode == kRowSelectOnly) return;
+  if (a.mode == kRowRing) {
+    R.x = a.x[R.sidx];
+    R.fresh = a.age[R.sidx] == 0;
+    R.thr_p = a.thr[R.pidx];
+    R.lse_p = a.lse[R.pidx];
+  } else {
+    R.x = a.x[R.widx];
+    R.fresh = a.fresh ? a.fresh[R.widx] != 0 : false;
+    R.thr_p = a.thr_prev[R.widx];
+    R.lse_p = a.lse_prev[R.widx];
+  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -582,7 +594,6 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
                                                         const int P, const int capE, const int rank,
                                                         const RowArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t hist[NBINS];
-  __shared__ uint32_t arr[NBINS];
   __shared__ Small sm;
   constexpr int PS = kSliceMax / ST;   // logits per thread
   const int tid = threadIdx.x;
@@ -639,7 +650,7 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
   const int nvalid = hi_id - lo_id;
   uint32_t cut = 0;                       // 0: the whole slice is emitted
   if (nvalid > rank)
-    cut = select_regs<PS, ST>(zv, ok, key_to_float(kmin), key_to_float(kmax), static_cast<uint32_t>(rank), hist, arr, sm);
+    cut = select_regs<PS, ST>(zv, ok, key_to_float(kmin), key_to_float(kmax), static_cast<uint32_t>(rank), hist, sm);
   bool take[PS];
   int mine = 0;
 #pragma unroll
@@ -744,25 +755,56 @@ __device__ __forceinline__ PRace p_race_of_row(const RowArgs& a, uint2 key, uint
   return {a.gumbel != 0, w3 | kStreamGumbel, 0};
 }
 
+// The draw of a row that concerns all of its ids, the accept test's uniform: ten Philox rounds by one wavefront
+// while the row's logits are on their way, not by all of them behind the normaliser.  Published by the next
+// barrier.
+__device__ __forceinline__ void draw_accept_uniform(const RowArgs& a, const RowRef& R, Small& sm) {
+  if (a.mode == kRowSelectOnly || wave_index() != NW - 1) return;
+  const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(R.p0 + R.s), static_cast<uint32_t>(R.it),
+                                            (static_cast<uint32_t>(R.b) << 8) | kStreamAccept), seed_key(a.seed));
+  if ((threadIdx.x & 63) == 0) sm.u_accept = u01(ra.x);
+}
+
+// Lanes below this one whose bit is set, plus `more`.
+__device__ __forceinline__ int lanes_before(unsigned long long mask, int more) {
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), static_cast<uint32_t>(more))));
+}
+// LDS operations of a wavefront are performed in order: what its lanes wrote before, its lanes read behind.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Kept ids that a wavefront parks in LDS; with more (only where a thread holds more than 8 logits) it works from
+// its registers, where then every second lane or more has work anyway.
+constexpr int kWaveCap = 512;
+template <int PER>
+constexpr int wave_cap() { return PER * kWave < kWaveCap ? PER * kWave : kWaveCap; }
+
 // Everything after the candidates sit in registers: threshold (if top-k filters),
 // normaliser, accept test, residual race.  Returns false if the threshold could not
 // be certified against `cut_max` (the caller then takes the complete path).
 // PREQ: zq[e] is the previous iteration's logit of id vid[e], read by the caller together
-// with zv (coalesced, long before a rejection may need it; unused for a fresh position).
-// Otherwise (ids scattered over the row) the previous logits of the KEPT ids are gathered
-// here, right after the compaction, so that the round trip hides behind the normaliser and
-// the accept draw.  The LDS arrays cid / cz / cq hold ccap entries each.
+// with zv (coalesced; unused for a fresh position).  Otherwise (ids scattered over the row) the previous
+// logits of the KEPT ids are gathered here, right after the compaction, so that the round trip hides behind the
+// normaliser.  LDS: hist (NBINS counts), and lds (NW * wave_cap * 12 or 8 bytes), which may lie over it.
+//
+// The kept ids are a random ~K/n of each thread's logits.  Every wavefront compacts its own into its part of LDS
+// (a fixed order), so that the expensive per-id work that follows runs on full wavefronts instead of at the pace
+// of the unluckiest lane; the positive residuals, about half of them, are compacted again before the race.  No
+// barrier stands between the threshold and the normaliser, nor between the normaliser and the race: with the
+// row compacted as a whole, three barriers and a prefix sum over the workgroup did (16 x 32 rows of 8192 ids 24 ->
+// 19 us, 32 rows of 16384 15 -> 13.5).  The callers deal ids out in small pieces, so the wavefronts' shares differ
+// by chance only.
 template <int PER, bool PREQ, bool GS, bool EXTRA>
 __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, const int (&vid)[PER],
                                             const float (&zv)[PER], const float (&zq)[PER],
                                             const bool (&ok)[PER], bool filter, uint32_t cut_max,
-                                            float zcx, float zpx, uint32_t* hist, uint32_t* cid,
-                                            float* cz, float* cq, int ccap, Small& sm, RowOut& out,
-                                            bool have_thr = false, float thr_given = 0.f) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                            float zcx, float zpx, uint32_t* hist, unsigned char* lds,
+                                            Small& sm, RowOut& out, bool have_thr = false, float thr_given = 0.f) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
   const int n = a.n;
   uint32_t kmin, kmax;
   bool nan;
+  draw_accept_uniform(a, R, sm);
   thread_range<PER>(zv, ok, kmin, kmax, nan);
   if (nan && a.flags) atomicOr(a.flags, 1);                    // NaN of either sign
   if (filter) zero_hist(hist);            // published by the barrier inside block_minmax
@@ -770,8 +812,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   const float m = key_to_float(kmax);
   float thr = have_thr ? thr_given : -INFINITY;   // given: the caller has applied the filters
   if (filter) {
-    // cid (ccap entries, all of them free until the compaction) takes the selected bin's members
-    const uint32_t tkey = select_regs<PER>(zv, ok, key_to_float(kmin), m, static_cast<uint32_t>(a.top_k), hist, cid, sm);
+    const uint32_t tkey = select_regs<PER>(zv, ok, key_to_float(kmin), m, static_cast<uint32_t>(a.top_k), hist, sm);
     if (tkey < cut_max) return false;     // an unseen logit could be >= the K-th candidate
     thr = key_to_float(tkey);
   }
@@ -787,59 +828,68 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
                                       reinterpret_cast<unsigned long long*>(hist), sm);
     thr = key_to_float(pkey);
   }
-  // Kept ids are a random ~K/n of each thread's logits; compacting them into LDS (count /
-  // scan / write: a fixed order) lets the expensive per-id work that follows be dealt out
-  // evenly, kKeptPer per thread, instead of at the pace of the unluckiest lane.
-  bool kept[PER];
-  int mine = 0;
+  constexpr int CAP = wave_cap<PER>();
+  constexpr bool ALL_FIT = CAP == PER * kWave;
+  uint32_t* const kid = reinterpret_cast<uint32_t*>(lds) + wave * (PREQ ? 3 : 2) * CAP;
+  float* const kz = reinterpret_cast<float*>(kid + CAP);
+  float* const kq = kz + CAP;
+  int cnt = 0;                            // this wavefront's kept ids, a scalar
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
-    kept[e] = ok[e] && zv[e] >= thr;
-    mine += kept[e] ? 1 : 0;
-  }
-  int Cn;
-  int off = block_offsets(mine, Cn, sm, 0, false);   // next barrier: after the compaction / in the sum
-  const bool compact = Cn <= ccap;
-  const bool want_q = a.mode != kRowSelectOnly && !R.fresh;
-  constexpr int KPT = kKeptCap / THREADS;   // ccap <= KPT * THREADS
-  int rid[KPT];
-  float rz[KPT], rq[KPT];
-  if (compact) {
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      if (kept[e]) {
-        cid[off] = static_cast<uint32_t>(vid[e]);
-        cz[off] = zv[e];
-        if (PREQ) cq[off] = zq[e];
-        ++off;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int i = tid + q * THREADS;
-      rid[q] = i < Cn ? static_cast<int>(cid[i]) : -1;
-      rz[q] = i < Cn ? cz[i] : 0.f;
-      rq[q] = (PREQ && i < Cn) ? cq[i] : 0.f;
-    }
-    if (!PREQ && want_q) {                    // unpredicated gathers (id 0 where there is none)
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) rq[q] = R.zp[rid[q] >= 0 ? rid[q] : 0];
+    const bool keep = ok[e] && zv[e] >= thr;
+    const unsigned long long mask = __ballot(keep);
+    const int at = lanes_before(mask, cnt);
+    cnt += __builtin_popcountll(mask);
+    if (keep && (ALL_FIT || at < CAP)) {
+      kid[at] = static_cast<uint32_t>(vid[e]);
+      kz[at] = zv[e];
+      if (PREQ) kq[at] = zq[e];
     }
   }
+  const bool compact = ALL_FIT || cnt <= CAP;
+  wave_lds_fence();
+  // the previous logits of the first kAhead lanes' worth of kept ids are requested now, of any more when needed
+  constexpr int kAhead = 3;
+  float qa[kAhead];
+  const bool gather = !PREQ && a.mode != kRowSelectOnly && !R.fresh;
+  if (gather) {
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) qa[s] = R.zp[s * kWave + lane < cnt ? kid[s * kWave + lane] : 0u];
+  }
+  // f(valid, id, z, q) for this wavefront's kept ids, every lane taking part in every call
+  auto from_lds = [&](auto&& f) {
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) {
+      const int i = s * kWave + lane;
+      if (s * kWave < cnt) f(i < cnt, static_cast<int>(kid[i]), kz[i], PREQ ? kq[i] : qa[s]);
+    }
+#pragma unroll 1
+    for (int s = kAhead * kWave; s < cnt; s += kWave) {
+      const int i = s + lane, id = i < cnt ? static_cast<int>(kid[i]) : 0;
+      f(i < cnt, id, kz[i], PREQ ? kq[i] : (gather ? R.zp[id] : 0.f));
+    }
+  };
+  auto each_kept = [&](auto&& f) {
+    if (compact) {
+      from_lds(f);
+    } else if constexpr (!ALL_FIT) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) f(ok[e] && zv[e] >= thr, vid[e], zv[e], zq[e]);
+    }
+  };
   float sum = 0.f;
-  if (compact) {
-#pragma unroll
-    for (int q = 0; q < KPT; ++q)
-      if (rid[q] >= 0) sum += expf(rz[q] - m);
-  } else {
-#pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (kept[e]) sum += expf(zv[e] - m);
-  }
+  each_kept([&](bool valid, int, float z, float) {
+    const float w = expf(z - m);
+    sum += valid ? w : 0.f;
+  });
   sum = wave_sum(sum);
-  if (lane == 0) sm.fred[wave] = sum;
+  if (lane == 0) {
+    sm.fred[wave] = sum;
+    sm.ired[wave] = cnt;
+  }
   __syncthreads();
+  int Cn;
+  fold_before<NW>(sm.ired, 0, Cn);
   const float S = fold_sum<NW>(sm.fred);
   const float lse_c = m + logf(S);
   if (tid == 0) {
@@ -858,53 +908,31 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   const bool x_ok = R.x >= 0 && R.x < n;
   out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
   out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
-  const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(j), static_cast<uint32_t>(R.it),
-                                            w3 | kStreamAccept), key);
-  out.accept = __fmul_rn(u01(ra.x), out.qx) <= out.px;
+  out.accept = __fmul_rn(sm.u_accept, out.qx) <= out.px;
   out.best = INFINITY;
   out.best_id = 0x7FFFFFFF;
   out.gbest = INFINITY;
   out.gbest_id = 0x7FFFFFFF;
+  auto q_of = [&](float z) { return R.fresh ? q_uniform : prob(z, R.thr_p, R.lse_p); };
   if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
     float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-    auto add = [&](float zc_v, float zq_v) {
-      const float pv = expf(zc_v - lse_c);
-      const float qv = R.fresh ? q_uniform : prob(zq_v, R.thr_p, R.lse_p);
+    each_kept([&](bool valid, int, float zc_v, float zq_v) {
+      const float pv = valid ? expf(zc_v - lse_c) : 0.f;
+      const float qv = valid ? q_of(zq_v) : 0.f;
       d0 += fminf(pv, qv);
       d1 += pv * qv;
       d2 += pv * pv;
-    };
-    if (compact) {
-#pragma unroll
-      for (int q = 0; q < KPT; ++q)
-        if (rid[q] >= 0) add(rz[q], rq[q]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < PER; ++e)
-        if (kept[e]) add(zv[e], PREQ ? zq[e] : (want_q ? R.zp[vid[e]] : 0.f));
-    }
+    });
     row_statistics_out(a, R, d0, d1, d2, q_uniform, sm);
   }
   if (GS) {                        // next draft should the row survive
     const PRace pr = p_race_of_row(a, key, w3, j, R.it);
     out.prace = pr.on;
-    if (pr.on) {
-      if (compact) {
-#pragma unroll
-        for (int q = 0; q < KPT; ++q)
-          if (rid[q] >= 0) {
-            const float pv = expf(rz[q] - lse_c);
-            if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, rid[q], pv);
-          }
-      } else {
-#pragma unroll
-        for (int e = 0; e < PER; ++e)
-          if (kept[e]) {
-            const float pv = expf(zv[e] - lse_c);
-            if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, vid[e], pv);
-          }
-      }
-    }
+    if (pr.on)
+      each_kept([&](bool valid, int v, float z, float) {
+        const float pv = valid ? expf(z - lse_c) : 0.f;
+        if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, v, pv);
+      });
   }
   if (out.accept) return true;     // uniform over the workgroup
 
@@ -918,45 +946,27 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
       out.best_id = v;
     }
   };
+  auto residual = [&](float z, float q) { return __fsub_rn(expf(z - lse_c), q_of(q)); };
   if (compact) {
-    // residuals r = p - q of the kept ids, then a second compaction of the positive ones
-    int npos = 0;
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      float rv = 0.f;
-      if (rid[q] >= 0) {
-        const float pv = expf(rz[q] - lse_c);
-        const float qv = R.fresh ? q_uniform : prob(rq[q], R.thr_p, R.lse_p);
-        rv = __fsub_rn(pv, qv);
+    int positive = 0;              // written over the entries, at or before the place just read
+    from_lds([&](bool valid, int v, float z, float q) {
+      const float rv = residual(z, q);
+      const bool pos = valid && rv > 0.f;
+      const unsigned long long mask = __ballot(pos);
+      const int at = lanes_before(mask, positive);
+      positive += __builtin_popcountll(mask);
+      if (pos) {
+        kid[at] = static_cast<uint32_t>(v);
+        kz[at] = rv;
       }
-      rz[q] = rv;
-      npos += rv > 0.f ? 1 : 0;
-    }
-    int ntot;
-    int o2 = block_offsets(npos, ntot, sm, 1, false);   // cid / cz were read before the sum's barrier
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      if (rz[q] > 0.f) {
-        cid[o2] = static_cast<uint32_t>(rid[q]);
-        cz[o2] = rz[q];
-        ++o2;
-      }
-    }
-    __syncthreads();
-    for (int i = tid; i < ntot; i += THREADS) race_one(static_cast<int>(cid[i]), cz[i]);
+    });
+    wave_lds_fence();
+    for (int i = lane; i < positive; i += kWave) race_one(static_cast<int>(kid[i]), kz[i]);
   } else {
-    float zq2[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) zq2[e] = PREQ ? zq[e] : ((want_q && kept[e]) ? R.zp[vid[e]] : 0.f);
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      if (kept[e]) {
-        const float pv = expf(zv[e] - lse_c);
-        const float qv = R.fresh ? q_uniform : prob(zq2[e], R.thr_p, R.lse_p);
-        const float rv = __fsub_rn(pv, qv);
-        if (rv > 0.f) race_one(vid[e], rv);
-      }
-    }
+    each_kept([&](bool valid, int v, float z, float q) {
+      const float rv = residual(z, q);
+      if (valid && rv > 0.f) race_one(v, rv);
+    });
   }
   return true;
 }
@@ -1110,14 +1120,9 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
     }
 #pragma unroll
     for (int e = 0; e < PER_LIST; ++e) zv[e] = ok[e] ? zc[vid[e]] : 0.f;
-    float zq[PER_LIST];                        // unused: finish_regs gathers what it needs
-#pragma unroll
-    for (int e = 0; e < PER_LIST; ++e) zq[e] = 0.f;
-    // the prefixes in LDS are spent: their space takes the compaction arrays
-    const int ccap = min(kKeptCap, static_cast<int>(static_cast<size_t>(n8) * 2 / 12));
-    finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zq, ok, !have_thr, 0u, zcx, zpx, hist,
-                          reinterpret_cast<uint32_t*>(smem), reinterpret_cast<float*>(smem) + ccap,
-                          reinterpret_cast<float*>(smem) + 2 * ccap, ccap, sm, out, have_thr, thr_given);
+    // the prefixes and the list in LDS are spent: their space takes what finish_regs parks
+    finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zv, ok, !have_thr, 0u, zcx, zpx, hist, smem, sm, out,
+                                            have_thr, thr_given);
   };
   if (filter) {
     prefix_hist(false, 0u);
@@ -1563,42 +1568,62 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   });
 }
 
-// The whole row in registers, PER logits per thread (n <= PER * THREADS).
+// The draft token's logits in this and the previous iteration: their latency hides behind the selection.
+__device__ __forceinline__ void draft_logits(const RowArgs& a, const RowRef& R, float& zcx, float& zpx) {
+  const bool x_ok = a.mode != kRowSelectOnly && R.x >= 0 && R.x < a.n;
+  zcx = x_ok ? R.zc[R.x] : 0.f;
+  zpx = (x_ok && !R.fresh) ? R.zp[R.x] : 0.f;
+}
+
+// The whole row in registers, PER logits per thread (n <= PER * THREADS).  A wavefront takes every NW-th piece of
+// 32 ids (a 128-byte line): ids that are likelier than others tend to be neighbours, and every wavefront works
+// on the kept ones among its own.
 template <int PER, bool GS, bool EXTRA>
-__device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, unsigned char* smem,
-                                            bool filter, float zcx, float zpx, Small& sm, RowOut& out) {
-  const int tid = threadIdx.x, n = a.n;
-  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
-  const bool want_q = a.mode != kRowSelectOnly && !R.fresh;   // previous logits, for a rejection
+__device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigned char* smem, bool filter, Small& sm,
+                                            RowOut& out) {
+  const int lane = threadIdx.x & 63, n = a.n;
+  const int first = wave_index() * 32 + (lane >> 3) * (NW * 32) + ((lane & 7) << 2);
+  auto group = [&](int u) { return first + u * (8 * NW * 32); };   // four ids each
   int vid[PER];
   float zv[PER], zq[PER];
   bool ok[PER];
 #pragma unroll
   for (int u = 0; u < PER / 4; ++u) {
-    const int v0 = (tid + u * THREADS) << 2;
+    const int v0 = group(u);
     if (v0 + 3 < n) {
       const float4 t = load4(R.zc + v0);
       zv[u * 4 + 0] = t.x; zv[u * 4 + 1] = t.y; zv[u * 4 + 2] = t.z; zv[u * 4 + 3] = t.w;
-      float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (want_q) q = load4(R.zp + v0);
-      zq[u * 4 + 0] = q.x; zq[u * 4 + 1] = q.y; zq[u * 4 + 2] = q.z; zq[u * 4 + 3] = q.w;
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        zv[u * 4 + e] = (v0 + e < n) ? R.zc[v0 + e] : 0.f;
-        zq[u * 4 + e] = (want_q && v0 + e < n) ? R.zp[v0 + e] : 0.f;
-      }
+      for (int e = 0; e < 4; ++e) zv[u * 4 + e] = (v0 + e < n) ? R.zc[v0 + e] : 0.f;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       vid[u * 4 + e] = v0 + e;
       ok[u * 4 + e] = v0 + e < n;
+      zq[u * 4 + e] = 0.f;
     }
   }
+  read_row_scalars(a, R);
+  if (a.mode != kRowSelectOnly && !R.fresh) {                      // previous logits, for a rejection
+#pragma unroll
+    for (int u = 0; u < PER / 4; ++u) {
+      const int v0 = group(u);
+      if (v0 + 3 < n) {
+        const float4 q = load4(R.zp + v0);
+        zq[u * 4 + 0] = q.x; zq[u * 4 + 1] = q.y; zq[u * 4 + 2] = q.z; zq[u * 4 + 3] = q.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zq[u * 4 + e] = (v0 + e < n) ? R.zp[v0 + e] : 0.f;
+      }
+    }
+  }
+  float zcx, zpx;
+  draft_logits(a, R, zcx, zpx);
   if (R.zw) {                                  // supplied logits: keep them for the next iteration
 #pragma unroll
     for (int u = 0; u < PER / 4; ++u) {
-      const int v0 = (tid + u * THREADS) << 2;
+      const int v0 = group(u);
       if (v0 + 3 < n) {
         store4(R.zw + v0, zv[u * 4], zv[u * 4 + 1], zv[u * 4 + 2], zv[u * 4 + 3]);
       } else {
@@ -1608,10 +1633,8 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, u
       }
     }
   }
-  uint32_t* cid = hist + NBINS;
-  finish_regs<PER, true, GS, EXTRA>(a, R, vid, zv, zq, ok, filter, 0u, zcx, zpx, hist, cid,
-                   reinterpret_cast<float*>(cid + kKeptCap),
-                   reinterpret_cast<float*>(cid + 2 * kKeptCap), kKeptCap, sm, out);
+  finish_regs<PER, true, GS, EXTRA>(a, R, vid, zv, zq, ok, filter, 0u, zcx, zpx, reinterpret_cast<uint32_t*>(smem), smem,
+                                    sm, out);
 }
 
 // GS: the row also makes a Gumbel-max draw from p; EXTRA: the optional parts are compiled in
@@ -1622,7 +1645,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, const RowRef& R, u
 // 129 us, with every option 206 -> 193 us.
 enum Path { kDirectHalf, kDirectWhole, kLists, kLong };
 template <bool GS, bool EXTRA, int PATH>
-__global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
+__global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
                                                       const int mode_, const int L_, const int N_,
                                                       const int P, const int capE, const RowArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1630,7 +1653,7 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = a.n;
   const int r = blockIdx.x;
-  const RowRef R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
+  RowRef R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
   if (!R.active) {
     if (tid == 0) {
       a.y[R.widx] = -1;
@@ -1647,24 +1670,18 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
     }
     return;
   }
-  // the two logits of the draft token: their latency hides behind the selection
-  const bool x_ok = a.mode != kRowSelectOnly && R.x >= 0 && R.x < n;
-  const float zcx = x_ok ? R.zc[R.x] : 0.f;
-  const float zpx = (x_ok && !R.fresh) ? R.zp[R.x] : 0.f;
   const bool filter = a.top_k > 0 && a.top_k < n;
 
   RowOut out{};
   out.accept = true;
   bool done = false;
+  [[maybe_unused]] float zcx = 0.f, zpx = 0.f;
   if constexpr (PATH == kDirectHalf || PATH == kDirectWhole) {
     // ---- the whole row in registers ------------------------------------------------
-    direct_path<PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, zcx, zpx, sm, out);
+    direct_path<PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, sm, out);
     done = true;
   } else if (filter && a.cand && P > 0) {
     // ---- candidates emitted by the slice kernel ----------------------------------
-    // LDS: the compaction arrays, then the histogram (behind the space of full_path's key prefixes)
-    const size_t arrays = PATH == kLong ? static_cast<size_t>(kKeptCap) * 12 : static_cast<size_t>((n + 7) & ~7) * 2;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + arrays);
     // The P counts and cuts of the row's lists (P slices of the slice kernel, or P column tiles
     // of the LM head's epilogue; thread t holds those of list t), the count that governs each
     // of this thread's candidate slots, and the slots themselves are fetched in ONE round trip:
@@ -1690,6 +1707,8 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
       slot_cnt[e] = cntp[p < P ? p : 0];
       if (p >= P) slot_cnt[e] = 0;
     }
+    read_row_scalars(a, R);
+    draft_logits(a, R, zcx, zpx);
     // every list fits its capacity, how many candidates there are, the largest cut
     {
       const int tot = wave_sum_i32(static_cast<int>(tc <= static_cast<uint32_t>(capE) ? tc : 0u));
@@ -1716,13 +1735,14 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
         vid[e] = ok[e] ? static_cast<int>(raw[e].x) : 0;
         zv[e] = ok[e] ? __uint_as_float(raw[e].y) : 0.f;
       }
-      float zq[PER_LIST];                      // unused: finish_regs gathers what it needs
-#pragma unroll
-      for (int e = 0; e < PER_LIST; ++e) zq[e] = 0.f;
-      const int ccap = min(kKeptCap, static_cast<int>(arrays / 12));
-      done = finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zq, ok, true, cut_max, zcx, zpx, hist,
-                                   reinterpret_cast<uint32_t*>(smem), reinterpret_cast<float*>(smem) + ccap,
-                                   reinterpret_cast<float*>(smem) + 2 * ccap, ccap, sm, out);
+      done = finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zv, ok, true, cut_max, zcx, zpx,
+                                                     reinterpret_cast<uint32_t*>(smem), smem, sm, out);
+    }
+  }
+  if constexpr (PATH == kLists || PATH == kLong) {
+    if (!(filter && a.cand && P > 0)) {                     // no lists: nothing has been read yet
+      read_row_scalars(a, R);
+      draft_logits(a, R, zcx, zpx);
     }
   }
   if constexpr (PATH == kLong) {
@@ -1899,9 +1919,15 @@ __global__ __launch_bounds__(THREADS) void row_kernel(const int32_t* const pos_,
   }
 }
 
+// LDS of a workgroup: the histogram and, over it, what the wavefronts park (finish_regs); long_path's three
+// arrays; full_path's key prefixes, histogram and list.
 size_t lds_bytes_for(int n) {
-  if (n <= kDirectMaxN || n > kRowKernelMaxN) return NBINS * sizeof(uint32_t) + kKeptCap * 12;
-  return static_cast<size_t>((n + 7) & ~7) * 2 + NBINS * sizeof(uint32_t) + kListCap * sizeof(uint16_t);
+  const size_t hist = NBINS * sizeof(uint32_t);
+  if (n <= kDirectMaxN / 2) return std::max(hist, static_cast<size_t>(NW) * wave_cap<PER_DIRECT / 2>() * 12);
+  if (n <= kDirectMaxN) return std::max(hist, static_cast<size_t>(NW) * wave_cap<PER_DIRECT>() * 12);
+  const size_t lists = std::max(hist, static_cast<size_t>(NW) * wave_cap<PER_LIST>() * 8);
+  if (n > kRowKernelMaxN) return std::max(lists, hist + static_cast<size_t>(kKeptCap) * 8);
+  return std::max(lists, static_cast<size_t>((n + 7) & ~7) * 2 + hist + kListCap * sizeof(uint16_t));
 }
 
 inline size_t small_block(int rows) {
@@ -1985,7 +2011,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   size_t none = 0;
   size_t& configured = lds_configured ? *lds_configured : none;
   if (configured == 0) {
-    const size_t most = lds_bytes_for(kRowKernelMaxN);
+    const size_t most = std::max(lds_bytes_for(kRowKernelMaxN), lds_bytes_for(kDirectMaxN));
     for (const auto& row : kernels)
       for (Kernel f : row)
         if (f)
