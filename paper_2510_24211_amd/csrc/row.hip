@@ -76,6 +76,7 @@ namespace {
 constexpr int THREADS = SCD_ROW_THREADS;
 constexpr int NW = THREADS / kWave;
 constexpr int NBINS = 4096;
+constexpr int kHistWords = NBINS + kWave;     // and a word per lane for what is not to be counted
 constexpr int kListCap = kRowListCap;         // candidate ids per row (LDS list / slice or tile output)
 constexpr int PER_LIST = kListCap / THREADS; // candidates per thread
 #ifndef SCD_ROW_DIRECT_MAX
@@ -168,7 +169,8 @@ __device__ __forceinline__ void zero_hist(uint32_t* hist) {
 }
 
 __device__ __forceinline__ float prob(float z, float thr, float lse) {
-  return z >= thr ? expf(z - lse) : 0.f;
+  const float e = exp_of(z - lse);
+  return z >= thr ? e : 0.f;
 }
 
 // Exclusive offset of this thread's `cnt` in a fixed thread order, and the total.
@@ -230,7 +232,7 @@ __device__ __forceinline__ void thread_range(const float (&zv)[PER], const bool 
   kmax = 0u;
   kmin = 0xFFFFFFFFu;
   nan = false;
-  if (__ballot(some) == 0ull) return;      // a wavefront past the end of a short row
+  if (__builtin_amdgcn_ballot_w64(some) == 0ull) return;      // a wavefront past the end of a short row
 #pragma unroll
   for (int e = 0; e + 1 < PER; e += 2) {
     hi = max3(hi, zv[e], zv[e + 1]);
@@ -245,7 +247,7 @@ __device__ __forceinline__ void thread_range(const float (&zv)[PER], const bool 
     sum += zv[e];
     plain &= ok[e];
   }
-  if (__ballot(!(plain && lo > kRangeFloor && sum == sum)) != 0ull) {
+  if (__builtin_amdgcn_ballot_w64(!(plain && lo > kRangeFloor && sum == sum)) != 0ull) {
     hi = -INFINITY;
     lo = INFINITY;
 #pragma unroll
@@ -285,33 +287,40 @@ static_assert(sizeof(Small::members) == kRankMax * 4, "a member per lane");
 template <int PER, int T = THREADS>
 __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bool (&ok)[PER], float zlo,
                                                 float zhi, uint32_t need, uint32_t* hist, Small& sm) {
-  // hist was zeroed by the caller before the barrier of block_minmax.  When a wavefront returns, no other
+  // hist (kHistWords) was zeroed by the caller before the barrier of block_minmax.  When a wavefront returns, no other
   // reads hist any more.
   const float scale = (zhi > zlo) ? fminf(__fdiv_rn(static_cast<float>(NBINS - 1), zhi - zlo), 3.0e38f) : 0.f;
+  const int lane = threadIdx.x & 63;
   uint32_t bin[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
     // Below the floor, or where the range is empty or infinite (NaN): bin 0, which the conversion gives for
     // what is negative or no number.  At most (zhi - zlo) * scale < NBINS (the scale is kept finite for ranges
-    // of a few denormal numbers).
-    bin[e] = saturating_u32((zv[e] - zlo) * scale);
+    // of a few denormal numbers).  No logit: a word of the lane's own behind the bins, so that the counting
+    // needs no branches.
+    const uint32_t b = saturating_u32((zv[e] - zlo) * scale);
+    bin[e] = ok[e] ? b : static_cast<uint32_t>(NBINS + lane);
   }
   if (threadIdx.x == 0) sm.cursor = 0u;          // append cursor, published by the next barrier
 #pragma unroll
-  for (int e = 0; e < PER; ++e)
-    if (ok[e]) atomicAdd(&hist[bin[e]], 1u);
+  for (int e = 0; e < PER; ++e) atomicAdd(&hist[bin[e]], 1u);
   __syncthreads();
   // no trailing barrier: sm.sel is next written after the barrier that follows the append
   uint32_t members;
   const uint32_t b1 = find_bin<T>(hist, need, members, sm, false);
   if (members <= kRankMax) {
+    bool any = false;
 #pragma unroll
-    for (int e = 0; e < PER; ++e)
-      if (ok[e] && bin[e] == b1) sm.members[atomicAdd(&sm.cursor, 1u)] = zkey(zv[e]);
+    for (int e = 0; e < PER; ++e) any |= bin[e] == b1;
+    if (__builtin_amdgcn_ballot_w64(any) != 0ull) {        // most wavefronts have none
+#pragma unroll
+      for (int e = 0; e < PER; ++e)
+        if (bin[e] == b1) sm.members[atomicAdd(&sm.cursor, 1u)] = zkey(zv[e]);
+    }
     __syncthreads();
     // Every wavefront holds one member per lane and ranks them against each other: the smallest that has fewer
     // than `need` above it is the one.
-    const int lane = threadIdx.x & 63, m = __builtin_amdgcn_readfirstlane(static_cast<int>(members));
+    const int m = __builtin_amdgcn_readfirstlane(static_cast<int>(members));
     const uint32_t mine = lane < m ? sm.members[lane] : 0u;
     uint32_t above = 0;
     for (int i = 0; i < m; ++i)
@@ -330,7 +339,7 @@ __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bo
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       const uint32_t k = zkey(zv[e]);
-      if (ok[e] && bin[e] == b1 && k >= lo && static_cast<uint64_t>(k - lo) < width)
+      if (bin[e] == b1 && k >= lo && static_cast<uint64_t>(k - lo) < width)
         atomicAdd(&hist[(k - lo) >> s2], 1u);
     }
     __syncthreads();
@@ -593,7 +602,7 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
                                                         const int mode_, const int L_, const int N_,
                                                         const int P, const int capE, const int rank,
                                                         const RowArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t hist[NBINS];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kHistWords];
   __shared__ Small sm;
   constexpr int PS = kSliceMax / ST;   // logits per thread
   const int tid = threadIdx.x;
@@ -730,7 +739,7 @@ __device__ __forceinline__ void gumbel_entry(RowOut& out, uint2 key, uint32_t w3
   const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
                                             static_cast<uint32_t>(it), w3s), key);
   const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
-  const float sc = __fdiv_rn(-logf(u01(lanes[v & 3])), pv);
+  const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), pv);
   if (sc < out.gbest || (sc == out.gbest && v < out.gbest_id)) {
     out.gbest = sc;
     out.gbest_id = v;
@@ -785,7 +794,7 @@ constexpr int wave_cap() { return PER * kWave < kWaveCap ? PER * kWave : kWaveCa
 // PREQ: zq[e] is the previous iteration's logit of id vid[e], read by the caller together
 // with zv (coalesced; unused for a fresh position).  Otherwise (ids scattered over the row) the previous
 // logits of the KEPT ids are gathered here, right after the compaction, so that the round trip hides behind the
-// normaliser.  LDS: hist (NBINS counts), and lds (NW * wave_cap * 12 or 8 bytes), which may lie over it.
+// normaliser.  LDS: hist (kHistWords), and lds (NW * wave_cap * 12 or 8 bytes), which may lie over it.
 //
 // The kept ids are a random ~K/n of each thread's logits.  Every wavefront compacts its own into its part of LDS
 // (a fixed order), so that the expensive per-id work that follows runs on full wavefronts instead of at the pace
@@ -837,7 +846,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
     const bool keep = ok[e] && zv[e] >= thr;
-    const unsigned long long mask = __ballot(keep);
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
     const int at = lanes_before(mask, cnt);
     cnt += __builtin_popcountll(mask);
     if (keep && (ALL_FIT || at < CAP)) {
@@ -879,7 +888,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   };
   float sum = 0.f;
   each_kept([&](bool valid, int, float z, float) {
-    const float w = expf(z - m);
+    const float w = exp_of(z - m);
     sum += valid ? w : 0.f;
   });
   sum = wave_sum(sum);
@@ -917,7 +926,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
     float d0 = 0.f, d1 = 0.f, d2 = 0.f;
     each_kept([&](bool valid, int, float zc_v, float zq_v) {
-      const float pv = valid ? expf(zc_v - lse_c) : 0.f;
+      const float pv = valid ? exp_of(zc_v - lse_c) : 0.f;
       const float qv = valid ? q_of(zq_v) : 0.f;
       d0 += fminf(pv, qv);
       d1 += pv * qv;
@@ -930,7 +939,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
     out.prace = pr.on;
     if (pr.on)
       each_kept([&](bool valid, int v, float z, float) {
-        const float pv = valid ? expf(z - lse_c) : 0.f;
+        const float pv = valid ? exp_of(z - lse_c) : 0.f;
         if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, v, pv);
       });
   }
@@ -940,19 +949,19 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
     const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
                                               static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
     const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
-    const float sc = __fdiv_rn(-logf(u01(lanes[v & 3])), rv);
+    const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), rv);
     if (sc < out.best || (sc == out.best && v < out.best_id)) {
       out.best = sc;
       out.best_id = v;
     }
   };
-  auto residual = [&](float z, float q) { return __fsub_rn(expf(z - lse_c), q_of(q)); };
+  auto residual = [&](float z, float q) { return __fsub_rn(exp_of(z - lse_c), q_of(q)); };
   if (compact) {
     int positive = 0;              // written over the entries, at or before the place just read
     from_lds([&](bool valid, int v, float z, float q) {
       const float rv = residual(z, q);
       const bool pos = valid && rv > 0.f;
-      const unsigned long long mask = __ballot(pos);
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(pos);
       const int at = lanes_before(mask, positive);
       positive += __builtin_popcountll(mask);
       if (pos) {
@@ -1264,7 +1273,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   int cnt = 0;
   for_each_logit([&](int, float z) {
     if (z >= thr) {
-      sum += expf(z - m);
+      sum += exp_of(z - m);
       ++cnt;
     }
   });
@@ -1333,7 +1342,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
           const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
                                                     static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
           const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
-          const float sc = __fdiv_rn(-logf(u01(lanes[v & 3])), rv);
+          const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), rv);
           if (sc < out.best || (sc == out.best && v < out.best_id)) {
             out.best = sc;
             out.best_id = v;
@@ -1476,7 +1485,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   int cnt = 0;
   each([&](int v, float z) {
     if (z >= thr) {
-      sum += expf(z - m);
+      sum += exp_of(z - m);
       ++cnt;
       if (park) {                         // ties at the threshold may be more than fit
         const uint32_t slot = atomicAdd(&sm.cursor, 1u);
@@ -1519,7 +1528,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   out.best_id = 0x7FFFFFFF;
   if (out.accept) return;
   auto enter = [&](uint32_t bits, int v, float rv) {          // exponential-race entry of id v
-    const float sc = __fdiv_rn(-logf(u01(bits)), rv);
+    const float sc = __fdiv_rn(neg_log(u01(bits)), rv);
     if (sc < out.best || (sc == out.best && v < out.best_id)) {
       out.best = sc;
       out.best_id = v;
@@ -1532,7 +1541,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   if (park && Cn <= kKeptCap) {
     for (int i = tid; i < Cn; i += THREADS) {
       const int v = static_cast<int>(kid[i]);
-      const float rv = __fsub_rn(expf(kz[i] - lse_c), R.fresh ? q_uniform : prob(R.zp[v], R.thr_p, R.lse_p));
+      const float rv = __fsub_rn(exp_of(kz[i] - lse_c), R.fresh ? q_uniform : prob(R.zp[v], R.thr_p, R.lse_p));
       if (!(rv > 0.f)) continue;
       const uint4 rr = noise(v);
       const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
@@ -1713,7 +1722,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(cons
     {
       const int tot = wave_sum_i32(static_cast<int>(tc <= static_cast<uint32_t>(capE) ? tc : 0u));
       const uint32_t cm = wave_max_u32(tq);
-      const bool anybad = __ballot(tc > static_cast<uint32_t>(capE)) != 0ull;
+      const bool anybad = __builtin_amdgcn_ballot_w64(tc > static_cast<uint32_t>(capE)) != 0ull;
       if (lane == 0) {
         sm.ired2[wave] = tot;
         sm.ured[wave] = cm;
@@ -1862,7 +1871,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(cons
   int first_rej = live;                                    // (a lane past the end repeats the last bit)
 #pragma unroll
   for (int c = 3; c >= 0; --c) {
-    const unsigned long long m = __ballot(kk[c] == 0);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(kk[c] == 0);
     if (m != 0ull) first_rej = min(c * kWave + __builtin_ctzll(m), live - 1);
   }
   const int acc = min(first_rej + 1, live);
@@ -1922,12 +1931,12 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(cons
 // LDS of a workgroup: the histogram and, over it, what the wavefronts park (finish_regs); long_path's three
 // arrays; full_path's key prefixes, histogram and list.
 size_t lds_bytes_for(int n) {
-  const size_t hist = NBINS * sizeof(uint32_t);
+  const size_t hist = kHistWords * sizeof(uint32_t);
   if (n <= kDirectMaxN / 2) return std::max(hist, static_cast<size_t>(NW) * wave_cap<PER_DIRECT / 2>() * 12);
   if (n <= kDirectMaxN) return std::max(hist, static_cast<size_t>(NW) * wave_cap<PER_DIRECT>() * 12);
   const size_t lists = std::max(hist, static_cast<size_t>(NW) * wave_cap<PER_LIST>() * 8);
   if (n > kRowKernelMaxN) return std::max(lists, hist + static_cast<size_t>(kKeptCap) * 8);
-  return std::max(lists, static_cast<size_t>((n + 7) & ~7) * 2 + hist + kListCap * sizeof(uint16_t));
+  return std::max(lists, static_cast<size_t>((n + 7) & ~7) * 2 + NBINS * sizeof(uint32_t) + kListCap * sizeof(uint16_t));
 }
 
 inline size_t small_block(int rows) {
