@@ -178,187 +178,262 @@ __device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc
 // ---- per-tile top-k candidates (first half of the top-k selection, fused into the epilogue) ----
 // A workgroup that owns COLS = 256 or 128 neighbouring columns parks its processed logits in LDS as a tile
 // zt[row][COLS + 8] and every wavefront then reduces some rows of it: of the row's COLS
-// logits it emits the `cap` largest or a few less as (id, logit) pairs in a FIXED order (column within
-// the lane, then lane), their number, and the cut = the smallest emitted logit (as a key): every logit of
+// logits it emits the `cap` largest or a few less as (id, logit) pairs in a FIXED order (lane, then column within
+// the lane), their number, and the cut = the smallest emitted logit (as a key): every logit of
 // the tile row that was not emitted lies strictly below it.  The row kernel selects the K-th largest
 // among the emitted logits of all tiles and accepts it only if it is not below any tile's cut (then no
 // logit that was not emitted can reach it): exact, and certified per row.
-//   The emitted set is found on a monotone 8-bit image of the logits, linear between the row's smallest
-// and largest (equal images: both emitted or neither), by counting it: one LDS histogram of 256 bins per
-// row, four per lane, a prefix sum over the lanes, and the lowest bin whose upper set holds at most
-// `cap` logits (a bin near the cut holds about one logit, so 23 to 24 of 24 slots are used).  Where the row's
-// range is wide against its spread (one far logit is enough) a bin holds tens of logits and the list would come
+//   The emitted set is found on a monotone 7-bit image of the logits, linear between the tile row's mean (only
+// what lies above it can be among the largest, unless the row is lopsided) and its largest (equal images: both
+// emitted or neither), by counting it: one LDS histogram of 128 bins per row, and the lowest bin whose upper set
+// holds at most `cap` logits (a bin near the cut holds about one logit, so 23 of 24 slots are used).  Where the
+// bins are wide against the spread of the logits (one far logit is enough) the list would come
 // out short or empty: if more than kTileSlack slots stay free, the bin below the cut is counted again on an image
-// of its own range (refine_cut).  A step of one sequence x 32 x 65536 with one logit per tile 100 times the
-// others' size: 255 us with rows read whole, 146 with full lists, 110 without such logits.  If more than `cap` logits tie at the top (or a logit is not finite, which
+// of its own range (refine_cut).  If more than `cap` logits tie at the top (or a logit is not finite, which
 // collapses the image) the tile reports an overflowing count and the row kernel reads the row whole.
-//   Bound by the vector and LDS instructions of a CU (about 100 per row).  A bisection on a 12-bit image
-// with wave ballots, 13 steps of about ten scalar operations per row, waited for the one scalar unit of
-// the CU: two sequences x 64 positions x 64000 ids, 16 rows per wavefront, 26 us against 18 us now; one
-// sequence x 32 x 65536, 4 rows per wavefront, 7 us against 3 us.
+//   Bound by the instructions of a CU: with one or two wavefronts per SIMD nothing else runs meanwhile.  Four tile
+// rows lie side by side in a wavefront, a row of 16 lanes each: reductions are four lane exchanges for four rows at once,
+// and what is once per row (range, cut, offsets) is once per four: about 130 instructions per tile row.  z is stored from here,
+// 16 bytes per lane.  Against a whole wavefront per tile row and 4-byte stores of z, four steps of two sequences
+// x 64 positions x 64000 ids over 4096 take 599 us for 645, of one sequence x 32 x 65536 398 for 408, of eight x 32 x
+// 65536 over 2048 without guidance 474 for 488 (tiles of 256 x 256 in two passes: the second one's logits spill).
 constexpr int kTilePad = 8;                 // floats: rows 4 apart fall into disjoint banks
-constexpr int kTileBins = 256;
-constexpr int kTileRows = 2;                // rows that a wavefront reduces side by side
-constexpr int kTileHist = kTileRows * kTileBins * 4;   // LDS bytes per wavefront
+constexpr int kTileBins = 128;
+constexpr int kTileRows = 4;                // rows that a wavefront reduces side by side
+constexpr int kTileLanes = kWave / kTileRows;
+constexpr int kTileBelow = kTileLanes;      // words in front of a row's bins, for logits below the first one
+constexpr int kTileHistRow = kTileBelow + kTileBins;
+constexpr int kTileHist = kTileRows * kTileHistRow * 4;   // LDS bytes per wavefront
+static_assert(kTileLanes == 16 && kTileBins % (4 * kTileLanes) == 0 && kTileHistRow % 4 == 0, "a DPP row per tile row");
 
-// Monotone image of a logit, linear over [lo, hi]: one fused multiply-add.  For non-finite logits scale / shift
-// degenerate and every image collapses to 0.
-struct TileImage {
-  float scale, shift;
-};
-__device__ __forceinline__ TileImage tile_image(float lo, float hi) {
-  const float scale = hi > lo ? __fdiv_rn(static_cast<float>(kTileBins - 1), hi - lo) : 0.f;
-  return {scale, -(lo * scale)};
+// Reductions over the 16 lanes of a tile row, in every lane.
+template <class T, class F>
+__device__ __forceinline__ T tile_row_fold(T v, F&& f) {
+  static_assert(sizeof(T) == 4, "one register");
+  auto other = [&](auto ctrl) { return __builtin_bit_cast(T, dpp_u32<decltype(ctrl)::value>(__builtin_bit_cast(uint32_t, v))); };
+  v = f(v, other(IntT<kDppXor1>{}));
+  v = f(v, other(IntT<kDppXor2>{}));
+  v = f(v, other(IntT<kDppHalfMirror>{}));
+  return f(v, other(IntT<kDppMirror>{}));
 }
-__device__ __forceinline__ int image_of(const TileImage& t, float v) {
-  return static_cast<int>(fminf(fmaxf(__fmaf_rn(v, t.scale, t.shift), 0.f), static_cast<float>(kTileBins - 1)));
+__device__ __forceinline__ float tile_row_max(float v) {
+  return tile_row_fold(v, [](float a, float b) { return fmaxf(a, b); });
 }
-// How many bins' upper sets hold more than `room` of the `all` logits counted in a row's histogram: the lowest bin
-// that can be emitted.
-__device__ __forceinline__ int find_cut(const uint32_t* hist, int lane, int all, int room) {
-  const uint4 c4 = *reinterpret_cast<const uint4*>(&hist[4 * lane]);
-  const int c[4] = {static_cast<int>(c4.x), static_cast<int>(c4.y), static_cast<int>(c4.z), static_cast<int>(c4.w)};
-  const int mine = (c[0] + c[1]) + (c[2] + c[3]);
-  int above = all - wave_inclusive_sum_i32(mine) + mine;           // logits in bins >= 4 * lane
+__device__ __forceinline__ float tile_row_min(float v) {
+  return tile_row_fold(v, [](float a, float b) { return fminf(a, b); });
+}
+__device__ __forceinline__ float tile_row_sum(float v) {
+  return tile_row_fold(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ int tile_row_sum(int v) {
+  return tile_row_fold(v, [](int a, int b) { return a + b; });
+}
+
+// The largest image is below kTileBins: scale times the range, rounding included.  0 for an empty range; kept finite
+// for ranges of a few denormal numbers.
+__device__ __forceinline__ float tile_scale(float range) {
+  return range > 0.f ? fminf(__builtin_amdgcn_rcpf(range) * (kTileBins - 1.01f), 3.0e38f) : 0.f;
+}
+// Per tile row: the lowest bin whose upper set holds at most `room` of the counted logits (kTileBins: not even
+// the last one's does).  A lane reads kTileBins / 16 bins.
+__device__ __forceinline__ void zero_tile_bins(uint32_t* bins, int l) {
+#pragma unroll
+  for (int j = 0; j < kTileBins / kTileLanes; j += 4)
+    *reinterpret_cast<uint4*>(&bins[l * (kTileBins / kTileLanes) + j]) = make_uint4(0u, 0u, 0u, 0u);
+}
+__device__ __forceinline__ int find_cut(const uint32_t* bins, int l, int room) {
+  constexpr int PER = kTileBins / kTileLanes;
+  int c[PER], above = 0;
+#pragma unroll
+  for (int j = 0; j < PER; j += 4) {
+    const uint4 t = *reinterpret_cast<const uint4*>(&bins[l * PER + j]);
+    c[j] = static_cast<int>(t.x); c[j + 1] = static_cast<int>(t.y);
+    c[j + 2] = static_cast<int>(t.z); c[j + 3] = static_cast<int>(t.w);
+    above += (c[j] + c[j + 1]) + (c[j + 2] + c[j + 3]);
+  }
+  above += dpp_i32<kDppRowShl + 1>(above);          // logits in this lane's bins and those of the lanes behind
+  above += dpp_i32<kDppRowShl + 2>(above);
+  above += dpp_i32<kDppRowShl + 4>(above);
+  above += dpp_i32<kDppRowShl + 8>(above);
   int cut = 0;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    cut += __builtin_popcountll(__builtin_amdgcn_ballot_w64(above > room));
-    above -= c[e];
+  for (int j = 0; j < PER; ++j) {
+    cut += above > room ? 1 : 0;
+    above -= c[j];
   }
-  return cut;
+  return tile_row_sum(cut);
 }
-// The logits `in` (those of the bin below the cut, more than there are free slots) are counted on an image of
-// their own range, and those of its upper bins join `take`, `total` of them in all; again on the next bin while
-// more than kTileSlack slots are free and the members differ (each round resolves the range 255 times finer).
+// bin[e] >= cut: the logit is emitted.  Where more than kTileSlack slots of a tile row stay free, the logits of the
+// bin below the cut (more than there are free slots) are counted on an image of
+// their own range, and those of its upper bins are lifted above every cut; again on the next bin while
+// more than kTileSlack slots are free and the members differ (each round resolves the range 127 times finer).
+// `may`: this lane's row is live and finite.
+constexpr int kTileLifted = 2 * kTileBins;
 template <int E>
-__device__ __forceinline__ void refine_cut(const float (&v)[E], bool (&in)[E], bool (&take)[E], int& total, int cap,
-                                           uint32_t* hist, int lane) {
+__device__ __forceinline__ void refine_cut(const float (&v)[E], int (&bin)[E], int cut, int cap, bool may, uint32_t* bins, int l) {
+  uint32_t in = 0u;                                      // a bit per logit
+  int taken = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    in |= (cut > 0 ? bin[e] == cut - 1 : bin[e] < 0 && bin[e] >= -kTileBelow) ? 1u << e : 0u;
+    taken += bin[e] >= cut ? 1 : 0;
+  }
+  int total = tile_row_sum(taken);
 #pragma unroll 1
-  for (int round = 0; round < 4 && total < cap - kTileSlack; ++round) {
+  for (int round = 0; round < 4; ++round) {
     float mx = -INFINITY, mn = INFINITY;
-    int all = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      mx = in[e] ? fmaxf(mx, v[e]) : mx;
-      mn = in[e] ? fminf(mn, v[e]) : mn;
-      all += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in[e]));
+      const bool is = (in >> e & 1u) != 0u;
+      mx = is ? fmaxf(mx, v[e]) : mx;
+      mn = is ? fminf(mn, v[e]) : mn;
     }
-    const float hi = wave_max_f32(mx), lo = wave_min_f32(mn);
-    if (!(hi > lo)) return;                              // uniform: they tie
-    const TileImage image = tile_image(lo, hi);
-    *reinterpret_cast<uint4*>(&hist[4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+    const float hi = tile_row_max(mx), lo = tile_row_min(mn);
+    const bool go = may && total < cap - kTileSlack && hi > lo;      // else: full enough, or they tie
+    if (__builtin_amdgcn_ballot_w64(go) == 0ull) return;
+    const float scale = tile_scale(hi - lo);
+    zero_tile_bins(bins, l);
     compiler_fence();
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (in[e]) atomicAdd(&hist[image_of(image, v[e])], 1u);
-    compiler_fence();
-    const int cut = find_cut(hist, lane, all, cap - total);
+    int image[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const int q = image_of(image, v[e]);
-      const bool up = in[e] && q >= cut;
-      take[e] |= up;
-      total += __builtin_popcountll(__builtin_amdgcn_ballot_w64(up));
-      in[e] = in[e] && q == cut - 1;
+      image[e] = static_cast<int>(__builtin_amdgcn_fmed3f((v[e] - lo) * scale, 0.f, kTileBins - 1.f));
+      if (go && (in >> e & 1u) != 0u) atomicAdd(&bins[image[e]], 1u);
     }
+    compiler_fence();
+    const int part = find_cut(bins, l, cap - total);     // at least 1: all members are more than fit
+    taken = 0;
+    uint32_t next = 0u;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const bool is = go && (in >> e & 1u) != 0u;
+      bin[e] = is && image[e] >= part ? kTileLifted : bin[e];
+      taken += is && image[e] >= part ? 1 : 0;
+      next |= is && image[e] == part - 1 ? 1u << e : 0u;
+    }
+    total += tile_row_sum(taken);
+    in = next;
   }
 }
 
-// Rows q0, q0 + 1 of the tile; wrow[i] = window row index (b * L + s) of tile row q0 + i, or -1
-// if it is not a live window row; v0 = id of the tile's first column; tile / T = its index and the
-// number of tiles per row.  Uniform over the wavefront.  hist: kTileHist bytes of this wavefront's own.
-template <int COLS>
-__device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, const float* zt, uint32_t* hist, int lane,
-                                                int q0, const int (&wrow)[kTileRows], int v0, int tile, int T) {
+// Rows q0 .. q0 + 3 of the tile, a row per 16 lanes; dest: where the lane's row is stored (row_dest) or -1, wrow: its
+// window row (b * L + s); v0 = id of the tile's first column; tile / T = its index and the
+// number of tiles per row.  hist: kTileHist bytes of this wavefront's own.  STORE: the logits are not in z yet.
+// The rows of zt are spent behind this: they take the emitted pairs on their way to memory.
+template <int COLS, bool STORE>
+__device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, float* zt, uint32_t* hist, int lane,
+                                                int q0, int dest, int wrow, int v0, int tile, int T) {
   const int cap = a.cand_cap;
-  constexpr int E = COLS / 64;                           // logits per lane
+  constexpr int E = COLS / kTileLanes;                   // logits per lane: columns 64 k + 4 l .. + 3
+  const int l = lane & (kTileLanes - 1), sub = lane / kTileLanes;
   const int nvalid = min(COLS, a.n - v0);                // columns of this tile that exist
-  const bool ragged = nvalid < COLS;                     // only the last tile of a row
-  bool ok[E];
+  const bool live = dest >= 0;
+  uint32_t* const bins = hist + sub * kTileHistRow + kTileBelow;
+  float* const ztrow = zt + (q0 + sub) * (COLS + kTilePad);
+  auto column = [&](int e) { return (e >> 2) * 64 + 4 * l + (e & 3); };
+  float v[E];
+  int bin[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) ok[e] = E * lane + e < nvalid;
-  float v[kTileRows][E];
-  int q[kTileRows][E];
-#pragma unroll
-  for (int i = 0; i < kTileRows; ++i) {
-    const float* const src = &zt[(q0 + i) * (COLS + kTilePad) + E * lane];
-    if constexpr (E == 4) {
-      const float4 t = *reinterpret_cast<const float4*>(src);
-      v[i][0] = t.x; v[i][1] = t.y; v[i][2] = t.z; v[i][3] = t.w;
-    } else {
-      const float2 t = *reinterpret_cast<const float2*>(src);
-      v[i][0] = t.x; v[i][1] = t.y;
-    }
-    *reinterpret_cast<uint4*>(&hist[i * kTileBins + 4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+  for (int k = 0; k < E / 4; ++k) {
+    const float4 t = *reinterpret_cast<const float4*>(ztrow + 4 * l + 64 * k);
+    v[4 * k] = t.x; v[4 * k + 1] = t.y; v[4 * k + 2] = t.z; v[4 * k + 3] = t.w;
   }
+  zero_tile_bins(bins, l);
+  float* const to = a.z + (static_cast<int64_t>(dest) * a.n + v0 + 4 * l);
+  float range;
+  // RAGGED: columns that do not exist (in the last tile of a row only)
+  auto images = [&](auto is_ragged) {
+    constexpr bool RAGGED = decltype(is_ragged)::value;
+    auto there = [&](int e) { return !RAGGED || column(e) < nvalid; };
+    if (STORE && live) {
 #pragma unroll
-  for (int i = 0; i < kTileRows; ++i) {
-    float mx = -INFINITY, mn = INFINITY, sum = 0.f;
+      for (int k = 0; k < E / 4; ++k) {
+        if (!RAGGED) {
+          store4(to + 64 * k, v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+        } else {
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (ragged) v[i][e] = ok[e] ? v[i][e] : 0.f;
-      mx = !ragged || ok[e] ? fmaxf(mx, v[i][e]) : mx;
-      mn = !ragged || ok[e] ? fminf(mn, v[i][e]) : mn;
-      sum += v[i][e];
+          for (int j = 0; j < 4; ++j)
+            if (there(4 * k + j)) to[64 * k + j] = v[4 * k + j];
+        }
+      }
+    }
+    float mx = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; e += 2) {
+      mx = max3(mx, there(e) ? v[e] : -INFINITY, there(e + 1) ? v[e + 1] : -INFINITY);
+      v[e] = there(e) ? v[e] : 0.f;
+      v[e + 1] = there(e + 1) ? v[e + 1] : 0.f;
+      sum += v[e];
+      sum += v[e + 1];
     }
     // a NaN (or +inf next to -inf) among the lane's logits poisons their sum
-    if (sum != sum && a.flags && wrow[i] >= 0) atomicOr(a.flags, 1);
-    const float hi = wave_max_f32(mx), lo = wave_min_f32(mn);
-    const TileImage image = tile_image(lo, hi);
+    if (sum != sum && a.flags && live) atomicOr(a.flags, 1);
+    const float mean = tile_row_sum(sum) * (RAGGED ? __fdiv_rn(1.f, static_cast<float>(nvalid)) : 1.f / COLS);
+    range = tile_row_max(mx) - mean;
+    const float scale = tile_scale(range), below = -1.f - static_cast<float>(l);
+    // What lies below the bins is counted in the words in front of them, far below in the lane's own (half of the
+    // lanes would add to one word otherwise).
 #pragma unroll
-    for (int e = 0; e < E; ++e) q[i][e] = image_of(image, v[i][e]);
-  }
+    for (int e = 0; e < E; ++e) {
+      bin[e] = static_cast<int>(__builtin_amdgcn_fmed3f((v[e] - mean) * scale, below, kTileBins - 1.f));
+      if (RAGGED) bin[e] = there(e) ? bin[e] : -1 - l;
+      atomicAdd(&bins[bin[e]], 1u);
+    }
+    if (RAGGED) {                                        // counted; from here on never emitted, or all of the others
+#pragma unroll
+      for (int e = 0; e < E; ++e) bin[e] = !there(e) ? -kTileLifted : nvalid <= cap ? kTileLifted : bin[e];
+    }
+  };
   // LDS operations of a wavefront are performed in order: the zeroing above, the counting, the reading
   compiler_fence();
-#pragma unroll
-  for (int i = 0; i < kTileRows; ++i)
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (!ragged || ok[e]) atomicAdd(&hist[i * kTileBins + q[i][e]], 1u);
+  if (nvalid == COLS) images(FalseT{});
+  else images(TrueT{});
   compiler_fence();
+  const int cut = find_cut(bins, l, cap);
+  int mine, incl, total;
+  auto offsets = [&]() {                                 // emitted logits of this lane, up to it, of the tile row
+    mine = 0;
 #pragma unroll
-  for (int i = 0; i < kTileRows; ++i) {
-    const int cutq = find_cut(&hist[i * kTileBins], lane, nvalid, cap);
-    if (wrow[i] < 0) continue;                           // uniform
-    // emitted logits in the fixed order (column within the lane, then lane)
-    bool take[E];
-    int at[E], total = 0;
-    float vmin = INFINITY;
-    auto place = [&]() {
-      total = 0;
+    for (int e = 0; e < E; ++e) mine += bin[e] >= cut ? 1 : 0;
+    incl = mine + dpp_i32<kDppRowShr + 1>(mine);
+    incl += dpp_i32<kDppRowShr + 2>(incl);
+    incl += dpp_i32<kDppRowShr + 4>(incl);
+    incl += dpp_i32<kDppRowShr + 8>(incl);
+    total = tile_row_sum(mine);
+  };
+  offsets();
+  const bool may = live && range < INFINITY;             // (no NaN)
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(may && total < min(nvalid, cap - kTileSlack)) != 0ull, 0)) {
+    refine_cut<E>(v, bin, cut, cap, may, bins, l);
+    offsets();
+  }
+  // The pairs are put in order in the row's part of zt (what is not emitted goes to a place of the lane's own behind
+  // them: a branch per logit takes longer) and leave it 16 at a time.
+  constexpr int PAIRS = (COLS + kTilePad) / 2;
+  uint2* const pairs = reinterpret_cast<uint2*>(ztrow);
+  compiler_fence();
+  int at = incl - mine;
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(take[e]);
-        at[e] = total + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
-        total += __builtin_popcountll(m);
-        vmin = take[e] ? fminf(vmin, v[i][e]) : vmin;
-      }
-    };
-#pragma unroll
-    for (int e = 0; e < E; ++e) take[e] = q[i][e] >= cutq && (!ragged || ok[e]);
-    place();
-    if (__builtin_expect(cutq > 0 && total < cap - kTileSlack, 0)) {   // uniform
-      bool in[E];
-#pragma unroll
-      for (int e = 0; e < E; ++e) in[e] = q[i][e] == cutq - 1 && (!ragged || ok[e]);
-      refine_cut<E>(v[i], in, take, total, cap, &hist[i * kTileBins], lane);
-      place();
+  for (int e = 0; e < E; ++e) {
+    const bool take = bin[e] >= cut;
+    pairs[take ? at : PAIRS - kTileLanes + l] = make_uint2(static_cast<uint32_t>(v0 + column(e)), __float_as_uint(v[e]));
+    at += take ? 1 : 0;
+  }
+  compiler_fence();
+  uint2* const dst = a.cand + (static_cast<size_t>(wrow) * kRowListCap + static_cast<size_t>(tile) * cap);
+  float vmin = INFINITY;
+  for (int i = l; i < cap; i += kTileLanes) {
+    const uint2 t = pairs[i];
+    if (live && i < total) {
+      dst[i] = t;
+      vmin = fminf(vmin, __uint_as_float(t.y));
     }
-    vmin = wave_min_f32(vmin);                           // smallest emitted logit (NaNs are never smallest)
-    const size_t slot = static_cast<size_t>(wrow[i]) * T + tile;
-    const bool fits = total > 0 && total <= cap;         // nothing emitted: more than cap tie at the top
-    if (fits) {
-      uint2* dst = a.cand + (static_cast<size_t>(wrow[i]) * kRowListCap + static_cast<size_t>(tile) * cap);
-#pragma unroll
-      for (int e = 0; e < E; ++e)
-        if (take[e]) dst[at[e]] = make_uint2(static_cast<uint32_t>(v0 + E * lane + e), __float_as_uint(v[i][e]));
-    }
-    if (lane == 0) {
-      a.cand_cnt[slot] = fits ? static_cast<uint32_t>(total) : static_cast<uint32_t>(cap) + 1u;   // > cap: overflow
-      a.cand_cut[slot] = cutq == 0 ? 0u : zkey(vmin);    // 0: the whole tile row is emitted
-    }
+  }
+  vmin = tile_row_min(vmin);                             // smallest emitted logit
+  if (live && l == 0) {
+    const size_t slot = static_cast<size_t>(wrow) * T + tile;
+    a.cand_cnt[slot] = total > 0 ? static_cast<uint32_t>(total) : static_cast<uint32_t>(cap) + 1u;   // > cap: overflow
+    a.cand_cut[slot] = total == nvalid ? 0u : zkey(vmin);    // 0: the whole tile row is emitted
   }
 }
 
@@ -567,14 +642,9 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
     __syncthreads();
     uint32_t* const hist = reinterpret_cast<uint32_t*>(zt + ZT) + wave * (kTileHist / 4);
 #pragma unroll 1
-    for (int g = 0; g < 4; g += kTileRows) {
-      int wrow[kTileRows];
-#pragma unroll
-      for (int i = 0; i < kTileRows; ++i) {
-        const int row = wave * 4 + g + i;
-        wrow[i] = __builtin_amdgcn_readfirstlane(table[row]) >= 0 ? p_base + row : -1;
-      }
-      tile_candidates<K::BN>(a, zt, hist, lane, wave * 4 + g, wrow, v_base, vt, VT);
+    for (int q0 = wave * 4; q0 < wave * 4 + 4; q0 += kTileRows) {
+      const int row = q0 + lane / kTileLanes;
+      tile_candidates<K::BN, false>(a, zt, hist, lane, q0, table[row], p_base + row, v_base, vt, VT);
     }
   }
 }
@@ -930,28 +1000,36 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
   int* const table = reinterpret_cast<int*>(lds);    // (the stages take all of LDS: no table before)
   if (tid < K::WR) table[tid] = row_dest(a, mine);
   __syncthreads();
-  // element j of a block: window row 8 * (j / 4) + 4 * lg + j % 4 of its 32, column ln; the processed logits
-  // replace the cond sums
+  // element j of a block: window row 8 * (j / 4) + 4 * lg + j % 4 of its 32, column ln
+  if (a.cand == nullptr) {                           // uniform
 #pragma unroll
-  for (int r = 0; r < K::RB; ++r) {
-    int4 to[4];
+    for (int r = 0; r < K::RB; ++r) {
+      int4 to[4];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[(wr * K::RB + r) * 32 + g * 8 + lg * 4]);
-    const int v = wc * K::CW + ln;                    // column of the tile
+      for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[(wr * K::RB + r) * 32 + g * 8 + lg * 4]);
+      const int v = wc * K::CW + ln;                  // column of the tile
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const int4 t = to[j >> 2];
-      const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
-      float* const zr = a.z + (static_cast<int64_t>(row) * a.n + vt * BN + v);
+      for (int j = 0; j < 16; ++j) {
+        const int4 t = to[j >> 2];
+        const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
+        float* const zr = a.z + (static_cast<int64_t>(row) * a.n + vt * BN + v);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const float z = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
-        acc[c][r * C][j] = z;
-        if (row >= 0 && v + c * 32 < v_left) zr[c * 32] = z;
+        for (int c = 0; c < NC; ++c) {
+          const float z = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
+          if (row >= 0 && v + c * 32 < v_left) zr[c * 32] = z;
+        }
       }
     }
+    return;
   }
-  if (a.cand == nullptr) return;                     // uniform
+  // the processed logits replace the cond sums; tile_candidates stores them from the tile in LDS, 16 bytes per lane
+#pragma unroll
+  for (int r = 0; r < K::RB; ++r)
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        acc[c][r * C][j] = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
   float* const zt = reinterpret_cast<float*>(lds + K::TABLE);
   uint32_t* const hist = reinterpret_cast<uint32_t*>(zt + K::ZROWS * K::PITCH_Z) + wave * (kTileHist / 4);
   constexpr int PASSES = K::WR / K::ZROWS;           // 128 window rows at a time
@@ -971,16 +1049,13 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
     }
     __syncthreads();
     constexpr int PER_WAVE = K::ZROWS / K::NW;
+    static_assert(PER_WAVE % kTileRows == 0, "rows per wavefront");
 #pragma unroll 1
-    for (int g = 0; g < PER_WAVE; g += kTileRows) {
-      const int q0 = wave * PER_WAVE + g;
-      int wrow[kTileRows];
-#pragma unroll
-      for (int i = 0; i < kTileRows; ++i) {
-        const int row = pass * K::ZROWS + q0 + i;
-        wrow[i] = __builtin_amdgcn_readfirstlane(table[row]) >= 0 ? p_base + row : -1;
-      }
-      tile_candidates<BN>(a, zt, hist, lane, q0, wrow, vt * BN, vt, VT);
+    for (int q0 = wave * PER_WAVE; q0 < (wave + 1) * PER_WAVE; q0 += kTileRows) {
+      const int row = pass * K::ZROWS + q0 + lane / kTileLanes;
+      const int dest = table[row];
+      if (__builtin_amdgcn_ballot_w64(dest >= 0) == 0ull) continue;
+      tile_candidates<BN, true>(a, zt, hist, lane, q0, dest, p_base + row, vt * BN, vt, VT);
     }
   }
 }

@@ -207,18 +207,6 @@ __device__ __forceinline__ void block_minmax(uint32_t& kmin, uint32_t& kmax, Sma
 }
 
 constexpr float kRangeFloor = -1.0e30f;
-// Three-way maximum / minimum of floats; a NaN operand is ignored.  As builtins they would come with a
-// quieting instruction per operand.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float min3(float a, float b, float c) {
-  float r;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
 // This thread's share of the row's range: keys of its largest logit (all ones if one is NaN) and of the
 // smallest above kRangeFloor, of PER logits valid where ok[e].  One instruction per logit where all of the
 // wavefront's are valid and above the floor; the rest (ragged rows, masked ids, NaN) is looked at one by one.

@@ -94,6 +94,19 @@ __device__ __forceinline__ void store4(float* p, float a, float b, float c, floa
   *reinterpret_cast<f32x4_u*>(p) = f32x4_u{a, b, c, d};
 }
 
+// Three-way maximum / minimum of floats; a NaN operand is ignored.  As builtins they would come with a
+// quieting instruction per operand.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 // ---- wavefront collectives ---------------------------------------------------------
 // Lane exchanges through the vector ALU's data-parallel primitives (DPP): no round trip through
 // the LDS crossbar, which a shuffle costs.  All of them must be called with the whole wavefront active.
@@ -102,6 +115,7 @@ enum : int {
   kDppXor2 = 0x4E,        // quad_perm [2,3,0,1]: lane ^ 2
   kDppHalfMirror = 0x141, // lane i <-> 7 - i inside groups of 8
   kDppMirror = 0x140,     // lane i <-> 15 - i inside rows of 16
+  kDppRowShl = 0x100,     // + n: lane i reads lane i + n of its row of 16 (0 if there is none)
   kDppRowShr = 0x110,     // + n: lane i reads lane i - n of its row of 16 (0 if there is none)
   kDppBcast15 = 0x142,    // rows 1 and 3 read the last lane of the row before
   kDppBcast31 = 0x143,    // rows 2 and 3 read the last lane of row 1

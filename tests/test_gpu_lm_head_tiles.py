@@ -144,3 +144,26 @@ def test_small_calls_add_up_in_parts(Bn, L, n, d, lam, parts, kernel):
     # the result, u the rms of a rounding error in units of the value, at most 2^-24 / sqrt(3) * 1.2 (one chain
     # would be u sqrt(T / 2), 1.4 times this bound and more)
     assert err <= 0.7 * 2.0 ** -24 * np.sqrt(d / 32 / parts + (parts + 1) / 2), err
+
+
+@pytest.mark.parametrize("Bn,L,n,d,lam,top_k", [
+    (1, 32, 32769, 128, 3.0, 2000),      # the last tile of a row is one column
+    (1, 30, 20503, 128, 3.0, 1500),      # 23 columns of 128, fewer than a list holds; rows of a wavefront that do not exist
+    (3, 43, 60003, 64, 3.0, 2000),       # 99 columns of 256, odd rows; a second row tile with one live row
+    (5, 45, 50179, 72, 0.0, 900),        # three columns; 225 rows in two passes
+    (1, 20, 50020, 200, 0.0, 900),       # the kernel with a shared h tile
+])
+def test_logits_stored_beside_lists_are_those_stored_without(Bn, L, n, d, lam, top_k):
+    W, h = _inputs(Bn, 2 if lam else 1, L, n, d, 0, n)
+    sc = B.Scd(B.make_config(B=Bn, L=L, N=L + 20, V=W.shape[0], d=d, v_hi=n, top_k=top_k, cfg_lambda=lam, seed=9), DEV)
+    st = sc.alloc_state()
+    sc.reset(st)
+    ring = sc.state_field(st, B.F_Z).view(2, Bn, L, n)
+    ring.fill_(float("nan"))
+    sc.step(h, W, st)
+    z = torch.empty(Bn, L, n, device=DEV)
+    sc.lm_head(h, W, z)
+    assert torch.equal(ring[0], z) and bool(ring[1].isnan().all())     # the same sums, and nothing past a row's end
+    want = torch.topk(z.view(Bn * L, n), top_k, dim=1).values[:, -1].view(Bn, L)
+    assert torch.equal(sc.state_field(st, B.F_THR).view(2, Bn, L)[0], want)
+    assert torch.equal(sc.state_field(st, B.F_NKEPT).view(2, Bn, L)[0].long(), (z >= want[..., None]).sum(2))
