@@ -52,6 +52,7 @@
 #include "scd_kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #ifdef SCD_ROW_BATCHED
 #define SCD_ROW_THREADS 512
@@ -357,8 +358,18 @@ constexpr int NBINS_P = NBINS / 2;
 static_assert(NBINS_P % THREADS == 0 || THREADS % NBINS_P == 0, "nucleus: bins per thread");
 static_assert(THREADS >= 512, "nucleus: a member per thread");
 
+// Both words of trunc(e^(z - m) 2^40), at most 2^40: multiplications by powers of two and the subtraction are exact,
+// so this is the conversion to 64 bits in 6 instructions (the general one takes twice as many).  NaN: 0.
 __device__ __forceinline__ unsigned long long mass_of(float z, float m) {
-  return static_cast<unsigned long long>(expf(z - m) * 1099511627776.0f);   // <= 2^40
+  // (exp_of without its care for what is far below: such a factor underflows here, and -inf, a NaN then, has no mass)
+  const float y = z - m;
+  const float t = __fmul_rn(y, 1.44269502f);
+  const float rest = __fmaf_rn(y, 1.92596303e-8f, __fmaf_rn(y, 1.44269502f, -t));
+  const float k = __builtin_rintf(t);
+  const float e = __builtin_ldexpf(__builtin_amdgcn_exp2f((t - k) + rest), static_cast<int>(k)) * 256.f;
+  const uint32_t hi = saturating_u32(e);
+  const uint32_t lo = saturating_u32((e - static_cast<float>(hi)) * 4294967296.f);
+  return static_cast<unsigned long long>(hi) << 32 | lo;
 }
 
 __device__ __forceinline__ unsigned long long wave_inclusive_sum_u64(unsigned long long v) {
@@ -430,7 +441,7 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
   const float zlo = fmaxf(zmin, m - 110.f);
   const float scale = (m > zlo) ? __fdiv_rn(static_cast<float>(NBINS_P - 1), m - zlo) : 0.f;
   auto lin_bin = [&](float z) {
-    return static_cast<int>(fminf(fmaxf((z - zlo) * scale, 0.f), static_cast<float>(NBINS_P - 1)));
+    return static_cast<int>(__builtin_amdgcn_fmed3f((z - zlo) * scale, 0.f, static_cast<float>(NBINS_P - 1)));
   };
   auto zero = [&]() {
     for (int i = tid; i < NBINS_P; i += THREADS) mh[i] = 0ull;
@@ -451,13 +462,17 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
     if (b1 < NBINS_P - 2) near_hi = zkey(zlo + static_cast<float>(b1 + 2) * inv);
   }
   prepare(near_lo, near_hi);
-  // A bin near the boundary holds a few dozen ids: they are parked in LDS, and each adds up the masses of
-  // those above it; the smallest key whose sum stays below the target is the threshold.
+  // A bin near the boundary holds a few dozen ids: they are parked in LDS, and for each the masses of those above it
+  // are added up, every wavefront taking its share of the summands (all of them in one thread per member are as many
+  // round trips to LDS: 11000 -> 5000 cycles on rows of 64000 ids); the smallest
+  // key whose sum stays below the target is the threshold.
   constexpr uint32_t kFew = 512;
   unsigned long long* const mm = mh;
-  uint32_t* const mk = reinterpret_cast<uint32_t*>(mh + kFew);
-  static_assert(NBINS_P * 8 >= kFew * 12, "members' masses and keys in the histogram's space");
+  unsigned long long* const over = mh + kFew;
+  uint32_t* const mk = reinterpret_cast<uint32_t*>(over + kFew);
+  static_assert(NBINS_P * 8 >= kFew * 20, "members' masses, sums and keys in the histogram's space");
   __syncthreads();                                  // the cursor may still be read by prepare()'s users
+  if (static_cast<uint32_t>(tid) < kFew) over[tid] = 0ull;
   if (tid == 0) {
     sm.cursor = 0u;
     sm.sel_bin = 0xFFFFFFFFu;
@@ -475,12 +490,14 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
   __syncthreads();
   const uint32_t members = sm.cursor;
   if (members <= kFew) {
-    if (static_cast<uint32_t>(tid) < members) {
-      const uint32_t key = mk[tid];
-      unsigned long long sum = above;
-      for (uint32_t i = 0; i < members; ++i) sum += mk[i] > key ? mm[i] : 0ull;
-      if (sum < target) atomicMin(&sm.sel_bin, key);
+    for (uint32_t a = tid & (kWave - 1); a < (members + kWave - 1) / kWave * kWave; a += kWave) {
+      const uint32_t key = a < members ? mk[a] : 0xFFFFFFFFu;
+      unsigned long long sum = 0ull;
+      for (uint32_t i = wave_index(); i < members; i += NW) sum += mk[i] > key ? mm[i] : 0ull;
+      if (sum != 0ull) atomicAdd(&over[a], sum);
     }
+    __syncthreads();
+    if (static_cast<uint32_t>(tid) < members && above + over[tid] < target) atomicMin(&sm.sel_bin, mk[tid]);
     __syncthreads();
     const uint32_t key = sm.sel_bin;
     __syncthreads();                                // the next user of the space or of sel_bin
@@ -776,6 +793,148 @@ constexpr int kWaveCap = 512;
 template <int PER>
 constexpr int wave_cap() { return PER * kWave < kWaveCap ? PER * kWave : kWaveCap; }
 
+// Normaliser, accept test, residual race (and the optional parts) over a row's kept ids, behind the threshold.  Every
+// wavefront works on its own: `cnt` of them parked at kid / kz / kq (compact), or those that each_reg(f) calls f with.
+template <bool PREQ, bool GS, bool EXTRA, class EachReg>
+__device__ __forceinline__ void finish_kept(const RowArgs& a, const RowRef& R, uint32_t* kid, float* kz, float* kq, int cnt,
+                                            bool compact, EachReg&& each_reg, float m, float thr, float zcx, float zpx,
+                                            Small& sm, RowOut& out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+  const int n = a.n;
+  wave_lds_fence();
+  // the previous logits of the first kAhead lanes' worth of kept ids are requested now, of any more when needed
+  constexpr int kAhead = 3;
+  float qa[kAhead];
+  const bool gather = !PREQ && a.mode != kRowSelectOnly && !R.fresh;
+  if (gather) {
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) qa[s] = R.zp[s * kWave + lane < cnt ? kid[s * kWave + lane] : 0u];
+  }
+  // f(valid, id, z, q) for this wavefront's kept ids, every lane taking part in every call
+  auto from_lds = [&](auto&& f) {
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) {
+      const int i = s * kWave + lane;
+      if (s * kWave < cnt) f(i < cnt, static_cast<int>(kid[i]), kz[i], PREQ ? kq[i] : qa[s]);
+    }
+    if constexpr (PREQ) {
+#pragma unroll 1
+      for (int s = kAhead * kWave; s < cnt; s += kWave) {
+        const int i = s + lane, id = i < cnt ? static_cast<int>(kid[i]) : 0;
+        f(i < cnt, id, kz[i], kq[i]);
+      }
+    } else if (cnt > kAhead * kWave) {
+      // the loads of the next round are under way while f works on this one
+      auto id_at = [&](int i) { return i < cnt ? static_cast<int>(kid[i]) : 0; };
+      int next = id_at(kAhead * kWave + lane);
+      float qnext = gather ? R.zp[next] : 0.f;
+#pragma unroll 1
+      for (int s = kAhead * kWave; s < cnt; s += kWave) {
+        const int i = s + lane, id = next;
+        const float q = qnext;
+        next = id_at(i + kWave);
+        if (gather && s + kWave < cnt) qnext = R.zp[next];
+        f(i < cnt, id, kz[i], q);
+      }
+    }
+  };
+  auto each_kept = [&](auto&& f) {
+    if (compact) from_lds(f);
+    else each_reg(f);
+  };
+  float sum = 0.f;
+  each_kept([&](bool valid, int, float z, float) {
+    const float w = exp_of(z - m);
+    sum += valid ? w : 0.f;
+  });
+  sum = wave_sum(sum);
+  if (lane == 0) {
+    sm.fred[wave] = sum;
+    sm.ired[wave] = cnt;
+  }
+  __syncthreads();
+  int Cn;
+  fold_before<NW>(sm.ired, 0, Cn);
+  const float S = fold_sum<NW>(sm.fred);
+  const float lse_c = m + logf(S);
+  if (tid == 0) {
+    a.thr[R.oidx] = thr;
+    a.lse[R.oidx] = lse_c;
+    a.nkept[R.oidx] = Cn;
+    if (a.flags && !(lse_c == lse_c && fabsf(lse_c) < INFINITY)) atomicOr(a.flags, 1);
+  }
+  if (a.mode == kRowSelectOnly) return;
+
+  // Modified Rejection Sampling
+  const int j = R.p0 + R.s;
+  const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
+  const uint2 key = seed_key(a.seed);
+  const uint32_t w3 = static_cast<uint32_t>(R.b) << 8;
+  const bool x_ok = R.x >= 0 && R.x < n;
+  out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
+  out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
+  out.accept = __fmul_rn(sm.u_accept, out.qx) <= out.px;
+  out.best = INFINITY;
+  out.best_id = 0x7FFFFFFF;
+  out.gbest = INFINITY;
+  out.gbest_id = 0x7FFFFFFF;
+  auto q_of = [&](float z) { return R.fresh ? q_uniform : prob(z, R.thr_p, R.lse_p); };
+  if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
+    float d0 = 0.f, d1 = 0.f, d2 = 0.f;
+    each_kept([&](bool valid, int, float zc_v, float zq_v) {
+      const float pv = valid ? exp_of(zc_v - lse_c) : 0.f;
+      const float qv = valid ? q_of(zq_v) : 0.f;
+      d0 += fminf(pv, qv);
+      d1 += pv * qv;
+      d2 += pv * pv;
+    });
+    row_statistics_out(a, R, d0, d1, d2, q_uniform, sm);
+  }
+  if (GS) {                        // next draft should the row survive
+    const PRace pr = p_race_of_row(a, key, w3, j, R.it);
+    out.prace = pr.on;
+    if (pr.on)
+      each_kept([&](bool valid, int v, float z, float) {
+        const float pv = valid ? exp_of(z - lse_c) : 0.f;
+        if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, v, pv);
+      });
+  }
+  if (out.accept) return;          // uniform over the workgroup
+
+  auto race_one = [&](int v, float rv) {   // exponential-race entry of id v, residual rv > 0
+    const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
+                                              static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
+    const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
+    const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), rv);
+    if (sc < out.best || (sc == out.best && v < out.best_id)) {
+      out.best = sc;
+      out.best_id = v;
+    }
+  };
+  auto residual = [&](float z, float q) { return __fsub_rn(exp_of(z - lse_c), q_of(q)); };
+  if (compact) {
+    int positive = 0;              // written over the entries, at or before the place just read
+    from_lds([&](bool valid, int v, float z, float q) {
+      const float rv = residual(z, q);
+      const bool pos = valid && rv > 0.f;
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(pos);
+      const int at = lanes_before(mask, positive);
+      positive += __builtin_popcountll(mask);
+      if (pos) {
+        kid[at] = static_cast<uint32_t>(v);
+        kz[at] = rv;
+      }
+    });
+    wave_lds_fence();
+    for (int i = lane; i < positive; i += kWave) race_one(static_cast<int>(kid[i]), kz[i]);
+  } else {
+    each_kept([&](bool valid, int v, float z, float q) {
+      const float rv = residual(z, q);
+      if (valid && rv > 0.f) race_one(v, rv);
+    });
+  }
+}
+
 // Everything after the candidates sit in registers: threshold (if top-k filters),
 // normaliser, accept test, residual race.  Returns false if the threshold could not
 // be certified against `cut_max` (the caller then takes the complete path).
@@ -797,8 +956,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
                                             const bool (&ok)[PER], bool filter, uint32_t cut_max,
                                             float zcx, float zpx, uint32_t* hist, unsigned char* lds,
                                             Small& sm, RowOut& out, bool have_thr = false, float thr_given = 0.f) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
-  const int n = a.n;
+  const int wave = wave_index();
   uint32_t kmin, kmax;
   bool nan;
   draw_accept_uniform(a, R, sm);
@@ -844,50 +1002,89 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
     }
   }
   const bool compact = ALL_FIT || cnt <= CAP;
-  wave_lds_fence();
-  // the previous logits of the first kAhead lanes' worth of kept ids are requested now, of any more when needed
-  constexpr int kAhead = 3;
-  float qa[kAhead];
-  const bool gather = !PREQ && a.mode != kRowSelectOnly && !R.fresh;
-  if (gather) {
-#pragma unroll
-    for (int s = 0; s < kAhead; ++s) qa[s] = R.zp[s * kWave + lane < cnt ? kid[s * kWave + lane] : 0u];
-  }
-  // f(valid, id, z, q) for this wavefront's kept ids, every lane taking part in every call
-  auto from_lds = [&](auto&& f) {
-#pragma unroll
-    for (int s = 0; s < kAhead; ++s) {
-      const int i = s * kWave + lane;
-      if (s * kWave < cnt) f(i < cnt, static_cast<int>(kid[i]), kz[i], PREQ ? kq[i] : qa[s]);
-    }
-#pragma unroll 1
-    for (int s = kAhead * kWave; s < cnt; s += kWave) {
-      const int i = s + lane, id = i < cnt ? static_cast<int>(kid[i]) : 0;
-      f(i < cnt, id, kz[i], PREQ ? kq[i] : (gather ? R.zp[id] : 0.f));
-    }
-  };
-  auto each_kept = [&](auto&& f) {
-    if (compact) {
-      from_lds(f);
-    } else if constexpr (!ALL_FIT) {
+  finish_kept<PREQ, GS, EXTRA>(a, R, kid, kz, kq, cnt, compact, [&](auto&& f) {
+    if constexpr (!ALL_FIT) {
 #pragma unroll
       for (int e = 0; e < PER; ++e) f(ok[e] && zv[e] >= thr, vid[e], zv[e], zq[e]);
     }
-  };
+  }, m, thr, zcx, zpx, sm, out);
+  return true;
+}
+
+// The draft token's logits in this and the previous iteration: their latency hides behind the selection.
+__device__ __forceinline__ void draft_logits(const RowArgs& a, const RowRef& R, float& zcx, float& zpx) {
+  const bool x_ok = a.mode != kRowSelectOnly && R.x >= 0 && R.x < a.n;
+  zcx = x_ok ? R.zc[R.x] : 0.f;
+  zpx = (x_ok && !R.fresh) ? R.zp[R.x] : 0.f;
+}
+
+// f(v0, z) for every four neighbouring ids v0 .. v0 + 3 of a row, -inf past its end, read in coalesced 32-byte pieces,
+// two per thread in flight.
+template <class F>
+__device__ __forceinline__ void each_four(const float* zc, int n, F&& f) {
+  const int nchunks = (n + 7) >> 3;
+  for (int c0 = threadIdx.x; c0 < nchunks; c0 += 2 * THREADS) {
+    float zz[2][2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int c = c0 + u * THREADS;
+      if (c < nchunks && (c << 3) + 7 < n) {
+        const float4 lo4 = load4(zc + (c << 3));
+        const float4 hi4 = load4(zc + (c << 3) + 4);
+        zz[u][0][0] = lo4.x; zz[u][0][1] = lo4.y; zz[u][0][2] = lo4.z; zz[u][0][3] = lo4.w;
+        zz[u][1][0] = hi4.x; zz[u][1][1] = hi4.y; zz[u][1][2] = hi4.z; zz[u][1][3] = hi4.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          zz[u][e >> 2][e & 3] = (c < nchunks && (c << 3) + e < n) ? zc[(c << 3) + e] : -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int c = c0 + u * THREADS;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (c < nchunks && (c << 3) + 4 * h < n) f((c << 3) + 4 * h, zz[u][h]);
+    }
+  }
+}
+// f(v, z) for every id
+template <class F>
+__device__ __forceinline__ void each_logit(const float* zc, int n, F&& f) {
+  each_four(zc, n, [&](int v0, const float (&z)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (v0 + e < n) f(v0 + e, z[e]);
+  });
+}
+
+// Normaliser, accept test and races over all ids that `for_each_logit` brings, where the kept ones are too many to park.
+// WHOLE: that is the whole row, and the residual race takes it four ids at a time, which share a draw of random bits (four
+// steps of 32 x 64000 ids of which 27000 are kept: 445 -> 396 us).
+template <bool GS, bool EXTRA, bool WHOLE, class Each>
+__device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& R, Each&& for_each_logit, float m, float thr,
+                                                float zcx, float zpx, Small& sm, RowOut& out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = a.n;
+  const float* const zp = R.zp;
   float sum = 0.f;
-  each_kept([&](bool valid, int, float z, float) {
-    const float w = exp_of(z - m);
-    sum += valid ? w : 0.f;
+  int cnt = 0;
+  for_each_logit([&](int, float z) {
+    if (z >= thr) {
+      sum += exp_of(z - m);
+      ++cnt;
+    }
   });
   sum = wave_sum(sum);
+  cnt = wave_sum_i32(cnt);
   if (lane == 0) {
     sm.fred[wave] = sum;
     sm.ired[wave] = cnt;
   }
   __syncthreads();
+  const float S = fold_sum<NW>(sm.fred);
   int Cn;
   fold_before<NW>(sm.ired, 0, Cn);
-  const float S = fold_sum<NW>(sm.fred);
   const float lse_c = m + logf(S);
   if (tid == 0) {
     a.thr[R.oidx] = thr;
@@ -895,9 +1092,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
     a.nkept[R.oidx] = Cn;
     if (a.flags && !(lse_c == lse_c && fabsf(lse_c) < INFINITY)) atomicOr(a.flags, 1);
   }
-  if (a.mode == kRowSelectOnly) return true;
-
-  // Modified Rejection Sampling
+  if (a.mode == kRowSelectOnly) return;
   const int j = R.p0 + R.s;
   const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
   const uint2 key = seed_key(a.seed);
@@ -905,67 +1100,269 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   const bool x_ok = R.x >= 0 && R.x < n;
   out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
   out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
-  out.accept = __fmul_rn(sm.u_accept, out.qx) <= out.px;
+  const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(j), static_cast<uint32_t>(R.it),
+                                            w3 | kStreamAccept), key);
+  out.accept = __fmul_rn(u01(ra.x), out.qx) <= out.px;
   out.best = INFINITY;
   out.best_id = 0x7FFFFFFF;
   out.gbest = INFINITY;
   out.gbest_id = 0x7FFFFFFF;
-  auto q_of = [&](float z) { return R.fresh ? q_uniform : prob(z, R.thr_p, R.lse_p); };
   if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
     float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-    each_kept([&](bool valid, int, float zc_v, float zq_v) {
-      const float pv = valid ? exp_of(zc_v - lse_c) : 0.f;
-      const float qv = valid ? q_of(zq_v) : 0.f;
-      d0 += fminf(pv, qv);
-      d1 += pv * qv;
-      d2 += pv * pv;
+    for_each_logit([&](int v, float z) {
+      const float pv = prob(z, thr, lse_c);
+      if (pv > 0.f) {
+        const float qv = R.fresh ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
+        d0 += fminf(pv, qv);
+        d1 += pv * qv;
+        d2 += pv * pv;
+      }
     });
     row_statistics_out(a, R, d0, d1, d2, q_uniform, sm);
   }
-  if (GS) {                        // next draft should the row survive
+  if (GS) {
     const PRace pr = p_race_of_row(a, key, w3, j, R.it);
     out.prace = pr.on;
-    if (pr.on)
-      each_kept([&](bool valid, int v, float z, float) {
-        const float pv = valid ? exp_of(z - lse_c) : 0.f;
+    if (pr.on) {
+      for_each_logit([&](int v, float z) {
+        const float pv = prob(z, thr, lse_c);
         if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, v, pv);
       });
-  }
-  if (out.accept) return true;     // uniform over the workgroup
-
-  auto race_one = [&](int v, float rv) {   // exponential-race entry of id v, residual rv > 0
-    const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
-                                              static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
-    const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
-    const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), rv);
-    if (sc < out.best || (sc == out.best && v < out.best_id)) {
-      out.best = sc;
-      out.best_id = v;
     }
-  };
-  auto residual = [&](float z, float q) { return __fsub_rn(exp_of(z - lse_c), q_of(q)); };
-  if (compact) {
-    int positive = 0;              // written over the entries, at or before the place just read
-    from_lds([&](bool valid, int v, float z, float q) {
-      const float rv = residual(z, q);
-      const bool pos = valid && rv > 0.f;
-      const unsigned long long mask = __builtin_amdgcn_ballot_w64(pos);
-      const int at = lanes_before(mask, positive);
-      positive += __builtin_popcountll(mask);
-      if (pos) {
-        kid[at] = static_cast<uint32_t>(v);
-        kz[at] = rv;
+  }
+  if (out.accept) return;
+  if constexpr (WHOLE) {
+    each_four(R.zc, n, [&](int v0, const float (&z)[4]) {
+      float q[4] = {0.f, 0.f, 0.f, 0.f}, rv[4];
+      bool any = false;
+      if (!R.fresh) {
+        if (v0 + 3 < n) {
+          const float4 t = load4(zp + v0);
+          q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) q[e] = v0 + e < n ? zp[v0 + e] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float pv = v0 + e < n ? prob(z[e], thr, lse_c) : 0.f;
+        rv[e] = pv > 0.f ? __fsub_rn(pv, R.fresh ? q_uniform : prob(q[e], R.thr_p, R.lse_p)) : 0.f;
+        any |= rv[e] > 0.f;
+      }
+      if (!any) return;
+      const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v0 >> 2), static_cast<uint32_t>(j),
+                                                static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
+      const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float sc = rv[e] > 0.f ? __fdiv_rn(neg_log(u01(lanes[e])), rv[e]) : INFINITY;
+        if (rv[e] > 0.f && (sc < out.best || (sc == out.best && v0 + e < out.best_id))) {
+          out.best = sc;
+          out.best_id = v0 + e;
+        }
       }
     });
-    wave_lds_fence();
-    for (int i = lane; i < positive; i += kWave) race_one(static_cast<int>(kid[i]), kz[i]);
   } else {
-    each_kept([&](bool valid, int v, float z, float q) {
-      const float rv = residual(z, q);
-      if (valid && rv > 0.f) race_one(v, rv);
+    for_each_logit([&](int v, float z) {
+      const float pv = prob(z, thr, lse_c);
+      if (pv > 0.f) {
+        const float qv = R.fresh ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
+        const float rv = __fsub_rn(pv, qv);
+        if (rv > 0.f) {
+          const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
+                                                    static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
+          const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
+          const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), rv);
+          if (sc < out.best || (sc == out.best && v < out.best_id)) {
+            out.best = sc;
+            out.best_id = v;
+          }
+        }
+      }
     });
   }
-  return true;
+}
+
+// Rows of more than kDirectMaxN ids under a nucleus filter alone: the whole row in registers, 32 or 64 logits per
+// thread, until the threshold is known and the kept ids are parked in LDS.
+//   Bound by the vector instructions of one CU per row, about 30 per id for the masses (an exponential, a conversion to
+// fixed point and a 64-bit LDS addition each): 28000 of 88000 cycles.  Against a row read from memory three times and
+// scanned three more through 16-bit prefixes in LDS, four steps on supplied logits of 32 x 65536 take 197 us for 228,
+// of 2 x 64 x 64000 ids behind the LM head 659 for 690, of 8 x 32 x 65536 without guidance 766 for 970.
+// Up to 18432 kept ids are parked (what LDS holds); rows that keep more are read again, which is the better way for them.
+constexpr int kNucleusCap = 1152;            // kept ids that a wavefront parks ...
+constexpr int kNucleusPark = kNucleusCap + kWave;   // ... and a place per lane for what is not kept
+template <int PER, bool GS>
+__device__ __forceinline__ void nucleus_path(const RowArgs& a, RowRef& R, unsigned char* smem, Small& sm, RowOut& out) {
+  const int lane = threadIdx.x & 63, wave = wave_index();
+  int n = a.n;
+  // the sizes' comparisons are made anew in every phase: kept, they fill the scalar registers
+  auto new_phase = [&]() { asm volatile("" : "+s"(n)); __builtin_amdgcn_sched_barrier(0); };
+  constexpr int STEP = 8 * NW * 32;          // ids per group of four registers, dealt out as in direct_path
+  const int first = wave * 32 + (lane >> 3) * (NW * 32) + ((lane & 7) << 2);
+  // Past the end of the row: -inf, which has no mass and is below every threshold (a mask per logit would be kept from
+  // phase to phase); whole groups past it are skipped.
+  // a scalar base and 32 bits per lane: no registers for addresses
+  auto at_byte = [](auto* base, uint32_t bytes) {
+    using T = decltype(base);
+    if constexpr (std::is_const_v<std::remove_pointer_t<T>>) return reinterpret_cast<T>(reinterpret_cast<const char*>(base) + bytes);
+    else return reinterpret_cast<T>(reinterpret_cast<char*>(base) + bytes);
+  };
+  float zv[PER];
+#pragma unroll
+  for (int u = 0; u < PER / 4; ++u) {
+    const int v0 = first + u * STEP;
+    if ((u + 1) * STEP <= n) {               // uniform
+      const float4 t = load4(at_byte(R.zc + u * STEP, 4u * first));
+      zv[4 * u] = t.x; zv[4 * u + 1] = t.y; zv[4 * u + 2] = t.z; zv[4 * u + 3] = t.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) zv[4 * u + e] = -INFINITY;
+      if (u * STEP < n) {
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = *at_byte(R.zc, 4u * min(v0 + e, n - 1));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zv[4 * u + e] = v0 + e < n ? t[e] : -INFINITY;
+      }
+    }
+  }
+  read_row_scalars(a, R);
+  float zcx, zpx;
+  draft_logits(a, R, zcx, zpx);
+  draw_accept_uniform(a, R, sm);
+  new_phase();
+  float hi = -INFINITY, lo = INFINITY;
+  bool nan = false;
+#pragma unroll
+  for (int u = 0; u < PER / 4; ++u) {
+    if (u * STEP >= n) continue;             // uniform
+    float* const z = &zv[4 * u];
+    const int v0 = first + u * STEP;
+    if (R.zw) {                              // supplied logits: keep them for the next iteration
+      if (v0 + 3 < n) {
+        store4(at_byte(R.zw + u * STEP, 4u * first), z[0], z[1], z[2], z[3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v0 + e < n) *at_byte(R.zw, 4u * (v0 + e)) = z[e];
+      }
+    }
+    hi = max3(max3(hi, z[0], z[1]), z[2], z[3]);
+    if ((u + 1) * STEP <= n) {
+      lo = min3(min3(lo, z[0], z[1]), z[2], z[3]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) lo = z[e] > -INFINITY ? min3(lo, z[e], z[e]) : lo;
+    }
+    const float sum = (z[0] + z[1]) + (z[2] + z[3]);
+    if (sum != sum) {                        // a NaN, or infinities of both signs
+#pragma unroll
+      for (int e = 0; e < 4; ++e) nan |= z[e] != z[e];
+    }
+  }
+  if (nan && a.flags) atomicOr(a.flags, 1);
+  uint32_t kmax = nan ? 0xFFFFFFFFu : zkey(hi), kmin = zkey(lo);
+  block_minmax(kmin, kmax, sm, false);
+  const float m = key_to_float(kmax);
+  // Members of the boundary's bin: gathered in LDS behind the histogram, then taken up by all threads evenly.
+  float* const list = reinterpret_cast<float*>(smem + NBINS_P * 8);
+  int near_cnt = 0;
+  bool near_dense = false;
+  float nz[PER_LIST];
+  const uint32_t pkey = nucleus_key(
+      [&](auto&& f) {
+        new_phase();
+#pragma unroll
+        for (int u = 0; u < PER / 4; ++u) {
+          if (u * STEP >= n) continue;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) f(0u, zv[4 * u + e]);
+          __builtin_amdgcn_sched_barrier(0);               // (64 logits leave no registers for more at a time)
+        }
+      },
+      [&](uint32_t klo, uint32_t khi) {
+        const float flo = klo != 0u ? key_to_float(klo) : -INFINITY, fhi = khi != 0xFFFFFFFFu ? key_to_float(khi) : INFINITY;
+        // four ids at a time, most of them far away: a distance to the interval's middle that none of its logits exceeds
+        const bool bounded = flo > -INFINITY && fhi < INFINITY;
+        const float middle = bounded ? 0.5f * flo + 0.5f * fhi : 0.f, reach = bounded ? 0.52f * (fhi - flo) : INFINITY;
+        if (threadIdx.x == 0) sm.cursor = 0u;
+        __syncthreads();
+        new_phase();
+#pragma unroll
+        for (int u = 0; u < PER / 4; ++u) {
+          if (u * STEP >= n) continue;
+          float d[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) d[e] = fabsf(zv[4 * u + e] - middle);
+          if (__builtin_amdgcn_ballot_w64(fminf(fminf(d[0], d[1]), fminf(d[2], d[3])) <= reach) == 0ull) continue;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float z = zv[4 * u + e];
+            if (z >= flo && z <= fhi) {
+              const uint32_t slot = atomicAdd(&sm.cursor, 1u);
+              if (slot < static_cast<uint32_t>(kListCap)) list[slot] = z;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        const uint32_t found = sm.cursor;
+        near_dense = found > static_cast<uint32_t>(kListCap);
+        near_cnt = near_dense ? 0 : static_cast<int>(found);
+#pragma unroll
+        for (int e = 0; e < PER_LIST; ++e) {
+          const int i = threadIdx.x + e * THREADS;
+          nz[e] = i < near_cnt ? list[i] : 0.f;
+        }
+      },
+      [&](auto&& f) {
+        if (near_dense) {
+          each_logit(R.zc, n, [&](int, float z) { f(zkey(z), z); });
+        } else {
+#pragma unroll
+          for (int e = 0; e < PER_LIST; ++e)
+            if (static_cast<int>(threadIdx.x) + e * THREADS < near_cnt) f(zkey(nz[e]), nz[e]);
+        }
+      },
+      m, key_to_float(kmin), a.top_p24, reinterpret_cast<unsigned long long*>(smem), sm);
+  const float thr = key_to_float(pkey);
+  new_phase();
+  int mine = 0;
+#pragma unroll
+  for (int u = 0; u < PER / 4; ++u) {
+    if (u * STEP >= n) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mine += zv[4 * u + e] >= thr ? 1 : 0;
+  }
+  const int incl = wave_inclusive_sum_i32(mine);
+  const int cnt = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (lane == 0) sm.ured[wave] = static_cast<uint32_t>(cnt);
+  __syncthreads();
+  if (fold_max<NW>(sm.ured) > static_cast<uint32_t>(kNucleusCap)) {        // uniform: a flat row
+    finish_in_place<GS, true, true>(a, R, [&](auto&& f) { each_logit(R.zc, n, f); }, m, thr, zcx, zpx, sm, out);
+    return;
+  }
+  uint32_t* const kid = reinterpret_cast<uint32_t*>(smem) + wave * 2 * kNucleusPark;
+  float* const kz = reinterpret_cast<float*>(kid + kNucleusPark);
+  int at = incl - mine;
+  new_phase();
+#pragma unroll
+  for (int u = 0; u < PER / 4; ++u) {
+    if (u * STEP >= n) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool keep = zv[4 * u + e] >= thr;
+      const int to = keep ? at : kNucleusCap + lane;
+      kid[to] = static_cast<uint32_t>(min(first + u * STEP + e, n - 1));
+      kz[to] = zv[4 * u + e];
+      at += keep ? 1 : 0;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  wave_lds_fence();
+  finish_kept<false, GS, true>(a, R, kid, kz, nullptr, cnt, true, [](auto&&) {}, m, thr, zcx, zpx, sm, out);
 }
 
 // The complete in-place path: one coalesced read of the row, 16-bit key prefixes in
@@ -981,7 +1378,6 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem + static_cast<size_t>(n8) * 2);
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + static_cast<size_t>(n8) * 2 + NBINS * 4);
   const float* zc = R.zc;
-  const float* zp = R.zp;
   float* const zw = a.cand ? nullptr : R.zw;     // the slice kernel has made the copy already
 
   // pass 1: batches of 8 independent 16-byte loads per thread
@@ -1156,29 +1552,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   // the few ids that pass the prefix test are gathered.
   auto for_each_logit = [&](auto&& f) {
     if (!pfilter) {
-      for (int c0 = tid; c0 < nchunks; c0 += 2 * THREADS) {
-        float zz[2][8];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int c = c0 + u * THREADS;
-          if (c < nchunks && (c << 3) + 7 < n) {
-            const float4 lo4 = load4(zc + (c << 3));
-            const float4 hi4 = load4(zc + (c << 3) + 4);
-            zz[u][0] = lo4.x; zz[u][1] = lo4.y; zz[u][2] = lo4.z; zz[u][3] = lo4.w;
-            zz[u][4] = hi4.x; zz[u][5] = hi4.y; zz[u][6] = hi4.z; zz[u][7] = hi4.w;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) zz[u][e] = (c < nchunks && (c << 3) + e < n) ? zc[(c << 3) + e] : 0.f;
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int c = c0 + u * THREADS;
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (c < nchunks && (c << 3) + e < n) f((c << 3) + e, zz[u][e]);
-        }
-      }
+      each_logit(zc, n, f);
     } else {
       for_each_candidate([&](int v, uint32_t) { f(v, zc[v]); });
     }
@@ -1257,88 +1631,8 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
       return;
     }
   }
-  float sum = 0.f;
-  int cnt = 0;
-  for_each_logit([&](int, float z) {
-    if (z >= thr) {
-      sum += exp_of(z - m);
-      ++cnt;
-    }
-  });
-  sum = wave_sum(sum);
-  cnt = wave_sum_i32(cnt);
-  if (lane == 0) {
-    sm.fred[wave] = sum;
-    sm.ired[wave] = cnt;
-  }
-  __syncthreads();
-  const float S = fold_sum<NW>(sm.fred);
-  int Cn;
-  fold_before<NW>(sm.ired, 0, Cn);
-  const float lse_c = m + logf(S);
-  if (tid == 0) {
-    a.thr[R.oidx] = thr;
-    a.lse[R.oidx] = lse_c;
-    a.nkept[R.oidx] = Cn;
-    if (a.flags && !(lse_c == lse_c && fabsf(lse_c) < INFINITY)) atomicOr(a.flags, 1);
-  }
-  if (a.mode == kRowSelectOnly) return;
-  const int j = R.p0 + R.s;
-  const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
-  const uint2 key = seed_key(a.seed);
-  const uint32_t w3 = static_cast<uint32_t>(R.b) << 8;
-  const bool x_ok = R.x >= 0 && R.x < n;
-  out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
-  out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
-  const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(j), static_cast<uint32_t>(R.it),
-                                            w3 | kStreamAccept), key);
-  out.accept = __fmul_rn(u01(ra.x), out.qx) <= out.px;
-  out.best = INFINITY;
-  out.best_id = 0x7FFFFFFF;
-  out.gbest = INFINITY;
-  out.gbest_id = 0x7FFFFFFF;
-  if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
-    float d0 = 0.f, d1 = 0.f, d2 = 0.f;
-    for_each_logit([&](int v, float z) {
-      const float pv = prob(z, thr, lse_c);
-      if (pv > 0.f) {
-        const float qv = R.fresh ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
-        d0 += fminf(pv, qv);
-        d1 += pv * qv;
-        d2 += pv * pv;
-      }
-    });
-    row_statistics_out(a, R, d0, d1, d2, q_uniform, sm);
-  }
-  if (GS) {
-    const PRace pr = p_race_of_row(a, key, w3, j, R.it);
-    out.prace = pr.on;
-    if (pr.on) {
-      for_each_logit([&](int v, float z) {
-        const float pv = prob(z, thr, lse_c);
-        if (pv > 0.f) gumbel_entry(out, key, pr.w3s, j, pr.it, v, pv);
-      });
-    }
-  }
-  if (!out.accept) {
-    for_each_logit([&](int v, float z) {
-      const float pv = prob(z, thr, lse_c);
-      if (pv > 0.f) {
-        const float qv = R.fresh ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
-        const float rv = __fsub_rn(pv, qv);
-        if (rv > 0.f) {
-          const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
-                                                    static_cast<uint32_t>(R.it), w3 | kStreamResid), key);
-          const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
-          const float sc = __fdiv_rn(neg_log(u01(lanes[v & 3])), rv);
-          if (sc < out.best || (sc == out.best && v < out.best_id)) {
-            out.best = sc;
-            out.best_id = v;
-          }
-        }
-      }
-    });
-  }
+  if (pfilter) finish_in_place<GS, EXTRA, false>(a, R, for_each_logit, m, thr, zcx, zpx, sm, out);
+  else finish_in_place<GS, EXTRA, true>(a, R, for_each_logit, m, thr, zcx, zpx, sm, out);
 }
 
 // Rows of more than kRowKernelMaxN ids whose candidates were not certified, or that have none
@@ -1565,13 +1859,6 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   });
 }
 
-// The draft token's logits in this and the previous iteration: their latency hides behind the selection.
-__device__ __forceinline__ void draft_logits(const RowArgs& a, const RowRef& R, float& zcx, float& zpx) {
-  const bool x_ok = a.mode != kRowSelectOnly && R.x >= 0 && R.x < a.n;
-  zcx = x_ok ? R.zc[R.x] : 0.f;
-  zpx = (x_ok && !R.fresh) ? R.zp[R.x] : 0.f;
-}
-
 // The whole row in registers, PER logits per thread (n <= PER * THREADS).  A wavefront takes every NW-th piece of
 // 32 ids (a 128-byte line): ids that are likelier than others tend to be neighbours, and every wavefront works
 // on the kept ones among its own.
@@ -1640,7 +1927,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
 // with all of them in one kernel the compiler keeps every way's arguments in scalar registers and spills them
 // (184 spills; 46 vector registers spilled in the optional instances).  Four-step decodes over 8192 ids: 132 ->
 // 129 us, with every option 206 -> 193 us.
-enum Path { kDirectHalf, kDirectWhole, kLists, kLong };
+enum Path { kDirectHalf, kDirectWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
 template <bool GS, bool EXTRA, int PATH>
 __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
                                                       const int mode_, const int L_, const int N_,
@@ -1676,6 +1963,9 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(cons
   if constexpr (PATH == kDirectHalf || PATH == kDirectWhole) {
     // ---- the whole row in registers ------------------------------------------------
     direct_path<PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, sm, out);
+    done = true;
+  } else if constexpr (PATH == kNucleusHalf || PATH == kNucleusWhole) {
+    nucleus_path<PATH == kNucleusHalf ? 32 : 64, GS>(a, R, smem, sm, out);
     done = true;
   } else if (filter && a.cand && P > 0) {
     // ---- candidates emitted by the slice kernel ----------------------------------
@@ -1927,6 +2217,10 @@ size_t lds_bytes_for(int n) {
   return std::max(lists, static_cast<size_t>((n + 7) & ~7) * 2 + NBINS * sizeof(uint32_t) + kListCap * sizeof(uint16_t));
 }
 
+constexpr size_t kNucleusLds = static_cast<size_t>(NW) * kNucleusPark * 8;      // the histogram of masses lies under it
+static_assert(kNucleusLds >= NBINS_P * 8 + kListCap * 4 && kNucleusLds + sizeof(Small) <= 160 * 1024, "nucleus_path: LDS");
+static_assert(64 * 1024 >= kRowKernelMaxN, "nucleus_path: a row in registers");
+
 inline size_t small_block(int rows) {
   return (static_cast<size_t>(rows) * kRowMaxTiles * 4 + 255) / 256 * 256;
 }
@@ -1990,7 +2284,8 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
   }
-  const size_t lds = lds_bytes_for(a.n);
+  const bool nucleus = a.n > kDirectMaxN && a.n <= kRowKernelMaxN && a.top_p24 != 0u && !(a.top_k > 0 && a.top_k < a.n);
+  const size_t lds = nucleus ? kNucleusLds : lds_bytes_for(a.n);
   const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
   const bool extra = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
   using Kernel = void (*)(const int32_t*, const int32_t*, int, int, int, int, int, RowArgs);
@@ -1998,7 +2293,9 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
   static const Kernel kernels[][4] = {SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
 #ifndef SCD_ROW_BATCHED
-                                      SCD_ROW_INSTANCES(kLists), {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr}
+                                      SCD_ROW_INSTANCES(kLists), {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
+                                      {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
+                                      {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
 #endif
   };
 #undef SCD_ROW_INSTANCES
@@ -2008,7 +2305,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   size_t none = 0;
   size_t& configured = lds_configured ? *lds_configured : none;
   if (configured == 0) {
-    const size_t most = std::max(lds_bytes_for(kRowKernelMaxN), lds_bytes_for(kDirectMaxN));
+    const size_t most = std::max({lds_bytes_for(kRowKernelMaxN), lds_bytes_for(kDirectMaxN), kNucleusLds});
     for (const auto& row : kernels)
       for (Kernel f : row)
         if (f)
@@ -2019,7 +2316,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
     configured = most;
   }
   const int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
-                   : a.n <= kRowKernelMaxN ? kLists : kLong;
+                   : nucleus ? (a.n <= 32 * THREADS ? kNucleusHalf : kNucleusWhole) : a.n <= kRowKernelMaxN ? kLists : kLong;
   const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
   if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
   a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;

@@ -1,0 +1,64 @@
+"""Rows of more than 16384 ids under a nucleus filter alone, which stay in registers, against the same rows under a
+top-k that drops one weightless id, which take the general path."""
+import pytest
+import torch
+
+from paper_2510_24211_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# the shortest row; whole groups of 4096 ids and one id more; the edges of 32 and 64 logits per thread; odd lengths;
+# the longest.  Spread 3: hundreds to thousands of ids kept; 0.3: more than are parked in LDS; with shared-noise
+# redrafts, independent ones and the statistics
+@pytest.mark.parametrize("n,spread,top_p,extra", [
+    (16385, 3.0, 0.8, {}),
+    (20480, 3.0, 0.9, dict(diagnostics=1)),
+    (20481, 0.3, 0.97, dict(coupling=B.COUPLING_GS)),
+    (32768, 3.0, 0.8, dict(sjd_mix=0.5)),
+    (32769, 3.0, 0.8, dict(coupling=B.COUPLING_GS)),
+    (45003, 0.3, 0.6, dict(diagnostics=1)),
+    (45003, 20.0, 0.9, {}),
+    (65535, 3.0, 0.95, {}),
+    (65536, 0.3, 0.9, {}),
+])
+def test_rows_in_registers_decide_like_the_general_path(n, spread, top_p, extra):
+    L, steps = 16, 3
+    g = torch.Generator(device=DEV).manual_seed(n)
+    base = spread * torch.randn(1, 1, n, device=DEV, generator=g)
+    xs = [base + 0.3 * spread * torch.randn(1, L, n, device=DEV, generator=g) for _ in range(steps)]
+    for x in xs:
+        x[..., 7] = x[..., 11] = x.amax(2)                   # equal logits at the top
+        x[..., n - 2] = -1.0e4                               # no mass: exp underflows
+    got = []
+    for top_k in (0, n - 1):
+        sc = B.Scd(B.make_config(B=1, L=L, N=200, V=n, top_k=top_k, top_p=top_p, seed=5, **extra), DEV)
+        st = sc.alloc_state()
+        sc.reset(st)
+        f = lambda field, *shape: sc.state_field(st, field).view(*shape).clone()  # noqa: E731
+        run = []
+        for it, x in enumerate(xs):
+            sc.step_logits(x, st)
+            thr, lse, nkept = (f(i, 2, L)[it & 1] for i in (B.F_THR, B.F_LSE, B.F_NKEPT))
+            run.append(dict(thr=thr, lse=lse, nkept=nkept, y=f(B.F_Y, L), k=f(B.F_K, L),
+                            px=f(B.F_PX, L), x=f(B.F_X, L), pos=f(B.F_POS, 1)))
+            if extra.get("diagnostics"):
+                run[-1]["stats"] = f(B.F_DIAG, L, 4)
+        got.append(run)
+        z = f(B.F_Z, 2, L, n)
+        assert torch.equal(z[(steps - 1) & 1].sort(0).values, xs[-1][0].sort(0).values)   # the ring's copy, by slot
+    rows = agree = 0
+    for a, b in zip(*got):
+        assert torch.equal(a["thr"], b["thr"]) and torch.equal(a["nkept"], b["nkept"])
+        # 32-bit sums of up to 65536 terms in another order, in the logarithm: a few units of the last place
+        assert bool(((a["lse"] - b["lse"]).abs() <= 1e-6 * b["lse"].abs().clamp(min=1.0)).all())
+        rows += L
+        agree += int(((a["y"] == b["y"]) & (a["k"] == b["k"])).sum())
+        if not all(torch.equal(a[i], b[i]) for i in ("y", "k", "x", "pos")):
+            break                                            # a near-tie: what follows starts from other drafts
+        assert bool(((a["px"] - b["px"]).abs() <= 4e-6 * (b["px"].abs() + 1e-30) * b["lse"].abs().max().clamp(min=1.0)).all())
+        if "stats" in a:
+            assert bool(((a["stats"] - b["stats"]).abs() <= 1e-4 * b["stats"].abs()).all())
+    # a score or an accept test moves by 1e-6 of itself: of 48 decisions over thousands of ids hardly one is that close
+    assert agree >= rows - 1
