@@ -1284,9 +1284,12 @@ __device__ __forceinline__ void nucleus_path(const RowArgs& a, RowRef& R, unsign
       },
       [&](uint32_t klo, uint32_t khi) {
         const float flo = klo != 0u ? key_to_float(klo) : -INFINITY, fhi = khi != 0xFFFFFFFFu ? key_to_float(khi) : INFINITY;
-        // four ids at a time, most of them far away: a distance to the interval's middle that none of its logits exceeds
+        // four ids at a time, most of them far away: a distance to a place in the interval that none of its logits exceeds.
+        // Both are rounded, and the interval may be a single float wide (its middle is then one of its ends): the larger
+        // distance of the two ends is computed like a logit's, and rounding keeps their order.
         const bool bounded = flo > -INFINITY && fhi < INFINITY;
-        const float middle = bounded ? 0.5f * flo + 0.5f * fhi : 0.f, reach = bounded ? 0.52f * (fhi - flo) : INFINITY;
+        const float middle = bounded ? 0.5f * flo + 0.5f * fhi : 0.f;
+        const float reach = bounded ? fmaxf(fhi - middle, middle - flo) : INFINITY;
         if (threadIdx.x == 0) sm.cursor = 0u;
         __syncthreads();
         new_phase();

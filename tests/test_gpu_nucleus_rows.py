@@ -1,8 +1,10 @@
-"""Rows of more than 16384 ids under a nucleus filter alone, which stay in registers, against the same rows under a
-top-k that drops one weightless id, which take the general path."""
+"""Rows of more than 16384 ids under a nucleus filter alone, which stay in registers: against the same rows under a
+top-k that drops one weightless id, which take the general path, and against the oracle."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import logits as lg
 from paper_2510_24211_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -62,3 +64,42 @@ def test_rows_in_registers_decide_like_the_general_path(n, spread, top_p, extra)
             assert bool(((a["stats"] - b["stats"]).abs() <= 1e-4 * b["stats"].abs()).all())
     # a score or an accept test moves by 1e-6 of itself: of 48 decisions over thousands of ids hardly one is that close
     assert agree >= rows - 1
+
+
+def _select(z, top_k, top_p):
+    rows, n = z.shape
+    sc = B.Scd(B.make_config(B=1, L=1, N=1, V=n, top_k=top_k, top_p=top_p), DEV)
+    thr, lse = torch.empty(rows, device=DEV), torch.empty(rows, device=DEV)
+    nkept = torch.empty(rows, dtype=torch.int32, device=DEV)
+    sc.select(torch.from_numpy(z).to(DEV), rows, thr, lse, nkept)
+    return thr.cpu().numpy(), lse.cpu().numpy(), nkept.cpu().numpy()
+
+
+# rows that span a few hundred to a few thousand units in the last place: a bin of the search holds one value, or none
+@pytest.mark.parametrize("n,offset,spread,top_p", [
+    (16385, 3e5, 3.0, 0.8),
+    (20480, 3e5, 3.0, 0.8),
+    (20481, -3e5, 3.0, 0.8),
+    (32768, 1e5, 3.0, 0.5),
+    (32769, 3e5, 3.0, 0.8),
+    (20000, 100.0, 0.001, 0.02),
+    (64000, 5e5, 3.0, 0.8),
+    (65536, 3e6, 3.0, 0.9),
+])
+def test_rows_in_registers_against_the_oracle_where_bins_are_narrow(n, offset, spread, top_p):
+    rng = np.random.default_rng(n)
+    z = (offset + spread * rng.standard_normal((64, n))).astype(np.float32)
+    thr, lse, nkept = _select(z, 0, top_p)
+    adopted = 0
+    for r in range(len(z)):
+        want = lg.nucleus_threshold(z[r], slice(None), top_p)
+        if thr[r] != want:          # a comparison of sums: within 2e-6 of the target mass either side is right
+            inner, outer = (lg.nucleus_threshold(z[r], slice(None), top_p + d) for d in (-2e-6, 2e-6))
+            assert outer <= thr[r] <= inner and (z[r] == thr[r]).any(), (r, thr[r], want)
+            adopted += 1
+        _, ref = lg.softmax_kept(z[r], thr[r])
+        m = float(z[r].max())
+        assert nkept[r] == (z[r] >= thr[r]).sum()
+        # the sum's logarithm as in the stage tests, and the rounding of its addition to the maximum
+        assert abs(lse[r] - ref) <= 1e-6 * max(1.0, abs(ref - m)) + 2.0 ** -23 * abs(ref), (r, lse[r], ref)
+    assert adopted <= 2
