@@ -361,8 +361,9 @@ static_assert(THREADS >= 512, "nucleus: a member per thread");
 // Both words of trunc(e^(z - m) 2^40), at most 2^40: multiplications by powers of two and the subtraction are exact,
 // so this is the conversion to 64 bits in 6 instructions (the general one takes twice as many).  NaN: 0.
 __device__ __forceinline__ unsigned long long mass_of(float z, float m) {
-  // (exp_of without its care for what is far below: such a factor underflows here, and -inf, a NaN then, has no mass)
-  const float y = z - m;
+  // As exp_of.  Far below, the product's rounding error alone would take the exponential unit to infinity: from e^-150 on
+  // there is no mass, nor has a NaN any.
+  const float y = fmaxf(z - m, -150.f);
   const float t = __fmul_rn(y, 1.44269502f);
   const float rest = __fmaf_rn(y, 1.92596303e-8f, __fmaf_rn(y, 1.44269502f, -t));
   const float k = __builtin_rintf(t);

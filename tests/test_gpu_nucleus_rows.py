@@ -103,3 +103,36 @@ def test_rows_in_registers_against_the_oracle_where_bins_are_narrow(n, offset, s
         # the sum's logarithm as in the stage tests, and the rounding of its addition to the maximum
         assert abs(lse[r] - ref) <= 1e-6 * max(1.0, abs(ref - m)) + 2.0 ** -23 * abs(ref), (r, lse[r], ref)
     assert adopted <= 2
+
+
+# Masked ids weigh nothing, whatever finite or infinite value masks them.  Rows 0 and 1: two ids, the second one's mass w
+# in units of 2^-40 100 above and below what top_p = 1 - 2^-20 asks for (2^40 * 2^24 < (2^24 - 16) (2^40 + w), that is
+# w >= 1048578; w comes out within 2 units), so that a mass of one unit per masked id decides; then half of the ids
+# masked, a stretch of them, all but one.
+@pytest.mark.parametrize("low", [-float("inf"), float(np.finfo(np.float32).min), -1e10, -2e10, -1e30, -1e38])
+@pytest.mark.parametrize("n,top_k", [
+    (1000, 0),            # rows in registers: of short rows ...
+    (12000, 5000),
+    (16385, 0),           # ... and of long ones
+    (20000, 0),
+    (65536, 0),
+    (65536, 2000),        # lists that are not certified: more ids tie at the mask than fit
+    (40000, 5000),        # no lists
+])
+def test_masked_ids_weigh_nothing(n, top_k, low):
+    rng = np.random.default_rng(n)
+    z = (3.0 * rng.standard_normal((5, n))).astype(np.float32)
+    z[:2], z[:2, 3] = low, 0.0
+    z[0, n - 5], z[1, n - 5] = np.log(np.array([1048578.0 + 100, 1048578.0 - 100]) / 2.0 ** 40)
+    z[2, rng.permutation(n)[:n // 2]] = low
+    z[3, n // 4:n - n // 4] = low
+    z[4, :n - 1] = low
+    thr, lse, nkept = _select(z, top_k, 1.0 - 2.0 ** -20)
+    assert thr[0] == z[0, n - 5] and nkept[0] == 2
+    assert thr[1] == 0.0 and nkept[1] == 1 and lse[1] == 0.0
+    assert thr[4] == z[4, n - 1] and nkept[4] == 1
+    thr, lse, nkept = _select(z, top_k, 0.8)
+    for r in range(5):
+        p, want, ref = lg.distribution(z[r], top_k, 0.8)
+        assert thr[r] == want and nkept[r] == (z[r] >= want).sum(), (r, thr[r], want)
+        assert abs(lse[r] - ref) <= 1e-6 * max(1.0, abs(ref))
