@@ -410,6 +410,7 @@ __device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, float* zt, 
   // The pairs are put in order in the row's part of zt (what is not emitted goes to a place of the lane's own behind
   // them: a branch per logit takes longer) and leave it 16 at a time.
   constexpr int PAIRS = (COLS + kTilePad) / 2;
+  static_assert(kRowListCap / (kRowDirectMaxN / COLS + 1) <= PAIRS - kTileLanes, "the longest list of the shortest row");
   uint2* const pairs = reinterpret_cast<uint2*>(ztrow);
   compiler_fence();
   int at = incl - mine;

@@ -81,7 +81,7 @@ constexpr int kHistWords = NBINS + kWave;     // and a word per lane for what is
 constexpr int kListCap = kRowListCap;         // candidate ids per row (LDS list / slice or tile output)
 constexpr int PER_LIST = kListCap / THREADS; // candidates per thread
 #ifndef SCD_ROW_DIRECT_MAX
-#define SCD_ROW_DIRECT_MAX 16384
+#define SCD_ROW_DIRECT_MAX kRowDirectMaxN
 #endif
 constexpr int kDirectMaxN = SCD_ROW_DIRECT_MAX;   // whole row in registers up to this many ids
 constexpr int PER_DIRECT = kDirectMaxN / THREADS;   // (rows of half that size take half of them)
@@ -2249,7 +2249,7 @@ bool row_uses_candidates(int n, int top_k) {
   const bool filter = top_k > 0 && top_k < n;
   // one list per slice, at most kRowMaxTiles lists per row (longer rows are read whole).  top-k: a slice
   // emits about twice its share of the row's top_k logits, which has to fit its part of the lists.
-  return n > kDirectMaxN && n <= kRowMaxTiles * kSliceMax && filter && top_k <= kListCap / 2;
+  return n > kRowDirectMaxN && n <= kRowMaxTiles * kSliceMax && filter && top_k <= kListCap / 2;
 }
 
 #endif  // !SCD_ROW_BATCHED

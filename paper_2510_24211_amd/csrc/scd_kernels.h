@@ -45,6 +45,8 @@ enum { kRowSelectOnly = 0, kRowPlain = 1, kRowRing = 2 };
 // longest row whose key prefixes fit LDS; longer ones run the LONG instance (top-k and the maximal
 // coupling only)
 constexpr int kRowKernelMaxN = 65536;
+// longest row that the row kernel holds in registers whole; only longer ones have candidate lists
+constexpr int kRowDirectMaxN = 16384;
 struct RowArgs {
   int mode;
   const float* z_cur;    // select-only: [rows, n]; plain: [B, L, n]; ring: base of [2, B, L, n]
