@@ -1537,8 +1537,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
     }
   }
 
-  // in place: no filter, or the candidates do not fit (massive ties)
-  bool pfilter = filter;                 // candidates = ids whose 16-bit key prefix is >= t16
+  // in place: no filter, or the candidates do not fit (massive ties).  Candidates: ids whose 16-bit key prefix is >= t16
   auto for_each_candidate = [&](auto&& f) {
     for (int c = tid; c < nchunks; c += THREADS) {
       const uint4 raw = *reinterpret_cast<const uint4*>(&k16[c << 3]);
@@ -1547,19 +1546,13 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
       for (int e = 0; e < 8; ++e) {
         const int v = (c << 3) + e;
         const uint32_t p = (w4[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu;
-        if (v < n && (!pfilter || p >= t16)) f(v, p);
+        if (v < n && p >= t16) f(v, p);
       }
     }
   };
-  // The same candidates with their logits: f(v, z).  Without a filter every id is a candidate
-  // and the row is read in coalesced 32-byte pieces, two chunks per thread in flight; with one
-  // the few ids that pass the prefix test are gathered.
+  // with their logits, gathered: f(v, z)
   auto for_each_logit = [&](auto&& f) {
-    if (!pfilter) {
-      each_logit(zc, n, f);
-    } else {
-      for_each_candidate([&](int v, uint32_t) { f(v, zc[v]); });
-    }
+    for_each_candidate([&](int v, uint32_t) { f(v, zc[v]); });
   };
   float thr = -INFINITY;
   if (filter) {
@@ -1580,9 +1573,8 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
     }
     thr = key_to_float((t16 << 16) | lowkey);
   }
-  if (EXTRA && a.top_p24 != 0u) {          // nucleus filter on what top-k left
+  if (EXTRA && a.top_p24 != 0u) {          // nucleus filter on what top-k left (alone: nucleus_path)
     const float thr_k = thr;
-    const float zmin = filter ? thr_k : key_to_float(p16min << 16);
     // members of the selected bin: ids found by the prefixes in LDS (appended in any order:
     // the masses are integers), their logits gathered once and kept for the three radix levels
     int near_cnt = 0;
@@ -1625,7 +1617,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
               if (tid + e * THREADS < near_cnt && nz[e] >= thr_k) f(zkey(nz[e]), nz[e]);
           }
         },
-        m, zmin, a.top_p24, reinterpret_cast<unsigned long long*>(hist), sm);
+        m, thr_k, a.top_p24, reinterpret_cast<unsigned long long*>(hist), sm);
     thr = key_to_float(pkey);
     // the kept ids sit at or above the threshold's prefix: a short list takes the common tail
     t16 = max(t16, pkey >> 16);
@@ -1635,8 +1627,8 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
       return;
     }
   }
-  if (pfilter) finish_in_place<GS, EXTRA, false>(a, R, for_each_logit, m, thr, zcx, zpx, sm, out);
-  else finish_in_place<GS, EXTRA, true>(a, R, for_each_logit, m, thr, zcx, zpx, sm, out);
+  if (filter) finish_in_place<GS, EXTRA, false>(a, R, for_each_logit, m, thr, zcx, zpx, sm, out);
+  else finish_in_place<GS, EXTRA, true>(a, R, [&](auto&& f) { each_logit(zc, n, f); }, m, thr, zcx, zpx, sm, out);
 }
 
 // Rows of more than kRowKernelMaxN ids whose candidates were not certified, or that have none
