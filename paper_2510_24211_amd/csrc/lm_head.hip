@@ -195,8 +195,8 @@ __device__ __forceinline__ void epilogue(const LmHeadArgs& a, const f32x16 (&acc
 // rows lie side by side in a wavefront, a row of 16 lanes each: reductions are four lane exchanges for four rows at once,
 // and what is once per row (range, cut, offsets) is once per four: about 130 instructions per tile row.  z is stored from here,
 // 16 bytes per lane.  Against a whole wavefront per tile row and 4-byte stores of z, four steps of two sequences
-// x 64 positions x 64000 ids over 4096 take 599 us for 645, of one sequence x 32 x 65536 398 for 408, of eight x 32 x
-// 65536 over 2048 without guidance 474 for 488 (tiles of 256 x 256 in two passes: the second one's logits spill).
+// x 64 positions x 64000 ids over 4096 take 590 us for 626, of one sequence x 32 x 65536 398 for 409, of eight x 32 x
+// 65536 over 2048 without guidance 507 for 526 (tiles of 256 x 256 in two passes: the second one's logits spill).
 constexpr int kTilePad = 8;                 // floats: rows 4 apart fall into disjoint banks
 constexpr int kTileBins = 128;
 constexpr int kTileRows = 4;                // rows that a wavefront reduces side by side
@@ -671,13 +671,15 @@ __global__ __launch_bounds__((Cfg<RBW, C, NWV>::THREADS)) void lm_head_kernel(
 //     the barrier queue at the CU's one address unit (16 clocks per instruction) with their MFMAs behind them
 //     (256 x 128 tiles, 64 workgroups: 52 -> 43 us).
 //   * A wavefront multiplies 64 x 128 or 64 x 64 (NC x NB accumulator tiles of 32 x 32): the LDS reads of a
-//     k-tile take less than its MFMAs.
+//     k-tile take less than its MFMAs (by the counters 33 of 66 thousand cycles on 256 x 128 tiles, no bank conflicts).
 //   * Small calls add k up in 4 or 8 partial sums (k_parts): every `per` k-tiles the accumulators are added to
 //     whole sums and start again from zero.  In the register form of the MFMAs (launch bounds of 512: with one
 //     wavefront per SIMD the compiler takes accumulation registers, and each fold copies them out and back)
 //     this takes 0 to 6 % (64 rows with guidance x 2000 ids over 4096: 17.7 -> 18.8 us).
-// What is left is power: with real operands all 256 CUs sustain about 1.45 PFLOP/s (MFMAs alone, operands
-// fixed in registers; 1.9 on zeros), and loads on top share that budget.  Against register-staged kernels:
+// What is left: on 1024 h rows x 8192 ids the matrix pipes are busy for 66 thousand cycles of the 96 that a CU has
+// wavefronts, a third of the wavefronts' cycles pass at waits and barriers, and a quarter of the kernel lies before a
+// CU's first and after its last wavefront.  Above it stands power: with real operands all 256 CUs sustain about 1.45 PFLOP/s
+// (MFMAs alone, operands fixed in registers; 1.9 on zeros).  Against register-staged kernels:
 // 1024 h rows x 8192 ids over 4096 84 -> 62 us (1.10 PFLOP/s; the vendor GEMM 66), 256 x 64000 148 -> 124
 // without candidates (4.2 TB/s and 1.08 PFLOP/s at once), 128 x 65536 107 -> 88, 64 x 30000 71 -> 44,
 // 120 packed rows x 51285 over 2048 63 -> 42.
@@ -1300,8 +1302,8 @@ hipError_t launch_split(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& 
 // In how many partial sums the k of a logit is added up outside the split kernel.  The rounding error of one
 // chain of 32-bit additions grows with its length: against 64 bits, over d = 4096 4.0e-7 of the logits' size in one
 // chain, 1.9e-7 in 4 parts, 1.4e-7 in 8.  Calls of up to 96 rows and 49024 ids have it at the lower levels (the
-// lines of the split kernel, which served them all at first); larger ones are bound by the matrix pipe and the
-// power it draws, and take one chain in every kernel.
+// lines of the split kernel, which served them all at first); larger ones load the matrix pipe most, and take
+// one chain in every kernel.
 int k_parts(const LmHeadArgs& a) {
   const int rows = a.B * a.L, KT = (a.d + BK - 1) / BK;
   if (rows > 96 || a.n > 49024 || KT < 16) return 1;

@@ -27,12 +27,13 @@
 // Rows of <= 16384 logits need no candidates (the whole row fits the row
 // kernel's registers); on longer ones the lists come from the LM head's
 // epilogue, one per column tile, when that kernel emits them.  If the verification fails (massive ties, adversarial
-// layouts) or top-k is off, the row kernel falls back to a complete in-place
+// layouts) or no list is long enough, the row kernel falls back to a complete in-place
 // path: one coalesced read of the row, 16-bit key prefixes parked in LDS,
-// histogram select, candidate list or in-place scans.
+// histogram select, candidate list or in-place scans; the scans alone where nothing filters.  Under a nucleus
+// filter without top-k such rows stay in registers too (nucleus_path).
 // Rows of more than 65536 logits (the LONG instance; top-k and the maximal coupling only) take the
-// slice kernel and the candidate path like the others.  32 rows of 131072 ids under top-k 2000: 16 us +
-// 18 us, where one kernel per stage (radix select over the row, MRS, commit) took 124 + 64 + 5 us.
+// slice kernel and the candidate path like the others.  32 rows of 131072 ids under top-k 2000: 11 us +
+// 15 us, where one kernel per stage (radix select over the row, MRS, commit) took 124 + 64 + 5 us.
 // Their complete path (long_path) makes whole passes over the row in memory.
 // Logits supplied by the caller (a.src) are copied into the ring by whichever kernel reads them first; a
 // copy kernel of its own took 66 us for 32 rows of 65536 ids (32 workgroups, 4-byte accesses), more than
@@ -44,7 +45,7 @@
 //
 // This file is compiled twice.  The second time (row_batched.hip defines
 // SCD_ROW_BATCHED) with 512 threads per row and rows of at most 8192 ids: such a
-// workgroup takes 122 registers per lane and 64 KB of LDS, so two of them share a
+// workgroup takes up to 118 registers per lane and 51 KB of LDS, so two of them share a
 // CU, and when there are more rows than CUs the barrier-separated phases of one
 // row overlap with another's instead of the rows queueing in rounds.  With few
 // rows the 1024-thread form is faster (half the work per lane).
@@ -1189,8 +1190,8 @@ __device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& 
 // thread, until the threshold is known and the kept ids are parked in LDS.
 //   Bound by the vector instructions of one CU per row, about 30 per id for the masses (an exponential, a conversion to
 // fixed point and a 64-bit LDS addition each): 28000 of 88000 cycles.  Against a row read from memory three times and
-// scanned three more through 16-bit prefixes in LDS, four steps on supplied logits of 32 x 65536 take 197 us for 228,
-// of 2 x 64 x 64000 ids behind the LM head 659 for 690, of 8 x 32 x 65536 without guidance 766 for 970.
+// scanned three more through 16-bit prefixes in LDS, four steps on supplied logits of 32 x 65536 take 198 us for 228,
+// of 2 x 64 x 64000 ids behind the LM head 678 for 705, of 8 x 32 x 65536 over 2048 without guidance 680 for 776.
 // Up to 18432 kept ids are parked (what LDS holds); rows that keep more are read again, which is the better way for them.
 constexpr int kNucleusCap = 1152;            // kept ids that a wavefront parks ...
 constexpr int kNucleusPark = kNucleusCap + kWave;   // ... and a place per lane for what is not kept
@@ -1387,8 +1388,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   // pass 1: batches of 8 independent 16-byte loads per thread
   const int ngroups8 = n8 >> 2;
   // (the range is taken on the floats, two instructions a logit, and turned into keys at the end; rows of odd
-  // length are read with 16-byte loads as well: 32 rows of 30001 ids under nucleus 0.8 88 -> 39 us an iteration,
-  // of 8191 ids under top-k 27 -> 18)
+  // length are read with 16-byte loads as well)
   float hi = -INFINITY, lo = INFINITY;
   bool nan = false;
   constexpr int UNR = 8;

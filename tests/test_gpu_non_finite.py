@@ -18,7 +18,7 @@ ROWS = [
     (1, 6, 30001, 1500, 0.0),      # slices and lists
     (1, 6, 65536, 2000, 0.8),
     (1, 6, 30001, 0, 0.0),         # in place
-    (1, 6, 30004, 0, 0.8),
+    (1, 6, 30004, 0, 0.8),         # in registers until the threshold is known
     (1, 6, 40000, 4000, 0.0),      # in place: too many for the lists
     (1, 6, 70001, 1500, 0.0),      # longer rows: lists, whole passes
     (1, 6, 70002, 0, 0.0),

@@ -176,7 +176,7 @@ def test_select_nucleus_against_oracle(n, top_k, top_p):
     (1, 32, 8192, 2000, 2304, [100], 0.0),
     (3, 5, 37, 7, 50, [0, 45, 49], 0.0),       # tiny vocabulary, windows of 5 / 5 / 1 rows
     (2, 16, 4096, 500, 100, [0, 90], 0.7),     # nucleus filter after top-k
-    (1, 24, 20000, 0, 64, [5], 0.9),           # nucleus filter alone on a long row (in-place path)
+    (1, 24, 20000, 0, 64, [5], 0.9),           # nucleus filter alone on a long row (in registers)
     # rows longer than 65536 ids: the row kernel's LONG instance
     (2, 6, 70000, 500, 40, [0, 37], 0.0),      # second window clipped to 3 rows
     (1, 5, 131072, 2000, 64, [9], 0.0),
@@ -317,7 +317,7 @@ def test_lockstep_scaled_cfg_temperature():
 @pytest.mark.parametrize("kw", [
     dict(N=40, L=8, seed=30, V=1000, top_p=0.8),                   # 8 logits per thread, no top-k
     dict(N=40, L=8, seed=31, V=12000, top_k=3000, top_p=0.9, age_cap=4),   # 16 per thread, after top-k
-    dict(N=12, L=4, seed=32, V=65536, top_p=0.8, age_cap=4),       # in-place path
+    dict(N=12, L=4, seed=32, V=65536, top_p=0.8, age_cap=4),       # long rows in registers
     dict(N=12, L=4, seed=33, V=40000, top_k=2000, top_p=0.5, age_cap=4),   # slice kernel + candidates
     dict(N=30, L=8, seed=34, V=2000, top_p=0.999),                 # nearly everything kept
     dict(N=30, L=8, seed=35, V=2000, top_p=0.001, B=2),            # the mode alone

@@ -16,7 +16,7 @@ DEV = "cuda:0"
     (1, 7, 40, 16383, 0, 0.0, 3),        # 16 logits per thread
     (2, 5, 12, 16385, 300, 0.0, 0),      # slice kernel; the window is clipped at the end
     (1, 6, 40, 65536, 2000, 0.0, 1),
-    (1, 6, 40, 30003, 0, 0.8, 0),        # whole row in place
+    (1, 6, 40, 30003, 0, 0.8, 0),        # whole row, in registers until the threshold is known
     (1, 6, 40, 30003, 4000, 0.0, 2),
     (1, 4, 40, 65537, 500, 0.0, 0),      # longer rows: with lists and without
     (1, 4, 40, 70002, 0, 0.0, 1),
