@@ -154,6 +154,24 @@ __device__ __forceinline__ float processed_logit(const LmHeadArgs& a, float c, f
   if (C == 2) z = __fsub_rn(__fmul_rn(a.one_plus_lam, c), __fmul_rn(a.lam, u));
   return a.tau == 1.0f ? z : __fdiv_rn(z, a.tau);
 }
+// A logit on its way to the ring.  THROUGH: written through the L2.  Every kernel stores its logits at its end; left in the
+// L2 they are written back when others need the room, or all together behind the last workgroup.  Where W is streamed past
+// the caches in several rounds of workgroups that costs most: four steps of one sequence x 32 x 131072 ids over 4096
+// 777 -> 743 us, 32 x 101632 over 2048 alone 81 -> 74.5; of 32 x 16384 over 1280 (split kernel) 97.7 -> 96.9; no gain in the
+// other kernels (sixteen x 32 x 8192 from 316 -> 311 to 328 -> 329).  Only where the 32 columns that a half wavefront
+// stores are whole 128-byte lines (through_lines): lines written in two parts cost more than they save (60 rows x 51285
+// ids over 2048 42.1 -> 43.5).  Nor where tile_candidates stores 16 bytes per lane (65536 ids 397 -> 399).
+template <bool THROUGH>
+__device__ __forceinline__ void store_logit(float* p, float z) {
+  if constexpr (THROUGH) __hip_atomic_store(p, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = z;
+}
+__device__ __forceinline__ bool through_lines(const LmHeadArgs& a) { return (a.n & 31) == 0; }
+template <class F>
+__device__ __forceinline__ void with_bool(bool b, F&& f) {
+  if (b) f(TrueT{});
+  else f(FalseT{});
+}
 // Epilogue of a wavefront that holds whole sums.  Element j of lane (ln, lg) is row
 // (j/4)*8 + lg*4 + j%4, column ln of the 32x32 tile.  zout takes the processed logits.
 // table: row_dest of the workgroup's RBW * 32 window rows.  v: this lane's column, `there` if it exists.
@@ -1005,24 +1023,26 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
   __syncthreads();
   // element j of a block: window row 8 * (j / 4) + 4 * lg + j % 4 of its 32, column ln
   if (a.cand == nullptr) {                           // uniform
+    with_bool(NT && through_lines(a), [&](auto through) {
 #pragma unroll
-    for (int r = 0; r < K::RB; ++r) {
-      int4 to[4];
+      for (int r = 0; r < K::RB; ++r) {
+        int4 to[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[(wr * K::RB + r) * 32 + g * 8 + lg * 4]);
-      const int v = wc * K::CW + ln;                  // column of the tile
+        for (int g = 0; g < 4; ++g) to[g] = *reinterpret_cast<const int4*>(&table[(wr * K::RB + r) * 32 + g * 8 + lg * 4]);
+        const int v = wc * K::CW + ln;                // column of the tile
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int4 t = to[j >> 2];
-        const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
-        float* const zr = a.z + (static_cast<int64_t>(row) * a.n + vt * BN + v);
+        for (int j = 0; j < 16; ++j) {
+          const int4 t = to[j >> 2];
+          const int row = (j & 3) == 0 ? t.x : (j & 3) == 1 ? t.y : (j & 3) == 2 ? t.z : t.w;
+          float* const zr = a.z + (static_cast<int64_t>(row) * a.n + vt * BN + v);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const float z = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
-          if (row >= 0 && v + c * 32 < v_left) zr[c * 32] = z;
+          for (int c = 0; c < NC; ++c) {
+            const float z = processed_logit<C>(a, acc[c][r * C][j], acc[c][r * C + C - 1][j]);
+            if (row >= 0 && v + c * 32 < v_left) store_logit<decltype(through)::value>(&zr[c * 32], z);
+          }
         }
       }
-    }
+    });
     return;
   }
   // the processed logits replace the cond sums; tile_candidates stores them from the tile in LDS, 16 bytes per lane
@@ -1221,22 +1241,25 @@ __global__ __launch_bounds__((SplitCfg<RBW, C, KS>::THREADS)) void lm_head_split
   // accumulator elements j = w, w + NWAVE, ... of every tile
   const int v = mapped_row(rm, xcd, jt, 32, ln);
   if (v >= a.n) return;
+  with_bool(through_lines(a), [&](auto through) {
 #pragma unroll
-  for (int rbw = 0; rbw < RBW; ++rbw) {
+    for (int rbw = 0; rbw < RBW; ++rbw) {
 #pragma unroll
-    for (int jj = 0; jj < 16 / NWAVE; ++jj) {
-      const int j = wave + jj * NWAVE;
-      const int row = table[rbw * 32 + (j >> 2) * 8 + lg * 4 + (j & 3)];
-      float c = red[((0 * NBLK + rbw * C) * 16 + j) * 64 + lane];
-      float u = red[((0 * NBLK + rbw * C + C - 1) * 16 + j) * 64 + lane];
+      for (int jj = 0; jj < 16 / NWAVE; ++jj) {
+        const int j = wave + jj * NWAVE;
+        const int row = table[rbw * 32 + (j >> 2) * 8 + lg * 4 + (j & 3)];
+        float c = red[((0 * NBLK + rbw * C) * 16 + j) * 64 + lane];
+        float u = red[((0 * NBLK + rbw * C + C - 1) * 16 + j) * 64 + lane];
 #pragma unroll
-      for (int w = 1; w < NWAVE; ++w) {
-        c += red[((w * NBLK + rbw * C) * 16 + j) * 64 + lane];
-        u += red[((w * NBLK + rbw * C + C - 1) * 16 + j) * 64 + lane];
+        for (int w = 1; w < NWAVE; ++w) {
+          c += red[((w * NBLK + rbw * C) * 16 + j) * 64 + lane];
+          u += red[((w * NBLK + rbw * C + C - 1) * 16 + j) * 64 + lane];
+        }
+        if (row >= 0)
+          store_logit<decltype(through)::value>(&a.z[static_cast<int64_t>(row) * a.n + v], processed_logit<C>(a, c, u));
       }
-      if (row >= 0) a.z[static_cast<int64_t>(row) * a.n + v] = processed_logit<C>(a, c, u);
     }
-  }
+  });
 }
 
 // Row map for these operands and the number of workgroup tiles per XCD it needs.
