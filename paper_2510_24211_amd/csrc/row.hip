@@ -43,12 +43,15 @@
 // floating-point sums use a fixed assignment of ids to threads and a fixed
 // reduction tree, so results are run-to-run identical.
 //
-// This file is compiled twice.  The second time (row_batched.hip defines
-// SCD_ROW_BATCHED) with 512 threads per row and rows of at most 8192 ids: such a
-// workgroup takes up to 118 registers per lane and 51 KB of LDS, so two of them share a
-// CU, and when there are more rows than CUs the barrier-separated phases of one
-// row overlap with another's instead of the rows queueing in rounds.  With few
-// rows the 1024-thread form is faster (half the work per lane).
+// This file is compiled three times: 1024 threads per row; 512 (row_batched.hip defines SCD_ROW_BATCHED) for rows of at
+// most 8192 ids; 256 (row_short.hip defines SCD_ROW_SHORT) for rows of at most 1024.  What a row does once (range, sums,
+// accept test, winners) every wavefront of it does, at 16 cycles an instruction when four share a SIMD: short rows spend
+// most of their time on that, so they take few wavefronts.  Long rows want all the lanes.  Four steps on supplied logits
+// (us, 1024 / 512 / 256 threads): 8 x 1024 ids 38.2 / 34.0 / 31.8; 32 x 2048 42.4 / 34.4 / 40.7, under top-k 500
+// 45.2 / 35.3 / 39.7, with all options 68.9 / 53.4 / 61.9; 32 x 4096 40.8 / 42.7, under top-k 40.0 / 39.2, with all
+// options 65.5 / 63.0; 32 x 8192 behind the LM head 107.4 / 111.4.
+//   More rows than CUs: a workgroup of 512 threads takes up to 118 registers per lane and 51 KB of LDS, so two of them
+// share a CU and the barrier-separated phases of one row overlap with another's instead of the rows queueing in rounds.
 #include "scd_device.h"
 #include "scd_kernels.h"
 
@@ -62,9 +65,19 @@
 #define slice_kernel slice_kernel_batched
 #define LAUNCH_ROW launch_row_batched
 #define SCD_ROW_WAVES(EXTRA) ((EXTRA) ? 2 : 4)   // wavefronts per SIMD: two workgroups per CU
+#elif defined(SCD_ROW_SHORT)
+#define SCD_ROW_THREADS 256
+#define SCD_ROW_DIRECT_MAX 4096              // (only the quarter of that is used)
+#define row_kernel row_kernel_short
+#define slice_kernel slice_kernel_short
+#define LAUNCH_ROW launch_row_short
+#define SCD_ROW_WAVES(EXTRA) ((EXTRA) ? 2 : 4)
 #else
 #define LAUNCH_ROW launch_row
 #define SCD_ROW_WAVES(EXTRA) 4
+#endif
+#if defined(SCD_ROW_BATCHED) || defined(SCD_ROW_SHORT)
+#define SCD_ROW_DIRECT_ONLY                  // whole rows in registers
 #endif
 
 namespace scd {
@@ -357,7 +370,6 @@ __device__ __forceinline__ uint32_t select_regs(const float (&zv)[PER], const bo
 // mh: NBINS_P 64-bit bins (the space of the count histogram).  Uniform over the workgroup.
 constexpr int NBINS_P = NBINS / 2;
 static_assert(NBINS_P % THREADS == 0 || THREADS % NBINS_P == 0, "nucleus: bins per thread");
-static_assert(THREADS >= 512, "nucleus: a member per thread");
 
 // Both words of trunc(e^(z - m) 2^40), at most 2^40: multiplications by powers of two and the subtraction are exact,
 // so this is the conversion to 64 bits in 6 instructions (the general one takes twice as many).  NaN: 0.
@@ -474,7 +486,7 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
   uint32_t* const mk = reinterpret_cast<uint32_t*>(over + kFew);
   static_assert(NBINS_P * 8 >= kFew * 20, "members' masses, sums and keys in the histogram's space");
   __syncthreads();                                  // the cursor may still be read by prepare()'s users
-  if (static_cast<uint32_t>(tid) < kFew) over[tid] = 0ull;
+  for (uint32_t i = tid; i < kFew; i += THREADS) over[i] = 0ull;
   if (tid == 0) {
     sm.cursor = 0u;
     sm.sel_bin = 0xFFFFFFFFu;
@@ -499,7 +511,8 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
       if (sum != 0ull) atomicAdd(&over[a], sum);
     }
     __syncthreads();
-    if (static_cast<uint32_t>(tid) < members && above + over[tid] < target) atomicMin(&sm.sel_bin, mk[tid]);
+    for (uint32_t i = tid; i < members; i += THREADS)
+      if (above + over[i] < target) atomicMin(&sm.sel_bin, mk[i]);
     __syncthreads();
     const uint32_t key = sm.sel_bin;
     __syncthreads();                                // the next user of the space or of sel_bin
@@ -1923,7 +1936,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
 // with all of them in one kernel the compiler keeps every way's arguments in scalar registers and spills them
 // (184 spills; 46 vector registers spilled in the optional instances).  Four-step decodes over 8192 ids: 132 ->
 // 129 us, with every option 206 -> 193 us.
-enum Path { kDirectHalf, kDirectWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
+enum Path { kDirectQuarter, kDirectHalf, kDirectWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
 template <bool GS, bool EXTRA, int PATH>
 __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
                                                       const int mode_, const int L_, const int N_,
@@ -1956,9 +1969,9 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(cons
   out.accept = true;
   bool done = false;
   [[maybe_unused]] float zcx = 0.f, zpx = 0.f;
-  if constexpr (PATH == kDirectHalf || PATH == kDirectWhole) {
+  if constexpr (PATH == kDirectQuarter || PATH == kDirectHalf || PATH == kDirectWhole) {
     // ---- the whole row in registers ------------------------------------------------
-    direct_path<PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, sm, out);
+    direct_path<PATH == kDirectQuarter ? PER_DIRECT / 4 : PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, sm, out);
     done = true;
   } else if constexpr (PATH == kNucleusHalf || PATH == kNucleusWhole) {
     nucleus_path<PATH == kNucleusHalf ? 32 : 64, GS>(a, R, smem, sm, out);
@@ -2213,9 +2226,11 @@ size_t lds_bytes_for(int n) {
   return std::max(lists, static_cast<size_t>((n + 7) & ~7) * 2 + NBINS * sizeof(uint32_t) + kListCap * sizeof(uint16_t));
 }
 
+#ifndef SCD_ROW_DIRECT_ONLY
 constexpr size_t kNucleusLds = static_cast<size_t>(NW) * kNucleusPark * 8;      // the histogram of masses lies under it
 static_assert(kNucleusLds >= NBINS_P * 8 + kListCap * 4 && kNucleusLds + sizeof(Small) <= 160 * 1024, "nucleus_path: LDS");
 static_assert(64 * 1024 >= kRowKernelMaxN, "nucleus_path: a row in registers");
+#endif
 
 inline size_t small_block(int rows) {
   return (static_cast<size_t>(rows) * kRowMaxTiles * 4 + 255) / 256 * 256;
@@ -2223,7 +2238,7 @@ inline size_t small_block(int rows) {
 
 }  // namespace
 
-#ifndef SCD_ROW_BATCHED
+#ifndef SCD_ROW_DIRECT_ONLY
 size_t row_candidate_bytes(int rows) {
   // per row: kListCap (id, logit) pairs, kRowMaxTiles list counts, kRowMaxTiles list cuts
   return static_cast<size_t>(rows) * kListCap * sizeof(uint2) + 2 * small_block(rows);
@@ -2244,16 +2259,20 @@ bool row_uses_candidates(int n, int top_k) {
   return n > kRowDirectMaxN && n <= kRowMaxTiles * kSliceMax && filter && top_k <= kListCap / 2;
 }
 
-#endif  // !SCD_ROW_BATCHED
+#endif  // !SCD_ROW_DIRECT_ONLY
 
 hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured) {
   if (a_in.rows <= 0) return hipSuccess;
-#ifdef SCD_ROW_BATCHED
-  if (a_in.n > kDirectMaxN) return hipErrorInvalidValue;     // this build holds whole rows in registers only
+#ifdef SCD_ROW_DIRECT_ONLY
+  if (a_in.n > kDirectMaxN) return hipErrorInvalidValue;     // these builds hold whole rows in registers only
 #else
-  // more rows than compute units (256 on this chip), short rows, the hot instances: the build
+  // short rows: few wavefronts (figures at the head of this file)
+  if (a_in.n <= kRowShortMaxN && a_in.L <= kRowShortMaxL)
+    return launch_row_short(a_in, s, lds_configured ? lds_configured + 2 : nullptr);
+  // more rows than compute units (256 on this chip), longer ones, the hot instances: the build
   // of this file whose workgroups pair up on a CU
-  if (a_in.rows > 256 && a_in.n <= kRowBatchedMaxN && a_in.top_p24 == 0u && a_in.diag == nullptr)
+  if (a_in.n <= kRowBatchedMaxN / 2 ||
+      (a_in.rows > 256 && a_in.n <= kRowBatchedMaxN && a_in.top_p24 == 0u && a_in.diag == nullptr))
     return launch_row_batched(a_in, s, lds_configured ? lds_configured + 1 : nullptr);
 #endif
   RowArgs a = a_in;
@@ -2280,18 +2299,29 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
   }
+#ifdef SCD_ROW_DIRECT_ONLY
+  const size_t lds = lds_bytes_for(a.n), most = lds_bytes_for(kDirectMaxN);
+#else
   const bool nucleus = a.n > kDirectMaxN && a.n <= kRowKernelMaxN && a.top_p24 != 0u && !(a.top_k > 0 && a.top_k < a.n);
   const size_t lds = nucleus ? kNucleusLds : lds_bytes_for(a.n);
+  const size_t most = std::max({lds_bytes_for(kRowKernelMaxN), lds_bytes_for(kDirectMaxN), kNucleusLds});
+#endif
   const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
   const bool extra = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
   using Kernel = void (*)(const int32_t*, const int32_t*, int, int, int, int, int, RowArgs);
 #define SCD_ROW_INSTANCES(PATH) \
   {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
-  static const Kernel kernels[][4] = {SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
-#ifndef SCD_ROW_BATCHED
-                                      SCD_ROW_INSTANCES(kLists), {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
-                                      {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
-                                      {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
+  static const Kernel kernels[][4] = {
+#if defined(SCD_ROW_SHORT)
+      SCD_ROW_INSTANCES(kDirectQuarter)
+#elif defined(SCD_ROW_BATCHED)
+      SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
+      {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr}
+#else
+      {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole), SCD_ROW_INSTANCES(kLists),
+      {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
+      {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
+      {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
 #endif
   };
 #undef SCD_ROW_INSTANCES
@@ -2301,7 +2331,6 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   size_t none = 0;
   size_t& configured = lds_configured ? *lds_configured : none;
   if (configured == 0) {
-    const size_t most = std::max({lds_bytes_for(kRowKernelMaxN), lds_bytes_for(kDirectMaxN), kNucleusLds});
     for (const auto& row : kernels)
       for (Kernel f : row)
         if (f)
@@ -2311,8 +2340,12 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
             return e;
     configured = most;
   }
+#ifdef SCD_ROW_DIRECT_ONLY
+  const int path = a.n <= kDirectMaxN / 4 ? kDirectQuarter : a.n <= kDirectMaxN / 2 ? kDirectHalf : kDirectWhole;
+#else
   const int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
                    : nucleus ? (a.n <= 32 * THREADS ? kNucleusHalf : kNucleusWhole) : a.n <= kRowKernelMaxN ? kLists : kLong;
+#endif
   const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
   if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
   a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;

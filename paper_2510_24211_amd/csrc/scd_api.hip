@@ -133,7 +133,7 @@ struct scd_ctx {
   int n;   // allowed ids
   int C;   // LM-head rows per window position
   hipEvent_t ev_start, ev_stop;   // optional instrumentation around the LM-head kernel
-  size_t row_lds[2];              // dynamic-LDS limit already set for the row kernels (launch_row, both builds)
+  size_t row_lds[3];              // dynamic-LDS limit already set for the row kernels (launch_row, its three builds)
 };
 
 namespace {
@@ -228,7 +228,7 @@ int scd_create(scd_ctx** out, const scd_config* cfg, void* d_workspace, size_t w
   c->C = cfg->cfg_lambda != 0.f ? 2 : 1;
   c->ev_start = nullptr;
   c->ev_stop = nullptr;
-  c->row_lds[0] = c->row_lds[1] = 0;
+  c->row_lds[0] = c->row_lds[1] = c->row_lds[2] = 0;
   // Set-up for scd_couple_draft_static: look the scratch address of the current device up now,
   // outside any stream capture.  Best effort (a host without a GPU can still create a context to
   // query layouts); the entry point repeats the lookup if it is still missing.

@@ -202,14 +202,14 @@ __device__ __forceinline__ int wave_sum_i32(int v) {
 }
 
 // ---- folds over the wavefronts of a workgroup ----------------------------------------------
-// Of W = 8 or 16 entries in LDS, one per wavefront, every lane reads one (lane modulo W) and the lanes of a
+// Of W = 4, 8 or 16 entries in LDS, one per wavefront, every lane reads one (lane modulo W) and the lanes of a
 // row exchange them: ten instructions, where reading all of them in every lane takes three per entry, in
 // every wavefront (a row kernel has about eight such folds; with them, the DPP-only reductions above and the
 // shorter selection, four steps on supplied logits of 32 x 65536 take 96 us instead of 111).  The caller's
 // barrier stands between the writes and these.
 template <int W>
 __device__ __forceinline__ int fold_entry() {
-  static_assert(W == 8 || W == 16, "wavefronts");
+  static_assert(W == 4 || W == 8 || W == 16, "wavefronts");
   return threadIdx.x & (W - 1);
 }
 __device__ __forceinline__ int wave_index() {        // as a scalar
@@ -221,7 +221,7 @@ __device__ __forceinline__ int fold_before(const int* ex, int wave, int& total) 
   int v = ex[fold_entry<W>()];
   v += dpp_i32<kDppRowShr + 1>(v);
   v += dpp_i32<kDppRowShr + 2>(v);
-  v += dpp_i32<kDppRowShr + 4>(v);
+  if constexpr (W >= 8) v += dpp_i32<kDppRowShr + 4>(v);
   if constexpr (W == 16) v += dpp_i32<kDppRowShr + 8>(v);
   total = __builtin_amdgcn_readlane(v, W - 1);
   return wave > 0 ? __builtin_amdgcn_readlane(v, wave > 0 ? wave - 1 : 0) : 0;
@@ -232,7 +232,7 @@ __device__ __forceinline__ uint32_t fold_max(const uint32_t* ex) {
   uint32_t v = ex[fold_entry<W>()];
   v = mx(v, dpp_u32<kDppXor1>(v));
   v = mx(v, dpp_u32<kDppXor2>(v));
-  v = mx(v, dpp_u32<kDppHalfMirror>(v));
+  if constexpr (W >= 8) v = mx(v, dpp_u32<kDppHalfMirror>(v));
   if constexpr (W == 16) v = mx(v, dpp_u32<kDppMirror>(v));
   return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
 }
@@ -241,7 +241,7 @@ __device__ __forceinline__ float fold_sum(const float* ex) {       // a fixed tr
   float v = ex[fold_entry<W>()];
   v += dpp_f32<kDppXor1>(v);
   v += dpp_f32<kDppXor2>(v);
-  v += dpp_f32<kDppHalfMirror>(v);
+  if constexpr (W >= 8) v += dpp_f32<kDppHalfMirror>(v);
   if constexpr (W == 16) v += dpp_f32<kDppMirror>(v);
   return readlane_f32(v, 0);
 }
