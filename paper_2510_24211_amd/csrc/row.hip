@@ -118,7 +118,7 @@ struct Small {
   uint32_t members[64];   // ... and what it appends
   float u_accept;         // the accept test's uniform
   int ired2[NW];          // second slot of block_offsets
-  uint2 win[2][NW];       // per-wavefront winners of the two races: (bits of the score, id)
+  unsigned long long win[2];   // winners of the two races: bits of the score, then the id
   int last;
   unsigned long long mtot[NW];   // nucleus: per-wavefront masses
   unsigned long long sel_mass;
@@ -544,12 +544,20 @@ struct RowRef {
   const float* zp;
   float* zw;      // supplied logits: the ring row that takes a copy of zc, else null
   float thr_p, lse_p;
-  bool fresh, active;
+  bool active;
+  int age;        // earlier evaluations of the position (kept as it is read: a comparison would wait for it on the spot)
+  __device__ __forceinline__ bool fresh() const { return age == 0; }
   int x, b, s, p0, live, it;
+  int first_slot; // ring slot of the window's first position
   size_t widx, oidx, sidx;
   size_t pidx;    // where the previous evaluation of the slot left its per-slot results (ring mode)
 };
 
+// v / L: by the reciprocal where launch_row has found that to be exact for every v that occurs (a division is about thirty
+// instructions, in every wavefront).
+__device__ __forceinline__ int div_window(int v, int L, uint32_t recip) {
+  return recip != 0u ? static_cast<int>(__umulhi(static_cast<uint32_t>(v), recip)) : v / L;
+}
 // pos, iter, mode, L, N repeat a.pos, a.iter, mode, L, N: the kernels receive them as plain
 // leading arguments, which the hardware preloads into SGPRs at wavefront launch, so that the first
 // dependent load (pos[b]) does not wait for a fetch of the kernel-argument segment.
@@ -566,8 +574,8 @@ __device__ __forceinline__ RowRef locate_row(const RowArgs& a, int r, const int3
     R.zc = a.z_cur + static_cast<size_t>(r) * n;
     return R;
   }
-  R.b = r / L;
-  R.s = r % L;
+  R.b = div_window(r, L, a.recip_L);
+  R.s = r - R.b * L;
   R.p0 = pos[R.b];
   R.live = max(0, min(L, N - R.p0));
   R.widx = static_cast<size_t>(R.b) * L + R.s;
@@ -577,8 +585,11 @@ __device__ __forceinline__ RowRef locate_row(const RowArgs& a, int r, const int3
   }
   if (mode == kRowRing) {
     R.it = iter[R.b];
+    R.first_slot = R.p0 - div_window(R.p0, L, a.recip_L) * L;
+    int slot = R.first_slot + R.s;
+    if (slot >= L) slot -= L;
     const int par = R.it & 1;
-    const size_t sidx = static_cast<size_t>(R.b) * L + (R.p0 + R.s) % L;
+    const size_t sidx = static_cast<size_t>(R.b) * L + slot;
     const size_t half = static_cast<size_t>(a.B) * L;
     R.oidx = par * half + sidx;
     R.pidx = (par ^ 1) * half + sidx;
@@ -594,21 +605,64 @@ __device__ __forceinline__ RowRef locate_row(const RowArgs& a, int r, const int3
   }
   return R;
 }
+// One word of a uniform address through the scalar cache, which nothing of this launch has written before (a row's words are
+// read before its sequence's commit, at the earliest behind all of them, rewrites them).  As vector loads the row's words
+// would come back behind its logits, and the draft's logits, whose addresses they give, be asked for a round trip later
+// (those four steps: 93.1 us for 94.4, 103.5 for 104.6).
+template <class T>
+__device__ __forceinline__ T scalar_word(const T* p) {
+  static_assert(sizeof(T) == 4, "a word");
+  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
 // The rest, for the caller to read once the row's logits are on their way: draft, whether its position is new,
 // what the slot's previous evaluation left (memory that exists and holds nothing useful for a new one; read
 // without waiting for the answer).  Before the loads of the logits this is a round trip of its own.
 __device__ __forceinline__ void read_row_scalars(const RowArgs& a, RowRef& R) {
   if (a.mode == kRowSelectOnly) return;
   if (a.mode == kRowRing) {
-    R.x = a.x[R.sidx];
-    R.fresh = a.age[R.sidx] == 0;
-    R.thr_p = a.thr[R.pidx];
-    R.lse_p = a.lse[R.pidx];
+    R.x = scalar_word(a.x + R.sidx);
+    R.age = scalar_word(a.age + R.sidx);
+    R.thr_p = scalar_word(a.thr + R.pidx);
+    R.lse_p = scalar_word(a.lse + R.pidx);
   } else {
-    R.x = a.x[R.widx];
-    R.fresh = a.fresh ? a.fresh[R.widx] != 0 : false;
-    R.thr_p = a.thr_prev[R.widx];
-    R.lse_p = a.lse_prev[R.widx];
+    R.age = a.fresh && a.fresh[R.widx] != 0 ? 0 : 1;
+    R.x = scalar_word(a.x + R.widx);
+    R.thr_p = scalar_word(a.thr_prev + R.widx);
+    R.lse_p = scalar_word(a.lse_prev + R.widx);
+  }
+}
+
+// Groups of four neighbouring logits of a row of `end` ids, those at group(0), group(1), ..., all requested before one is
+// waited for.  A group that is not whole reads the row's last four and is shifted into place afterwards (load4 needs no
+// alignment); what lies past the end holds any logit of the row.  No lane leaves the line meanwhile: with element-wise
+// loads in a branch for the ragged group, the compiler waited for every group before it requested the next (their
+// registers may be in flight from either side of the branch).  Without, four steps of 32 x 16384 ids over 1280 take 94.4 us
+// for 96.5, of 32 x 8192 over 4096 104.6 for 107.1.
+// TINY: rows of less than four ids.
+template <int PER, bool TINY = false, class Group>
+__device__ __forceinline__ void load_groups(const float* row, int end, Group&& group, float (&z)[PER]) {
+#pragma unroll
+  for (int u = 0; u < PER / 4; ++u) {
+    if constexpr (TINY) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[u * 4 + e] = row[min(group(u) + e, end - 1)];
+    } else {
+      const float4 t = load4(row + min(group(u), end - 4));
+      z[u * 4 + 0] = t.x; z[u * 4 + 1] = t.y; z[u * 4 + 2] = t.z; z[u * 4 + 3] = t.w;
+    }
+  }
+}
+// The shift, once the logits are wanted: rows of a multiple of four ids have no such group.
+template <int PER, class Group>
+__device__ __forceinline__ void align_groups(int end, Group&& group, float (&z)[PER]) {
+  if ((end & 3) == 0) return;                  // uniform
+#pragma unroll
+  for (int u = 0; u < PER / 4; ++u) {
+    const int by = group(u) - (end - 4);       // 1 .. 3: that many of the four are the group's predecessors
+    const float t1 = z[u * 4 + 1], t2 = z[u * 4 + 2], t3 = z[u * 4 + 3];
+    z[u * 4] = by == 1 ? t1 : by == 2 ? t2 : by == 3 ? t3 : z[u * 4];
+    z[u * 4 + 1] = by == 1 ? t2 : by == 2 ? t3 : t1;
+    z[u * 4 + 2] = by == 1 ? t3 : t2;
   }
 }
 
@@ -645,16 +699,12 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
   float zv[PS];
   int vid[PS];
   bool ok[PS];
+  auto group = [&](int u) { return lo_id + ((tid + u * ST) << 2); };
+  load_groups<PS>(R.zc, hi_id, group, zv);     // (rows that have slices are long: hi_id > 4)
+  align_groups<PS>(hi_id, group, zv);
 #pragma unroll
   for (int u = 0; u < PS / 4; ++u) {
-    const int v0 = lo_id + ((tid + u * ST) << 2);
-    if (v0 + 3 < hi_id) {
-      const float4 t = load4(R.zc + v0);
-      zv[u * 4 + 0] = t.x; zv[u * 4 + 1] = t.y; zv[u * 4 + 2] = t.z; zv[u * 4 + 3] = t.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) zv[u * 4 + e] = (v0 + e < hi_id) ? R.zc[v0 + e] : 0.f;
-    }
+    const int v0 = group(u);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       vid[u * 4 + e] = v0 + e;
@@ -728,7 +778,7 @@ __device__ __forceinline__ void row_statistics_out(const RowArgs& a, const RowRe
       s1 += sm.dred[1][w];
       s2 += sm.dred[2][w];
     }
-    const float s2q = R.fresh ? q_uniform : a.s2[R.pidx];
+    const float s2q = R.fresh() ? q_uniform : a.s2[R.pidx];
     *reinterpret_cast<float4*>(a.diag + R.widx * 4) = make_float4(s0, s1, s2, s2q);
     a.s2[R.oidx] = s2;
   }
@@ -820,7 +870,7 @@ __device__ __forceinline__ void finish_kept(const RowArgs& a, const RowRef& R, u
   // the previous logits of the first kAhead lanes' worth of kept ids are requested now, of any more when needed
   constexpr int kAhead = 3;
   float qa[kAhead];
-  const bool gather = !PREQ && a.mode != kRowSelectOnly && !R.fresh;
+  const bool gather = !PREQ && a.mode != kRowSelectOnly && !R.fresh();
   if (gather) {
 #pragma unroll
     for (int s = 0; s < kAhead; ++s) qa[s] = R.zp[s * kWave + lane < cnt ? kid[s * kWave + lane] : 0u];
@@ -882,18 +932,18 @@ __device__ __forceinline__ void finish_kept(const RowArgs& a, const RowRef& R, u
 
   // Modified Rejection Sampling
   const int j = R.p0 + R.s;
-  const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
+  const float q_uniform = a.q_uniform;
   const uint2 key = seed_key(a.seed);
   const uint32_t w3 = static_cast<uint32_t>(R.b) << 8;
   const bool x_ok = R.x >= 0 && R.x < n;
   out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
-  out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
+  out.qx = R.fresh() ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
   out.accept = __fmul_rn(sm.u_accept, out.qx) <= out.px;
   out.best = INFINITY;
   out.best_id = 0x7FFFFFFF;
   out.gbest = INFINITY;
   out.gbest_id = 0x7FFFFFFF;
-  auto q_of = [&](float z) { return R.fresh ? q_uniform : prob(z, R.thr_p, R.lse_p); };
+  auto q_of = [&](float z) { return R.fresh() ? q_uniform : prob(z, R.thr_p, R.lse_p); };
   if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
     float d0 = 0.f, d1 = 0.f, d2 = 0.f;
     each_kept([&](bool valid, int, float zc_v, float zq_v) {
@@ -1030,7 +1080,7 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
 __device__ __forceinline__ void draft_logits(const RowArgs& a, const RowRef& R, float& zcx, float& zpx) {
   const bool x_ok = a.mode != kRowSelectOnly && R.x >= 0 && R.x < a.n;
   zcx = x_ok ? R.zc[R.x] : 0.f;
-  zpx = (x_ok && !R.fresh) ? R.zp[R.x] : 0.f;
+  zpx = x_ok ? R.zp[R.x] : 0.f;              // (of a new position: never used)
 }
 
 // f(v0, z) for every four neighbouring ids v0 .. v0 + 3 of a row, -inf past its end, read in coalesced 32-byte pieces,
@@ -1109,12 +1159,12 @@ __device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& 
   }
   if (a.mode == kRowSelectOnly) return;
   const int j = R.p0 + R.s;
-  const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
+  const float q_uniform = a.q_uniform;
   const uint2 key = seed_key(a.seed);
   const uint32_t w3 = static_cast<uint32_t>(R.b) << 8;
   const bool x_ok = R.x >= 0 && R.x < n;
   out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
-  out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
+  out.qx = R.fresh() ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
   const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(j), static_cast<uint32_t>(R.it),
                                             w3 | kStreamAccept), key);
   out.accept = __fmul_rn(u01(ra.x), out.qx) <= out.px;
@@ -1127,7 +1177,7 @@ __device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& 
     for_each_logit([&](int v, float z) {
       const float pv = prob(z, thr, lse_c);
       if (pv > 0.f) {
-        const float qv = R.fresh ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
+        const float qv = R.fresh() ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
         d0 += fminf(pv, qv);
         d1 += pv * qv;
         d2 += pv * pv;
@@ -1150,7 +1200,7 @@ __device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& 
     each_four(R.zc, n, [&](int v0, const float (&z)[4]) {
       float q[4] = {0.f, 0.f, 0.f, 0.f}, rv[4];
       bool any = false;
-      if (!R.fresh) {
+      if (!R.fresh()) {
         if (v0 + 3 < n) {
           const float4 t = load4(zp + v0);
           q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
@@ -1162,7 +1212,7 @@ __device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& 
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float pv = v0 + e < n ? prob(z[e], thr, lse_c) : 0.f;
-        rv[e] = pv > 0.f ? __fsub_rn(pv, R.fresh ? q_uniform : prob(q[e], R.thr_p, R.lse_p)) : 0.f;
+        rv[e] = pv > 0.f ? __fsub_rn(pv, R.fresh() ? q_uniform : prob(q[e], R.thr_p, R.lse_p)) : 0.f;
         any |= rv[e] > 0.f;
       }
       if (!any) return;
@@ -1182,7 +1232,7 @@ __device__ __forceinline__ void finish_in_place(const RowArgs& a, const RowRef& 
     for_each_logit([&](int v, float z) {
       const float pv = prob(z, thr, lse_c);
       if (pv > 0.f) {
-        const float qv = R.fresh ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
+        const float qv = R.fresh() ? q_uniform : prob(zp[v], R.thr_p, R.lse_p);
         const float rv = __fsub_rn(pv, qv);
         if (rv > 0.f) {
           const uint4 rr = philox4x32_10(make_uint4(static_cast<uint32_t>(v >> 2), static_cast<uint32_t>(j),
@@ -1806,12 +1856,12 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   }
   if (a.mode == kRowSelectOnly) return;
   const int j = R.p0 + R.s;
-  const float q_uniform = __fdiv_rn(1.0f, static_cast<float>(n));
+  const float q_uniform = a.q_uniform;
   const uint2 key = seed_key(a.seed);
   const uint32_t w3 = static_cast<uint32_t>(R.b) << 8;
   const bool x_ok = R.x >= 0 && R.x < n;
   out.px = x_ok ? prob(zcx, thr, lse_c) : 0.f;
-  out.qx = R.fresh ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
+  out.qx = R.fresh() ? q_uniform : (x_ok ? prob(zpx, R.thr_p, R.lse_p) : 0.f);
   const uint4 ra = philox4x32_10(make_uint4(0u, static_cast<uint32_t>(j), static_cast<uint32_t>(R.it),
                                             w3 | kStreamAccept), key);
   out.accept = __fmul_rn(u01(ra.x), out.qx) <= out.px;
@@ -1832,7 +1882,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   if (park && Cn <= kKeptCap) {
     for (int i = tid; i < Cn; i += THREADS) {
       const int v = static_cast<int>(kid[i]);
-      const float rv = __fsub_rn(exp_of(kz[i] - lse_c), R.fresh ? q_uniform : prob(R.zp[v], R.thr_p, R.lse_p));
+      const float rv = __fsub_rn(exp_of(kz[i] - lse_c), R.fresh() ? q_uniform : prob(R.zp[v], R.thr_p, R.lse_p));
       if (!(rv > 0.f)) continue;
       const uint4 rr = noise(v);
       const uint32_t lanes[4] = {rr.x, rr.y, rr.z, rr.w};
@@ -1842,7 +1892,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   }
   groups(-INFINITY, [&](int v0, const float (&z)[4]) {
     float q[4] = {0.f, 0.f, 0.f, 0.f};
-    if (!R.fresh) {
+    if (!R.fresh()) {
       if (v0 + 3 < n) {
         const float4 t = load4(R.zp + v0);
         q[0] = t.x; q[1] = t.y; q[2] = t.z; q[3] = t.w;
@@ -1856,7 +1906,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float pv = v0 + e < n ? prob(z[e], thr, lse_c) : 0.f;
-      rv[e] = __fsub_rn(pv, R.fresh ? q_uniform : prob(q[e], R.thr_p, R.lse_p));
+      rv[e] = __fsub_rn(pv, R.fresh() ? q_uniform : prob(q[e], R.thr_p, R.lse_p));
       any |= pv > 0.f && rv[e] > 0.f;
     }
     if (!any) return;
@@ -1871,7 +1921,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
 // The whole row in registers, PER logits per thread (n <= PER * THREADS).  A wavefront takes every NW-th piece of
 // 32 ids (a 128-byte line): ids that are likelier than others tend to be neighbours, and every wavefront works
 // on the kept ones among its own.
-template <int PER, bool GS, bool EXTRA>
+template <int PER, bool TINY, bool GS, bool EXTRA>
 __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigned char* smem, bool filter, Small& sm,
                                             RowOut& out) {
   const int lane = threadIdx.x & 63, n = a.n;
@@ -1881,38 +1931,20 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
   float zv[PER], zq[PER];
   bool ok[PER];
 #pragma unroll
-  for (int u = 0; u < PER / 4; ++u) {
-    const int v0 = group(u);
-    if (v0 + 3 < n) {
-      const float4 t = load4(R.zc + v0);
-      zv[u * 4 + 0] = t.x; zv[u * 4 + 1] = t.y; zv[u * 4 + 2] = t.z; zv[u * 4 + 3] = t.w;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) zv[u * 4 + e] = (v0 + e < n) ? R.zc[v0 + e] : 0.f;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      vid[u * 4 + e] = v0 + e;
-      ok[u * 4 + e] = v0 + e < n;
-      zq[u * 4 + e] = 0.f;
-    }
+  for (int e = 0; e < PER; ++e) {
+    vid[e] = group(e >> 2) + (e & 3);
+    ok[e] = vid[e] < n;
+    zq[e] = 0.f;
   }
+  load_groups<PER, TINY>(R.zc, n, group, zv);
+  if (a.mode != kRowSelectOnly) load_groups<PER, TINY>(R.zp, n, group, zq);   // previous logits, for a rejection
   read_row_scalars(a, R);
-  if (a.mode != kRowSelectOnly && !R.fresh) {                      // previous logits, for a rejection
-#pragma unroll
-    for (int u = 0; u < PER / 4; ++u) {
-      const int v0 = group(u);
-      if (v0 + 3 < n) {
-        const float4 q = load4(R.zp + v0);
-        zq[u * 4 + 0] = q.x; zq[u * 4 + 1] = q.y; zq[u * 4 + 2] = q.z; zq[u * 4 + 3] = q.w;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) zq[u * 4 + e] = (v0 + e < n) ? R.zp[v0 + e] : 0.f;
-      }
-    }
-  }
   float zcx, zpx;
   draft_logits(a, R, zcx, zpx);
+  if constexpr (!TINY) {
+    align_groups<PER>(n, group, zv);
+    align_groups<PER>(n, group, zq);
+  }
   if (R.zw) {                                  // supplied logits: keep them for the next iteration
 #pragma unroll
     for (int u = 0; u < PER / 4; ++u) {
@@ -1930,149 +1962,151 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
                                     sm, out);
 }
 
+// What a position that is not live any more leaves.
+template <bool GS, bool EXTRA>
+__device__ __forceinline__ void inactive_row(const RowArgs& a, const RowRef& R) {
+  if (threadIdx.x != 0) return;
+  a.y[R.widx] = -1;
+  a.k[R.widx] = 1;
+  if (GS) a.g[R.widx] = -1;
+  if (a.px) a.px[R.widx] = 0.f;
+  if (a.qx) a.qx[R.widx] = 0.f;
+  if (a.mode == kRowRing && R.s == 0) a.accept_len[R.b] = 0;   // finished sequence
+  if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
+    *reinterpret_cast<float4*>(a.diag + R.widx * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (R.s == 0)
+      for (int i = 0; i < 6; ++i) a.hamm[6 * R.b + i] = 0;
+  }
+}
+
 // GS: the row also makes a Gumbel-max draw from p; EXTRA: the optional parts are compiled in
 // (nucleus filter, per-position statistics; kept out of the other instances: their live ranges
 // cost the hot kernels registers).  PATH: which way rows of this length go.  One instance per way, because
 // with all of them in one kernel the compiler keeps every way's arguments in scalar registers and spills them
 // (184 spills; 46 vector registers spilled in the optional instances).  Four-step decodes over 8192 ids: 132 ->
 // 129 us, with every option 206 -> 193 us.
-enum Path { kDirectQuarter, kDirectHalf, kDirectWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
+enum Path { kDirectTiny, kDirectQuarter, kDirectHalf, kDirectWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
 template <bool GS, bool EXTRA, int PATH>
-__global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(const int32_t* const pos_, const int32_t* const iter_,
-                                                      const int mode_, const int L_, const int N_,
-                                                      const int P, const int capE, const RowArgs a) {
+__global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
+    const int32_t* const pos_, const int32_t* const iter_, const uint2* const cand_, const uint32_t* const cand_cnt_,
+    const int mode_, const int L_, const int N_, const int P, const int capE, const RowArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ Small sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = a.n;
   const int r = blockIdx.x;
-  RowRef R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
-  if (!R.active) {
-    if (tid == 0) {
-      a.y[R.widx] = -1;
-      a.k[R.widx] = 1;
-      if (GS) a.g[R.widx] = -1;
-      if (a.px) a.px[R.widx] = 0.f;
-      if (a.qx) a.qx[R.widx] = 0.f;
-      if (a.mode == kRowRing && R.s == 0) a.accept_len[R.b] = 0;   // finished sequence
-      if (EXTRA && a.diag != nullptr && a.mode == kRowRing) {
-        *reinterpret_cast<float4*>(a.diag + R.widx * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (R.s == 0)
-          for (int i = 0; i < 6; ++i) a.hamm[6 * R.b + i] = 0;
-      }
-    }
-    return;
-  }
-  const bool filter = a.top_k > 0 && a.top_k < n;
-
+  RowRef R;
   RowOut out{};
   out.accept = true;
-  bool done = false;
-  [[maybe_unused]] float zcx = 0.f, zpx = 0.f;
-  if constexpr (PATH == kDirectQuarter || PATH == kDirectHalf || PATH == kDirectWhole) {
+  if (tid < 2) sm.win[tid] = ~0ull;          // (barriers stand between this and the races)
+  if constexpr (PATH <= kDirectWhole) {
+    R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
+    if (!R.active) {
+      inactive_row<GS, EXTRA>(a, R);
+      return;
+    }
     // ---- the whole row in registers ------------------------------------------------
-    direct_path<PATH == kDirectQuarter ? PER_DIRECT / 4 : PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT, GS, EXTRA>(a, R, smem, filter, sm, out);
-    done = true;
+    constexpr int PER = PATH <= kDirectQuarter ? PER_DIRECT / 4 : PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT;
+    direct_path<PER, PATH == kDirectTiny, GS, EXTRA>(a, R, smem, a.top_k > 0 && a.top_k < n, sm, out);
   } else if constexpr (PATH == kNucleusHalf || PATH == kNucleusWhole) {
+    R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
+    if (!R.active) {
+      inactive_row<GS, EXTRA>(a, R);
+      return;
+    }
     nucleus_path<PATH == kNucleusHalf ? 32 : 64, GS>(a, R, smem, sm, out);
-    done = true;
-  } else if (filter && a.cand && P > 0) {
-    // ---- candidates emitted by the slice kernel ----------------------------------
+  } else {
+    // ---- candidate lists (P > 0: a top-k filters and somebody has made them) ---------
     // The P counts and cuts of the row's lists (P slices of the slice kernel, or P column tiles
     // of the LM head's epilogue; thread t holds those of list t), the count that governs each
-    // of this thread's candidate slots, and the slots themselves are fetched in ONE round trip:
-    // slots are read whether filled or not (always inside the row's kListCap pairs) and masked
+    // of this thread's candidate slots, and the slots themselves are fetched in ONE round trip, that of the row's place in
+    // the window: slots are read whether filled or not (always inside the row's kListCap pairs) and masked
     // by the counts afterwards.
-    const uint32_t* const cntp = a.cand_cnt + static_cast<size_t>(r) * P;
-    const uint32_t* const cutp = a.cand_cut + static_cast<size_t>(r) * P;
     uint32_t tc = 0, tq = 0;
-    if (tid < P) {
-      tc = cntp[tid];
-      tq = cutp[tid];
-    }
-    const uint2* src = a.cand + static_cast<size_t>(r) * kListCap;
     uint2 raw[PER_LIST];
     uint32_t slot_cnt[PER_LIST];
     int slot_off[PER_LIST];
+    if (P > 0) {
+      const uint2* const src = cand_ + static_cast<size_t>(r) * kListCap;
+      const uint32_t* const cntp = cand_cnt_ + static_cast<size_t>(r) * P;
 #pragma unroll
-    for (int e = 0; e < PER_LIST; ++e) {
-      const int i = tid + e * THREADS;
-      const int p = static_cast<int>(__umulhi(static_cast<uint32_t>(i), a.cand_recip));   // i / capE
-      slot_off[e] = i - p * capE;
-      raw[e] = src[i];
-      slot_cnt[e] = cntp[p < P ? p : 0];
-      if (p >= P) slot_cnt[e] = 0;
-    }
-    read_row_scalars(a, R);
-    draft_logits(a, R, zcx, zpx);
-    // every list fits its capacity, how many candidates there are, the largest cut
-    {
-      const int tot = wave_sum_i32(static_cast<int>(tc <= static_cast<uint32_t>(capE) ? tc : 0u));
-      const uint32_t cm = wave_max_u32(tq);
-      const bool anybad = __builtin_amdgcn_ballot_w64(tc > static_cast<uint32_t>(capE)) != 0ull;
-      if (lane == 0) {
-        sm.ired2[wave] = tot;
-        sm.ured[wave] = cm;
-        sm.ired[wave] = anybad ? 1 : 0;
-      }
-    }
-    __syncthreads();                // their next writers sit behind the barrier of block_minmax
-    int bad, total;
-    fold_before<NW>(sm.ired, 0, bad);
-    fold_before<NW>(sm.ired2, 0, total);
-    const uint32_t cut_max = fold_max<NW>(sm.ured);
-    if (bad == 0 && total >= a.top_k) {
-      int vid[PER_LIST];
-      float zv[PER_LIST];
-      bool ok[PER_LIST];
+      for (int e = 0; e < PER_LIST; ++e) raw[e] = src[tid + e * THREADS];
+      if (tid < P) tc = cntp[tid];
 #pragma unroll
       for (int e = 0; e < PER_LIST; ++e) {
-        ok[e] = static_cast<uint32_t>(slot_off[e]) < slot_cnt[e] && raw[e].x < static_cast<uint32_t>(n);
-        vid[e] = ok[e] ? static_cast<int>(raw[e].x) : 0;
-        zv[e] = ok[e] ? __uint_as_float(raw[e].y) : 0.f;
+        const int i = tid + e * THREADS;
+        const int p = static_cast<int>(__umulhi(static_cast<uint32_t>(i), a.cand_recip));   // i / capE
+        slot_off[e] = i - p * capE;
+        slot_cnt[e] = cntp[p < P ? p : 0];
+        if (p >= P) slot_cnt[e] = 0;
       }
-      done = finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zv, ok, true, cut_max, zcx, zpx,
-                                                     reinterpret_cast<uint32_t*>(smem), smem, sm, out);
+      if (tid < P) tq = (a.cand_cut + static_cast<size_t>(r) * P)[tid];
     }
-  }
-  if constexpr (PATH == kLists || PATH == kLong) {
-    if (!(filter && a.cand && P > 0)) {                     // no lists: nothing has been read yet
-      read_row_scalars(a, R);
-      draft_logits(a, R, zcx, zpx);
+    R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
+    if (!R.active) {
+      inactive_row<GS, EXTRA>(a, R);
+      return;
     }
-  }
-  if constexpr (PATH == kLong) {
-    if (!done) long_path(a, R, smem, zcx, zpx, sm, out);
-  } else if constexpr (PATH == kLists) {
-    if (!done) full_path<GS, EXTRA>(a, R, smem, zcx, zpx, sm, out);
+    bool done = false;
+    float zcx = 0.f, zpx = 0.f;
+    read_row_scalars(a, R);
+    draft_logits(a, R, zcx, zpx);
+    if (P > 0) {
+      // every list fits its capacity, how many candidates there are, the largest cut
+      {
+        const int tot = wave_sum_i32(static_cast<int>(tc <= static_cast<uint32_t>(capE) ? tc : 0u));
+        const uint32_t cm = wave_max_u32(tq);
+        const bool anybad = __builtin_amdgcn_ballot_w64(tc > static_cast<uint32_t>(capE)) != 0ull;
+        if (lane == 0) {
+          sm.ired2[wave] = tot;
+          sm.ured[wave] = cm;
+          sm.ired[wave] = anybad ? 1 : 0;
+        }
+      }
+      __syncthreads();                // their next writers sit behind the barrier of block_minmax
+      int bad, total;
+      fold_before<NW>(sm.ired, 0, bad);
+      fold_before<NW>(sm.ired2, 0, total);
+      const uint32_t cut_max = fold_max<NW>(sm.ured);
+      if (bad == 0 && total >= a.top_k) {
+        int vid[PER_LIST];
+        float zv[PER_LIST];
+        bool ok[PER_LIST];
+#pragma unroll
+        for (int e = 0; e < PER_LIST; ++e) {
+          ok[e] = static_cast<uint32_t>(slot_off[e]) < slot_cnt[e] && raw[e].x < static_cast<uint32_t>(n);
+          vid[e] = ok[e] ? static_cast<int>(raw[e].x) : 0;
+          zv[e] = ok[e] ? __uint_as_float(raw[e].y) : 0.f;
+        }
+        done = finish_regs<PER_LIST, false, GS, EXTRA>(a, R, vid, zv, zv, ok, true, cut_max, zcx, zpx,
+                                                       reinterpret_cast<uint32_t*>(smem), smem, sm, out);
+      }
+    }
+    if constexpr (PATH == kLong) {
+      if (!done) long_path(a, R, smem, zcx, zpx, sm, out);
+    } else {
+      if (!done) full_path<GS, EXTRA>(a, R, smem, zcx, zpx, sm, out);
+    }
   }
   if (a.mode == kRowSelectOnly) return;
 
   // ---- winners of the races (lexicographic (score, id) minima) ------------------
-  // One entry per wavefront, one barrier for both races; the last wavefront folds them and does everything
-  // up to the hand-off, because the first ones prepare the commit meanwhile.  What every wavefront of a row repeats
-  // is paid four times over per SIMD: a fold of all entries in all 16 took 3600 cycles of the 36000 of a row of
-  // 8192 ids, one wavefront's takes 900; requesting the commit's words before the ticket comes back takes its
-  // 5500 to 3000.  Four-step decodes: 8 x 1024 ids 50.0 -> 45.6 us, 32 x 8192 behind the LM head 128.0 -> 122.0.
-  if (!out.accept) {
-    wave_min_score_id(out.best, out.best_id);
-    if (lane == 0) sm.win[0][wave] = make_uint2(__float_as_uint(out.best), static_cast<uint32_t>(out.best_id));
-  }
-  if (GS) {
-    wave_min_score_id(out.gbest, out.gbest_id);
-    if (lane == 0) sm.win[1][wave] = make_uint2(__float_as_uint(out.gbest), static_cast<uint32_t>(out.gbest_id));
-  }
+  // Score and id as one integer, the smallest of the wavefronts' by one LDS atomic each, one barrier for both races; the
+  // last wavefront alone does everything up to the hand-off, because the first ones prepare the commit meanwhile: what every
+  // wavefront of a row repeats is paid four times over per SIMD.  Requesting the commit's words before the ticket comes back
+  // takes its 5500 cycles to 3000.  Four-step decodes: 8 x 1024 ids 50.0 -> 45.6 us, 32 x 8192 behind the LM head 128.0 -> 122.0.
+  auto enter_winner = [&](int which, float score, int id) {
+    wave_min_score_id(score, id);
+    if (lane == 0)
+      atomicMin(&sm.win[which], static_cast<unsigned long long>(__float_as_uint(score)) << 32 | static_cast<uint32_t>(id));
+  };
+  if (!out.accept) enter_winner(0, out.best, out.best_id);
+  if (GS) enter_winner(1, out.gbest, out.gbest_id);
   if (GS || !out.accept) __syncthreads();
   const bool speaker = wave == NW - 1;
   int y_out = R.x, k_out = 1, g_out = -1;
   if (speaker) {
-    auto winner = [&](int which) {
-      const uint2 e = sm.win[which][lane & (NW - 1)];
-      float score = __uint_as_float(e.x);
-      int id = static_cast<int>(e.y);
-      wave_min_score_id(score, id);
-      return id;
-    };
+    auto winner = [&](int which) { return __builtin_amdgcn_readfirstlane(static_cast<int>(sm.win[which])); };
     if (!out.accept) {
       const int id = winner(0);
       if (id != 0x7FFFFFFF) {      // else: empty residual (rounding only) counts as accept
@@ -2114,7 +2148,8 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(cons
   // took an earlier ticket is visible to the workgroup that takes the last one.
   const int b = R.b, p0 = R.p0, live = R.live;
   const size_t base = static_cast<size_t>(b) * a.L;
-  const int slot = tid < a.L ? (p0 + tid) % a.L : 0;
+  int slot = tid < a.L ? R.first_slot + tid : 0;
+  if (slot >= a.L) slot -= a.L;
   int age_old = 0, verified_old = 0, entering = -1;
   if (speaker) {
     if (lane == 0) {
@@ -2276,6 +2311,10 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
     return launch_row_batched(a_in, s, lds_configured ? lds_configured + 1 : nullptr);
 #endif
   RowArgs a = a_in;
+  a.q_uniform = 1.0f / static_cast<float>(a.n);
+  // ceil(2^32 / L) gives v / L by a multiplication for v L < 2^32 (its excess over 2^32 / L is below 1)
+  const int64_t most_v = std::max<int64_t>(a.rows, static_cast<int64_t>(a.N) + 2 * a.L);
+  a.recip_L = a.L > 1 && most_v * a.L < (1ll << 32) ? static_cast<uint32_t>(((1ull << 32) + a.L - 1) / a.L) : 0u;
   int P = 0, capE = 0;
   a.cand = nullptr;
   if (a.cand_base && row_uses_candidates(a.n, a.top_k)) {
@@ -2308,17 +2347,17 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
 #endif
   const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
   const bool extra = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
-  using Kernel = void (*)(const int32_t*, const int32_t*, int, int, int, int, int, RowArgs);
+  using Kernel = void (*)(const int32_t*, const int32_t*, const uint2*, const uint32_t*, int, int, int, int, int, RowArgs);
 #define SCD_ROW_INSTANCES(PATH) \
   {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
   static const Kernel kernels[][4] = {
 #if defined(SCD_ROW_SHORT)
-      SCD_ROW_INSTANCES(kDirectQuarter)
+      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter)
 #elif defined(SCD_ROW_BATCHED)
-      SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
+      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
       {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr}
 #else
-      {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole), SCD_ROW_INSTANCES(kLists),
+      {}, {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole), SCD_ROW_INSTANCES(kLists),
       {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
       {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
       {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
@@ -2341,7 +2380,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
     configured = most;
   }
 #ifdef SCD_ROW_DIRECT_ONLY
-  const int path = a.n <= kDirectMaxN / 4 ? kDirectQuarter : a.n <= kDirectMaxN / 2 ? kDirectHalf : kDirectWhole;
+  const int path = a.n < 4 ? kDirectTiny : a.n <= kDirectMaxN / 4 ? kDirectQuarter : a.n <= kDirectMaxN / 2 ? kDirectHalf : kDirectWhole;
 #else
   const int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
                    : nucleus ? (a.n <= 32 * THREADS ? kNucleusHalf : kNucleusWhole) : a.n <= kRowKernelMaxN ? kLists : kLong;
@@ -2349,7 +2388,8 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
   if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
   a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;
-  hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(THREADS), lds, s, a.pos, a.iter, a.mode, a.L, a.N, P, capE, a);
+  hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(THREADS), lds, s, a.pos, a.iter, a.cand, a.cand_cnt, a.mode, a.L, a.N, P, capE,
+                     a);
   return hipGetLastError();
 }
 

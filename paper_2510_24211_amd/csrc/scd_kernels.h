@@ -103,6 +103,8 @@ struct RowArgs {
   // tiles > 0: the LM head's epilogue has already filled the candidate scratch with `tiles`
   // lists of kRowListCap / tiles pairs per row (launch_row then skips the slice kernel)
   int tiles;
+  float q_uniform;       // set by launch_row: 1 / n
+  uint32_t recip_L;      // set by launch_row: ceil(2^32 / L), or 0 where that does not divide exactly
   uint32_t cand_recip;   // set by launch_row: ceil(2^32 / pairs per candidate list)
   uint2* cand;           // set by launch_row
   uint32_t* cand_cnt;    // set by launch_row
