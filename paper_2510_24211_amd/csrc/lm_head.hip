@@ -146,13 +146,9 @@ __device__ __forceinline__ int h_row(int p0, int r, int c, int C, int L, int row
   return (b * C + c) * L + s;
 }
 
-// Guidance mix and temperature of one logit (cond sum c, uncond sum u): three fp32 roundings
-// for the mix, one for the division (skipped for tau = 1, where it changes nothing).
 template <int C>
 __device__ __forceinline__ float processed_logit(const LmHeadArgs& a, float c, float u) {
-  float z = c;
-  if (C == 2) z = __fsub_rn(__fmul_rn(a.one_plus_lam, c), __fmul_rn(a.lam, u));
-  return a.tau == 1.0f ? z : __fdiv_rn(z, a.tau);
+  return scd::processed_logit<C>(a.lam, a.one_plus_lam, a.tau, c, u);
 }
 // A logit on its way to the ring.  THROUGH: written through the L2.  Every kernel stores its logits at its end; left in the
 // L2 they are written back when others need the room, or all together behind the last workgroup.  Where W is streamed past
@@ -717,6 +713,7 @@ struct TileCfg {
   static constexpr int WB = BN * 128, HB = HR * 128; // bytes per stage
   static constexpr int SW = S_, SH = HR == 256 && BN == 256 ? S_ - 1 : S_;   // stages
   static_assert(SW >= 3 && SH >= 2, "stages");
+  static constexpr bool SPLITS = HR == 64 && BN == 128;      // may have k dealt over workgroups
   static constexpr bool PARTS = HR * BN < 256 * 256; // registers left for whole sums beside the partial ones
   static constexpr int STAGES = SW * WB + SH * HB;
   // epilogue: row table, then the logit tile of up to 128 window rows and the histograms
@@ -757,14 +754,19 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 template <int C, int HR, int BN, int S, bool NT>
-__global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, const int VT, const int MT, const int per) {
+__global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, const int VT, const int MT, const int KS,
+                                                            const int per) {
   using K = TileCfg<C, HR, BN, S>;
   constexpr int NC = K::NC, NB = K::NB, WL = K::WL, HL = K::HL, SW = K::SW, SH = K::SH;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[K::LDS_BYTES];
   // Workgroups with consecutive ids land on different XCDs; the MT row tiles that share a slab of W get
-  // ids 8 apart: the same XCD, the same L2.
+  // ids 8 apart: the same XCD, the same L2; so do the KS parts of k (1 unless the sums go to a.part).
   const int id = blockIdx.x, xcd = id % 8;
-  const int vt = (id / (8 * MT)) * 8 + xcd, mt = (id / 8) % MT;
+  int mt = (id / 8) % MT, kp = 0, vt = (id / (8 * MT)) * 8 + xcd;
+  if (KS > 1) {
+    kp = (id / (8 * MT)) % KS;
+    vt = id / (8 * MT * KS) * 8 + xcd;
+  }
   if (vt >= VT) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -772,7 +774,9 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
   const int ln = lane & 31, lg = lane >> 5;
   const int d = a.d, rows = a.B * a.L, p_base = mt * K::WR;
   const int v_left = a.n - vt * BN;                  // columns that exist from this tile's first
-  const int KT = d / 64, dtail = d % 64;             // whole k-tiles; elements of the ragged one
+  // whole k-tiles of this part of k, its first, elements of the ragged one (the last part's)
+  const int KT_all = d / 64, kt0 = KT_all * kp / KS, KT = KT_all * (kp + 1) / KS - kt0;
+  const int dtail = kp == KS - 1 ? d % 64 : 0;
   const int rot = (MT > 1 ? xcd * 5 : vt * 5) % KT;  // where this workgroup's cyclic walk over k starts
 
   const RowState mine = row_state(a, p_base + tid);  // for the epilogue's row table
@@ -794,8 +798,8 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
     ho[i] = static_cast<uint32_t>(h_row(min(p_base + (blk / C) * 32, rows - 1), r & 31, blk % C, C, a.L, rows) - h0) *
                 static_cast<uint32_t>(d) * 2u + piece_chunk(r) * 16;
   }
-  const uint64_t wbase = reinterpret_cast<uint64_t>(a.W) + static_cast<uint64_t>(vt) * BN * d * 2;
-  const uint64_t hbase = reinterpret_cast<uint64_t>(a.h) + static_cast<uint64_t>(h0) * d * 2;
+  const uint64_t wbase = reinterpret_cast<uint64_t>(a.W) + static_cast<uint64_t>(vt) * BN * d * 2 + static_cast<uint32_t>(kt0) * 128u;
+  const uint64_t hbase = reinterpret_cast<uint64_t>(a.h) + static_cast<uint64_t>(h0) * d * 2 + static_cast<uint32_t>(kt0) * 128u;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) void*)lds));
   const uint32_t ldsW = lds0 + wave * WL * 1024, ldsH = lds0 + SW * K::WB + wave * HL * 1024;
 
@@ -1016,6 +1020,25 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
     }
   }
 
+  if constexpr (K::SPLITS) {
+    if (a.part) {                                    // uniform
+      // ---- sums of this part of k, for the row kernel -----------------------------------------------
+      float* const part = a.part + static_cast<int64_t>(kp) * C * rows * a.n;
+      with_bool(through_lines(a), [&](auto through) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int row = p_base + (wr * K::RB + i / C) * 32 + (j >> 2) * 8 + lg * 4 + (j & 3);
+            float* const to = part + (static_cast<int64_t>(i % C) * rows + row) * a.n + vt * BN + wc * K::CW + ln;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              if (row < rows && wc * K::CW + c * 32 + ln < v_left) store_logit<decltype(through)::value>(to + c * 32, acc[c][i][j]);
+          }
+      });
+      return;
+    }
+  }
   // ---- epilogue: guidance mix, temperature, z; then the per-tile candidates ---------------------------
   __syncthreads();                                   // every wavefront is done with the stages
   int* const table = reinterpret_cast<int*>(lds);    // (the stages take all of LDS: no table before)
@@ -1337,10 +1360,12 @@ template <int C, int HR, int BN, int S>
 hipError_t launch_tile(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) {
   using K = TileCfg<C, HR, BN, S>;
   const int VT = (a.n - 1) / BN + 1, MT = (a.B * a.L + K::WR - 1) / K::WR;
-  const dim3 grid((VT + 7) / 8 * 8 * MT);
-  const int KT = a.d / 64, parts = k_parts(a), per = parts > 1 ? (KT + parts - 1) / parts : KT + 1;
-  if (stream_w(a)) launch_kernel(lm_head_tile_kernel<C, HR, BN, S, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT, per);
-  else launch_kernel(lm_head_tile_kernel<C, HR, BN, S, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT, per);
+  const int KS = K::SPLITS && a.part ? a.ksplit : 1;
+  const dim3 grid((VT + 7) / 8 * 8 * MT * KS);
+  // (a part of k in KS is added up in its share of the partial sums)
+  const int KT = a.d / 64 / KS, parts = (k_parts(a) + KS - 1) / KS, per = parts > 1 ? (KT + parts - 1) / parts : KT + 2;
+  if (stream_w(a)) launch_kernel(lm_head_tile_kernel<C, HR, BN, S, true>, grid, dim3(K::THREADS), s, ev, a, VT, MT, KS, per);
+  else launch_kernel(lm_head_tile_kernel<C, HR, BN, S, false>, grid, dim3(K::THREADS), s, ev, a, VT, MT, KS, per);
   return hipGetLastError();
 }
 
@@ -1412,7 +1437,28 @@ hipError_t launch_c(const LmHeadArgs& a, hipStream_t s, const LaunchEvents& ev) 
 
 hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const LaunchEvents ev{ev_start, ev_stop};
+  if (a.part) return a.C == 2 ? launch_tile<2, 64, 128, 6>(a, s, ev) : launch_tile<1, 64, 128, 6>(a, s, ev);
   return a.C == 2 ? launch_c<2>(a, s, ev) : launch_c<1>(a, s, ev);
+}
+
+// Few tiles leave most of the chip idle: k is dealt over as many workgroups per 64 x 128 tile as make 128 of them (with
+// 256 the row kernel's reads cost more than is won), no part below four k-tiles.  What it saves grows with d and with
+// the rows; what it costs, with the arrays that a row reads.  One step, LM head and rows, in one part : in the parts taken
+// here (us): 64 rows with guidance x 1024 ids over 4096 28.8 : 18.7, over 1280 19.4 : 16.8; x 4096 30.3 : 24.6, 20.9 : 19.6;
+// 128 rows without x 2048 23.8 : 19.9, 18.1 : 17.8; 256 x 2048 30.2 : 24.4, 22.1 : 20.0.  Not taken: d of 512 (64 rows with
+// guidance x 2048 16.4 : 16.5); two parts where the split kernel runs in one round (128 rows without guidance x 4096 over 1280
+// 19.8 : 20.0, 64 x 8192 20.9 : 21.9); up to 32 rows, whose kernel fills more CUs, but for d of 4096 on few ids (with
+// guidance x 2048 20.4 : 18.8, x 8192 26.6 : 27.9; without x 1024 16.5 : 16.2, x 4096 18.9 : 20.2).
+int lm_head_ksplit(const LmHeadArgs& a) {
+  const long rows = static_cast<long>(a.B) * a.L;
+  const long tiles = (rows * a.C + 63) / 64 * ((a.n - 1) / 128 + 1);
+  const int KT = a.d / 64;
+  if (a.n < 256 || a.n > kRowDirectMaxN || tiles > 64) return 1;
+  int ks = a.n <= 2048 ? kMaxKSplit : 4;             // (registers of the row kernel)
+  while (ks > 1 && (tiles * ks > 128 || KT < 4 * ks)) ks /= 2;
+  const int least = rows <= 32 ? (KT < 64 ? kMaxKSplit + 1 : a.C == 2 ? 4 : 8)
+                    : KT < 20 ? kMaxKSplit + 1 : a.C == 1 && rows <= 128 ? 4 : 2;
+  return ks >= least ? ks : 1;
 }
 
 int lm_head_tiles(const LmHeadArgs& a) {

@@ -1921,7 +1921,8 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
 // The whole row in registers, PER logits per thread (n <= PER * THREADS).  A wavefront takes every NW-th piece of
 // 32 ids (a 128-byte line): ids that are likelier than others tend to be neighbours, and every wavefront works
 // on the kept ones among its own.
-template <int PER, bool TINY, bool GS, bool EXTRA>
+//   PARTS: this iteration's logits come as the LM head's sums over parts of k.
+template <int PER, bool TINY, bool PARTS, bool GS, bool EXTRA>
 __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigned char* smem, bool filter, Small& sm,
                                             RowOut& out) {
   const int lane = threadIdx.x & 63, n = a.n;
@@ -1936,11 +1937,64 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
     ok[e] = vid[e] < n;
     zq[e] = 0.f;
   }
-  load_groups<PER, TINY>(R.zc, n, group, zv);
-  if (a.mode != kRowSelectOnly) load_groups<PER, TINY>(R.zp, n, group, zq);   // previous logits, for a rejection
-  read_row_scalars(a, R);
   float zcx, zpx;
-  draft_logits(a, R, zcx, zpx);
+  if constexpr (PARTS) {
+    const size_t arr = static_cast<size_t>(a.rows) * n;                         // floats between the arrays [part][cond, uncond]
+    const float* const mine = a.part + R.widx * n;
+    auto previous = [&]() {
+      load_groups<PER>(R.zp, n, group, zq);
+      read_row_scalars(a, R);
+    };
+    zcx = 0.f;
+    auto add_up = [&](auto c_, auto ks_) {
+      constexpr int C = decltype(c_)::value, KS = decltype(ks_)::value;
+      float t[C * KS][PER];
+#pragma unroll
+      for (int q = 0; q < C * KS; ++q) load_groups<PER>(mine + q * arr, n, group, t[q]);   // q = part * C + {cond, uncond}
+      previous();
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        float c = t[0][e], u = t[C - 1][e];
+#pragma unroll
+        for (int p = 1; p < KS; ++p) {
+          c += t[p * C][e];
+          u += t[p * C + C - 1][e];
+        }
+        zv[e] = processed_logit<C>(a.lam, a.one_plus_lam, a.tau, c, u);
+      }
+      if (R.x >= 0 && R.x < n) {                                                // the draft's, by itself
+        float d[C * KS];
+#pragma unroll
+        for (int q = 0; q < C * KS; ++q) d[q] = scalar_word(mine + q * arr + R.x);
+        float c = d[0], u = d[C - 1];
+#pragma unroll
+        for (int p = 1; p < KS; ++p) {
+          c += d[p * C];
+          u += d[p * C + C - 1];
+        }
+        zcx = processed_logit<C>(a.lam, a.one_plus_lam, a.tau, c, u);
+      }
+    };
+    using std::integral_constant;
+    auto by_parts = [&](auto c_) {
+      if constexpr (PER <= 4) {
+        if (a.ksplit == 8) return add_up(c_, integral_constant<int, 8>{});
+      }
+      if constexpr (PER <= 8) {
+        if (a.ksplit == 4) return add_up(c_, integral_constant<int, 4>{});
+      }
+      add_up(c_, integral_constant<int, 2>{});
+    };
+    if (a.C == 2) by_parts(integral_constant<int, 2>{});
+    else by_parts(integral_constant<int, 1>{});
+    zpx = R.x >= 0 && R.x < n ? R.zp[R.x] : 0.f;
+    R.zw = const_cast<float*>(R.zc);
+  } else {
+    load_groups<PER, TINY>(R.zc, n, group, zv);
+    if (a.mode != kRowSelectOnly) load_groups<PER, TINY>(R.zp, n, group, zq);   // previous logits, for a rejection
+    read_row_scalars(a, R);
+    draft_logits(a, R, zcx, zpx);
+  }
   if constexpr (!TINY) {
     align_groups<PER>(n, group, zv);
     align_groups<PER>(n, group, zq);
@@ -1985,7 +2039,7 @@ __device__ __forceinline__ void inactive_row(const RowArgs& a, const RowRef& R) 
 // with all of them in one kernel the compiler keeps every way's arguments in scalar registers and spills them
 // (184 spills; 46 vector registers spilled in the optional instances).  Four-step decodes over 8192 ids: 132 ->
 // 129 us, with every option 206 -> 193 us.
-enum Path { kDirectTiny, kDirectQuarter, kDirectHalf, kDirectWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
+enum Path { kDirectTiny, kDirectQuarter, kDirectHalf, kDirectWhole, kPartsQuarter, kPartsHalf, kPartsWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
 template <bool GS, bool EXTRA, int PATH>
 __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
     const int32_t* const pos_, const int32_t* const iter_, const uint2* const cand_, const uint32_t* const cand_cnt_,
@@ -1999,15 +2053,17 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
   RowOut out{};
   out.accept = true;
   if (tid < 2) sm.win[tid] = ~0ull;          // (barriers stand between this and the races)
-  if constexpr (PATH <= kDirectWhole) {
+  if constexpr (PATH <= kPartsWhole) {
     R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
     if (!R.active) {
       inactive_row<GS, EXTRA>(a, R);
       return;
     }
     // ---- the whole row in registers ------------------------------------------------
-    constexpr int PER = PATH <= kDirectQuarter ? PER_DIRECT / 4 : PATH == kDirectHalf ? PER_DIRECT / 2 : PER_DIRECT;
-    direct_path<PER, PATH == kDirectTiny, GS, EXTRA>(a, R, smem, a.top_k > 0 && a.top_k < n, sm, out);
+    constexpr bool PARTS = PATH >= kPartsQuarter;
+    constexpr int PER = PATH == kDirectWhole || PATH == kPartsWhole ? PER_DIRECT
+                        : PATH == kDirectHalf || PATH == kPartsHalf ? PER_DIRECT / 2 : PER_DIRECT / 4;
+    direct_path<PER, PATH == kDirectTiny, PARTS, GS, EXTRA>(a, R, smem, a.top_k > 0 && a.top_k < n, sm, out);
   } else if constexpr (PATH == kNucleusHalf || PATH == kNucleusWhole) {
     R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
     if (!R.active) {
@@ -2352,12 +2408,15 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
   static const Kernel kernels[][4] = {
 #if defined(SCD_ROW_SHORT)
-      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter)
+      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), {}, {}, SCD_ROW_INSTANCES(kPartsQuarter)
 #elif defined(SCD_ROW_BATCHED)
       SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
-      {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr}
+      {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr},
+      SCD_ROW_INSTANCES(kPartsQuarter), SCD_ROW_INSTANCES(kPartsHalf),
+      {row_kernel<false, false, kPartsWhole>, row_kernel<true, false, kPartsWhole>, nullptr, nullptr}
 #else
-      {}, {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole), SCD_ROW_INSTANCES(kLists),
+      {}, {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
+      {}, SCD_ROW_INSTANCES(kPartsHalf), SCD_ROW_INSTANCES(kPartsWhole), SCD_ROW_INSTANCES(kLists),
       {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
       {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
       {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
@@ -2380,11 +2439,12 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
     configured = most;
   }
 #ifdef SCD_ROW_DIRECT_ONLY
-  const int path = a.n < 4 ? kDirectTiny : a.n <= kDirectMaxN / 4 ? kDirectQuarter : a.n <= kDirectMaxN / 2 ? kDirectHalf : kDirectWhole;
+  int path = a.n < 4 ? kDirectTiny : a.n <= kDirectMaxN / 4 ? kDirectQuarter : a.n <= kDirectMaxN / 2 ? kDirectHalf : kDirectWhole;
 #else
-  const int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
+  int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
                    : nucleus ? (a.n <= 32 * THREADS ? kNucleusHalf : kNucleusWhole) : a.n <= kRowKernelMaxN ? kLists : kLong;
 #endif
+  if (a.part) path += kPartsQuarter - kDirectQuarter;
   const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
   if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
   a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;

@@ -4,6 +4,7 @@
 // except scd_status.
 #include "../../include/scd.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -92,9 +93,21 @@ size_t small_need(const scd_config& c) {
   const size_t rows = static_cast<size_t>(c.B) * c.L;
   return 6 * align_up(4 * rows);
 }
-// ... followed by the per-row candidate scratch of the slice kernel.
+// The LM head's sums over parts of k: in how many parts scd_step has it dealt over workgroups, and their bytes.
+int parts_of(const scd_config& c) {
+  if (c.d <= 0) return 1;
+  scd::LmHeadArgs a{};
+  a.B = c.B; a.C = c.cfg_lambda != 0.f ? 2 : 1; a.L = c.L; a.d = c.d; a.n = c.v_hi - c.v_lo;
+  return scd::lm_head_ksplit(a);
+}
+size_t parts_need(const scd_config& c) {
+  const int parts = parts_of(c);
+  return parts > 1 ? sizeof(float) * parts * (c.cfg_lambda != 0.f ? 2 : 1) * c.B * c.L * (c.v_hi - c.v_lo) : 0;
+}
+// ... followed by the per-row candidate scratch of the slice kernel, in the place of which shorter rows have the LM head's
+// sums over parts of k (no row has both).
 size_t workspace_need(const scd_config& c) {
-  return small_need(c) + align_up(scd::row_candidate_bytes(c.B * c.L));
+  return small_need(c) + align_up(std::max(scd::row_candidate_bytes(c.B * c.L), parts_need(c)));
 }
 
 // ---- scratch of the entry point that allocates nothing -----------------------------------
@@ -147,7 +160,7 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 
 // Everything after the LM head.  tiles > 0: it has left its candidate lists; z of this iteration is in
 // place in the ring, or at `src` in window order.
-int run_tail(scd_ctx* c, void* st, int tiles, const float* src) {
+int run_tail(scd_ctx* c, void* st, int tiles, const float* src, const scd::LmHeadArgs* lm = nullptr) {
   const size_t half = static_cast<size_t>(c->cfg.B) * c->cfg.L * c->n;
   // one fused launch: select + softmax + MRS per row, commit by each sequence's last row
   scd::RowArgs ra{};
@@ -155,6 +168,10 @@ int run_tail(scd_ctx* c, void* st, int tiles, const float* src) {
   ra.mode = scd::kRowRing;
   ra.z_cur = field<float>(c, st, SCD_F_Z);
   ra.src = src;
+  if (lm && lm->part) {
+    ra.part = lm->part; ra.ksplit = lm->ksplit; ra.C = lm->C;
+    ra.lam = lm->lam; ra.one_plus_lam = lm->one_plus_lam; ra.tau = lm->tau;
+  }
   ra.parity_stride = half;
   ra.thr = field<float>(c, st, SCD_F_THR);
   ra.lse = field<float>(c, st, SCD_F_LSE);
@@ -413,11 +430,15 @@ int scd_step(scd_ctx* c, const uint16_t* d_h, const uint16_t* d_W, void* st) {
     a.cand_cap = scd::kRowListCap / tiles;
     a.flags = field<int32_t>(c, st, SCD_F_FLAGS);
   }
+  if (const int parts = parts_of(c->cfg); parts > 1) {
+    a.part = reinterpret_cast<float*>(static_cast<char*>(c->ws) + small_need(c->cfg));
+    a.ksplit = parts;
+  }
   const bool timed = c->ev_start && c->ev_stop;
   if (hipError_t e = scd::launch_lm_head(a, c->stream, timed ? c->ev_start : nullptr, timed ? c->ev_stop : nullptr);
       e != hipSuccess)
     return SCD_EHIP;
-  return run_tail(c, st, tiles, nullptr);
+  return run_tail(c, st, tiles, nullptr, &a);
 }
 
 int scd_set_lm_head_events(scd_ctx* c, void* ev_start, void* ev_stop) {

@@ -255,4 +255,13 @@ __device__ __forceinline__ void wave_min_score_id(float& score, int& id) {
   score = __uint_as_float(least);
 }
 
+// Guidance mix and temperature of one logit (cond sum c, uncond sum u): three fp32 roundings
+// for the mix, one for the division (skipped for tau = 1, where it changes nothing).
+template <int C>
+__device__ __forceinline__ float processed_logit(float lam, float one_plus_lam, float tau, float c, float u) {
+  float z = c;
+  if (C == 2) z = __fsub_rn(__fmul_rn(one_plus_lam, c), __fmul_rn(lam, u));
+  return tau == 1.0f ? z : __fdiv_rn(z, tau);
+}
+
 }  // namespace scd

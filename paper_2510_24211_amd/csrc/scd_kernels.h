@@ -26,6 +26,10 @@ struct LmHeadArgs {
   uint32_t* cand_cnt;
   uint32_t* cand_cut;
   int cand_cap;         // pairs per (row, tile)
+  // Optional (scd_step only): instead of z, the sums over each of `ksplit` parts of k, cond and uncond, unprocessed:
+  // fp32 [ksplit, C, B * L, n] in window order, for the row kernel to add up.  Null / 0 => off.
+  float* part;
+  int ksplit;
   int32_t* flags;       // numeric-fault bits (NaN logits are reported here), may be null
 };
 // ev_start / ev_stop (both or neither): events that take the kernel's own start and stop time
@@ -34,6 +38,10 @@ hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_star
 // Name (as a profiler prints it, without namespaces and arguments) of the kernel that
 // launch_lm_head picks for these sizes (only B, C, L, d, n are read); snprintf semantics.
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap);
+// In how many parts scd_step has k dealt over workgroups for these sizes (LmHeadArgs::part; only B, C, L, d, n are read);
+// 1: it does not.  More than 1 only for rows that the row kernel holds in registers.
+int lm_head_ksplit(const LmHeadArgs& a);
+constexpr int kMaxKSplit = 8;
 // Slots that the epilogue may leave free in a tile's list of cand_cap (unless logits tie or are not finite).
 constexpr int kTileSlack = 8;
 // Number of column tiles per row (256 or 128 columns each) if the kernel that launch_lm_head picks for these sizes can
@@ -109,6 +117,11 @@ struct RowArgs {
   uint2* cand;           // set by launch_row
   uint32_t* cand_cnt;    // set by launch_row
   uint32_t* cand_cut;    // set by launch_row
+  // ring mode with the LM head's sums over `ksplit` parts of k (LmHeadArgs::part): added up, processed and left in the ring;
+  // null: off.  C, lam, one_plus_lam, tau as there.
+  const float* part;
+  int ksplit, C;
+  float lam, one_plus_lam, tau;
 };
 size_t row_candidate_bytes(int rows);
 // Where the candidate scratch (row_candidate_bytes(rows) bytes at base) keeps its parts: per row

@@ -1,0 +1,55 @@
+"""Steps whose LM head deals k over workgroups (up to 8 parts per 64 x 128 tile), against the oracle: the row kernel adds the
+parts up, processes the logits and leaves them in the ring.  Ragged ids, rows and k; every number of parts; every option."""
+import pytest
+import torch
+
+from lockstep import LockStep
+from paper_2510_24211_amd import binding as B
+from paper_2510_24211_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("parts,kw,opts", [
+    (2, dict(B=2, L=32, V=3000, d=1280, v_lo=3, v_hi=2900), dict()),              # five k-tiles of ten in flight, odd rows
+    (2, dict(B=5, L=26, V=1285, d=1288, cfg_lambda=0.0), dict()),                 # ragged k-tile, 130 rows, no guidance
+    (4, dict(B=2, L=32, V=1031, d=1280), dict(coupling="gs", diagnostics=True)),
+    (4, dict(B=1, L=40, V=2047, d=1304, top_p=0.9), dict()),
+    (4, dict(B=1, L=64, V=4090, d=1280, cfg_lambda=0.0), dict()),                 # 8 logits per thread, four arrays
+    (8, dict(B=3, L=16, V=260, d=2048, temperature=0.8), dict(sjd_mix=0.5)),      # short rows, windows below 32
+    (8, dict(B=1, L=64, V=1024, d=2056, cfg_lambda=0.0), dict(diagnostics=True)),
+    (8, dict(B=1, L=32, V=1900, d=4096, top_p=0.95), dict(coupling="gs")),        # up to 32 rows
+    (4, dict(B=1, L=30, V=4000, d=4096), dict()),
+])
+def test_lockstep_with_k_in_parts(parts, kw, opts):
+    kw = dict(dict(N=3 * kw["L"] + 5, age_cap=8, top_k=kw["V"] // 5), **kw)
+    w = wl.scaled(wl.WORKLOADS["C2"], name="parts", **dict(dict(v_lo=0, v_hi=kw["V"]), **kw))
+    ls = LockStep(w, "cuda:0", **opts)
+    # the arrays of the parts, [parts, 1 + CFG, rows, n], behind six arrays of a word per row in the workspace
+    small = 6 * ((4 * w.B * w.L + 255) // 256 * 256) // 4
+    words = ls.gpu.workspace[:ls.gpu.workspace.numel() // 4 * 4].view(torch.int32)
+    words.fill_(-1)
+    ls.step()
+    used = parts * w.C * w.B * w.L * w.n_allowed
+    assert (words[small:small + used] != -1).all() and (words[small + used:] == -1).all()
+    st = ls.run()
+    assert ls.oracle.done()
+    # the lock-step tests' bounds on adopted decisions; a logit itself has to lie within the measured-discrepancy cap
+    assert st["adopt_accept"] + st["adopt_resid"] <= max(3, 1e-3 * st["draws"])
+    assert st["adopt_topk"] <= max(3, 1e-2 * st["draws"])
+
+
+def test_parts_are_run_to_run_identical():
+    s = B.Scd(B.make_config(B=2, L=32, N=400, V=2048, d=2048, top_k=500, cfg_lambda=3.0, seed=5))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    W = torch.randn(2048, 2048, device="cuda", generator=g).to(torch.bfloat16) * 0.02
+    hs = [torch.randn(2, 2, 32, 2048, device="cuda", generator=g).to(torch.bfloat16) for _ in range(4)]
+    got = []
+    for _ in range(2):
+        st = s.alloc_state().fill_(0x7f)
+        s.reset(st)
+        for h in hs:
+            s.step(h, W, st)
+        got.append([s.state_field(st, f).clone() for f in (B.F_OUT, B.F_Z, B.F_LSE, B.F_PX)])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
