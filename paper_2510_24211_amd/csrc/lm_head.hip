@@ -438,11 +438,9 @@ __device__ __forceinline__ void tile_candidates(const LmHeadArgs& a, float* zt, 
   uint2* const dst = a.cand + (static_cast<size_t>(wrow) * kRowListCap + static_cast<size_t>(tile) * cap);
   float vmin = INFINITY;
   for (int i = l; i < cap; i += kTileLanes) {
-    const uint2 t = pairs[i];
-    if (live && i < total) {
-      dst[i] = t;
-      vmin = fminf(vmin, __uint_as_float(t.y));
-    }
+    const uint2 t = i < total ? pairs[i] : make_uint2(kNoId, __float_as_uint(INFINITY));
+    if (live) dst[i] = t;
+    vmin = fminf(vmin, __uint_as_float(t.y));
   }
   vmin = tile_row_min(vmin);                             // smallest emitted logit
   if (live && l == 0) {

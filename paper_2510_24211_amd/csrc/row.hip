@@ -690,6 +690,8 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
   uint32_t* const cnt_out = a.cand_cnt + static_cast<size_t>(r) * P;
   uint32_t* const cut_out = a.cand_cut + static_cast<size_t>(r) * P;
   if (lo_id >= hi_id) {
+    for (int i = tid; i < capE; i += ST)
+      a.cand[static_cast<size_t>(r) * kListCap + static_cast<size_t>(p) * capE + i] = make_uint2(kNoId, 0u);
     if (tid == 0) {
       cnt_out[p] = 0;
       cut_out[p] = 0;
@@ -740,6 +742,7 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
   int total;
   int off = block_offsets<ST>(mine, total, sm, 0, false);
   uint2* const dst = a.cand + (static_cast<size_t>(r) * kListCap + static_cast<size_t>(p) * capE);
+  for (int i = total + tid; i < capE; i += ST) dst[i] = make_uint2(kNoId, 0u);
 #pragma unroll
   for (int e = 0; e < PS; ++e) {
     if (take[e]) {
@@ -1024,7 +1027,6 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   const int wave = wave_index();
   uint32_t kmin, kmax;
   bool nan;
-  draw_accept_uniform(a, R, sm);
   thread_range<PER>(zv, ok, kmin, kmax, nan);
   if (nan && a.flags) atomicOr(a.flags, 1);                    // NaN of either sign
   if (filter) zero_hist(hist);            // published by the barrier inside block_minmax
@@ -1995,6 +1997,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
     read_row_scalars(a, R);
     draft_logits(a, R, zcx, zpx);
   }
+  draw_accept_uniform(a, R, sm);
   if constexpr (!TINY) {
     align_groups<PER>(n, group, zv);
     align_groups<PER>(n, group, zq);
@@ -2074,29 +2077,19 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
   } else {
     // ---- candidate lists (P > 0: a top-k filters and somebody has made them) ---------
     // The P counts and cuts of the row's lists (P slices of the slice kernel, or P column tiles
-    // of the LM head's epilogue; thread t holds those of list t), the count that governs each
-    // of this thread's candidate slots, and the slots themselves are fetched in ONE round trip, that of the row's place in
-    // the window: slots are read whether filled or not (always inside the row's kListCap pairs) and masked
-    // by the counts afterwards.
+    // of the LM head's epilogue; thread t holds those of list t) and the slots themselves are fetched in ONE round trip,
+    // that of the row's place in the window.  Slots that a list does not fill hold an id past the end (kNoId); behind the
+    // P lists' slots there may be room that nobody writes.
     uint32_t tc = 0, tq = 0;
     uint2 raw[PER_LIST];
-    uint32_t slot_cnt[PER_LIST];
-    int slot_off[PER_LIST];
     if (P > 0) {
       const uint2* const src = cand_ + static_cast<size_t>(r) * kListCap;
-      const uint32_t* const cntp = cand_cnt_ + static_cast<size_t>(r) * P;
 #pragma unroll
       for (int e = 0; e < PER_LIST; ++e) raw[e] = src[tid + e * THREADS];
-      if (tid < P) tc = cntp[tid];
-#pragma unroll
-      for (int e = 0; e < PER_LIST; ++e) {
-        const int i = tid + e * THREADS;
-        const int p = static_cast<int>(__umulhi(static_cast<uint32_t>(i), a.cand_recip));   // i / capE
-        slot_off[e] = i - p * capE;
-        slot_cnt[e] = cntp[p < P ? p : 0];
-        if (p >= P) slot_cnt[e] = 0;
+      if (tid < P) {
+        tc = (cand_cnt_ + static_cast<size_t>(r) * P)[tid];
+        tq = (a.cand_cut + static_cast<size_t>(r) * P)[tid];
       }
-      if (tid < P) tq = (a.cand_cut + static_cast<size_t>(r) * P)[tid];
     }
     R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
     if (!R.active) {
@@ -2107,6 +2100,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
     float zcx = 0.f, zpx = 0.f;
     read_row_scalars(a, R);
     draft_logits(a, R, zcx, zpx);
+    draw_accept_uniform(a, R, sm);
     if (P > 0) {
       // every list fits its capacity, how many candidates there are, the largest cut
       {
@@ -2130,7 +2124,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
         bool ok[PER_LIST];
 #pragma unroll
         for (int e = 0; e < PER_LIST; ++e) {
-          ok[e] = static_cast<uint32_t>(slot_off[e]) < slot_cnt[e] && raw[e].x < static_cast<uint32_t>(n);
+          ok[e] = raw[e].x < static_cast<uint32_t>(n) && tid + e * THREADS < P * capE;
           vid[e] = ok[e] ? static_cast<int>(raw[e].x) : 0;
           zv[e] = ok[e] ? __uint_as_float(raw[e].y) : 0.f;
         }
@@ -2447,7 +2441,6 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   if (a.part) path += kPartsQuarter - kDirectQuarter;
   const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
   if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
-  a.cand_recip = capE > 0 ? static_cast<uint32_t>(((1ull << 32) + capE - 1) / capE) : 0u;
   hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(THREADS), lds, s, a.pos, a.iter, a.cand, a.cand_cnt, a.mode, a.L, a.N, P, capE,
                      a);
   return hipGetLastError();

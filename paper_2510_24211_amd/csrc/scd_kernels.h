@@ -113,7 +113,6 @@ struct RowArgs {
   int tiles;
   float q_uniform;       // set by launch_row: 1 / n
   uint32_t recip_L;      // set by launch_row: ceil(2^32 / L), or 0 where that does not divide exactly
-  uint32_t cand_recip;   // set by launch_row: ceil(2^32 / pairs per candidate list)
   uint2* cand;           // set by launch_row
   uint32_t* cand_cnt;    // set by launch_row
   uint32_t* cand_cut;    // set by launch_row
@@ -128,6 +127,7 @@ size_t row_candidate_bytes(int rows);
 // kRowListCap (id, logit) pairs, then kRowMaxTiles counts, then kRowMaxTiles cuts.
 constexpr int kRowListCap = 6144;
 constexpr int kRowMaxTiles = 256;
+constexpr uint32_t kNoId = 0xFFFFFFFFu;       // the id in a list's slots behind its pairs
 void row_candidate_layout(void* base, int rows, uint2** cand, uint32_t** cnt, uint32_t** cut);
 // whether launch_row, given scratch, runs the slice kernel for rows of n ids under this top-k
 bool row_uses_candidates(int n, int top_k);
