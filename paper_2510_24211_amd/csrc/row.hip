@@ -56,6 +56,7 @@
 #include "scd_kernels.h"
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #ifdef SCD_ROW_BATCHED
@@ -538,6 +539,14 @@ __device__ __forceinline__ uint32_t nucleus_key(Each&& each, Prepare&& prepare, 
   return lo;
 }
 
+// Lanes below this one whose bit is set, plus `more`.
+__device__ __forceinline__ int lanes_before(unsigned long long mask, int more) {
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), static_cast<uint32_t>(more))));
+}
+// LDS operations of a wavefront are performed in order: what its lanes wrote before, its lanes read behind.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // Where a kernel instance finds its row.
 struct RowRef {
   const float* zc;
@@ -756,6 +765,238 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
   }
 }
 
+#ifndef SCD_ROW_DIRECT_ONLY
+// ---------------------------------------------------------------------------------
+// list kernel: the same lists from pieces that a wavefront holds in registers
+// ---------------------------------------------------------------------------------
+// A wavefront takes 64 E neighbouring ids of a row and emits the `cap` largest of them or somewhat fewer as (id, logit)
+// pairs in a fixed order, with their number and a cut: every logit of the piece that is not emitted lies below it.
+// As in the LM head's epilogue the emitted set is found on a monotone image of the logits, linear between their mean and
+// their largest: one LDS histogram per wavefront, the lowest bin whose upper set holds at most `cap`.  A list needs no exact
+// length, only to hold what the row's K-th largest leaves to this piece, so that bins of a few logits will do; where they
+// are too wide (a far logit, masks of -1e10) the bin below the cut is counted again on its own range (refine_list).
+// Masked ids (kListFloor and below) are never emitted.  What is not finite, or ties by the hundred, reports more pairs than
+// fit: the row kernel reads the row whole.
+//   Bound by latency: a wavefront works for itself, 400 instructions and no barrier, where the slice kernel's
+// workgroups select an exact rank in eight barrier-separated phases.  Four steps on supplied logits of 32 x 65536 ids take
+// 79.1 us for 91.2, of 32 x 81146 83.2 for 100.3, four steps of 32 x 131072 behind the LM head 737.8 for 745.7, three stage
+// calls on 60 x 30001 42.4 for 48.5.
+constexpr int kListBins = 256;
+constexpr int kListHist = kWave + kListBins;       // words: one per lane for what lies far below the bins
+constexpr int kListWaves = 4;                      // per workgroup
+constexpr float kListFloor = kRangeFloor;
+__device__ __forceinline__ float list_scale(float range) {
+  return range > 0.f ? fminf(__builtin_amdgcn_rcpf(range) * (kListBins - 1.01f), 3.0e38f) : 0.f;
+}
+__device__ __forceinline__ void zero_list_bins(uint32_t* bins, int lane) {
+  *reinterpret_cast<uint4*>(&bins[4 * lane]) = make_uint4(0u, 0u, 0u, 0u);
+}
+// The lowest bin whose upper set holds at most `room` of the counted logits (kListBins: not even the last one's), and
+// how many that are.
+__device__ __forceinline__ int list_cut(const uint32_t* bins, int lane, int room, int& taken) {
+  static_assert(kListBins == 4 * kWave, "four bins per lane");
+  const uint4 t = *reinterpret_cast<const uint4*>(&bins[kListBins - 4 - 4 * lane]);      // top bins in lane 0
+  const int c[4] = {static_cast<int>(t.w), static_cast<int>(t.z), static_cast<int>(t.y), static_cast<int>(t.x)};
+  const int local = (c[0] + c[1]) + (c[2] + c[3]);
+  int sum = wave_inclusive_sum_i32(local) - local;
+  int fits = 0;
+  taken = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    sum += c[j];
+    fits += __builtin_popcountll(__builtin_amdgcn_ballot_w64(sum <= room));
+    taken = max(taken, sum <= room ? sum : 0);
+  }
+  taken = static_cast<int>(wave_max_u32(static_cast<uint32_t>(taken)));
+  return kListBins - fits;
+}
+// bin[e] >= cut: the logit is emitted.  Where the list stays short, the logits of the bin below the cut (more than there are
+// free slots) are counted on an image of their own range, and those of its upper bins are lifted above every cut; again
+// on the next bin while the list is short and the members differ.
+constexpr int kListLifted = 1 << 20;
+template <int E>
+__device__ __forceinline__ void refine_list(const float (&v)[E], int (&bin)[E], int cut, int cap, int enough, int total,
+                                            uint32_t* bins, int lane) {
+  uint64_t in = 0;                                       // a bit per logit (E <= 64)
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    in |= (cut > 0 ? bin[e] == cut - 1 : bin[e] < 0 && bin[e] >= -kWave) ? 1ull << e : 0ull;
+#pragma unroll 1
+  for (int round = 0; round < 6 && total < enough; ++round) {
+    float mx = -INFINITY, mn = INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const bool is = (in >> e & 1u) != 0u;
+      mx = is ? fmaxf(mx, v[e]) : mx;
+      mn = is ? fminf(mn, v[e]) : mn;
+    }
+    const float hi = wave_max_f32(mx), lo = wave_min_f32(mn);
+    if (!(hi > lo)) return;                              // they tie (or there are none)
+    const float scale = list_scale(hi - lo);
+    zero_list_bins(bins, lane);
+    wave_lds_fence();
+    int image[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      image[e] = static_cast<int>(__builtin_amdgcn_fmed3f((v[e] - lo) * scale, 0.f, kListBins - 1.f));
+      if ((in >> e & 1u) != 0u) atomicAdd(&bins[image[e]], 1u);
+    }
+    wave_lds_fence();
+    int taken;
+    const int part = list_cut(bins, lane, cap - total, taken);
+    total += taken;
+    uint64_t next = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const bool is = (in >> e & 1u) != 0u;
+      bin[e] = is && image[e] >= part ? kListLifted : bin[e];
+      next |= is && image[e] == part - 1 ? 1ull << e : 0ull;
+    }
+    in = next;
+  }
+}
+
+template <int E>
+__global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t* const pos_, const int32_t* const iter_,
+                                                                  const float* const rows_, const int mode_, const int L_,
+                                                                  const int N_, const int n_, const int P, const int cap,
+                                                                  const RowArgs a) {
+  // rows_: the rows' logits in the order of the launch, or null: in the ring, where pos and iter say
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kListWaves * kListHist];
+  const int lane = threadIdx.x & 63, wave = wave_index();
+  const int r = blockIdx.x, p = static_cast<int>(blockIdx.y) * kListWaves + wave;
+  if (p >= P) return;
+  uint32_t* const bins = hist + wave * kListHist + kWave;
+  const int lo_id = p * (kWave * E), hi_id = min(n_, lo_id + kWave * E);
+  auto group = [&](int u) { return lo_id + ((lane + u * kWave) << 2); };
+  float v[E];
+  RowRef R;
+  const float* row = rows_ + static_cast<size_t>(r) * n_;
+  if (!rows_) {
+    R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
+    if (!R.active) return;
+    row = R.zc;
+  }
+  load_groups<E>(row, hi_id, group, v);
+  zero_list_bins(bins, lane);
+  if (rows_) {                                           // (while they are on their way)
+    R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
+    if (!R.active) return;
+  }
+  align_groups<E>(hi_id, group, v);
+  const bool whole = hi_id - lo_id == kWave * E;
+  float given[E];                                        // (the copy's: the logits may change below)
+#pragma unroll
+  for (int e = 0; e < E; ++e) given[e] = v[e];
+  float mx = -INFINITY, mn = INFINITY, sum = 0.f;
+  int there = kWave * E;                                 // logits above the floor
+#pragma unroll
+  for (int e = 0; e < E; e += 2) {
+    mx = max3(mx, v[e], v[e + 1]);
+    mn = min3(mn, v[e], v[e + 1]);
+    sum += v[e];
+    sum += v[e + 1];
+  }
+  bool nan = false;
+  if (!whole || __builtin_amdgcn_ballot_w64(!(mn > kListFloor && sum == sum)) != 0ull) {
+    // ragged, masked, or not finite: those do not count (they take a value below every other's from here on)
+    int mine = 0;
+    sum = 0.f;
+    mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const bool is = group(e >> 2) + (e & 3) < hi_id;
+      nan |= is && v[e] != v[e];
+      const bool counts = is && v[e] > kListFloor;
+      v[e] = counts ? v[e] : -INFINITY;
+      sum += counts ? v[e] : 0.f;
+      mx = fmaxf(mx, v[e]);
+      mine += counts ? 1 : 0;
+    }
+    there = wave_sum_i32(mine);
+  }
+  nan = __builtin_amdgcn_ballot_w64(nan) != 0ull;
+  if (nan && a.flags && lane == 0) atomicOr(a.flags, 1);         // NaN of either sign
+  mx = wave_max_f32(mx);
+  const float mean = there > 0 ? wave_sum(sum) * __builtin_amdgcn_rcpf(static_cast<float>(there)) : 0.f;
+  const float range = mx - mean;
+  const size_t list = static_cast<size_t>(r) * P + p;
+  uint2* const dst = a.cand + (static_cast<size_t>(r) * kListCap + static_cast<size_t>(p) * cap);
+  int bin[E], cut = 0, total = 0;
+  const bool all = there <= cap;                         // every logit above the floor is emitted
+  const bool finite = !nan && mx < INFINITY && mean > -INFINITY;
+  if (all) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) bin[e] = v[e] > -INFINITY ? 0 : -1;
+  } else if (finite) {
+    const float scale = list_scale(range), below = -1.f - static_cast<float>(lane);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      bin[e] = static_cast<int>(__builtin_amdgcn_fmed3f((v[e] - mean) * scale, below, kListBins - 1.f));
+      atomicAdd(&bins[bin[e]], 1u);
+      if (v[e] == -INFINITY) bin[e] = -1 - kWave;        // never a member of anything
+    }
+    wave_lds_fence();
+    cut = list_cut(bins, lane, cap, total);
+    const int enough = min(cap - cap / 4, there * 3 / 8);    // (a short piece at the row's end has a smaller share)
+    if (__builtin_expect(total < enough, 0)) refine_list<E>(v, bin, cut, cap, enough, total, bins, lane);
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) bin[e] = -1;
+  }
+  int at = 0;
+  float vmin = INFINITY;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool take = bin[e] >= cut;
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(take);
+    if (take) {
+      dst[lanes_before(mask, at)] = make_uint2(static_cast<uint32_t>(group(e >> 2) + (e & 3)), __float_as_uint(v[e]));
+      vmin = fminf(vmin, v[e]);
+    }
+    at += __builtin_popcountll(mask);
+  }
+  for (int i = at + lane; i < cap; i += kWave) dst[i] = make_uint2(kNoId, 0u);
+  // Supplied logits: keep them for the next iteration.  Last, so that nothing waits behind the stores, and through the L2:
+  // 32 x 65536 ids 83.2 -> 79.1 us in four steps (81.2 with plain stores here), x 81146 88.4 -> 83.2.
+  if (R.zw) {
+    const auto ring = row_buffer(R.zw, n_);
+#pragma unroll
+    for (int u = 0; u < E / 4; ++u) {
+      const int v0 = group(u);
+      if (whole || v0 + 3 < hi_id) {
+        store4_through(ring, v0, given[u * 4], given[u * 4 + 1], given[u * 4 + 2], given[u * 4 + 3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v0 + e < hi_id) R.zw[v0 + e] = given[u * 4 + e];
+      }
+    }
+  }
+  vmin = wave_min_f32(vmin);
+  if (lane == 0) {
+    const bool good = all || (finite && at > 0);
+    a.cand_cnt[list] = good && !nan ? static_cast<uint32_t>(at) : static_cast<uint32_t>(cap) + 1u;   // > cap: overflow
+    // what is not emitted lies below this key: nothing (0), masked ids, everything below the smallest emitted
+    a.cand_cut[list] = !all ? zkey(vmin) : at == hi_id - lo_id ? 0u : zkey(kListFloor) + 1u;
+  }
+}
+
+// Ids per lane of the list kernel for these rows (a list per 64 times as many), or 0: the slice kernel.  The lists of a row
+// share kRowListCap slots; a list has to hold what the row's top_k leaves to its piece: its mean, five of its standard
+// deviations and some more have to fit into the three quarters of the slots that are filled.  Longer pieces vary less.
+// (top-k 2000: up to 131072 ids; 3072: up to 65536.)
+int list_width(int n, int top_k) {
+  for (int per : {16, 32}) {
+    const int P = (n + kWave * per - 1) / (kWave * per);
+    if (P > kRowMaxTiles) continue;
+    const double cap = kRowListCap / P, mean = static_cast<double>(top_k) / P;
+    if (mean + 5.0 * std::sqrt(mean) + 4.0 <= 0.75 * cap) return per;
+  }
+  return 0;
+}
+#endif  // !SCD_ROW_DIRECT_ONLY
+
 // Per-position statistics of the iteration (Sec. 3: acceptance rate beta = 1 - D_TV(p, q) =
 // sum_v min(p_v, q_v); Prop. "SJD Collision Probability": C = sum_v p_v q_v and its bound
 // sqrt(sum p^2 * sum q^2) = exp(-(H_2(p) + H_2(q)) / 2)).  d0..d2: this thread's share of
@@ -846,14 +1087,6 @@ __device__ __forceinline__ void draw_accept_uniform(const RowArgs& a, const RowR
                                             (static_cast<uint32_t>(R.b) << 8) | kStreamAccept), seed_key(a.seed));
   if ((threadIdx.x & 63) == 0) sm.u_accept = u01(ra.x);
 }
-
-// Lanes below this one whose bit is set, plus `more`.
-__device__ __forceinline__ int lanes_before(unsigned long long mask, int more) {
-  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), static_cast<uint32_t>(more))));
-}
-// LDS operations of a wavefront are performed in order: what its lanes wrote before, its lanes read behind.
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Kept ids that a wavefront parks in LDS; with more (only where a thread holds more than 8 logits) it works from
 // its registers, where then every second lane or more has work anyway.
@@ -2374,6 +2607,16 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       P = a.tiles;
       capE = kListCap / P;
     } else {
+#ifndef SCD_ROW_DIRECT_ONLY
+      if (const int per = list_width(a.n, a.top_k); per > 0) {
+        P = (a.n + kWave * per - 1) / (kWave * per);
+        capE = kListCap / P;
+        hipLaunchKernelGGL(per == 16 ? list_kernel<16> : list_kernel<32>, dim3(a.rows, (P + kListWaves - 1) / kListWaves),
+                           dim3(kListWaves * kWave), 0, s, a.pos, a.iter,
+                           a.src ? a.src : a.mode == kRowRing ? nullptr : a.z_cur, a.mode, a.L, a.N, a.n, P, capE, a);
+      } else
+#endif
+      {
       P = (a.n + kSliceMax - 1) / kSliceMax;                     // 3 .. kRowMaxTiles
       capE = kListCap / P;
       int rank = (2 * a.top_k + P - 1) / P;
@@ -2385,6 +2628,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       else
         hipLaunchKernelGGL(slice_kernel<THREADS>, dim3(a.rows * P), dim3(THREADS), 0, s, a.pos, a.iter, a.mode, a.L,
                            a.N, P, capE, rank, a);
+      }
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
   }

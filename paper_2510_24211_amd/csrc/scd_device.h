@@ -95,6 +95,18 @@ __device__ __forceinline__ void store4(float* p, float a, float b, float c, floa
   *reinterpret_cast<f32x4_u*>(p) = f32x4_u{a, b, c, d};
 }
 
+// The same into a row of n floats (short enough for 32-bit byte offsets), written through the L2: what a kernel leaves in it is
+// written back behind its last workgroup, 1 us and more for 8 MB, before the next kernel starts.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(float* row, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc(row, 0, 4 * n, 0x00020000);       // raw, bounds in bytes
+}
+__device__ __forceinline__ void store4_through(__amdgpu_buffer_rsrc_t row, int at, float a, float b, float c, float d) {
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  constexpr int kSc1 = 16;                                                    // agent scope
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)},
+                                         row, 4 * at, 0, kSc1);
+}
+
 // Three-way maximum / minimum of floats; a NaN operand is ignored.  As builtins they would come with a
 // quieting instruction per operand.
 __device__ __forceinline__ float max3(float a, float b, float c) {
