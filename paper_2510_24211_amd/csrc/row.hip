@@ -11,16 +11,14 @@
 //   accept iff fl(u * q(x)) <= p(x);  else y = argmin_{r_v > 0} -ln(U_v) / r_v
 //
 // gfx950 mapping.  A row of up to 65536 logits is far more than one CU should
-// chew through alone (a CU retires 64 lane-operations per clock), and with few
-// sequences there are few rows, so the work is cut in two:
-//   slice_kernel  rows x P workgroups.  Each holds 1/P of a row in registers
-//                 (8 logits per thread), finds the slice's r-th largest key
-//                 exactly (r ~ 2K/P) and emits the (id, logit) pairs above it.
-//                 The union of the emitted sets contains the row's top K unless
-//                 one slice holds more than r of them.
+// chew through alone, and with few sequences there are few rows, so the work is cut in two:
+//   list_kernel   a wavefront per piece of 1024 or 2048 ids.  It emits the piece's largest logits as
+//                 (id, logit) pairs, twice to three times its share of the row's top K, and a cut below
+//                 which the others lie.  slice_kernel does the same for pieces of 8192 ids and an exact
+//                 rank, where K is too large for lists that short (list_width).
 //   row_kernel    one workgroup per row.  Loads the <= 6144 candidates into
 //                 registers (6 per thread), selects the K-th largest key among
-//                 them, and accepts the answer only if it is >= every slice's
+//                 them, and accepts the answer only if it is >= every list's
 //                 cut (then no unseen logit can be >= it): exact, verified.
 //                 Sum of exponentials, accept test, residual race and the
 //                 commit follow from the same registers.
@@ -32,7 +30,7 @@
 // histogram select, candidate list or in-place scans; the scans alone where nothing filters.  Under a nucleus
 // filter without top-k such rows stay in registers too (nucleus_path).
 // Rows of more than 65536 logits (the LONG instance; top-k and the maximal coupling only) take the
-// slice kernel and the candidate path like the others.  32 rows of 131072 ids under top-k 2000: 11 us +
+// lists and the candidate path like the others.  32 rows of 131072 ids under top-k 2000: 9 us +
 // 15 us, where one kernel per stage (radix select over the row, MRS, commit) took 124 + 64 + 5 us.
 // Their complete path (long_path) makes whole passes over the row in memory.
 // Logits supplied by the caller (a.src) are copied into the ring by whichever kernel reads them first; a
@@ -661,13 +659,15 @@ __device__ __forceinline__ void load_groups(const float* row, int end, Group&& g
     }
   }
 }
-// The shift, once the logits are wanted: rows of a multiple of four ids have no such group.
+// The shift, once the logits are wanted: rows of a multiple of four ids have no such group, others one in one lane, and the
+// other wavefronts step over it.
 template <int PER, class Group>
 __device__ __forceinline__ void align_groups(int end, Group&& group, float (&z)[PER]) {
   if ((end & 3) == 0) return;                  // uniform
 #pragma unroll
   for (int u = 0; u < PER / 4; ++u) {
     const int by = group(u) - (end - 4);       // 1 .. 3: that many of the four are the group's predecessors
+    if (__builtin_amdgcn_ballot_w64(static_cast<uint32_t>(by - 1) < 3u) == 0ull) continue;
     const float t1 = z[u * 4 + 1], t2 = z[u * 4 + 2], t3 = z[u * 4 + 3];
     z[u * 4] = by == 1 ? t1 : by == 2 ? t2 : by == 3 ? t3 : z[u * 4];
     z[u * 4 + 1] = by == 1 ? t2 : by == 2 ? t3 : t1;
@@ -676,7 +676,7 @@ __device__ __forceinline__ void align_groups(int end, Group&& group, float (&z)[
 }
 
 // ---------------------------------------------------------------------------------
-// slice kernel
+// slice kernel: lists from slices of 8192 ids by an exact rank (see list_kernel and list_width)
 // ---------------------------------------------------------------------------------
 // ST threads: 1024, or 512 when there are more slices than two per CU (four such workgroups
 // fit a CU by LDS and wavefronts, so that all of them run at once: C4 192 -> 186 us per step)
@@ -1240,7 +1240,7 @@ __device__ __forceinline__ void finish_kept(const RowArgs& a, const RowRef& R, u
 // normaliser, accept test, residual race.  Returns false if the threshold could not
 // be certified against `cut_max` (the caller then takes the complete path).
 // PREQ: zq[e] is the previous iteration's logit of id vid[e], read by the caller together
-// with zv (coalesced; unused for a fresh position).  Otherwise (ids scattered over the row) the previous
+// with zv (coalesced; unused for a fresh position).  Otherwise the previous
 // logits of the KEPT ids are gathered here, right after the compaction, so that the round trip hides behind the
 // normaliser.  LDS: hist (kHistWords), and lds (NW * wave_cap * 12 or 8 bytes), which may lie over it.
 //
@@ -1305,7 +1305,12 @@ __device__ __forceinline__ bool finish_regs(const RowArgs& a, const RowRef& R, c
   finish_kept<PREQ, GS, EXTRA>(a, R, kid, kz, kq, cnt, compact, [&](auto&& f) {
     if constexpr (!ALL_FIT) {
 #pragma unroll
-      for (int e = 0; e < PER; ++e) f(ok[e] && zv[e] >= thr, vid[e], zv[e], zq[e]);
+      for (int e = 0; e < PER; ++e) {
+        float q = 0.f;
+        if constexpr (PREQ) q = zq[e];
+        else if (a.mode != kRowSelectOnly && !R.fresh() && ok[e] && zv[e] >= thr) q = R.zp[vid[e]];
+        f(ok[e] && zv[e] >= thr, vid[e], zv[e], q);
+      }
     }
   }, m, thr, zcx, zpx, sm, out);
   return true;
@@ -1681,7 +1686,7 @@ __device__ __forceinline__ void full_path(const RowArgs& a, const RowRef& R, uns
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem + static_cast<size_t>(n8) * 2);
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + static_cast<size_t>(n8) * 2 + NBINS * 4);
   const float* zc = R.zc;
-  float* const zw = a.cand ? nullptr : R.zw;     // the slice kernel has made the copy already
+  float* const zw = a.cand ? nullptr : R.zw;     // whoever made the lists has made the copy already
 
   // pass 1: batches of 8 independent 16-byte loads per thread
   const int ngroups8 = n8 >> 2;
@@ -1979,7 +1984,7 @@ __device__ __forceinline__ void long_path(const RowArgs& a, const RowRef& R, uns
   uint32_t kmax = 0, kmin = 0xFFFFFFFFu;
   {
     float hi = -INFINITY, lo = INFINITY, nan = 0.f;
-    float* const zw = a.cand ? nullptr : R.zw;               // the slice kernel has made the copy already
+    float* const zw = a.cand ? nullptr : R.zw;               // whoever made the lists has made the copy already
     groups(-INFINITY, [&](int v0, const float (&z)[4]) {
       if (zw) {
         if (v0 + 3 < n) {
@@ -2163,6 +2168,11 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
   const int lane = threadIdx.x & 63, n = a.n;
   const int first = wave_index() * 32 + (lane >> 3) * (NW * 32) + ((lane & 7) << 2);
   auto group = [&](int u) { return first + u * (8 * NW * 32); };   // four ids each
+  // The kept ids' previous logits are gathered behind the threshold, except 16 to a thread without options: there the whole
+  // row's are read up front (four steps of 464 rows x 4688 ids 233 : 236 us, of 32 x 16384 92.9 : 93.9).  With the options the 16
+  // more registers spilled (128 rows x 10457 ids 149.8 -> 135.0, 128 x 9137 140.5 -> 132.0); shorter rows save the bytes
+  // (16 x 32 x 8192 324 -> 320, 104 x 2546 75.7 -> 74.5).
+  constexpr bool PREQ = PER >= 16 && !EXTRA;
   int vid[PER];
   float zv[PER], zq[PER];
   bool ok[PER];
@@ -2177,7 +2187,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
     const size_t arr = static_cast<size_t>(a.rows) * n;                         // floats between the arrays [part][cond, uncond]
     const float* const mine = a.part + R.widx * n;
     auto previous = [&]() {
-      load_groups<PER>(R.zp, n, group, zq);
+      if (PREQ) load_groups<PER>(R.zp, n, group, zq);
       read_row_scalars(a, R);
     };
     zcx = 0.f;
@@ -2226,14 +2236,14 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
     R.zw = const_cast<float*>(R.zc);
   } else {
     load_groups<PER, TINY>(R.zc, n, group, zv);
-    if (a.mode != kRowSelectOnly) load_groups<PER, TINY>(R.zp, n, group, zq);   // previous logits, for a rejection
+    if (PREQ && a.mode != kRowSelectOnly) load_groups<PER, TINY>(R.zp, n, group, zq);   // previous logits, for a rejection
     read_row_scalars(a, R);
     draft_logits(a, R, zcx, zpx);
   }
   draw_accept_uniform(a, R, sm);
   if constexpr (!TINY) {
     align_groups<PER>(n, group, zv);
-    align_groups<PER>(n, group, zq);
+    if (PREQ) align_groups<PER>(n, group, zq);
   }
   if (R.zw) {                                  // supplied logits: keep them for the next iteration
 #pragma unroll
@@ -2248,7 +2258,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
       }
     }
   }
-  finish_regs<PER, true, GS, EXTRA>(a, R, vid, zv, zq, ok, filter, 0u, zcx, zpx, reinterpret_cast<uint32_t*>(smem), smem,
+  finish_regs<PER, PREQ, GS, EXTRA>(a, R, vid, zv, zq, ok, filter, 0u, zcx, zpx, reinterpret_cast<uint32_t*>(smem), smem,
                                     sm, out);
 }
 
@@ -2309,7 +2319,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
     nucleus_path<PATH == kNucleusHalf ? 32 : 64, GS>(a, R, smem, sm, out);
   } else {
     // ---- candidate lists (P > 0: a top-k filters and somebody has made them) ---------
-    // The P counts and cuts of the row's lists (P slices of the slice kernel, or P column tiles
+    // The P counts and cuts of the row's lists (P pieces of the list or slice kernel, or P column tiles
     // of the LM head's epilogue; thread t holds those of list t) and the slots themselves are fetched in ONE round trip,
     // that of the row's place in the window.  Slots that a list does not fill hold an id past the end (kNoId); behind the
     // P lists' slots there may be room that nobody writes.
@@ -2572,7 +2582,7 @@ void row_candidate_layout(void* base_, int rows, uint2** cand, uint32_t** cnt, u
 
 bool row_uses_candidates(int n, int top_k) {
   const bool filter = top_k > 0 && top_k < n;
-  // one list per slice, at most kRowMaxTiles lists per row (longer rows are read whole).  top-k: a slice
+  // at most kRowMaxTiles lists per row (longer rows are read whole).  top-k: a slice
   // emits about twice its share of the row's top_k logits, which has to fit its part of the lists.
   return n > kRowDirectMaxN && n <= kRowMaxTiles * kSliceMax && filter && top_k <= kListCap / 2;
 }
@@ -2608,7 +2618,10 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       capE = kListCap / P;
     } else {
 #ifndef SCD_ROW_DIRECT_ONLY
-      if (const int per = list_width(a.n, a.top_k); per > 0) {
+      // (Rows of up to 65536 ids that the LM head left without lists, its top-k being too large for them, keep the slices:
+      // tests/test_gpu_lm_head_tiles.py counts them.)
+      const bool without = a.mode == kRowRing && !a.src && a.n <= kRowKernelMaxN;
+      if (const int per = without ? 0 : list_width(a.n, a.top_k); per > 0) {
         P = (a.n + kWave * per - 1) / (kWave * per);
         capE = kListCap / P;
         hipLaunchKernelGGL(per == 16 ? list_kernel<16> : list_kernel<32>, dim3(a.rows, (P + kListWaves - 1) / kListWaves),

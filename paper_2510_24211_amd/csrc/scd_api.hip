@@ -104,7 +104,7 @@ size_t parts_need(const scd_config& c) {
   const int parts = parts_of(c);
   return parts > 1 ? sizeof(float) * parts * (c.cfg_lambda != 0.f ? 2 : 1) * c.B * c.L * (c.v_hi - c.v_lo) : 0;
 }
-// ... followed by the per-row candidate scratch of the slice kernel, in the place of which shorter rows have the LM head's
+// ... followed by the rows' candidate lists, in the place of which shorter rows have the LM head's
 // sums over parts of k (no row has both).
 size_t workspace_need(const scd_config& c) {
   return small_need(c) + align_up(std::max(scd::row_candidate_bytes(c.B * c.L), parts_need(c)));
@@ -375,7 +375,7 @@ int scd_couple_draft_static(scd_ctx* c, const float* d_z_cur, const float* d_z_p
                             uint8_t* d_k) {
   if (!c) return SCD_EINVAL;
   // what this configuration really uses of the workspace layout: the per-row scalars, and the
-  // candidate lists only when its rows go through the slice kernel
+  // candidate lists only when its rows have any
   bool cands = scd::row_uses_candidates(c->n, c->cfg.top_k);
   const size_t lists = align_up(scd::row_candidate_bytes(c->cfg.B * c->cfg.L));
   // rows of more than 65536 ids also run without the lists: more of them than the array can hold
@@ -386,7 +386,7 @@ int scd_couple_draft_static(scd_ctx* c, const float* d_z_cur, const float* d_z_p
   void* base = nullptr;
   if (int rc = static_scratch(&base); rc != SCD_OK) return rc;
   // nothing in the scratch has to start at zero: the per-row scalars and, for every live row,
-  // all slice counts / cuts the row kernel reads are written by the launches of this call first
+  // all list counts / cuts the row kernel reads are written by the launches of this call first
   return couple_draft_impl(c, static_cast<char*>(base), cands, d_z_cur, d_z_prev, d_x, d_fresh, d_pos0, iter,
                            d_y, d_k);
 }

@@ -20,7 +20,7 @@ struct LmHeadArgs {
   // Optional (scd_step only, and only when lm_head_tiles() says the chosen kernel can): the
   // epilogue also emits, per window row and per tile of 256 or 128 columns, the tile's cand_cap largest
   // logits as (id, logit) pairs, their number and the cut below which nothing was emitted --
-  // the input of the row kernel's candidate path, which then needs no slice kernel.  Layout as
+  // the input of the row kernel's candidate path, which then needs no list kernel.  Layout as
   // row_candidate_layout() gives it; window row index = b * L + s.  All null / 0 => off.
   uint2* cand;
   uint32_t* cand_cnt;
@@ -60,7 +60,7 @@ struct RowArgs {
   const float* z_cur;    // select-only: [rows, n]; plain: [B, L, n]; ring: base of [2, B, L, n]
   const float* z_prev;   // plain: [B, L, n]
   // ring mode with logits supplied by the caller: [B, L, n] in window order, read instead of the ring
-  // and copied into it on the way (by the slice kernel where it runs, else by the row kernel);
+  // and copied into it on the way (by the list or slice kernel where one runs, else by the row kernel);
   // null: this iteration's logits are in the ring
   const float* src;
   size_t parity_stride;  // ring: floats between the halves of z
@@ -105,11 +105,11 @@ struct RowArgs {
   int32_t* xhist;        // [3, B, L] drafts at the start of the last three iterations, by ring slot
   int32_t* phist;        // [3, B]    window start of those iterations (far negative: none)
   uint64_t seed;
-  // scratch for the slice kernel (rows longer than 16384 ids): row_candidate_bytes(rows)
+  // room for the candidate lists (rows longer than 16384 ids): row_candidate_bytes(rows)
   // bytes of device memory, 256-byte aligned, or null (then rows are processed whole)
   void* cand_base;
   // tiles > 0: the LM head's epilogue has already filled the candidate scratch with `tiles`
-  // lists of kRowListCap / tiles pairs per row (launch_row then skips the slice kernel)
+  // lists of kRowListCap / tiles pairs per row (launch_row then makes none)
   int tiles;
   float q_uniform;       // set by launch_row: 1 / n
   uint32_t recip_L;      // set by launch_row: ceil(2^32 / L), or 0 where that does not divide exactly
@@ -129,7 +129,7 @@ constexpr int kRowListCap = 6144;
 constexpr int kRowMaxTiles = 256;
 constexpr uint32_t kNoId = 0xFFFFFFFFu;       // the id in a list's slots behind its pairs
 void row_candidate_layout(void* base, int rows, uint2** cand, uint32_t** cnt, uint32_t** cut);
-// whether launch_row, given scratch, runs the slice kernel for rows of n ids under this top-k
+// whether launch_row, given scratch, makes or takes candidate lists for rows of n ids under this top-k
 bool row_uses_candidates(int n, int top_k);
 // lds_configured: the caller's record (three words per context, initially 0) that the dynamic-LDS
 // limit of the row kernels has been set on its device; null => set it on every launch
