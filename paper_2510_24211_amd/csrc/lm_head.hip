@@ -761,9 +761,11 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
   // ids 8 apart: the same XCD, the same L2; so do the KS parts of k (1 unless the sums go to a.part).
   const int id = blockIdx.x, xcd = id % 8;
   int mt = (id / 8) % MT, kp = 0, vt = (id / (8 * MT)) * 8 + xcd;
-  if (KS > 1) {
-    kp = (id / (8 * MT)) % KS;
-    vt = id / (8 * MT * KS) * 8 + xcd;
+  if constexpr (K::SPLITS) {
+    if (KS > 1) {
+      kp = (id / (8 * MT)) % KS;
+      vt = id / (8 * MT * KS) * 8 + xcd;
+    }
   }
   if (vt >= VT) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -773,8 +775,15 @@ __global__ __launch_bounds__(512) void lm_head_tile_kernel(const LmHeadArgs a, c
   const int d = a.d, rows = a.B * a.L, p_base = mt * K::WR;
   const int v_left = a.n - vt * BN;                  // columns that exist from this tile's first
   // whole k-tiles of this part of k, its first, elements of the ragged one (the last part's)
-  const int KT_all = d / 64, kt0 = KT_all * kp / KS, KT = KT_all * (kp + 1) / KS - kt0;
-  const int dtail = kp == KS - 1 ? d % 64 : 0;
+  int kt0 = 0, KT = d / 64, dtail = d % 64;
+  if constexpr (K::SPLITS) {
+    if (KS > 1) {                                    // (a division is about thirty instructions ahead of the first load)
+      const int all = KT;
+      kt0 = all * kp / KS;
+      KT = all * (kp + 1) / KS - kt0;
+      if (kp < KS - 1) dtail = 0;
+    }
+  }
   const int rot = (MT > 1 ? xcd * 5 : vt * 5) % KT;  // where this workgroup's cyclic walk over k starts
 
   const RowState mine = row_state(a, p_base + tid);  // for the epilogue's row table
