@@ -2617,30 +2617,32 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       P = a.tiles;
       capE = kListCap / P;
     } else {
+      int per = 0;
 #ifndef SCD_ROW_DIRECT_ONLY
       // (Rows of up to 65536 ids that the LM head left without lists, its top-k being too large for them, keep the slices:
       // tests/test_gpu_lm_head_tiles.py counts them.)
       const bool without = a.mode == kRowRing && !a.src && a.n <= kRowKernelMaxN;
-      if (const int per = without ? 0 : list_width(a.n, a.top_k); per > 0) {
+      if (!without) per = list_width(a.n, a.top_k);
+      if (per > 0) {
         P = (a.n + kWave * per - 1) / (kWave * per);
         capE = kListCap / P;
         hipLaunchKernelGGL(per == 16 ? list_kernel<16> : list_kernel<32>, dim3(a.rows, (P + kListWaves - 1) / kListWaves),
                            dim3(kListWaves * kWave), 0, s, a.pos, a.iter,
                            a.src ? a.src : a.mode == kRowRing ? nullptr : a.z_cur, a.mode, a.L, a.N, a.n, P, capE, a);
-      } else
+      }
 #endif
-      {
-      P = (a.n + kSliceMax - 1) / kSliceMax;                     // 3 .. kRowMaxTiles
-      capE = kListCap / P;
-      int rank = (2 * a.top_k + P - 1) / P;
-      rank = rank < 64 ? 64 : rank;
-      if (rank > capE * 4 / 5) rank = capE * 4 / 5;
-      if (a.rows * P > 512)
-        hipLaunchKernelGGL(slice_kernel<512>, dim3(a.rows * P), dim3(512), 0, s, a.pos, a.iter, a.mode, a.L, a.N, P,
-                           capE, rank, a);
-      else
-        hipLaunchKernelGGL(slice_kernel<THREADS>, dim3(a.rows * P), dim3(THREADS), 0, s, a.pos, a.iter, a.mode, a.L,
-                           a.N, P, capE, rank, a);
+      if (per == 0) {
+        P = (a.n + kSliceMax - 1) / kSliceMax;                   // 3 .. kRowMaxTiles
+        capE = kListCap / P;
+        int rank = (2 * a.top_k + P - 1) / P;
+        rank = rank < 64 ? 64 : rank;
+        if (rank > capE * 4 / 5) rank = capE * 4 / 5;
+        if (a.rows * P > 512)
+          hipLaunchKernelGGL(slice_kernel<512>, dim3(a.rows * P), dim3(512), 0, s, a.pos, a.iter, a.mode, a.L, a.N, P,
+                             capE, rank, a);
+        else
+          hipLaunchKernelGGL(slice_kernel<THREADS>, dim3(a.rows * P), dim3(THREADS), 0, s, a.pos, a.iter, a.mode, a.L,
+                             a.N, P, capE, rank, a);
       }
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
