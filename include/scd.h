@@ -158,10 +158,15 @@ typedef enum scd_field {
   SCD_F_COUNT = 23
 } scd_field;
 
-/* Bytes of caller-provided device scratch a context needs; 0 on a bad config. */
+/* Bytes of caller-provided device scratch a context needs; 0 on a bad config.  Nothing in it outlives
+ * a call.  scd_couple_draft writes it, and so do scd_select, scd_step and scd_step_logits where a
+ * top-k of up to 3072 filters rows of more than 16384 ids; those calls must not overlap in time on
+ * the GPU with others that were given the same workspace. */
 size_t scd_workspace_bytes(const scd_config* cfg);
 
-/* Bytes of the device-resident decode state; 0 on a bad config. */
+/* Bytes of the device-resident decode state; 0 on a bad config.  The fields of scd_field come first;
+ * behind them, where scd_step deals the LM head's k over workgroups (short rows, few of them), lie
+ * that step's partial sums, up to 4 MiB of which nothing outlives the step. */
 size_t scd_state_bytes(const scd_config* cfg);
 
 /* Validates cfg, copies it, remembers the workspace (256-byte aligned device

@@ -4,7 +4,6 @@
 // except scd_status.
 #include "../../include/scd.h"
 
-#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstring>
@@ -20,6 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t off[SCD_F_COUNT];
   size_t bytes[SCD_F_COUNT];
+  size_t parts;   // behind the fields: the LM head's sums over parts of k
   size_t total;
 };
 
@@ -48,6 +48,20 @@ uint32_t top_p24_of(const scd_config& c) {
   if (!(c.top_p > 0.f && c.top_p < 1.f)) return 0u;
   const long v = std::lround(static_cast<double>(c.top_p) * 16777216.0);
   return static_cast<uint32_t>(v < 1 ? 1 : v);
+}
+
+// The LM head's sums over parts of k: in how many parts scd_step has it dealt over workgroups, and their bytes.  They
+// lie at the end of the state, behind its fields: a state is stepped by one call at a time, while a workspace may serve
+// several (decodes of one context in two graphs, contexts on two streams), of which steps on rows without lists leave it alone.
+int parts_of(const scd_config& c) {
+  if (c.d <= 0) return 1;
+  scd::LmHeadArgs a{};
+  a.B = c.B; a.C = c.cfg_lambda != 0.f ? 2 : 1; a.L = c.L; a.d = c.d; a.n = c.v_hi - c.v_lo;
+  return scd::lm_head_ksplit(a);
+}
+size_t parts_need(const scd_config& c) {
+  const int parts = parts_of(c);
+  return parts > 1 ? sizeof(float) * parts * (c.cfg_lambda != 0.f ? 2 : 1) * c.B * c.L * (c.v_hi - c.v_lo) : 0;
 }
 
 Layout make_layout(const scd_config& c) {
@@ -83,7 +97,8 @@ Layout make_layout(const scd_config& c) {
     lay.bytes[f] = sz[f];
     o += align_up(sz[f]);
   }
-  lay.total = o;
+  lay.parts = o;
+  lay.total = o + align_up(parts_need(c));
   return lay;
 }
 
@@ -93,21 +108,9 @@ size_t small_need(const scd_config& c) {
   const size_t rows = static_cast<size_t>(c.B) * c.L;
   return 6 * align_up(4 * rows);
 }
-// The LM head's sums over parts of k: in how many parts scd_step has it dealt over workgroups, and their bytes.
-int parts_of(const scd_config& c) {
-  if (c.d <= 0) return 1;
-  scd::LmHeadArgs a{};
-  a.B = c.B; a.C = c.cfg_lambda != 0.f ? 2 : 1; a.L = c.L; a.d = c.d; a.n = c.v_hi - c.v_lo;
-  return scd::lm_head_ksplit(a);
-}
-size_t parts_need(const scd_config& c) {
-  const int parts = parts_of(c);
-  return parts > 1 ? sizeof(float) * parts * (c.cfg_lambda != 0.f ? 2 : 1) * c.B * c.L * (c.v_hi - c.v_lo) : 0;
-}
-// ... followed by the rows' candidate lists, in the place of which shorter rows have the LM head's
-// sums over parts of k (no row has both).
+// ... followed by the rows' candidate lists.
 size_t workspace_need(const scd_config& c) {
-  return small_need(c) + align_up(std::max(scd::row_candidate_bytes(c.B * c.L), parts_need(c)));
+  return small_need(c) + align_up(scd::row_candidate_bytes(c.B * c.L));
 }
 
 // ---- scratch of the entry point that allocates nothing -----------------------------------
@@ -431,7 +434,7 @@ int scd_step(scd_ctx* c, const uint16_t* d_h, const uint16_t* d_W, void* st) {
     a.flags = field<int32_t>(c, st, SCD_F_FLAGS);
   }
   if (const int parts = parts_of(c->cfg); parts > 1) {
-    a.part = reinterpret_cast<float*>(static_cast<char*>(c->ws) + small_need(c->cfg));
+    a.part = reinterpret_cast<float*>(static_cast<char*>(st) + c->lay.parts);
     a.ksplit = parts;
   }
   const bool timed = c->ev_start && c->ev_stop;

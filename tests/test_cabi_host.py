@@ -62,6 +62,24 @@ def test_size_queries_validate_config():
         assert B.state_bytes(cfg) == 0, kw
 
 
+@pytest.mark.parametrize("kw", [
+    dict(B=2, L=32, V=2048, d=2048, cfg_lambda=3.0, top_k=500),      # k in 4 parts
+    dict(B=1, L=64, V=4090, d=1280),                                  # in 4, without guidance
+    dict(B=5, L=26, V=1285, d=1288),                                  # in 2
+    dict(B=1, L=32, V=16384, d=1280, top_k=1000),                     # not split
+])
+def test_a_step_on_short_rows_has_its_scratch_in_the_state(kw):
+    """The workspace of such a context may serve another stream meanwhile: it holds what the stages and the lists need
+    (six words per row; 6144 pairs, 256 counts and 256 cuts per row), whether or not there is an LM head."""
+    cfg, bare = B.make_config(N=400, **kw), B.make_config(N=400, **dict(kw, d=0))
+    rows = kw["B"] * kw["L"]
+    up = lambda b: (b + 255) // 256 * 256  # noqa: E731
+    assert B.workspace_bytes(cfg) == 6 * up(4 * rows) + up(rows * 6144 * 8 + 2 * up(rows * 256 * 4))
+    assert B.workspace_bytes(cfg) == B.workspace_bytes(bare)
+    extra = B.state_bytes(cfg) - B.state_bytes(bare)
+    assert extra <= 4 << 20 and (extra > 0) == (kw["V"] < 16384)
+
+
 def test_create_rejects_bad_arguments_without_touching_the_device():
     lib = B.load()
     cfg = B.make_config(B=1, L=8, N=64, V=1024)

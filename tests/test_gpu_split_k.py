@@ -10,6 +10,12 @@ from paper_2510_24211_amd import workload as wl
 pytestmark = pytest.mark.gpu
 
 
+def _fields_end(sc, state):
+    views = [sc.state_field(state, f) for f in range(B.F_COUNT)]
+    end = max(v.data_ptr() + v.numel() * v.element_size() for v in views) - state.data_ptr()
+    return (end + 255) // 256 * 256
+
+
 @pytest.mark.parametrize("parts,kw,opts", [
     (2, dict(B=2, L=32, V=3000, d=1280, v_lo=3, v_hi=2900), dict()),              # five k-tiles of ten in flight, odd rows
     (2, dict(B=5, L=26, V=1285, d=1288, cfg_lambda=0.0), dict()),                 # ragged k-tile, 130 rows, no guidance
@@ -25,13 +31,14 @@ def test_lockstep_with_k_in_parts(parts, kw, opts):
     kw = dict(dict(N=3 * kw["L"] + 5, age_cap=8, top_k=kw["V"] // 5), **kw)
     w = wl.scaled(wl.WORKLOADS["C2"], name="parts", **dict(dict(v_lo=0, v_hi=kw["V"]), **kw))
     ls = LockStep(w, "cuda:0", **opts)
-    # the arrays of the parts, [parts, 1 + CFG, rows, n], behind six arrays of a word per row in the workspace
-    small = 6 * ((4 * w.B * w.L + 255) // 256 * 256) // 4
-    words = ls.gpu.workspace[:ls.gpu.workspace.numel() // 4 * 4].view(torch.int32)
+    # the arrays of the parts, [parts, 1 + CFG, rows, n], behind the fields of the state; the workspace is left alone
+    words = ls.state[_fields_end(ls.gpu, ls.state):].view(torch.int32)
     words.fill_(-1)
+    ls.gpu.workspace.fill_(0xA5)
     ls.step()
     used = parts * w.C * w.B * w.L * w.n_allowed
-    assert (words[small:small + used] != -1).all() and (words[small + used:] == -1).all()
+    assert (words[:used] != -1).all() and (words[used:] == -1).all() and words.numel() - used < 64
+    assert (ls.gpu.workspace == 0xA5).all()
     st = ls.run()
     assert ls.oracle.done()
     # the lock-step tests' bounds on adopted decisions; a logit itself has to lie within the measured-discrepancy cap
