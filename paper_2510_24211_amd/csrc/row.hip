@@ -769,8 +769,17 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
 // ---------------------------------------------------------------------------------
 // list kernel: the same lists from pieces that a wavefront holds in registers
 // ---------------------------------------------------------------------------------
-// A wavefront takes 64 E neighbouring ids of a row and emits the `cap` largest of them or somewhat fewer as (id, logit)
-// pairs in a fixed order, with their number and a cut: every logit of the piece that is not emitted lies below it.
+// A wavefront takes 64 E ids of a row, one line of 64 out of every P, and emits the `cap` largest of them or somewhat
+// fewer as (id, logit) pairs in a fixed order, with their number and a cut: every logit of the piece that is not emitted
+// lies below it.
+//   Lines are dealt over the pieces because likely ids tend to be neighbours: of neighbouring ids alone, a piece holds a
+// whole such neighbourhood, more than a list takes, and the row is read whole.  Four steps on supplied logits of 32 x 65536
+// ids, top-k 2000, in pieces of neighbours : of lines (us): independent logits 79.3 : 79.4, runs of 1024 ids that differ by
+// half of a logit's own deviation 183 : 78, logits falling with log(id) 209 : 76, one half masked 282 : 96, sorted 352 : 86;
+// of 32 x 131072, top-k 1000, 80.9 : 81.2, 285 : 82, 272 : 270, 855 : 114, 479 : 488.  Lines of 32 take falling logits there
+// too (81) but cost independent ones more (65536 ids 80.4, 81146 84.9 for 82.7 in lines of 64: rows of any length, whose lines
+// are not the memory's); lines of 128 fail runs of 128 to 512 ids.  A line's place moves by two from stripe to stripe: at one
+// place in all, a load's lines lie 8 KB apart at 65536 ids, on few channels (82.4).
 // As in the LM head's epilogue the emitted set is found on a monotone image of the logits, linear between their mean and
 // their largest: one LDS histogram per wavefront, the lowest bin whose upper set holds at most `cap`.  A list needs no exact
 // length, only to hold what the row's K-th largest leaves to this piece, so that bins of a few logits will do; where they
@@ -784,6 +793,7 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
 constexpr int kListBins = 256;
 constexpr int kListHist = kWave + kListBins;       // words: one per lane for what lies far below the bins
 constexpr int kListWaves = 4;                      // per workgroup
+constexpr int kListLine = 64, kListSkew = 2;
 constexpr float kListFloor = kRangeFloor;
 __device__ __forceinline__ float list_scale(float range) {
   return range > 0.f ? fminf(__builtin_amdgcn_rcpf(range) * (kListBins - 1.01f), 3.0e38f) : 0.f;
@@ -867,8 +877,23 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
   const int r = blockIdx.x, p = static_cast<int>(blockIdx.y) * kListWaves + wave;
   if (p >= P) return;
   uint32_t* const bins = hist + wave * kListHist + kWave;
-  const int lo_id = p * (kWave * E), hi_id = min(n_, lo_id + kWave * E);
-  auto group = [&](int u) { return lo_id + ((lane + u * kWave) << 2); };
+  // The piece's line of stripe j, P lines each, is its (p + 2 j mod P)-th; four stripes in a load, and only the last load's
+  // may end before their P lines (list_width).
+  constexpr int kLanes = kListLine / 4, kStripes = kWave / kLanes, kLast = E - 4;
+  int ids[E / 4];                                        // the lane's four of each load begin here
+  {
+    int j = lane / kLanes, at = p + kListSkew * j;
+    at = at >= P ? at - P : at;
+#pragma unroll
+    for (int u = 0; u < E / 4; ++u) {
+      ids[u] = (j * P + at) * kListLine + ((lane & (kLanes - 1)) << 2);
+      j += kStripes;
+      at += kListSkew * kStripes;
+      at = at >= P ? at - P : at;
+    }
+  }
+  auto group = [&](int u) { return ids[u]; };
+  const bool whole = __builtin_amdgcn_ballot_w64(group(E / 4 - 1) + 3 >= n_) == 0ull;
   float v[E];
   RowRef R;
   const float* row = rows_ + static_cast<size_t>(r) * n_;
@@ -877,37 +902,53 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
     if (!R.active) return;
     row = R.zc;
   }
-  load_groups<E>(row, hi_id, group, v);
+  load_groups<E>(row, n_, group, v);
   zero_list_bins(bins, lane);
   if (rows_) {                                           // (while they are on their way)
     R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
     if (!R.active) return;
   }
-  align_groups<E>(hi_id, group, v);
-  const bool whole = hi_id - lo_id == kWave * E;
+  int have = kWave * E;                                  // ids of the piece
+  float least[4], addend[4];                             // of the last load
+  {
+    float last[4] = {v[kLast], v[kLast + 1], v[kLast + 2], v[kLast + 3]};
+    align_groups<4>(n_, [&](int) { return group(E / 4 - 1); }, last);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[kLast + e] = least[e] = addend[e] = last[e];
+  }
+  if (!whole) {                                          // what lies past the end takes a value below every other's
+    have = kWave * kLast;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool is = group(E / 4 - 1) + e < n_;
+      have += __builtin_popcountll(__builtin_amdgcn_ballot_w64(is));
+      v[kLast + e] = is ? v[kLast + e] : -INFINITY;
+      least[e] = is ? least[e] : INFINITY;
+      addend[e] = is ? addend[e] : 0.f;
+    }
+  }
   float given[E];                                        // (the copy's: the logits may change below)
 #pragma unroll
   for (int e = 0; e < E; ++e) given[e] = v[e];
   float mx = -INFINITY, mn = INFINITY, sum = 0.f;
-  int there = kWave * E;                                 // logits above the floor
+  int there = have;                                      // logits above the floor
 #pragma unroll
   for (int e = 0; e < E; e += 2) {
     mx = max3(mx, v[e], v[e + 1]);
-    mn = min3(mn, v[e], v[e + 1]);
-    sum += v[e];
-    sum += v[e + 1];
+    mn = e < kLast ? min3(mn, v[e], v[e + 1]) : min3(mn, least[e & 3], least[(e & 3) + 1]);
+    sum += e < kLast ? v[e] : addend[e & 3];
+    sum += e < kLast ? v[e + 1] : addend[(e & 3) + 1];
   }
   bool nan = false;
-  if (!whole || __builtin_amdgcn_ballot_w64(!(mn > kListFloor && sum == sum)) != 0ull) {
-    // ragged, masked, or not finite: those do not count (they take a value below every other's from here on)
+  if (__builtin_amdgcn_ballot_w64(!(mn > kListFloor && sum == sum)) != 0ull) {
+    // masked, or not finite: those do not count either
     int mine = 0;
     sum = 0.f;
     mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      const bool is = group(e >> 2) + (e & 3) < hi_id;
-      nan |= is && v[e] != v[e];
-      const bool counts = is && v[e] > kListFloor;
+      nan |= v[e] != v[e];
+      const bool counts = v[e] > kListFloor;
       v[e] = counts ? v[e] : -INFINITY;
       sum += counts ? v[e] : 0.f;
       mx = fmaxf(mx, v[e]);
@@ -938,7 +979,7 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
     }
     wave_lds_fence();
     cut = list_cut(bins, lane, cap, total);
-    const int enough = min(cap - cap / 4, there * 3 / 8);    // (a short piece at the row's end has a smaller share)
+    const int enough = min(cap - cap / 4, there * 3 / 8);    // (a piece that is masked for the most part has a smaller share)
     if (__builtin_expect(total < enough, 0)) refine_list<E>(v, bin, cut, cap, enough, total, bins, lane);
   } else {
 #pragma unroll
@@ -964,12 +1005,12 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
 #pragma unroll
     for (int u = 0; u < E / 4; ++u) {
       const int v0 = group(u);
-      if (whole || v0 + 3 < hi_id) {
+      if (u < E / 4 - 1 || whole || v0 + 3 < n_) {
         store4_through(ring, v0, given[u * 4], given[u * 4 + 1], given[u * 4 + 2], given[u * 4 + 3]);
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (v0 + e < hi_id) R.zw[v0 + e] = given[u * 4 + e];
+          if (v0 + e < n_) R.zw[v0 + e] = given[u * 4 + e];
       }
     }
   }
@@ -978,7 +1019,7 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
     const bool good = all || (finite && at > 0);
     a.cand_cnt[list] = good && !nan ? static_cast<uint32_t>(at) : static_cast<uint32_t>(cap) + 1u;   // > cap: overflow
     // what is not emitted lies below this key: nothing (0), masked ids, everything below the smallest emitted
-    a.cand_cut[list] = !all ? zkey(vmin) : at == hi_id - lo_id ? 0u : zkey(kListFloor) + 1u;
+    a.cand_cut[list] = !all ? zkey(vmin) : at == have ? 0u : zkey(kListFloor) + 1u;
   }
 }
 
@@ -989,7 +1030,8 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
 int list_width(int n, int top_k) {
   for (int per : {16, 32}) {
     const int P = (n + kWave * per - 1) / (kWave * per);
-    if (P > kRowMaxTiles) continue;
+    // list_kernel looks for the row's end in the last load only: a piece has `per` lines, its last four may be missing
+    if (P > kRowMaxTiles || (P - 1) * per < (per - 4) * P) continue;
     const double cap = kRowListCap / P, mean = static_cast<double>(top_k) / P;
     if (mean + 5.0 * std::sqrt(mean) + 4.0 <= 0.75 * cap) return per;
   }

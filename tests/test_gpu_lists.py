@@ -26,7 +26,7 @@ def _rows(kind, rows, n, seed):
         z[mask] = float("-inf") if kind == "masked" else -1.0e10
     elif kind == "lopsided":
         z = -torch.exp(z)
-    elif kind == "sorted":                     # one piece holds most of the top-k: its list overflows the certificate
+    elif kind == "sorted":
         z = torch.sort(z, dim=1).values
     elif kind == "tied":
         z = torch.round(z)
@@ -79,3 +79,39 @@ def test_lists_do_not_depend_on_the_alignment_and_are_repeatable(n, top_k, kind)
     for other in got[1:]:
         for a, b in zip(got[0], other):
             assert np.array_equal(a, b)
+
+
+def _certified(sc, rows, n, top_k, thr):
+    """Whether each row's lists were enough: none overflowed, and its threshold is not below their largest cut."""
+    for per in (1024, 2048):                   # ids per list, as the launcher picks them
+        lists = -(-n // per)
+        if lists <= 256 and top_k / lists + 5 * (top_k / lists) ** 0.5 + 4 <= 0.75 * (6144 // lists):
+            break
+    behind = 6 * ((4 * rows + 255) // 256 * 256) + rows * 6144 * 8
+    block = (rows * 256 * 4 + 255) // 256 * 256
+    words = lambda at: sc.workspace[at:at + 4 * rows * lists].view(torch.int32).view(rows, lists).cpu().numpy()  # noqa: E731
+    counts, cuts = words(behind), words(behind + block).view(np.uint32)
+    bits = thr.cpu().numpy().view(np.uint32)
+    key = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31))
+    return (counts <= 6144 // lists).all(1) & (counts.sum(1) >= top_k) & (key >= cuts.max(1))
+
+
+@pytest.mark.parametrize("n,top_k", [(65536, 2000), (81146, 2000), (30001, 1500), (16385, 1000), (131071, 1000)])
+def test_neighbours_that_are_likely_together_do_not_overflow_a_list(n, top_k):
+    """Ids whose logits rise and fall together in runs, fall with the id, or are masked over a range: the lists still hold
+    every row's top-k, so that no row is read whole."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    z = 2.0 * torch.randn(6, n, device=DEV, generator=g)
+    ids = torch.arange(n, device=DEV)
+    for row, width in ((0, 1024), (1, 200)):
+        z[row] += 0.75 * torch.randn(-(-n // width), device=DEV, generator=g).repeat_interleave(width)[:n]
+    z[2] -= 0.5 * torch.log1p(ids.float())
+    z[3, n // 3:] = float("-inf")
+    z[4, :n // 2] = -1.0e10
+    rows = len(z)
+    sc = B.Scd(B.make_config(B=1, L=rows, N=400, V=n, top_k=top_k, seed=3), DEV)
+    thr, lse = torch.empty(rows, device=DEV), torch.empty(rows, device=DEV)
+    nk = torch.empty(rows, dtype=torch.int32, device=DEV)
+    sc.select(z, rows, thr, lse, nk)
+    assert torch.equal(thr, torch.topk(z, top_k, dim=1).values[:, -1])
+    assert _certified(sc, rows, n, top_k, thr).all()
