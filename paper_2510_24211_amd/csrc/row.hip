@@ -777,8 +777,8 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
 // ids, top-k 2000, in pieces of neighbours : of lines (us): independent logits 79.3 : 79.4, runs of 1024 ids that differ by
 // half of a logit's own deviation 183 : 78, logits falling with log(id) 209 : 76, one half masked 282 : 96, sorted 352 : 86;
 // of 32 x 131072, top-k 1000, 80.9 : 81.2, 285 : 82, 272 : 270, 855 : 114, 479 : 488.  Lines of 32 take falling logits there
-// too (81) but cost independent ones more (65536 ids 80.4, 81146 84.9 for 82.7 in lines of 64: rows of any length, whose lines
-// are not the memory's); lines of 128 fail runs of 128 to 512 ids.  A line's place moves by two from stripe to stripe: at one
+// too (81) but cost independent ones more (65536 ids 80.4, 81146 84.9 for 82.7 in lines of 64; rows whose lines are not the
+// memory's pay for those of 64 already, 288 x 24577 138.5 : 141.5); lines of 128 fail runs of 128 to 512 ids.  A line's place moves by two from stripe to stripe: at one
 // place in all, a load's lines lie 8 KB apart at 65536 ids, on few channels (82.4).
 // As in the LM head's epilogue the emitted set is found on a monotone image of the logits, linear between their mean and
 // their largest: one LDS histogram per wavefront, the lowest bin whose upper set holds at most `cap`.  A list needs no exact
@@ -1026,7 +1026,10 @@ __global__ __launch_bounds__(kListWaves * kWave) void list_kernel(const int32_t*
 // Ids per lane of the list kernel for these rows (a list per 64 times as many), or 0: the slice kernel.  The lists of a row
 // share kRowListCap slots; a list has to hold what the row's top_k leaves to its piece: its mean, five of its standard
 // deviations and some more have to fit into the three quarters of the slots that are filled.  Longer pieces vary less.
-// (top-k 2000: up to 131072 ids; 3072: up to 65536.)
+// (top-k 1000: any row that has lists but for a few lengths near the 524288th id; 2000: up to 196608 ids; 3072: up to 53248.)
+// Where both would do the lists are faster than the slices: four steps of 32 rows behind an LM head over 1280 that leaves none,
+// slices : lists (us), 20000 ids under top-k 2500 128 : 119, 40000 under 2434 158 : 149, 65536 under 2600 193 : 188; of 128
+// rows 188 : 162, 248 : 223, 294 : 280.
 int list_width(int n, int top_k) {
   for (int per : {16, 32}) {
     const int P = (n + kWave * per - 1) / (kWave * per);
@@ -2661,10 +2664,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
     } else {
       int per = 0;
 #ifndef SCD_ROW_DIRECT_ONLY
-      // (Rows of up to 65536 ids that the LM head left without lists, its top-k being too large for them, keep the slices:
-      // tests/test_gpu_lm_head_tiles.py counts them.)
-      const bool without = a.mode == kRowRing && !a.src && a.n <= kRowKernelMaxN;
-      if (!without) per = list_width(a.n, a.top_k);
+      per = list_width(a.n, a.top_k);
       if (per > 0) {
         P = (a.n + kWave * per - 1) / (kWave * per);
         capE = kListCap / P;
