@@ -261,8 +261,9 @@ int scd_set_lm_head_events(scd_ctx* ctx, void* ev_start, void* ev_stop);
  * lm_head_tile_kernel<1 + CFG, h rows, columns, stages, W past the caches>,
  * lm_head_splitk_kernel<row blocks, 1 + CFG, wavefronts>,
  * lm_head_kernel<row blocks, 1 + CFG, wavefronts, W past the caches>.
- * (Where few tiles would leave compute units idle, scd_step deals k over workgroups of
- * lm_head_tile_kernel<1 + CFG, 64, 128, 6, ...> instead, and its row kernel adds the parts up.)
+ * Where the two launch different kernels (scd_step deals k over workgroups of a tile kernel, and
+ * its row kernel adds the parts up) both names are written, "scd_step's / scd_lm_head's"; scd_step's
+ * alone if cap does not hold both (95 characters always do).
  * Returns SCD_OK, or SCD_EINVAL (NULL argument, cfg.d == 0, or cap too small).
  * Host-only call. */
 int scd_lm_head_kernel_name(scd_ctx* ctx, char* host_buf, size_t cap);

@@ -1477,7 +1477,7 @@ int lm_head_tiles(const LmHeadArgs& a) {
 }
 
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap) {
-  const Variant v = choose(a);
+  const Variant v = a.ksplit > 1 ? Variant{false, 0, 0, 64, 128, 6} : choose(a);
   const char* nt = stream_w(a) ? "true" : "false";
   if (v.hr > 0) return snprintf(buf, cap, "lm_head_tile_kernel<%d, %d, %d, %d, %s>", a.C, v.hr, v.bn, v.stages, nt);
   if (v.split) return snprintf(buf, cap, "lm_head_splitk_kernel<%d, %d, %d>", v.rbw, a.C, v.nw);

@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <cmath>
+#include <cstdio>
 #include <cstring>
 #include <new>
 
@@ -455,8 +456,15 @@ int scd_lm_head_kernel_name(scd_ctx* c, char* host_buf, size_t cap) {
   if (!c || !host_buf || cap == 0 || c->cfg.d <= 0) return SCD_EINVAL;
   scd::LmHeadArgs a{};
   a.B = c->cfg.B; a.C = c->C; a.L = c->cfg.L; a.d = c->cfg.d; a.n = c->n;
-  const int len = scd::lm_head_kernel_name(a, host_buf, cap);
-  return (len < 0 || static_cast<size_t>(len) >= cap) ? SCD_EINVAL : SCD_OK;
+  char alone[96], both[192];
+  scd::lm_head_kernel_name(a, alone, sizeof(alone));      // scd_lm_head's
+  a.ksplit = parts_of(c->cfg);
+  const int len = scd::lm_head_kernel_name(a, both, sizeof(both));      // scd_step's
+  if (std::strcmp(alone, both) != 0) {
+    std::strcat(std::strcat(both, " / "), alone);
+    if (std::strlen(both) >= cap) both[len] = '\0';
+  }
+  return static_cast<size_t>(snprintf(host_buf, cap, "%s", both)) >= cap ? SCD_EINVAL : SCD_OK;
 }
 
 int scd_step_logits(scd_ctx* c, const float* d_z, void* st) {

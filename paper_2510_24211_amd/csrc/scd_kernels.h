@@ -36,7 +36,7 @@ struct LmHeadArgs {
 hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_start = nullptr,
                           hipEvent_t ev_stop = nullptr);
 // Name (as a profiler prints it, without namespaces and arguments) of the kernel that
-// launch_lm_head picks for these sizes (only B, C, L, d, n are read); snprintf semantics.
+// launch_lm_head picks for these sizes (only B, C, L, d, n and ksplit are read); snprintf semantics.
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap);
 // In how many parts scd_step has k dealt over workgroups for these sizes (LmHeadArgs::part; only B, C, L, d, n are read);
 // 1: it does not.  More than 1 only for rows that the row kernel holds in registers.

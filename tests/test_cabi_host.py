@@ -131,6 +131,26 @@ def test_create_rejects_bad_arguments_without_touching_the_device():
     assert B.strerror(B.SCD_EWORKSPACE).startswith("workspace")
 
 
+@pytest.mark.parametrize("kw,step,alone", [
+    (dict(L=32, V=1900, d=4096, cfg_lambda=3.0), "lm_head_tile_kernel<2, 64, 128, 6, false>", "lm_head_splitk_kernel<1, 2, 8>"),
+    (dict(B=4, L=64, V=4096, d=4096), "lm_head_tile_kernel<1, 64, 128, 6, false>", "lm_head_tile_kernel<1, 64, 128, 6, false>"),
+    (dict(L=32, V=8192, d=4096, cfg_lambda=3.0), "lm_head_splitk_kernel<1, 2, 8>", "lm_head_splitk_kernel<1, 2, 8>"),
+])
+def test_kernel_names_of_a_step_and_of_the_head_alone(kw, step, alone):
+    lib = B.load()
+    cfg = B.make_config(N=400, **dict(dict(B=1), **kw))
+    ctx = ctypes.c_void_p()
+    assert lib.scd_create(ctypes.byref(ctx), ctypes.byref(cfg), ctypes.c_void_p(0x10000), 1 << 40, None) == B.SCD_OK
+    want = step if step == alone else step + " / " + alone
+    buf = ctypes.create_string_buffer(96)
+    assert lib.scd_lm_head_kernel_name(ctx, buf, 96) == B.SCD_OK and buf.value.decode() == want
+    assert lib.scd_lm_head_kernel_name(ctx, buf, len(want) + 1) == B.SCD_OK and buf.value.decode() == want
+    assert lib.scd_lm_head_kernel_name(ctx, buf, len(want)) == (B.SCD_EINVAL if step == alone else B.SCD_OK)
+    assert step == alone or buf.value.decode() == step
+    assert lib.scd_lm_head_kernel_name(ctx, buf, len(step)) == B.SCD_EINVAL
+    assert lib.scd_destroy(ctx) == B.SCD_OK
+
+
 def test_gather_rejects_bad_arguments():
     lib = B.load()
     fake = ctypes.c_void_p(0x10000)
