@@ -1460,8 +1460,8 @@ int lm_head_ksplit(const LmHeadArgs& a) {
   const long rows = static_cast<long>(a.B) * a.L;
   const long tiles = (rows * a.C + 63) / 64 * ((a.n - 1) / 128 + 1);
   const int KT = a.d / 64;
-  if (a.n < 256 || a.n > kRowDirectMaxN || tiles > 64) return 1;
-  int ks = a.n <= 2048 ? kMaxKSplit : 4;             // (registers of the row kernel)
+  if (a.n < 256 || a.n > kRowPartsMaxN || tiles > 64) return 1;
+  int ks = a.n <= kRowPartsMaxN / 2 ? kMaxKSplit : 4;
   while (ks > 1 && (tiles * ks > 128 || KT < 4 * ks)) ks /= 2;
   const int least = rows <= 32 ? (KT < 64 ? kMaxKSplit + 1 : a.C == 2 ? 4 : 8)
                     : KT < 20 ? kMaxKSplit + 1 : a.C == 1 && rows <= 128 ? 4 : 2;

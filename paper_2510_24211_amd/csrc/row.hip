@@ -675,6 +675,7 @@ __device__ __forceinline__ void align_groups(int end, Group&& group, float (&z)[
   }
 }
 
+#ifndef SCD_ROW_DIRECT_ONLY
 // ---------------------------------------------------------------------------------
 // slice kernel: lists from slices of 8192 ids by an exact rank (see list_kernel and list_width)
 // ---------------------------------------------------------------------------------
@@ -765,7 +766,6 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
   }
 }
 
-#ifndef SCD_ROW_DIRECT_ONLY
 // ---------------------------------------------------------------------------------
 // list kernel: the same lists from pieces that a wavefront holds in registers
 // ---------------------------------------------------------------------------------
@@ -2231,17 +2231,14 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
   if constexpr (PARTS) {
     const size_t arr = static_cast<size_t>(a.rows) * n;                         // floats between the arrays [part][cond, uncond]
     const float* const mine = a.part + R.widx * n;
-    auto previous = [&]() {
-      if (PREQ) load_groups<PER>(R.zp, n, group, zq);
-      read_row_scalars(a, R);
-    };
+    static_assert(!PREQ, "the previous logits are not read here");
     zcx = 0.f;
     auto add_up = [&](auto c_, auto ks_) {
       constexpr int C = decltype(c_)::value, KS = decltype(ks_)::value;
       float t[C * KS][PER];
 #pragma unroll
       for (int q = 0; q < C * KS; ++q) load_groups<PER>(mine + q * arr, n, group, t[q]);   // q = part * C + {cond, uncond}
-      previous();
+      read_row_scalars(a, R);
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
         float c = t[0][e], u = t[C - 1][e];
@@ -2266,13 +2263,11 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
       }
     };
     using std::integral_constant;
-    auto by_parts = [&](auto c_) {
+    auto by_parts = [&](auto c_) {                                              // (as many as launch_row lets through)
       if constexpr (PER <= 4) {
         if (a.ksplit == 8) return add_up(c_, integral_constant<int, 8>{});
       }
-      if constexpr (PER <= 8) {
-        if (a.ksplit == 4) return add_up(c_, integral_constant<int, 4>{});
-      }
+      if (a.ksplit == 4) return add_up(c_, integral_constant<int, 4>{});
       add_up(c_, integral_constant<int, 2>{});
     };
     if (a.C == 2) by_parts(integral_constant<int, 2>{});
@@ -2330,7 +2325,7 @@ __device__ __forceinline__ void inactive_row(const RowArgs& a, const RowRef& R) 
 // with all of them in one kernel the compiler keeps every way's arguments in scalar registers and spills them
 // (184 spills; 46 vector registers spilled in the optional instances).  Four-step decodes over 8192 ids: 132 ->
 // 129 us, with every option 206 -> 193 us.
-enum Path { kDirectTiny, kDirectQuarter, kDirectHalf, kDirectWhole, kPartsQuarter, kPartsHalf, kPartsWhole, kLists, kLong, kNucleusHalf, kNucleusWhole };
+enum Path { kDirectTiny, kDirectQuarter, kDirectHalf, kDirectWhole, kPartsQuarter, kPartsHalf, kLists, kLong, kNucleusHalf, kNucleusWhole };
 template <bool GS, bool EXTRA, int PATH>
 __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
     const int32_t* const pos_, const int32_t* const iter_, const uint2* const cand_, const uint32_t* const cand_cnt_,
@@ -2344,7 +2339,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
   RowOut out{};
   out.accept = true;
   if (tid < 2) sm.win[tid] = ~0ull;          // (barriers stand between this and the races)
-  if constexpr (PATH <= kPartsWhole) {
+  if constexpr (PATH <= kPartsHalf) {
     R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
     if (!R.active) {
       inactive_row<GS, EXTRA>(a, R);
@@ -2352,8 +2347,7 @@ __global__ __launch_bounds__(THREADS, SCD_ROW_WAVES(EXTRA)) void row_kernel(
     }
     // ---- the whole row in registers ------------------------------------------------
     constexpr bool PARTS = PATH >= kPartsQuarter;
-    constexpr int PER = PATH == kDirectWhole || PATH == kPartsWhole ? PER_DIRECT
-                        : PATH == kDirectHalf || PATH == kPartsHalf ? PER_DIRECT / 2 : PER_DIRECT / 4;
+    constexpr int PER = PATH == kDirectWhole ? PER_DIRECT : PATH == kDirectHalf || PATH == kPartsHalf ? PER_DIRECT / 2 : PER_DIRECT / 4;
     direct_path<PER, PATH == kDirectTiny, PARTS, GS, EXTRA>(a, R, smem, a.top_k > 0 && a.top_k < n, sm, out);
   } else if constexpr (PATH == kNucleusHalf || PATH == kNucleusWhole) {
     R = locate_row(a, r, pos_, iter_, mode_, L_, N_);
@@ -2655,6 +2649,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   a.recip_L = a.L > 1 && most_v * a.L < (1ll << 32) ? static_cast<uint32_t>(((1ull << 32) + a.L - 1) / a.L) : 0u;
   int P = 0, capE = 0;
   a.cand = nullptr;
+#ifndef SCD_ROW_DIRECT_ONLY
   if (a.cand_base && row_uses_candidates(a.n, a.top_k)) {
     row_candidate_layout(a.cand_base, a.rows, &a.cand, &a.cand_cnt, &a.cand_cut);
     if (a.tiles > 0) {
@@ -2662,18 +2657,14 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       P = a.tiles;
       capE = kListCap / P;
     } else {
-      int per = 0;
-#ifndef SCD_ROW_DIRECT_ONLY
-      per = list_width(a.n, a.top_k);
+      const int per = list_width(a.n, a.top_k);
       if (per > 0) {
         P = (a.n + kWave * per - 1) / (kWave * per);
         capE = kListCap / P;
         hipLaunchKernelGGL(per == 16 ? list_kernel<16> : list_kernel<32>, dim3(a.rows, (P + kListWaves - 1) / kListWaves),
                            dim3(kListWaves * kWave), 0, s, a.pos, a.iter,
                            a.src ? a.src : a.mode == kRowRing ? nullptr : a.z_cur, a.mode, a.L, a.N, a.n, P, capE, a);
-      }
-#endif
-      if (per == 0) {
+      } else {
         P = (a.n + kSliceMax - 1) / kSliceMax;                   // 3 .. kRowMaxTiles
         capE = kListCap / P;
         int rank = (2 * a.top_k + P - 1) / P;
@@ -2689,6 +2680,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
       if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
   }
+#endif
 #ifdef SCD_ROW_DIRECT_ONLY
   const size_t lds = lds_bytes_for(a.n), most = lds_bytes_for(kDirectMaxN);
 #else
@@ -2707,11 +2699,10 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
 #elif defined(SCD_ROW_BATCHED)
       SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
       {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr},
-      SCD_ROW_INSTANCES(kPartsQuarter), SCD_ROW_INSTANCES(kPartsHalf),
-      {row_kernel<false, false, kPartsWhole>, row_kernel<true, false, kPartsWhole>, nullptr, nullptr}
+      SCD_ROW_INSTANCES(kPartsQuarter), SCD_ROW_INSTANCES(kPartsHalf)
 #else
       {}, {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
-      {}, SCD_ROW_INSTANCES(kPartsHalf), SCD_ROW_INSTANCES(kPartsWhole), SCD_ROW_INSTANCES(kLists),
+      {}, {}, SCD_ROW_INSTANCES(kLists),
       {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
       {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
       {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
@@ -2739,7 +2730,12 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   int path = a.n <= kDirectMaxN / 2 ? kDirectHalf : a.n <= kDirectMaxN ? kDirectWhole
                    : nucleus ? (a.n <= 32 * THREADS ? kNucleusHalf : kNucleusWhole) : a.n <= kRowKernelMaxN ? kLists : kLong;
 #endif
-  if (a.part) path += kPartsQuarter - kDirectQuarter;
+  if (a.part) {
+    const bool quarter = path == kDirectQuarter;
+    if (!(quarter || path == kDirectHalf) || !(a.ksplit == 2 || a.ksplit == 4 || (quarter && a.ksplit == 8)))
+      return hipErrorInvalidValue;                   // sums that no instance adds up
+    path += kPartsQuarter - kDirectQuarter;
+  }
   const Kernel kernel = kernels[path][(gs ? 1 : 0) + (extra ? 2 : 0)];
   if (!kernel) return hipErrorInvalidValue;          // long rows with options: refused when the context is created
   hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(THREADS), lds, s, a.pos, a.iter, a.cand, a.cand_cnt, a.mode, a.L, a.N, P, capE,

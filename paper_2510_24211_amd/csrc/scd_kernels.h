@@ -39,8 +39,10 @@ hipError_t launch_lm_head(const LmHeadArgs& a, hipStream_t s, hipEvent_t ev_star
 // launch_lm_head picks for these sizes (only B, C, L, d, n and ksplit are read); snprintf semantics.
 int lm_head_kernel_name(const LmHeadArgs& a, char* buf, size_t cap);
 // In how many parts scd_step has k dealt over workgroups for these sizes (LmHeadArgs::part; only B, C, L, d, n are read);
-// 1: it does not.  More than 1 only for rows that the row kernel holds in registers.
+// 1: it does not.  More than 1 only for rows of up to kRowPartsMaxN ids: the row kernels that hold up to 8 logits per
+// thread add up to 4 parts, those that hold 4 (rows of up to half as many) up to 8.
 int lm_head_ksplit(const LmHeadArgs& a);
+constexpr int kRowPartsMaxN = 4096;
 constexpr int kMaxKSplit = 8;
 // Slots that the epilogue may leave free in a tile's list of cand_cap (unless logits tie or are not finite).
 constexpr int kTileSlack = 8;
@@ -138,6 +140,7 @@ hipError_t launch_row(const RowArgs& a, hipStream_t s, size_t* lds_configured);
 // workgroups per compute unit); launch_row hands over to it when there are more rows than
 // compute units, and rows of up to half that length in any case.  lds_configured: one word.
 constexpr int kRowBatchedMaxN = 8192;
+static_assert(kRowPartsMaxN <= kRowBatchedMaxN / 2, "parts are added up in these kernels");
 hipError_t launch_row_batched(const RowArgs& a, hipStream_t s, size_t* lds_configured);
 // And with 256 threads per row for rows of at most kRowShortMaxN ids; its commit takes windows of up to kRowShortMaxL
 // positions (three of the four wavefronts prepare it).

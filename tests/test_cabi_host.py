@@ -80,6 +80,22 @@ def test_a_step_on_short_rows_has_its_scratch_in_the_state(kw):
     assert extra <= 4 << 20 and (extra > 0) == (kw["V"] < 16384)
 
 
+def test_k_is_dealt_in_parts_that_the_row_kernels_add_up():
+    """Eight logits per thread in up to 4 parts (rows of up to 4096 ids), four (2048) in up to 8; longer rows in one."""
+    seen = set()
+    for n in (255, 256, 1000, 1024, 1025, 2048, 2049, 3000, 4095, 4096, 4097, 5000, 8192, 8193, 16384):
+        for rows in (1, 8, 32, 33, 60, 64, 65, 96, 97, 128, 129, 256, 500, 1024):
+            for d in (64, 1024, 1280, 2048, 4096, 16384):
+                for lam in (0.0, 3.0):
+                    kw = dict(B=-(-rows // 64), L=min(rows, 64), N=400, V=n, cfg_lambda=lam)
+                    extra = B.state_bytes(B.make_config(d=d, **kw)) - B.state_bytes(B.make_config(**kw))
+                    one = 4 * kw["B"] * kw["L"] * n * (2 if lam else 1)
+                    parts = extra // one                 # (each array's share of the last 255 bytes is less than one)
+                    assert extra - parts * one < 256 and parts in ((0, 2, 4, 8) if n <= 2048 else (0, 2, 4) if n <= 4096 else (0,))
+                    seen.add((n <= 2048, parts))
+    assert {(True, 2), (True, 4), (True, 8), (False, 2), (False, 4)} <= seen
+
+
 def test_create_rejects_bad_arguments_without_touching_the_device():
     lib = B.load()
     cfg = B.make_config(B=1, L=8, N=64, V=1024)
