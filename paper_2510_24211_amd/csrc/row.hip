@@ -52,6 +52,7 @@
 // share a CU and the barrier-separated phases of one row overlap with another's instead of the rows queueing in rounds.
 #include "scd_device.h"
 #include "scd_kernels.h"
+#include "window_division.h"
 
 #include <algorithm>
 #include <cmath>
@@ -560,11 +561,6 @@ struct RowRef {
   size_t pidx;    // where the previous evaluation of the slot left its per-slot results (ring mode)
 };
 
-// v / L: by the reciprocal where launch_row has found that to be exact for every v that occurs (a division is about thirty
-// instructions, in every wavefront).
-__device__ __forceinline__ int div_window(int v, int L, uint32_t recip) {
-  return recip != 0u ? static_cast<int>(__umulhi(static_cast<uint32_t>(v), recip)) : v / L;
-}
 // pos, iter, mode, L, N repeat a.pos, a.iter, mode, L, N: the kernels receive them as plain
 // leading arguments, which the hardware preloads into SGPRs at wavefront launch, so that the first
 // dependent load (pos[b]) does not wait for a fetch of the kernel-argument segment.
@@ -2644,9 +2640,7 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
 #endif
   RowArgs a = a_in;
   a.q_uniform = 1.0f / static_cast<float>(a.n);
-  // ceil(2^32 / L) gives v / L by a multiplication for v L < 2^32 (its excess over 2^32 / L is below 1)
-  const int64_t most_v = std::max<int64_t>(a.rows, static_cast<int64_t>(a.N) + 2 * a.L);
-  a.recip_L = a.L > 1 && most_v * a.L < (1ll << 32) ? static_cast<uint32_t>(((1ull << 32) + a.L - 1) / a.L) : 0u;
+  a.recip_L = window_reciprocal(a.rows, a.N, a.L);
   int P = 0, capE = 0;
   a.cand = nullptr;
 #ifndef SCD_ROW_DIRECT_ONLY
