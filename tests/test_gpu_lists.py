@@ -1,5 +1,5 @@
-"""Candidate lists of supplied logits: every decision on rows of all kinds must equal the one on the row read whole (the
-entry point without lists takes that path for them), bit for bit; and the selection must equal the oracle's."""
+"""Candidate lists of supplied logits on rows of all kinds: the selection must equal the oracle's and that of rows read whole
+bit for bit, and so must every decision of a draft (the entry point without lists reads long rows whole)."""
 import numpy as np
 import pytest
 import torch
@@ -35,16 +35,26 @@ def _rows(kind, rows, n, seed):
     return z.contiguous()
 
 
-@pytest.mark.parametrize("n,top_k", [
-    (16385, 1500),       # the last piece holds one id
-    (16385, 3072),
-    (17411, 20),         # three ids of a last group
-    (65536, 2000),
-    (65535, 3072),       # pieces of 2048
-    (131071, 2000),      # pieces of 2048, rows of more than 65536 ids
-    (131072, 300),
+def _list_words(sc, rows):
+    """Counts and cuts of a call's lists: behind six arrays of a word per row and 6144 pairs per row."""
+    behind = 6 * ((4 * rows + 255) // 256 * 256) + rows * 6144 * 8
+    block = (rows * 256 * 4 + 255) // 256 * 256
+    return [sc.workspace[at:at + 4 * rows * 256].view(torch.int32) for at in (behind, behind + block)]
+
+
+@pytest.mark.parametrize("n,top_k,lists", [
+    (16385, 1500, 17),       # pieces of 1024 ids in lines of 64; one id in the last line
+    (16385, 3072, 17),
+    (17411, 20, 18),         # three ids of a last group
+    (65536, 2000, 64),
+    (53000, 3072, 26),       # pieces of 2048 ids
+    (65535, 3072, 8),        # slices of 8192
+    (98305, 2000, 49),       # pieces of 2048, rows of more than 65536 ids
+    (131071, 2000, 64),
+    (131072, 300, 128),
+    (510007, 1000, 250),
 ])
-def test_selection_on_rows_of_all_kinds(n, top_k):
+def test_selection_on_rows_of_all_kinds(n, top_k, lists):
     rows = len(KINDS)
     z = torch.cat([_rows(kind, 1, n, n + i) for i, kind in enumerate(KINDS)])
     sc = B.Scd(B.make_config(B=1, L=rows, N=400, V=n, top_k=top_k, seed=3), DEV)
@@ -52,6 +62,13 @@ def test_selection_on_rows_of_all_kinds(n, top_k):
     nk = torch.empty(rows, dtype=torch.int32, device=DEV)
     sc.workspace.fill_(0xEE)                   # slots that nobody writes must not be read as pairs
     sc.select(z, rows, thr, lse, nk)
+    for words in _list_words(sc, rows):
+        written = words != -0x11111112
+        assert written[:rows * lists].all() and not written[rows * lists:].any()
+    # a call for more rows than the workspace has lists for reads every row whole
+    more = [torch.empty(rows + 1, dtype=t.dtype, device=DEV) for t in (thr, lse, nk)]
+    sc.select(torch.cat([z, z[:1]]), rows + 1, *more)
+    assert torch.equal(more[0][:rows], thr) and torch.equal(more[2][:rows], nk)
     for i, kind in enumerate(KINDS):
         row = z[i].cpu().numpy()
         _, want, want_lse = lg.distribution(row, top_k)
@@ -81,16 +98,32 @@ def test_lists_do_not_depend_on_the_alignment_and_are_repeatable(n, top_k, kind)
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("n,top_k", [(65537, 1500), (98305, 2000), (131071, 2000)])      # pieces of 1024, of 2048
+def test_drafts_from_lists_are_those_of_rows_read_whole(n, top_k):
+    Bn, L = 8, 21                              # 168 rows: more than the static array holds lists for
+    z, z_prev = (torch.cat([_rows(KINDS[i % len(KINDS)], 1, n, seed + i) for i in range(Bn * L)]) for seed in (n, 2 * n))
+    z_prev = torch.where(torch.isfinite(z), 0.4 * z_prev + 0.6 * z, z)      # (the same ids masked; near the other rows)
+    sc = B.Scd(B.make_config(B=Bn, L=L, N=400, V=n, top_k=top_k, seed=3), DEV)
+    x = z_prev.argmax(1).to(torch.int32).view(Bn, L)
+    fresh = (torch.arange(L, device=DEV) % 4 == 3).to(torch.uint8).repeat(Bn, 1)
+    pos = torch.arange(0, 50 * Bn, 50, dtype=torch.int32, device=DEV)
+    got = []
+    for call in (sc.couple_draft, sc.couple_draft_static):
+        y, k = torch.empty(Bn, L, dtype=torch.int32, device=DEV), torch.empty(Bn, L, dtype=torch.uint8, device=DEV)
+        call(z, z_prev, x, fresh, pos, 4, y, k)
+        got.append((y, k))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert 0 < int((got[0][1] == 0).sum()) < Bn * L
+
+
 def _certified(sc, rows, n, top_k, thr):
     """Whether each row's lists were enough: none overflowed, and its threshold is not below their largest cut."""
     for per in (1024, 2048):                   # ids per list, as the launcher picks them
         lists = -(-n // per)
         if lists <= 256 and top_k / lists + 5 * (top_k / lists) ** 0.5 + 4 <= 0.75 * (6144 // lists):
             break
-    behind = 6 * ((4 * rows + 255) // 256 * 256) + rows * 6144 * 8
-    block = (rows * 256 * 4 + 255) // 256 * 256
-    words = lambda at: sc.workspace[at:at + 4 * rows * lists].view(torch.int32).view(rows, lists).cpu().numpy()  # noqa: E731
-    counts, cuts = words(behind), words(behind + block).view(np.uint32)
+    counts, cuts = (w[:rows * lists].view(rows, lists).cpu().numpy() for w in _list_words(sc, rows))
+    cuts = cuts.view(np.uint32)
     bits = thr.cpu().numpy().view(np.uint32)
     key = np.where(bits >> 31, ~bits, bits | np.uint32(1 << 31))
     return (counts <= 6144 // lists).all(1) & (counts.sum(1) >= top_k) & (key >= cuts.max(1))

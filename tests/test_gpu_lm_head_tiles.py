@@ -89,6 +89,8 @@ def test_logits_against_64_bits(Bn, L, n, d, lam, kernel):
     (5, 50, 65536, 64, 0.0, 2000, "tile_kernel<1, 256, 256, 3, false>", 256),     # 250 rows in two passes
     (1, 8, 40000, 64, 3.0, 2433, "tile_kernel<2, 64, 256, 4, false>", 157),       # the largest top-k for these lists
     (1, 8, 40000, 64, 3.0, 2434, "tile_kernel<2, 64, 256, 4, false>", 40),        # one more: a list per 1024 ids
+    (1, 8, 50001, 64, 3.0, 3000, "tile_kernel<2, 64, 256, 4, false>", 25),        # a list per 2048 ids
+    (2, 7, 100003, 64, 3.0, 2000, "tile_kernel<2, 64, 256, 4, false>", 49),       # more tiles than a row has room for lists
 ])
 def test_step_selects_what_a_selection_over_its_logits_does(Bn, L, n, d, lam, top_k, kernel, lists):
     C = 2 if lam else 1

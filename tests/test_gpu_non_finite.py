@@ -127,3 +127,23 @@ def test_lists_of_the_lm_head(L, n, d, lam, top_k, kernel):
         assert rc == B.SCD_OK and fault == 0 and bool((z[:, n // 2] == -INF).all())
         want = torch.topk(z, top_k, dim=1).values[:, -1]
         assert torch.equal(thr, want) and torch.equal(nkept.long(), (z >= want[:, None]).sum(1))
+
+
+@pytest.mark.parametrize("Bn,L,n,top_k,top_p", [(2, 3, 3, 0, 0.0), (1, 6, 700, 100, 0.0), (1, 6, 3000, 0, 0.9), (9, 32, 6001, 0, 0.0)] +
+                         ROWS)
+def test_the_previous_logits_of_a_new_position_decide_nothing(Bn, L, n, top_k, top_p):
+    g = torch.Generator(device=DEV).manual_seed(n)
+    z, z_prev = (2.0 * torch.randn(Bn, L, n, device=DEV, generator=g) for _ in range(2))
+    fresh = (torch.arange(L, device=DEV) % 2).to(torch.uint8).repeat(Bn, 1)
+    x = (torch.arange(Bn * L, device=DEV).to(torch.int32) * 7 % n).view(Bn, L)
+    pos = torch.zeros(Bn, dtype=torch.int32, device=DEV)
+    sc = B.Scd(B.make_config(B=Bn, L=L, N=1000, V=n, top_k=top_k, top_p=top_p, seed=5), DEV)
+    got = []
+    for value in (None, float("nan"), INF, -INF):
+        if value is not None:
+            z_prev[fresh.bool()] = value
+        y, k = torch.empty(Bn, L, dtype=torch.int32, device=DEV), torch.empty(Bn, L, dtype=torch.uint8, device=DEV)
+        sc.couple_draft(z, z_prev, x, fresh, pos, 3, y, k)
+        got.append((y, k))
+    for y, k in got[1:]:
+        assert torch.equal(y, got[0][0]) and torch.equal(k, got[0][1])

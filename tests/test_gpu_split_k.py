@@ -1,11 +1,13 @@
 """Steps whose LM head deals k over workgroups (up to 8 parts per 64 x 128 tile), against the oracle: the row kernel adds the
 parts up, processes the logits and leaves them in the ring.  Ragged ids, rows and k; every number of parts; every option."""
+import numpy as np
 import pytest
 import torch
 
 from lockstep import LockStep
 from paper_2510_24211_amd import binding as B
 from paper_2510_24211_amd import workload as wl
+from test_gpu_lm_head_tiles import _inputs, _want
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +62,36 @@ def test_parts_are_run_to_run_identical():
         got.append([s.state_field(st, f).clone() for f in (B.F_OUT, B.F_Z, B.F_LSE, B.F_PX)])
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("parts,chains,Bn,L,n,d,lam", [
+    (2, 4, 2, 32, 2897, 1280, 3.0),       # two sums per part; odd rows
+    (2, 2, 5, 26, 1285, 1288, 0.0),       # a ragged k-tile
+    (4, 4, 2, 32, 1031, 1280, 3.0),
+    (4, 4, 1, 64, 4090, 1288, 0.0),
+    (4, 8, 1, 30, 3999, 4104, 3.0),
+    (8, 8, 3, 16, 260, 2048, 3.0),
+    (8, 8, 1, 32, 1901, 4096, 3.0),
+])
+def test_logits_of_a_step_against_64_bits(parts, chains, Bn, L, n, d, lam):
+    """The ring after a step with k in parts, as the tests of the LM head bound its kernels. (scd_lm_head adds up in another
+    order on these shapes: the two agree to rounding only.)"""
+    v_lo, tau = 5, 0.8
+    W, h = _inputs(Bn, 2 if lam else 1, L, n, d, v_lo, n + d)
+    sc = B.Scd(B.make_config(B=Bn, L=L, N=400, V=W.shape[0], d=d, v_lo=v_lo, v_hi=v_lo + n, temperature=tau, cfg_lambda=lam,
+                             top_k=n // 5), "cuda:0")
+    st = sc.alloc_state()
+    sc.reset(st)
+    assert (st.numel() - _fields_end(sc, st)) // (4 * Bn * L * n * (2 if lam else 1)) == parts
+    ring = sc.state_field(st, B.F_Z).view(2, Bn, L, n)
+    ring.fill_(float("nan"))
+    sc.step(h, W, st)
+    want, bound = _want(W, h, n, v_lo, lam, tau)
+    diff = ring[0].double() - want
+    assert bool((diff.abs() <= bound).all()) and bool(ring[1].isnan().all())
+    # the tiles' bound on the rounding of a logit added up in `chains` chains
+    err = float(diff.norm() / want.norm())
+    assert err <= 0.7 * 2.0 ** -24 * np.sqrt(d / 32 / chains + (chains + 1) / 2), err
+    alone = torch.empty(Bn, L, n, device="cuda:0")
+    sc.lm_head(h, W, alone)
+    assert bool(((alone.double() - ring[0].double()).abs() <= 2 * bound).all())
