@@ -2641,6 +2641,27 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
   RowArgs a = a_in;
   a.q_uniform = 1.0f / static_cast<float>(a.n);
   a.recip_L = window_reciprocal(a.rows, a.N, a.L);
+  // (mentioned first, these kernels lie first in the library: behind the list kernels, which shrank, all options on 32 x 8192 ids
+  // took 136.7 us for 135.2 with the same instructions)
+  using Kernel = void (*)(const int32_t*, const int32_t*, const uint2*, const uint32_t*, int, int, int, int, int, RowArgs);
+#define SCD_ROW_INSTANCES(PATH) \
+  {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
+  static const Kernel kernels[][4] = {
+#if defined(SCD_ROW_SHORT)
+      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), {}, {}, SCD_ROW_INSTANCES(kPartsQuarter)
+#elif defined(SCD_ROW_BATCHED)
+      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
+      {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr},
+      SCD_ROW_INSTANCES(kPartsQuarter), SCD_ROW_INSTANCES(kPartsHalf)
+#else
+      {}, {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
+      {}, {}, SCD_ROW_INSTANCES(kLists),
+      {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
+      {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
+      {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
+#endif
+  };
+#undef SCD_ROW_INSTANCES
   int P = 0, capE = 0;
   a.cand = nullptr;
 #ifndef SCD_ROW_DIRECT_ONLY
@@ -2684,25 +2705,6 @@ hipError_t LAUNCH_ROW(const RowArgs& a_in, hipStream_t s, size_t* lds_configured
 #endif
   const bool gs = (a.gumbel || a.alpha < 1.0f) && a.g && a.mode != kRowSelectOnly;
   const bool extra = a.top_p24 != 0u || a.diag != nullptr;   // the instances with the optional parts
-  using Kernel = void (*)(const int32_t*, const int32_t*, const uint2*, const uint32_t*, int, int, int, int, int, RowArgs);
-#define SCD_ROW_INSTANCES(PATH) \
-  {row_kernel<false, false, PATH>, row_kernel<true, false, PATH>, row_kernel<false, true, PATH>, row_kernel<true, true, PATH>}
-  static const Kernel kernels[][4] = {
-#if defined(SCD_ROW_SHORT)
-      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), {}, {}, SCD_ROW_INSTANCES(kPartsQuarter)
-#elif defined(SCD_ROW_BATCHED)
-      SCD_ROW_INSTANCES(kDirectTiny), SCD_ROW_INSTANCES(kDirectQuarter), SCD_ROW_INSTANCES(kDirectHalf),
-      {row_kernel<false, false, kDirectWhole>, row_kernel<true, false, kDirectWhole>, nullptr, nullptr},
-      SCD_ROW_INSTANCES(kPartsQuarter), SCD_ROW_INSTANCES(kPartsHalf)
-#else
-      {}, {}, SCD_ROW_INSTANCES(kDirectHalf), SCD_ROW_INSTANCES(kDirectWhole),
-      {}, {}, SCD_ROW_INSTANCES(kLists),
-      {row_kernel<false, false, kLong>, nullptr, nullptr, nullptr},
-      {nullptr, nullptr, row_kernel<false, true, kNucleusHalf>, row_kernel<true, true, kNucleusHalf>},
-      {nullptr, nullptr, row_kernel<false, true, kNucleusWhole>, row_kernel<true, true, kNucleusWhole>}
-#endif
-  };
-#undef SCD_ROW_INSTANCES
   // The dynamic-LDS limit is an attribute of the function on a device.  Every context asks
   // for the same value, the largest any row needs, once (a context has one stream, hence one
   // device), so contexts of different row lengths cannot lower each other's limit.
