@@ -205,8 +205,8 @@ int scd_select(scd_ctx* ctx, const float* d_z, int32_t rows, float* d_thr, float
  * redraft in one call (Alg. 1; Alg. SCD(pi_MC) parallel-for).
  *   d_z_cur, d_z_prev fp32 [B, L, n] processed logits of this / the previous
  *   iteration, window order;  d_x int32 [B, L] draft token offsets;
- *   d_fresh uint8 [B, L], nonzero = never evaluated (q uniform; d_z_prev row
- *   unread), may be NULL = none fresh;  d_pos0 int32 [B];  iter = iteration
+ *   d_fresh uint8 [B, L], nonzero = never evaluated (q uniform; the d_z_prev row
+ *   must be readable, its values decide nothing), may be NULL = none fresh;  d_pos0 int32 [B];  iter = iteration
  *   index used in the random-number counters;
  *   outputs d_y int32 [B, L], d_k uint8 [B, L]. */
 int scd_couple_draft(scd_ctx* ctx, const float* d_z_cur, const float* d_z_prev,
@@ -216,13 +216,13 @@ int scd_couple_draft(scd_ctx* ctx, const float* d_z_cur, const float* d_z_prev,
 /* scd_couple_draft for callers that cannot allocate device memory -- code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels,
  * same results; the scratch that scd_couple_draft keeps in the context's workspace (per-row
- * thresholds / normalisers / kept counts of both logit arrays and the slice kernel's candidate
+ * thresholds / normalisers / kept counts of both logit arrays and the rows' candidate
  * lists) lives in a static device array of SCD_STATIC_SCRATCH_BYTES inside the library instead
  * (one copy per GPU, held until the process ends).  The call allocates and frees nothing and
  * does not touch the context's workspace.  Returns SCD_ESCRATCH when the configuration needs
  * more: 24 bytes per window row (B * L rows, each of the six arrays rounded up to 256 bytes),
  * plus 51200 bytes per window row when top-k filters rows of 16385..65536 ids with
- * top_k <= 3072 (the slice kernel's candidate lists), i.e. up to 163 such rows.  Longer rows take
+ * top_k <= 3072 (their candidate lists), i.e. up to 163 such rows.  Longer rows take
  * the lists while they fit; beyond that they are read whole, and their normalisers, summed in
  * another order, may differ from scd_couple_draft's in the last bits.
  * All calls on one GPU share that array and it keeps the last call's contents (nothing in it has
@@ -245,7 +245,10 @@ int scd_verify(scd_ctx* ctx, const uint8_t* d_k, const int32_t* d_y, const int32
 /* One whole iteration (steps 1-4 incl. window slide) on the device-resident
  * state.  d_h as in scd_lm_head for the CURRENT windows (row s <-> position
  * i_b + s; rows past the sequence end are ignored but must be readable).
- * Finished sequences cost nothing and change nothing.  Requires cfg.d > 0. */
+ * Finished sequences cost nothing and change nothing.  Requires cfg.d > 0.
+ * On rows of up to 4096 ids, if they are few, the logits are added up over k in another order than
+ * scd_lm_head's: the two may differ in the last bits there, and so may a decision that hangs on
+ * them.  On all other shapes the logits are the same. */
 int scd_step(scd_ctx* ctx, const uint16_t* d_h, const uint16_t* d_W, void* d_state);
 
 /* Optional instrumentation for benchmarks: while both events are non-NULL,

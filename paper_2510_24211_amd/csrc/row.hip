@@ -48,6 +48,9 @@
 // (us, 1024 / 512 / 256 threads): 8 x 1024 ids 38.2 / 34.0 / 31.8; 32 x 2048 42.4 / 34.4 / 40.7, under top-k 500
 // 45.2 / 35.3 / 39.7, with all options 68.9 / 53.4 / 61.9; 32 x 4096 40.8 / 42.7, under top-k 40.0 / 39.2, with all
 // options 65.5 / 63.0; 32 x 8192 behind the LM head 107.4 / 111.4.
+// The lines were drawn with 8 and 32 rows; with more rows than CUs the same way round (four steps, 512 rows, 1024 threads where
+// options are on and else 512, against now): 1024 ids 53.3 / 48.1, with all options 135.1 / 71.5; 2048 ids 55.2 / 50.9,
+// 136.1 / 73.9; 4096 ids (512 threads before, where no option is on) 68.7 / 64.0, 138.8 / 89.0.
 //   More rows than CUs: a workgroup of 512 threads takes up to 118 registers per lane and 51 KB of LDS, so two of them
 // share a CU and the barrier-separated phases of one row overlap with another's instead of the rows queueing in rounds.
 #include "scd_device.h"
@@ -2212,7 +2215,7 @@ __device__ __forceinline__ void direct_path(const RowArgs& a, RowRef& R, unsigne
   // The kept ids' previous logits are gathered behind the threshold, except 16 to a thread without options: there the whole
   // row's are read up front (four steps of 464 rows x 4688 ids 233 : 236 us, of 32 x 16384 92.9 : 93.9).  With the options the 16
   // more registers spilled (128 rows x 10457 ids 149.8 -> 135.0, 128 x 9137 140.5 -> 132.0); shorter rows save the bytes
-  // (16 x 32 x 8192 324 -> 320, 104 x 2546 75.7 -> 74.5).
+  // (104 x 2546 75.7 -> 74.5; 512 x 8192 behind the LM head the same).
   constexpr bool PREQ = PER >= 16 && !EXTRA;
   int vid[PER];
   float zv[PER], zq[PER];

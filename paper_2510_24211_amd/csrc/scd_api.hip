@@ -116,8 +116,8 @@ size_t workspace_need(const scd_config& c) {
 
 // ---- scratch of the entry point that allocates nothing -----------------------------------
 // scd_couple_draft_static keeps what scd_couple_draft keeps in the caller's workspace (the
-// thresholds / normalisers / kept counts of its two logit arrays and the candidate lists of the
-// slice kernel) in this array.  Every GPU the library runs on holds its own copy at its own
+// thresholds / normalisers / kept counts of its two logit arrays and the rows' candidate
+// lists) in this array.  Every GPU the library runs on holds its own copy at its own
 // address until the process ends; `scratch` itself is only the host-side name of the symbol, so
 // host code uses the per-device address that hipGetSymbolAddress returned, never the name.
 __device__ __align__(256) unsigned char scratch[SCD_STATIC_SCRATCH_BYTES];
