@@ -776,9 +776,10 @@ __global__ __launch_bounds__(ST) void slice_kernel(const int32_t* const pos_, co
 // ids, top-k 2000, in pieces of neighbours : of lines (us): independent logits 79.3 : 79.4, runs of 1024 ids that differ by
 // half of a logit's own deviation 183 : 78, logits falling with log(id) 209 : 76, one half masked 282 : 96, sorted 352 : 86;
 // of 32 x 131072, top-k 1000, 80.9 : 81.2, 285 : 82, 272 : 270, 855 : 114, 479 : 488.  Lines of 32 take falling logits there
-// too (81) but cost independent ones more (65536 ids 80.4, 81146 84.9 for 82.7 in lines of 64; rows whose lines are not the
-// memory's pay for those of 64 already, 288 x 24577 138.5 : 141.5); lines of 128 fail runs of 128 to 512 ids.  A line's place moves by two from stripe to stripe: at one
-// place in all, a load's lines lie 8 KB apart at 65536 ids, on few channels (82.4).
+// too (81) but cost independent ones more: 65536 ids 80.4, 81146 84.9 for 82.7 in lines of 64 (rows whose lines are not the
+// memory's pay for those of 64 already, 288 x 24577 138.5 : 141.5).  Lines of 128 fail runs of 128 to 512 ids.
+//   A line's place moves by two from stripe to stripe: at one place in all, a load's lines lie 8 KB apart at 65536 ids, on
+// few channels (82.4).
 // As in the LM head's epilogue the emitted set is found on a monotone image of the logits, linear between their mean and
 // their largest: one LDS histogram per wavefront, the lowest bin whose upper set holds at most `cap`.  A list needs no exact
 // length, only to hold what the row's K-th largest leaves to this piece, so that bins of a few logits will do; where they
